@@ -142,7 +142,13 @@ enum {
  * PG_CAREFUL_WALKS makes every valuation of this game take the host-driven
  * rounds directly: slower, same results; it exists to test that path.
  *
- * A best-response iteration (walks, valuation, All_Odd) of pg_solve and
+ * A valuation of pg_solve or pg_best_response that follows few switches is
+ * computed by its changed part only (rank valuations; not with a trace,
+ * PG_CAREFUL_WALKS or PG_HOST_REDUCED_LIST): same results.  The first such
+ * call lays out the game's in-edges for it (4 bytes per edge, 12 per
+ * vertex); without room for them every valuation is a full one.
+ *
+ * A full best-response iteration (walks, valuation, All_Odd) of pg_solve and
  * pg_best_response is captured once per game as a HIP graph (on a stream of
  * the library's own) and replayed on the caller's stream; the event
  * profiler and the host-driven fallback launch kernels one by one.
@@ -340,7 +346,9 @@ typedef struct pg_stats {
     double seconds;         /* wall time of the solve on the host clock      */
     double iteration_ms;    /* device time of the best-response iterations,
                                summed (HIP events on the call's stream
-                               around each; 0 for Bellman-Ford and batches) */
+                               around each, or around several of them and
+                               the All_Even steps between where they run in
+                               one kernel; 0 for Bellman-Ford and batches)  */
     int64_t n_traced;       /* entries written to the trace arrays           */
 } pg_stats;
 

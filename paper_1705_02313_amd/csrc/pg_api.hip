@@ -664,6 +664,7 @@ void free_game(pg_game *g) {
     dev_free(g->vsum[k]);
     dev_free(g->vbase[k]);
   }
+  inc_release(g);
   host_free(g->hctr);
   host_free(g->h_rl);
   if (g->iter_exec) (void)hipGraphExecDestroy(g->iter_exec);
@@ -1131,23 +1132,80 @@ struct Trace {
   }
 };
 
-// The inner loop of Algorithm 1 on the play graph in g->sp.
-pg_status inner_loop(pg_game *g, int32_t max_inner, hipStream_t s,
-                     int64_t *n_val, int64_t *n_sw, Trace *tr = nullptr,
-                     double *iter_ms = nullptr) {
-  int32_t inner = 0;
+// A run of Algorithm 1 by one-player strategy improvement on the play graph
+// in g->sp: whole, or (br_only) its first best response.  Valuations are full
+// ones (iteration_device) or, when few vertices switched before them, by
+// their changed part (pg_inc.hip); both take the same switches.
+struct Run {
+  int32_t max_major = 0, max_inner = 0;
+  bool reset = false, br_only = false;
+  Trace *tr = nullptr;
+  int64_t n_major = 0, n_val = 0, n_odd = 0, n_even = 0;
+  double iter_ms = 0.0;
+};
+
+pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
+  const int32_t N = (int32_t)g->n_aug;
+  // a trace reports every valuation's ranks
+  const bool inc = !(r->tr && r->tr->o->trace_cap > 0) && inc_prepare(g, s);
+  if (!inc) g->inc.on = false;
+  int32_t &inner = g->inc.inner, &major = g->inc.major;
+  major = 0;
   for (;;) {
-    if (max_inner > 0 && inner >= max_inner)
-      return pg_fail(PG_EITERLIMIT, "best response: valuation cap reached");
+    if (r->max_major > 0 && major >= r->max_major) {
+      inc_commit(g, s);
+      r->n_major = major;
+      return pg_fail(PG_EITERLIMIT, "solve: outer iteration cap reached");
+    }
+    ++major;
+    inner = 0;
+    if (r->reset) {
+      inc_commit(g, s);
+      hipLaunchKernelGGL(k_sp_reset_odd, dim3(grid_for(N)), dim3(kBlock), 0, s,
+                         g->off, g->tgt, g->owner, g->pri, g->sp, N);
+    }
+    int end = INC_MORE;
+    while (end == INC_MORE) {
+      r->n_major = major;
+      if (r->max_inner > 0 && inner >= r->max_inner) {
+        inc_commit(g, s);
+        return pg_fail(PG_EITERLIMIT, "best response: valuation cap reached");
+      }
+      if (inc && inc_ready(g)) {
+        IncOut o;
+        PG_TRY(inc_step(g, s, !r->reset && !r->br_only, r->max_inner,
+                        r->max_major, &o));
+        r->iter_ms += g->last_ms;
+        r->n_val += o.nval;
+        r->n_odd += o.odd;
+        r->n_even += o.even;
+        end = o.state;
+      } else {
+        int32_t c = 0;
+        int64_t nf = 0;
+        inc_before_full(g, s);
+        PG_TRY(iteration_device(g, s, &c, &nf));
+        inc_after_full(g, c);
+        r->iter_ms += g->last_ms;
+        if (r->tr) r->tr->record(g, s, c, nf);
+        ++inner;
+        ++r->n_val;
+        r->n_odd += c;
+        if (c == 0) end = INC_BR;
+      }
+    }
+    r->n_major = major;
+    if (end == INC_CAP) continue;
+    if (end == INC_SOLVED || r->br_only) return PG_OK;
+    // a best response: its top vertices stay top from here on
+    mark_top(g, s);
     int32_t c = 0;
-    int64_t nf = 0;
-    PG_TRY(iteration_device(g, s, &c, &nf));
-    if (iter_ms) *iter_ms += g->last_ms;
-    if (tr) tr->record(g, s, c, nf);
-    ++inner;
-    ++*n_val;
-    *n_sw += c;
+    if (inc) PG_TRY(inc_even(g, s, &c));
+    else PG_TRY(switch_device(g, false, s, &c));
+    r->n_even += c;
     if (c == 0) return PG_OK;
+    // a new inner loop: Even's switches may make finite vertices top
+    if (!inc) fates_reset(g, s);
   }
 }
 
@@ -1308,35 +1366,32 @@ pg_status solve_game(pg_game *g, const pg_solve_opts *opts, uint8_t *winner,
     fill_i32((int32_t *)hb.p, 0, 2 * (int64_t)o.trace_cap, s);
     tr.dhash = hb.p;
   }
-  int64_t n_major = 0, n_val = 0, n_odd = 0, n_even = 0;
-  double iter_ms = 0.0;
+  Run r;
+  r.max_major = o.max_major;
+  r.max_inner = o.max_inner;
+  r.reset = o.best_response == PG_BR_SI_RESET;
+  r.tr = &tr;
   pg_status st = PG_OK;
-  for (;;) {
-    if (o.max_major > 0 && n_major >= o.max_major) {
-      st = pg_fail(PG_EITERLIMIT, "solve: outer iteration cap reached");
-      break;
-    }
-    ++n_major;
-    if (o.best_response == PG_BR_SI_RESET)
-      hipLaunchKernelGGL(k_sp_reset_odd, dim3(grid_for(N)), dim3(kBlock), 0, s,
-                         g->off, g->tgt, g->owner, g->pri, g->sp, (int32_t)N);
-    if (o.best_response == PG_BR_BELLMAN_FORD) {
+  if (o.best_response != PG_BR_BELLMAN_FORD) {
+    st = run_si(g, &r, s);
+  } else {
+    for (;;) {
+      if (o.max_major > 0 && r.n_major >= o.max_major) {
+        st = pg_fail(PG_EITERLIMIT, "solve: outer iteration cap reached");
+        break;
+      }
+      ++r.n_major;
       int64_t rounds = 0;
       st = bf_best_response(g, s, &rounds);
-      n_val += rounds;
-    } else {
-      st = inner_loop(g, o.max_inner, s, &n_val, &n_odd, &tr, &iter_ms);
-      // a best response: its top vertices stay top from here on
-      if (st == PG_OK) mark_top(g, s);
+      r.n_val += rounds;
+      if (st != PG_OK) break;
+      int32_t c = 0;
+      st = switch_device(g, false, s, &c);
+      if (st != PG_OK) break;
+      r.n_even += c;
+      if (c == 0) break;
+      fates_reset(g, s);
     }
-    if (st != PG_OK) break;
-    int32_t c = 0;
-    st = switch_device(g, false, s, &c);
-    if (st != PG_OK) break;
-    n_even += c;
-    if (c == 0) break;
-    // a new inner loop: Even's switches may make finite vertices top
-    fates_reset(g, s);
   }
   if (tr.dhash && tr.n > 0) {
     // the trace is the caller's even when the run stopped early
@@ -1354,11 +1409,11 @@ pg_status solve_game(pg_game *g, const pg_solve_opts *opts, uint8_t *winner,
     stats->m = g->m;
     stats->n_aug = g->n_aug;
     stats->m_aug = g->m_aug;
-    stats->n_major = n_major;
-    stats->n_valuations = n_val;
-    stats->n_odd_switches = n_odd;
-    stats->n_even_switches = n_even;
-    stats->iteration_ms = iter_ms;
+    stats->n_major = r.n_major;
+    stats->n_valuations = r.n_val;
+    stats->n_odd_switches = r.n_odd;
+    stats->n_even_switches = r.n_even;
+    stats->iteration_ms = r.iter_ms;
     stats->n_traced = tr.n;
   }
   const bool report = !(o.flags & PG_KEEP_DUMMIES);
@@ -1608,10 +1663,16 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
   const bool dev = flags & PG_PTR_DEVICE;
   PG_TRY(import_strats(g, sigma, tau, dev, s));
   valuation_reset(g, s);
-  int64_t nv = 0, nsw = 0;
-  pg_status st = inner_loop(g, max_inner, s, &nv, &nsw);
-  if (n_valuations) *n_valuations = (int32_t)nv;
+  Run r;
+  r.max_inner = max_inner;
+  r.br_only = true;
+  const pg_status st = run_si(g, &r, s);
+  if (n_valuations) *n_valuations = (int32_t)r.n_val;
   if (st != PG_OK) return st;
+  if (key && inc_dirty(g)) {   // the ranks of the vertices changed last
+    fates_reset(g, s);
+    PG_TRY(valuation_device(g, s, nullptr));
+  }
   PG_TRY(export_strats(g, nullptr, tau, dev, s, false));
   if (key) PG_TRY(export_keys(g, key, dev, s));
   PG_HIP(hipStreamSynchronize(s));

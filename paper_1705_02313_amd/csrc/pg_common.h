@@ -18,6 +18,9 @@ constexpr int kBlock = 256;            // threads per block for flat kernels
 // sp[v].y (the priority of v's successor) of a vertex known to stay top for
 // the rest of a solve: its play, and every play through it, is infinite
 constexpr int32_t kTopMark = INT32_MIN;
+// key[v] of a vertex whose valuation changed since the last full valuation
+// (pg_inc.hip); no rank is negative
+constexpr int32_t kKeyDirty = -1;
 constexpr int kWave = 64;              // CDNA wavefront width
 constexpr int kMaxVertices = (1 << 30) - 2;
 
@@ -31,6 +34,7 @@ enum Counter : int {
   C_MISC = 4,         // scratch counter (preprocessing changes, odd count,
                       // open vertices of host-driven walk rounds)
   C_NINNER = 5,       // finite vertices whose parent is not the sink
+  C_NDEC = 6,         // entries of All_Odd's switch list (single rank games)
   // Hot counts are spread over kDistSlots slots kDistStride ints apart (one
   // atomic per block into slot blockIdx % kDistSlots) and summed afterwards:
   // a single address hit by every block serialises.  The switch slots are
@@ -72,7 +76,8 @@ enum KId : int {
   K_FILL = 0, K_NG_WALK, K_NG_ROUND, K_ROOT_WALK, K_ROOT_ROUND,
   K_SORT_SPLIT, K_SORT_HIST, K_SCAN, K_SORT_PASS, K_LINK_INFO, K_LINK_BUILD,
   K_LR_SUM1, K_LR_SUMK, K_LR_TOP, K_LR_DISTK, K_LR_EMIT1, K_ODD_SWITCH,
-  K_EVEN_SWITCH, K_ODD_STAGE, K_OTHER, K_COUNT
+  K_EVEN_SWITCH, K_ODD_STAGE, K_INC_FIND, K_INC_WALK, K_INC_DECIDE,
+  K_INC_BLOCK, K_OTHER, K_COUNT
 };
 extern const char *const kKernelNames[K_COUNT];
 
@@ -276,6 +281,30 @@ struct pg_game {
   int32_t *vsum[pgk::kMaxLevels] = {};   // per level: dw ints per splitter
   int32_t *vbase[pgk::kMaxLevels] = {};
 
+  // valuations by their changed part (pg_inc.hip)
+  struct Inc {
+    int state = 0;               // 0 not built, 1 built, -1 no memory
+    uint32_t *in_off = nullptr;  // [n_aug+1] in-edge lists (at the first solve)
+    uint32_t *in = nullptr;      // [m_aug] source, its owner in bit 31
+    int32_t *mark = nullptr;     // [n_aug] last step that changed the vertex
+    int32_t *cmark = nullptr;    // [n_aug] last step it was a candidate of
+    int32_t *ic = nullptr;       // a step's counters
+    int32_t *h = nullptr;        // pinned host mirror
+    int32_t epoch = 0;           // number of the last step
+    // the run in progress
+    bool on = false;
+    bool dirty = false;     // keys dirty since the last full valuation
+    bool pending = false;   // nsw decisions in list `cur` to apply
+    bool d_valid = false;   // the list's first a0 entries hold every change
+                            // since the last All_Even
+    bool even = false;      // Even switched since the last full valuation
+    bool grown = false;     // the block form gave the pending step up
+    int cur = 0;
+    int32_t nsw = 0, a0 = 0;
+    int32_t inner = 0, major = 0;   // the run's iteration counts
+    int skip = 0, back = 0;         // full valuations to take after a give-up
+  } inc;
+
   unsigned long long *u64tmp = nullptr;  // [2] scratch for 64-bit sums
   int32_t *ctr = nullptr;    // [C_TOTAL] device counters
   int32_t *hctr = nullptr;   // pinned host mirror
@@ -373,6 +402,28 @@ __device__ __forceinline__ void append_block(int32_t *cnt, int32_t *list,
     s_base = atomicAdd(&cnt[slot * kDistStride], s_n);
   __syncthreads();
   if (pred) list[(int64_t)slot * cap + s_base + off] = v;
+}
+
+// Appends {v, to} (where pred holds) to a list whose length counts at *cnt,
+// one device atomic per block.  Every thread of the block must call it.
+__device__ __forceinline__ void list_block(int32_t *cnt, int2 *list,
+                                           bool pred, int32_t v, int32_t to) {
+  __shared__ int32_t s_n, s_base;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  const uint64_t b = __ballot(pred);
+  const int lane = threadIdx.x & (kWave - 1);
+  int32_t off = 0;
+  if (b) {
+    int32_t wbase = 0;
+    if (lane == 0) wbase = atomicAdd(&s_n, (int32_t)__popcll(b));
+    wbase = __shfl(wbase, 0);
+    off = wbase + (int32_t)__popcll(b & ((1ull << lane) - 1ull));
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && s_n) s_base = atomicAdd(cnt, s_n);
+  __syncthreads();
+  if (pred) list[s_base + off] = make_int2(v, to);
 }
 
 __device__ __forceinline__ int ld_relaxed(const int32_t *p) {
@@ -495,6 +546,36 @@ void fates_reset(pg_game *g, hipStream_t s);
 // iteration's device time between two HIP events on s.
 pg_status iteration_device(pg_game *g, hipStream_t s, int32_t *count,
                            int64_t *n_finite = nullptr);
+}  // namespace pgk
+
+// ---- valuations by their changed part (pg_inc.hip) -------------------------
+namespace pgk {
+// Rows read by All_Odd's row form list its switches only up to this many Odd
+// vertices (one counter takes an atomic per block).
+constexpr int64_t kIncRowOdd = int64_t(1) << 20;
+bool inc_eligible(const pg_game *g);
+// Start of a run: builds the in-edge lists if they are not there; false
+// when the game takes full valuations only.
+bool inc_prepare(pg_game *g, hipStream_t s);
+void inc_release(pg_game *g);
+// true when the pending switches are few enough for inc_step
+bool inc_ready(const pg_game *g);
+bool inc_dirty(const pg_game *g);
+void inc_commit(pg_game *g, hipStream_t s);
+void inc_before_full(pg_game *g, hipStream_t s);
+void inc_after_full(pg_game *g, int32_t switches);
+enum IncEnd : int { INC_MORE = 0, INC_BR, INC_SOLVED, INC_CAP };
+struct IncOut {
+  int state = INC_MORE;
+  int64_t nval = 0, odd = 0, even = 0;   // valuations, switches of the step
+};
+// g->inc.inner and g->inc.major count on; with_even: All_Even and further
+// outer iterations may run too.  INC_MORE: go
+// on (or inner has reached its cap); INC_CAP: major has, between two outer
+// iterations.
+pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
+                   int32_t max_inner, int32_t max_major, IncOut *out);
+pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count);
 }  // namespace pgk
 
 // ---- count valuations (pg_count.hip) ---------------------------------------

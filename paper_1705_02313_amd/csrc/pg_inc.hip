@@ -1,0 +1,1192 @@
+// Valuations by their changed part (rank valuations, single games).
+//
+// Along a run most valuations follow a handful of switches.  A switch at w
+// changes the play of exactly the vertices whose play passes w (with the
+// strategy after the switch): call the union over all switched vertices A.
+// Every other vertex keeps its play, hence its nearest greater vertex, its
+// fate and its valuation, and any two of them keep their order.  A step here
+// therefore
+//   find    collects A from the switched vertices backwards over the game's
+//           in-edges (u joins when its current successor is in A)
+//   walk    recomputes ng for the vertices of A only, jumping over everyone
+//           else's ng
+//   fate    follows their ng chains to the sink or to top
+//   decide  evaluates the switching rule for the vertices whose row holds a
+//           vertex of A: nobody else's options changed since it last did not
+//           switch
+// and the keys of A become kKeyDirty.  Two clean keys compare as before; a
+// comparison with a dirty vertex climbs the two ng chains to their meeting
+// point and decides there by signed priority, which is the order a full
+// valuation lists the tree in (pg_val.hip), so the switches are the same.
+// A full valuation makes every key clean again.
+//
+// Decisions go to a list of {vertex, new successor} pairs (`dec`) that the
+// next step applies, so a step that gives up (a hub with too many in-edges,
+// a chain or walk longer than its bound, a full list) has changed nothing a
+// full valuation does not recompute.
+//
+// Two forms: a few kernels over the whole device for large A, and one block
+// that runs whole inner and outer iterations by itself while A stays small
+// (no launches, no host in between).
+//
+// Every access is a random line, so a step costs its round trips (small A)
+// or its lines (large A), a full valuation the whole game's lines whatever
+// changed: on the 10M-vertex random game 12 of the 95 valuations stay full
+// (1.4 ms each), 38 take the device form (0.1-0.4 ms mostly) and 45 the
+// block form (25-40 us each).  Solves, load included: 146 -> 64 ms there,
+// 15.1 -> 9.8 ms at 1M vertices, 59.6 -> 19.6 ms on the 2M-vertex chain,
+// 3.6 -> 1.6 ms at 1,000 vertices.
+#include <algorithm>
+
+#include "pg_common.h"
+
+namespace pgk {
+
+// words of a step's counters (g->inc.ic)
+enum IncCounter : int {
+  I_ERR = 0,      // ERR_* bits (C_ERR's index: the walk sets it)
+  I_STOP = 1,     // the step gave up: redo it as a full valuation
+  I_NA = 2,       // vertices in A
+  I_NC = 3,       // candidates of the decide kernel
+  I_NDEC = 4,     // decisions
+  // block form only
+  I_STATE = 5, I_NVAL = 6, I_ODDSW = 7, I_EVENSW = 8, I_MAJOR = 9,
+  I_INNER = 10, I_A0 = 11, I_CUR = 12, I_EPOCH = 13,
+  I_NF = 16,      // frontier lengths, one per find round
+  I_WORDS = 64
+};
+static_assert((int)I_ERR == (int)C_ERR, "the ng walk reports through ctr[0]");
+constexpr int kIncRounds = 8;        // most find rounds of the device form
+constexpr int kFindRounds = 3;       // find rounds of the device form
+constexpr int kFindLevels = 128;     // levels of one round
+constexpr int kIncMaxDegree = 2048;  // in-edges of one vertex, else give up
+constexpr int kIncClimb = 512;       // ng steps of one comparison
+constexpr int kIncFate = 1024;       // ng steps of one fate
+constexpr int kIncBlocks = 1024;
+
+// ---------------------------------------------------------------------------
+// the in-edge lists
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_in_count(
+    const int32_t *__restrict__ tgt, uint32_t *cnt, int64_t m) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < m) atomicAdd(&cnt[tgt[e]], 1u);
+}
+
+// An in-edge is its source with the owner in bit 31.
+__global__ __launch_bounds__(kBlock) void k_in_fill(
+    const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
+    const uint8_t *__restrict__ owner, uint32_t *cursor, uint32_t *in,
+    int32_t N) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= N) return;
+  const uint32_t x = (uint32_t)v | ((uint32_t)owner[v] << 31);
+  for (int64_t e = off[v], end = off[v + 1]; e < end; e += 4) {
+    int32_t t[4];
+    uint32_t at[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = e + j < end ? tgt[e + j] : -1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      at[j] = t[j] >= 0 ? atomicAdd(&cursor[t[j]], 1u) : 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (t[j] >= 0) in[at[j]] = x;
+  }
+}
+
+__global__ void k_copy_u32(const uint32_t *a, uint32_t *b, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) b[i] = a[i];
+}
+
+// ---------------------------------------------------------------------------
+// shared device code
+// ---------------------------------------------------------------------------
+struct IncP {
+  int32_t N, n_oddpri;
+  const int64_t *off;
+  const int32_t *tgt, *pri;
+  const uint32_t *in_off, *in;
+  int2 *sp;
+  int32_t *key, *ng, *cand;
+  uint8_t *rs;
+  int32_t *mark, *cmark;   // epoch of the last step that took the vertex
+  int32_t *list;           // A of every step since the last All_Even
+  int32_t list_cap;
+  int32_t *cl;             // candidates (with repeats: cmark tells them)
+  int32_t cl_cap;
+  int32_t *f[2];           // find frontiers
+  int32_t f_cap;
+};
+
+// 1, 0 or -1: Val(x) above, equal to or below Val(y), for finite x and y,
+// one of them dirty.  The ng chains meet at their least common ancestor; in
+// the tree's listing order a vertex lies above its odd and below its even
+// children's subtrees, and siblings are in signed-priority order, which is
+// the order of the (relabeled) ids.
+__device__ __forceinline__ int inc_climb(const IncP &P, int32_t x, int32_t y,
+                                         bool *stop) {
+  const int32_t N = P.N;
+  int32_t a = x, b = y, ca = -1, cb = -1;
+  // a vertex's ng is fetched with its priority: one round trip a step
+  int32_t pa = a >= N ? 2147483647 : P.pri[a], na = a >= N ? N : P.ng[a];
+  int32_t pb = b >= N ? 2147483647 : P.pri[b], nb = b >= N ? N : P.ng[b];
+  for (int s = 0; a != b; ++s) {
+    if (s >= kIncClimb) {
+      *stop = true;
+      return 0;
+    }
+    if (pa < pb) {
+      ca = a;
+      a = na;
+      pa = a >= N ? 2147483647 : P.pri[a];
+      na = a >= N ? N : P.ng[a];
+    } else {
+      cb = b;
+      b = nb;
+      pb = b >= N ? 2147483647 : P.pri[b];
+      nb = b >= N ? N : P.ng[b];
+    }
+  }
+  if (ca < 0) return cb < 0 ? 0 : (cb >= P.n_oddpri ? -1 : 1);
+  if (cb < 0) return ca >= P.n_oddpri ? 1 : -1;
+  return ca > cb ? 1 : -1;
+}
+
+// the same for any two vertices (or the sink) with their keys
+__device__ __forceinline__ int inc_cmp(const IncP &P, int32_t x, int32_t kx,
+                                       int32_t y, int32_t ky, bool *stop) {
+  if (kx >= 0 && ky >= 0) return kx < ky ? -1 : kx > ky;
+  if (x == y) return 0;
+  if (kx == PG_KEY_TOP) return 1;
+  if (ky == PG_KEY_TOP) return -1;
+  return inc_climb(P, x, y, stop);
+}
+
+// All_Odd and All_Even (section 4, section 3) for one vertex: true when v
+// switches, to *to.  A row without a dirty vertex compares keys only.
+__device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
+                                           int32_t *to, bool *stop) {
+  const int2 me = P.sp[v];
+  if (me.y == kTopMark) return false;   // known to stay top
+  const int64_t e0 = P.off[v], e1 = P.off[v + 1];
+  const int32_t cur = me.x;
+  const int32_t kn = odd ? 0 : P.key[P.N];
+  int32_t best = odd ? -1 : P.N, kb = kn, kc = kn;
+  bool have = !odd && cur == P.N, dirty = false;
+  for (int64_t q = e0; q < e1; q += 4) {
+    int32_t u[4], k[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u[j] = q + j < e1 ? P.tgt[q + j] : -1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) k[j] = u[j] >= 0 ? P.key[u[j]] : 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (u[j] < 0) continue;
+      dirty |= k[j] < 0;
+      if (u[j] == cur) {
+        kc = k[j];
+        have = true;
+      }
+      if (odd ? best < 0 || k[j] < kb : k[j] > kb) {
+        best = u[j];
+        kb = k[j];
+      }
+    }
+  }
+  if (!have) kc = P.key[cur];
+  if (!dirty && kc >= 0) {
+    *to = best;
+    return odd ? kb < kc : kb > kc;
+  }
+  best = odd ? -1 : P.N;
+  kb = kn;
+  for (int64_t q = e0; q < e1; ++q) {
+    const int32_t u = P.tgt[q], k = P.key[u];
+    if (best >= 0) {
+      const int c = inc_cmp(P, u, k, best, kb, stop);
+      if (!(odd ? c < 0 : c > 0)) continue;
+    }
+    best = u;
+    kb = k;
+  }
+  if (best == cur) return false;
+  const int c = inc_cmp(P, best, kb, cur, kc, stop);
+  *to = best;
+  return odd ? c < 0 : c > 0;
+}
+
+// The ng of a vertex of A is open until its walk.
+__device__ __forceinline__ void inc_open(const IncP &P, int32_t v) {
+  P.ng[v] = -1;
+  P.cand[v] = -1;
+}
+
+// Applies a decision; the switched vertex is in A.
+__device__ __forceinline__ void inc_apply(const IncP &P, int32_t epoch,
+                                          int2 d) {
+  P.sp[d.x] = make_int2(d.y, d.y == P.N ? 2147483647 : P.pri[d.y]);
+  P.mark[d.x] = epoch;
+  inc_open(P, d.x);
+}
+
+// Wave-wide append: every lane of the wave calls it; lanes with pred get
+// consecutive places from *ctr.  One atomic per wave.
+__device__ __forceinline__ int32_t wave_place(int32_t *ctr, bool pred) {
+  const uint64_t b = __ballot(pred);
+  if (!b) return 0;
+  const int lane = threadIdx.x & (kWave - 1);
+  int32_t base = 0;
+  if (lane == 0) base = atomicAdd(ctr, (int32_t)__popcll(b));
+  base = __shfl(base, 0);
+  return base + (int32_t)__popcll(b & ((1ull << lane) - 1ull));
+}
+
+// The walk of one vertex of A (ng_walk of pg_val.hip on the changed part: an
+// open vertex is one of A, everyone else's ng is jumped over).  False when
+// the steps ran out (the candidate is kept).
+__device__ __forceinline__ bool inc_walk(const IncP &P, int32_t *err,
+                                         int32_t v, int steps) {
+  const int32_t N = P.N;
+  int32_t u = ld_relaxed(&P.cand[v]);
+  if (u < 0) {
+    const int2 me = P.sp[v];
+    if (me.y == kTopMark) {
+      st_relaxed(&P.ng[v], N + 1);
+      return true;
+    }
+    u = me.x;
+  }
+  const int32_t pv = P.pri[v];
+  int32_t res = -1;
+  for (int s = 0; s < steps; ++s) {
+    if (u == N) {
+      res = N;
+      break;
+    }
+    if (u == v) {
+      // the largest vertex of its cycle, whose priority must be even for an
+      // admissible sigma (section 3)
+      if (pv & 1) atomicOr(err, ERR_INADMISSIBLE);
+      res = N + 1;
+      break;
+    }
+    if (P.pri[u] > pv) {
+      res = u;
+      break;
+    }
+    const int32_t r = ld_relaxed(&P.ng[u]);
+    if (r >= N) {
+      res = r;
+      break;
+    }
+    if (r >= 0) {
+      u = r;
+      continue;
+    }
+    const int32_t c = ld_relaxed(&P.cand[u]);
+    if (c >= 0) {
+      u = c;
+    } else {
+      const int2 su = P.sp[u];
+      if (su.y == kTopMark) {
+        res = N + 1;
+        break;
+      }
+      u = su.x;
+    }
+  }
+  if (res >= 0) st_relaxed(&P.ng[v], res);
+  else st_relaxed(&P.cand[v], u);
+  return res >= 0;
+}
+
+// The fate of one vertex of A: along its ng chain to the sink, to top or to
+// a vertex outside A, whose fate stands.
+__device__ __forceinline__ bool inc_fate(const IncP &P, int32_t epoch,
+                                         int32_t v) {
+  const int32_t N = P.N;
+  int32_t r = P.ng[v];
+  int f = 0;
+  for (int s = 0; s < kIncFate; ++s) {
+    if (r >= N) {
+      f = r == N ? 1 : 2;
+      break;
+    }
+    if (P.mark[r] != epoch) {
+      f = P.rs[r];
+      break;
+    }
+    r = P.ng[r];
+  }
+  if (!f) return false;
+  P.rs[v] = (uint8_t)f;
+  P.key[v] = f == 2 ? PG_KEY_TOP : kKeyDirty;
+  return true;
+}
+
+// ---------------------------------------------------------------------------
+// the device form: one step in a few kernels
+// ---------------------------------------------------------------------------
+// Applies the decisions: A and the first frontier start with them.
+__global__ __launch_bounds__(kBlock) void k_inc_begin(
+    IncP P, int32_t epoch, int32_t a0, const int2 *__restrict__ dec,
+    int32_t nsw, int32_t *ic) {
+  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nsw;
+       i += gridDim.x * blockDim.x) {
+    const int2 d = dec[i];
+    inc_apply(P, epoch, d);
+    P.list[a0 + i] = d.x;
+    P.f[0][i] = d.x;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ic[I_NA] = nsw;
+    ic[I_NF] = nsw;
+  }
+}
+
+// One in-edge x of w in A: its source joins A when w is its successor; true
+// once per source (a repeated edge or a switched vertex meets its mark; two
+// lanes of w's group with the same source are told apart by shuffles).  Also
+// returns the source's own in-edge range: the loads are independent, so a
+// level of a find costs two round trips (the range was fetched with the
+// level before).  A source that slips through twice is harmless: it is only
+// walked twice.
+__device__ __forceinline__ bool inc_edge(const IncP &P, int32_t epoch,
+                                         int32_t w, uint32_t x, bool live,
+                                         int L, uint2 *range) {
+  const int32_t u = (int32_t)(x & 0x7fffffffu);
+  bool a = false;
+  *range = make_uint2(0u, 0u);
+  if (live) {
+    const int32_t su = P.sp[u].x;
+    const int32_t mk = ld_relaxed(&P.mark[u]);
+    range->x = P.in_off[u];
+    range->y = P.in_off[u + 1];
+    a = su == w && mk != epoch;
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint64_t ba = __ballot(a);
+  if (L > 1 && __ballot(a && __popcll((ba >> (lane & ~(L - 1))) &
+                                      ((1ull << L) - 1ull)) > 1)) {
+    const int32_t mine = a ? u : -1;
+    for (int k = 1; k < L; ++k) {
+      const int32_t other = __shfl_up(mine, k);
+      if ((lane & (L - 1)) >= k && a && other == u) a = false;
+    }
+  }
+  if (a) {
+    st_relaxed(&P.mark[u], epoch);
+    inc_open(P, u);
+  }
+  return a;
+}
+
+// Lanes per vertex of a find level of n vertices for T threads: a level is
+// bound by its round trips, so few vertices spread their in-edges over up
+// to 8 lanes.
+__device__ __forceinline__ int find_lanes(int n, int T) {
+  return n * 8 <= T ? 8 : n * 4 <= T ? 4 : n * 2 <= T ? 2 : 1;
+}
+
+// One find round: a block takes chunks of the frontier and follows the
+// in-edges breadth first by itself, its part of A and its candidates (the
+// Odd sources: they have an option in A) in LDS
+// (plays inside A are tens of vertices long: a kernel per level would be
+// mostly launches, and a place in a global list per level mostly atomics'
+// round trips).  A level too wide for the block, or past max_levels, goes to
+// the next round's frontier.
+constexpr int kFindChunk = 64, kFindA = 2048, kFindC = 2048;
+__global__ __launch_bounds__(kBlock) void k_inc_find(
+    IncP P, int32_t epoch, int32_t a0, int round, int max_levels, int last,
+    int32_t *ic) {
+  __shared__ int32_t la[kFindA], lc[kFindC];
+  __shared__ uint2 lr[kFindA];   // in-edge ranges of la
+  __shared__ int32_t s_na, s_nc, s_base, s_stop;
+  if (ic[I_STOP]) return;
+  const int tid = threadIdx.x;
+  const int32_t cnt = ic[I_NF + round];
+  const int32_t *fin = P.f[round & 1];
+  int32_t *fout = P.f[(round + 1) & 1];
+  if (tid == 0) s_stop = 0;
+  // entries [from, to) of an LDS list to a global one (all threads)
+  auto flush = [&](const int32_t *l, int from, int to, int32_t *ctr,
+                   int32_t *out, int32_t cap) {
+    if (from >= to) return;
+    __syncthreads();
+    if (tid == 0) s_base = atomicAdd(ctr, to - from);
+    __syncthreads();
+    for (int i = from + tid; i < to; i += kBlock) {
+      const int32_t at = s_base + (i - from);
+      if (at < cap) out[at] = l[i];
+      else s_stop = 1;
+    }
+    __syncthreads();
+  };
+  for (int32_t c0 = blockIdx.x * kFindChunk; c0 < cnt;
+       c0 += gridDim.x * kFindChunk) {
+    int beg = 0, end = min(kFindChunk, cnt - c0);
+    int flushed = end;   // the frontier is in A's list already
+    __syncthreads();
+    if (tid < end) {
+      const int32_t w = fin[c0 + tid];
+      la[tid] = w;
+      lr[tid] = make_uint2(P.in_off[w], P.in_off[w + 1]);
+    }
+    if (tid == 0) {
+      s_na = end;
+      s_nc = 0;
+    }
+    __syncthreads();
+    for (int level = 0; beg < end; ++level) {
+      if (level >= max_levels || end - beg > kFindA / 2) {
+        flush(la, beg, end, &ic[I_NF + round + 1], fout, P.f_cap);
+        if (last && tid == 0) s_stop = 1;
+        break;
+      }
+      const int L = find_lanes(end - beg, kBlock);
+      for (int i0 = beg; i0 < end; i0 += kBlock / L) {
+        const int i = i0 + tid / L;
+        uint32_t e = 0, e1 = 0;
+        int32_t w = -1;
+        if (i < end) {
+          w = la[i];
+          e = lr[i].x + tid % L;
+          e1 = lr[i].y;
+          if (e1 > e + (uint32_t)kIncMaxDegree) {
+            s_stop = 1;
+            e1 = 0;
+          }
+        }
+        for (; __ballot(e < e1); e += L) {
+          const bool live = e < e1;
+          const uint32_t x = live ? P.in[e] : 0u;
+          uint2 range;
+          const bool a = inc_edge(P, epoch, w, x, live, L, &range);
+          const bool c = live && (x >> 31);
+          const int32_t u = (int32_t)(x & 0x7fffffffu);
+          const int pc = wave_place(&s_nc, c);
+          if (c && pc < kFindC) lc[pc] = u;
+          const int pa = wave_place(&s_na, a);
+          if (a && pa < kFindA) {
+            la[pa] = u;
+            lr[pa] = range;
+          }
+          // past the LDS lists (rare): to the global ones
+          const bool oc = c && pc >= kFindC, oa = a && pa >= kFindA;
+          if (__ballot(oc)) {
+            const int32_t at = wave_place(&ic[I_NC], oc);
+            if (oc && at < P.cl_cap) P.cl[at] = u;
+            else if (oc) s_stop = 1;
+          }
+          if (__ballot(oa)) {
+            const int32_t at = wave_place(&ic[I_NA], oa);
+            const int32_t af = wave_place(&ic[I_NF + round + 1], oa);
+            if (oa && last) s_stop = 1;
+            if (oa && (a0 + at >= P.list_cap || af >= P.f_cap)) s_stop = 1;
+            else if (oa) {
+              P.list[a0 + at] = u;
+              fout[af] = u;
+            }
+          }
+        }
+      }
+      __syncthreads();
+      const int na = min(s_na, kFindA), nc = min(s_nc, kFindC);
+      __syncthreads();
+      beg = end;
+      end = na;
+      if (nc > kFindC / 2) {
+        flush(lc, 0, nc, &ic[I_NC], P.cl, P.cl_cap);
+        if (tid == 0) s_nc = 0;
+      }
+      if (end > kFindA / 2) {
+        // the level moves to the front of the list
+        flush(la, flushed, end, &ic[I_NA], P.list + a0, P.list_cap - a0);
+        const int n = end - beg;
+        if (n <= kFindA / 2) {
+          int32_t t[kFindA / 2 / kBlock];
+          uint2 tr[kFindA / 2 / kBlock];
+#pragma unroll
+          for (int k = 0; k < kFindA / 2 / kBlock; ++k) {
+            const int i = k * kBlock + tid;
+            t[k] = i < n ? la[beg + i] : 0;
+            tr[k] = i < n ? lr[beg + i] : make_uint2(0u, 0u);
+          }
+          __syncthreads();
+#pragma unroll
+          for (int k = 0; k < kFindA / 2 / kBlock; ++k) {
+            const int i = k * kBlock + tid;
+            if (i < n) {
+              la[i] = t[k];
+              lr[i] = tr[k];
+            }
+          }
+          beg = 0;
+          end = n;
+          if (tid == 0) s_na = n;
+        }
+        flushed = end;
+      }
+      __syncthreads();
+    }
+    flush(la, flushed, end, &ic[I_NA], P.list + a0, P.list_cap - a0);
+    __syncthreads();
+    flush(lc, 0, min(s_nc, kFindC), &ic[I_NC], P.cl, P.cl_cap);
+  }
+  __syncthreads();
+  if (tid == 0 && s_stop) atomicOr(&ic[I_STOP], 1);
+}
+
+__global__ __launch_bounds__(kBlock) void k_inc_walk(IncP P, int32_t a0,
+                                                     int steps, int pass,
+                                                     int last, int32_t *ic) {
+  if (ic[I_STOP] || (pass > 0 && !ic[I_NF + kIncRounds + pass])) return;
+  const int32_t n = ic[I_NA];
+  bool open = false;
+  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += gridDim.x * blockDim.x) {
+    const int32_t v = P.list[a0 + i];
+    if (pass > 0 && ld_relaxed(&P.ng[v]) >= 0) continue;
+    open |= !inc_walk(P, &ic[I_ERR], v, steps);
+  }
+  if (open) atomicOr(last ? &ic[I_STOP] : &ic[I_NF + kIncRounds + pass + 1],
+                     1);
+}
+
+__global__ __launch_bounds__(kBlock) void k_inc_fate(IncP P, int32_t epoch,
+                                                     int32_t a0, int32_t *ic) {
+  if (ic[I_STOP]) return;
+  const int32_t n = ic[I_NA];
+  bool open = false;
+  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += gridDim.x * blockDim.x)
+    open |= !inc_fate(P, epoch, P.list[a0 + i]);
+  if (open) atomicOr(&ic[I_STOP], 1);
+}
+
+// The rule for every candidate.
+__global__ __launch_bounds__(kBlock) void k_inc_decide(IncP P, int32_t epoch,
+                                                       int odd, int2 *dec,
+                                                       int32_t *ic) {
+  if (ic[I_STOP]) return;
+  const int32_t n = ic[I_NC];
+  bool stop = false;
+  for (int32_t i0 = blockIdx.x * blockDim.x; i0 < n;
+       i0 += gridDim.x * blockDim.x) {
+    const int32_t i = i0 + threadIdx.x;
+    bool sw = false;
+    int32_t v = 0, to = 0;
+    if (i < n) {
+      v = P.cl[i];
+      if (!odd || atomicExch(&P.cmark[v], epoch) != epoch)
+        sw = inc_decide(P, v, odd != 0, &to, &stop);
+    }
+    const int32_t p = wave_place(&ic[I_NDEC], sw);
+    if (sw) dec[p] = make_int2(v, to);
+  }
+  if (stop) atomicOr(&ic[I_STOP], 1);
+}
+
+// The Even vertices with an option among the vertices changed since the
+// last All_Even (list[0..nd)).
+__global__ __launch_bounds__(kBlock) void k_inc_even_cand(IncP P,
+                                                          int32_t epoch,
+                                                          int32_t nd,
+                                                          int32_t *ic) {
+  for (int32_t i0 = blockIdx.x * blockDim.x; i0 < nd;
+       i0 += gridDim.x * blockDim.x) {
+    const int32_t i = i0 + threadIdx.x;
+    uint32_t e = 0, e1 = 0;
+    if (i < nd) {
+      const int32_t w = P.list[i];
+      e = P.in_off[w];
+      e1 = P.in_off[w + 1];
+    }
+    for (; __ballot(e < e1); ++e) {
+      const uint32_t x = e < e1 ? P.in[e] : 0x80000000u;
+      const bool c =
+          e < e1 && !(x >> 31) && atomicExch(&P.cmark[x], epoch) != epoch;
+      const int32_t p = wave_place(&ic[I_NC], c);
+      if (c) P.cl[p] = (int32_t)x;
+    }
+  }
+}
+
+// All_Even over every Even vertex, keys clean or dirty; decisions only.
+constexpr int kEvenBlock = 1024;
+__global__ __launch_bounds__(kEvenBlock) void k_inc_even_all(
+    IncP P, int64_t count, const int32_t *__restrict__ ids, int2 *dec,
+    int32_t *ic) {
+  __shared__ int32_t n, base;
+  if (threadIdx.x == 0) n = 0;
+  __syncthreads();
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  bool sw = false, stop = false;
+  int32_t v = 0, to = 0;
+  if (t < count) {
+    v = ids[t];
+    sw = inc_decide(P, v, false, &to, &stop);
+  }
+  const int32_t at = wave_place(&n, sw);
+  __syncthreads();
+  if (threadIdx.x == 0 && n) base = atomicAdd(&ic[I_NDEC], n);
+  __syncthreads();
+  if (sw) dec[base + at] = make_int2(v, to);
+  if (stop) atomicOr(&ic[I_STOP], 1);
+}
+
+// Applies decisions before a full valuation or an export.
+__global__ __launch_bounds__(kBlock) void k_inc_commit(
+    const int2 *__restrict__ dec, int32_t n, const int32_t *__restrict__ pri,
+    int32_t N, int2 *sp) {
+  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int2 d = dec[i];
+  sp[d.x] = make_int2(d.y, d.y == N ? 2147483647 : pri[d.y]);
+}
+
+// ---------------------------------------------------------------------------
+// the block form
+// ---------------------------------------------------------------------------
+// One block runs valuations and switch steps until nothing switches, a cap
+// is reached, or a step outgrows it.  Every dependent access costs a
+// round trip to the L2, so its steps are bound by the length of their
+// chains (the depth of A, the ng chains), not by their size.
+constexpr int kIncThreads = 1024;
+constexpr int32_t kBlockA = 4096;  // most vertices of its A (LDS)
+constexpr int kBlockEven = 8192;   // most changed vertices of its All_Even
+enum IncState : int {
+  IS_GROWN = 0,    // the pending decisions need the device form (or full)
+  IS_BR = 1,       // best response reached; All_Even is the host's
+  IS_SOLVED = 2,   // All_Even switched nothing: the run is over
+  IS_CAP = 3,      // an iteration cap: decisions pending
+};
+
+struct IncRun {
+  int32_t epoch, a0, nsw, cur;   // pending decisions: dec[cur], nsw of them
+  int32_t a_cap;                 // most vertices of one step's A
+  int32_t val_cap;               // most valuations of this launch
+  int32_t inner_cap, inner;      // valuations of this best response (0: none)
+  int32_t major_cap, major;      // outer iterations (0: none)
+  int32_t d_valid;               // list[0..a0) holds every change since the
+                                 // last All_Even
+  int32_t with_even;             // run All_Even and go on
+};
+
+__global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
+                                                           int2 *dec0,
+                                                           int2 *dec1,
+                                                           int32_t *ic) {
+  __shared__ int32_t la[kBlockA];   // A
+  __shared__ uint2 lr[kBlockA];     // its in-edge ranges
+  __shared__ int32_t s_na, s_nc, s_nd, s_stop, s_open, s_err;
+  const int tid = threadIdx.x;
+  int32_t nval = 0, oddsw = 0, evensw = 0, state = IS_GROWN;
+  if (tid == 0) s_err = 0;
+  for (;;) {
+    if (nval >= R.val_cap) break;
+    const int2 *din = R.cur ? dec1 : dec0;
+    int2 *dout = R.cur ? dec0 : dec1;
+    if (R.nsw > R.a_cap || R.a0 + R.a_cap > P.list_cap) break;
+    const int32_t epoch = R.epoch++;
+    if (tid == 0) {
+      s_na = R.nsw;
+      s_nc = 0;
+      s_nd = 0;
+      s_stop = 0;
+    }
+    for (int32_t i = tid; i < R.nsw; i += kIncThreads) {
+      const int2 d = din[i];
+      inc_apply(P, epoch, d);
+      la[i] = d.x;
+      lr[i] = make_uint2(P.in_off[d.x], P.in_off[d.x + 1]);
+    }
+    __syncthreads();
+    // find, level by level: a level is a stretch of the list
+    int32_t beg = 0, end = R.nsw;
+    while (beg < end) {
+      const int L = find_lanes(end - beg, kIncThreads);
+      for (int32_t i0 = beg; i0 < end; i0 += kIncThreads / L) {
+        const int32_t i = i0 + tid / L;
+        uint32_t e = 0, e1 = 0;
+        int32_t w = -1;
+        if (i < end) {
+          w = la[i];
+          e = lr[i].x + tid % L;
+          e1 = lr[i].y;
+          if (e1 > e + (uint32_t)kIncMaxDegree) {
+            s_stop = 1;
+            e1 = 0;
+          }
+        }
+        for (; __ballot(e < e1); e += L) {
+          const bool live = e < e1;
+          const uint32_t x = live ? P.in[e] : 0u;
+          uint2 range;
+          const bool a = inc_edge(P, epoch, w, x, live, L, &range);
+          const bool c = live && (x >> 31);
+          const int32_t u = (int32_t)(x & 0x7fffffffu);
+          const int32_t pc = wave_place(&s_nc, c);
+          if (c && pc < P.cl_cap) P.cl[pc] = u;
+          const int32_t pa = wave_place(&s_na, a);
+          if (a && pa < R.a_cap) {
+            la[pa] = u;
+            lr[pa] = range;
+          }
+        }
+      }
+      __syncthreads();
+      beg = end;
+      end = s_na;
+      if (end > R.a_cap || s_nc > P.cl_cap || s_stop) break;
+      __syncthreads();
+    }
+    // (every thread leaves the loop with the same beg and end)
+    if (end > R.a_cap || s_nc > P.cl_cap || s_stop) break;
+    const int32_t na = end;
+    for (int32_t i = tid; i < na; i += kIncThreads) P.list[R.a0 + i] = la[i];
+    // walks: passes until none is open
+    bool failed = true;
+    for (int pass = 0; pass < 8; ++pass) {
+      if (tid == 0) s_open = 0;
+      __syncthreads();
+      for (int32_t i = tid; i < na; i += kIncThreads) {
+        const int32_t v = la[i];
+        if (ld_relaxed(&P.ng[v]) >= 0) continue;
+        if (!inc_walk(P, &s_err, v, 64)) s_open = 1;
+      }
+      __syncthreads();
+      const bool open = s_open != 0;
+      __syncthreads();
+      if (!open) {
+        failed = false;
+        break;
+      }
+    }
+    if (failed) break;
+    for (int32_t i = tid; i < na; i += kIncThreads)
+      if (!inc_fate(P, epoch, la[i])) s_stop = 1;
+    __syncthreads();
+    const int32_t nc = s_nc;
+    const bool bad = s_stop || s_err;
+    __syncthreads();   // the next phase writes s_stop
+    if (bad) break;
+    for (int32_t i0 = 0; i0 < nc; i0 += kIncThreads) {
+      const int32_t i = i0 + tid;
+      bool sw = false, stop = false;
+      int32_t v = 0, to = 0;
+      if (i < nc) {
+        v = P.cl[i];
+        if (atomicExch(&P.cmark[v], epoch) != epoch)
+          sw = inc_decide(P, v, true, &to, &stop);
+      }
+      if (stop) s_stop = 1;
+      const int32_t p = wave_place(&s_nd, sw);
+      if (sw) dout[p] = make_int2(v, to);
+    }
+    __syncthreads();
+    if (s_stop) break;
+    // the valuation and its All_Odd step are done
+    const int32_t nd = s_nd;
+    __syncthreads();
+    ++nval;
+    ++R.inner;
+    R.a0 += na;
+    oddsw += nd;
+    R.nsw = nd;
+    R.cur ^= 1;
+    if (nd > 0) {
+      if (R.inner_cap > 0 && R.inner >= R.inner_cap) {
+        state = IS_CAP;
+        break;
+      }
+      continue;
+    }
+    // a best response
+    state = IS_BR;
+    if (!R.with_even || !R.d_valid || R.a0 > kBlockEven) break;
+    const int32_t ep2 = R.epoch++;
+    int2 *eout = R.cur ? dec1 : dec0;
+    if (tid == 0) {
+      s_nc = 0;
+      s_nd = 0;
+    }
+    __syncthreads();
+    for (int32_t i0 = 0; i0 < R.a0; i0 += kIncThreads) {
+      const int32_t i = i0 + tid;
+      uint32_t e = 0, e1 = 0;
+      if (i < R.a0) {
+        const int32_t w = P.list[i];
+        e = P.in_off[w];
+        e1 = P.in_off[w + 1];
+      }
+      for (; __ballot(e < e1); ++e) {
+        const uint32_t x = e < e1 ? P.in[e] : 0x80000000u;
+        const bool c =
+            e < e1 && !(x >> 31) && atomicExch(&P.cmark[x], ep2) != ep2;
+        const int32_t p = wave_place(&s_nc, c);
+        if (c) P.cl[p] = (int32_t)x;
+      }
+    }
+    __syncthreads();
+    const int32_t ne = s_nc;
+    for (int32_t i0 = 0; i0 < ne; i0 += kIncThreads) {
+      const int32_t i = i0 + tid;
+      bool sw = false, stop = false;
+      int32_t v = 0, to = 0;
+      if (i < ne) {
+        v = P.cl[i];
+        sw = inc_decide(P, v, false, &to, &stop);
+      }
+      if (stop) s_stop = 1;
+      const int32_t p = wave_place(&s_nd, sw);
+      if (sw) eout[p] = make_int2(v, to);
+    }
+    __syncthreads();
+    if (s_stop) break;   // the host's All_Even (it starts over)
+    const int32_t sw = s_nd;
+    __syncthreads();
+    evensw += sw;
+    R.nsw = sw;
+    R.a0 = 0;
+    if (sw == 0) {
+      state = IS_SOLVED;
+      break;
+    }
+    if (R.major_cap > 0 && R.major >= R.major_cap) {
+      state = IS_CAP;
+      R.inner = 0;
+      break;
+    }
+    ++R.major;
+    R.inner = 0;
+    state = IS_GROWN;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    ic[I_ERR] = s_err;
+    ic[I_STATE] = state;
+    ic[I_NVAL] = nval;
+    ic[I_ODDSW] = oddsw;
+    ic[I_EVENSW] = evensw;
+    ic[I_MAJOR] = R.major;
+    ic[I_INNER] = R.inner;
+    ic[I_A0] = R.a0;
+    ic[I_CUR] = R.cur;
+    ic[I_NDEC] = R.nsw;
+    ic[I_EPOCH] = R.epoch;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+// A step starts when at most one vertex in kIncSwitchShare switched (A is
+// two to six times the switched vertices on the workloads), in the block
+// form up to kBlockSwitches of them.
+constexpr int64_t kIncSwitchShare = 24;
+constexpr int32_t kBlockSwitches = 512;
+constexpr int32_t kBlockVals = 64;
+
+static IncP inc_params(const pg_game *g) {
+  const int32_t N = (int32_t)g->n_aug;
+  IncP P;
+  P.N = N;
+  P.n_oddpri = g->n_oddpri;
+  P.off = g->off;
+  P.tgt = g->tgt;
+  P.pri = g->pri;
+  P.in_off = g->inc.in_off;
+  P.in = g->inc.in;
+  P.sp = g->sp;
+  P.key = g->key;
+  P.ng = g->ng;
+  P.cand = g->cand;
+  P.rs = g->rs;
+  P.mark = g->inc.mark;
+  P.cmark = g->inc.cmark;
+  // the Euler list's records (4 N ints) and the parent sort's keys (N each)
+  // are free between full valuations
+  P.list = reinterpret_cast<int32_t *>(g->aux);
+  P.list_cap = 2 * N;
+  P.cl = P.list + 2 * (int64_t)N;
+  P.cl_cap = 2 * N;
+  P.f[0] = reinterpret_cast<int32_t *>(g->sk0);
+  P.f[1] = reinterpret_cast<int32_t *>(g->sk1);
+  P.f_cap = N;
+  return P;
+}
+
+// The decision lists live in the Euler list's elements (2 N pairs); the
+// full valuation's All_Odd lists its switches in the first.
+static int2 *inc_dec(const pg_game *g, int i) { return g->elem + i * g->n_aug; }
+
+bool inc_eligible(const pg_game *g) {
+  return !g->dense && g->relabeled && !g->careful && !g->host_rl &&
+         g->n_aug >= 2 && g->m_aug < (int64_t(1) << 31) &&
+         (g->tsw || g->n_odd <= kIncRowOdd);
+}
+
+// Builds the in-edge lists at the first solve of a game.  Without memory
+// for them the game keeps full valuations.
+bool inc_prepare(pg_game *g, hipStream_t s) {
+  pg_game::Inc &x = g->inc;
+  x.dirty = x.pending = x.d_valid = x.grown = x.even = false;
+  x.nsw = x.a0 = 0;
+  x.skip = x.back = 0;
+  x.on = false;
+  if (x.state < 0 || !inc_eligible(g)) return false;
+  const int64_t N = g->n_aug, M = g->m_aug;
+  if (x.state == 0) {
+    pg_status st = dev_alloc(&x.in_off, N + 1);
+    if (st == PG_OK) st = dev_alloc(&x.in, M);
+    if (st == PG_OK) st = dev_alloc(&x.mark, N);
+    if (st == PG_OK) st = dev_alloc(&x.cmark, N);
+    if (st == PG_OK) st = dev_alloc(&x.ic, I_WORDS);
+    if (st == PG_OK)
+      st = host_alloc((void **)&x.h, sizeof(int32_t) * I_WORDS);
+    if (st != PG_OK) {
+      inc_release(g);
+      x.state = -1;
+      pg_fail(PG_OK, "");
+      return false;
+    }
+    fill_i32((int32_t *)x.in_off, 0, N, s);
+    hipLaunchKernelGGL(k_in_count, dim3(grid_for(M)), dim3(kBlock), 0, s,
+                       g->tgt, x.in_off, M);
+    scan_excl_u32(x.in_off, x.in_off, N, g->scan_tmp, s);
+    fill_i32((int32_t *)x.in_off + N, (int32_t)M, 1, s);
+    uint32_t *cursor = reinterpret_cast<uint32_t *>(g->elem);
+    hipLaunchKernelGGL(k_copy_u32, dim3(grid_for(N)), dim3(kBlock), 0, s,
+                       x.in_off, cursor, N);
+    hipLaunchKernelGGL(k_in_fill, dim3(grid_for(N)), dim3(kBlock), 0, s,
+                       g->off, g->tgt, g->owner, cursor, x.in, (int32_t)N);
+    fill_i32(x.mark, 0, N, s);
+    fill_i32(x.cmark, 0, N, s);
+    x.epoch = 0;
+    x.state = 1;
+  } else if (x.epoch > (1 << 30)) {
+    fill_i32(x.mark, 0, N, s);
+    fill_i32(x.cmark, 0, N, s);
+    x.epoch = 0;
+  }
+  x.on = true;
+  return true;
+}
+
+void inc_release(pg_game *g) {
+  pg_game::Inc &x = g->inc;
+  void *ptrs[] = {x.in_off, x.in, x.mark, x.cmark, x.ic};
+  for (void *p : ptrs) dev_free(p);
+  host_free(x.h);
+  x = pg_game::Inc();
+}
+
+static pg_status inc_read(pg_game *g, hipStream_t s) {
+  PG_HIP(hipMemcpyAsync(g->inc.h, g->inc.ic, sizeof(int32_t) * I_WORDS,
+                        hipMemcpyDeviceToHost, s));
+  PG_HIP(hipStreamSynchronize(s));
+  if (g->prof.on) g->prof.flush();
+  if (g->inc.h[I_ERR] & ERR_INADMISSIBLE)
+    return pg_fail(PG_EINADMISSIBLE,
+                   "the play graph has a cycle whose largest priority is odd");
+  return PG_OK;
+}
+
+// Puts the pending decisions into the play graph.
+void inc_commit(pg_game *g, hipStream_t s) {
+  pg_game::Inc &x = g->inc;
+  if (!x.on || !x.pending) return;
+  x.pending = false;
+  if (x.nsw > 0)
+    PG_LAUNCH(&g->prof, K_OTHER, 24.0 * x.nsw, k_inc_commit,
+              dim3(grid_for(x.nsw)), dim3(kBlock), 0, s, inc_dec(g, x.cur),
+              x.nsw, g->pri, (int32_t)g->n_aug, g->sp);
+}
+
+bool inc_ready(const pg_game *g) {
+  const pg_game::Inc &x = g->inc;
+  return x.on && x.pending && x.skip == 0 &&
+         ((int64_t)x.nsw * kIncSwitchShare <= g->n_aug ||
+          g->n_aug <= kBlockA);
+}
+
+// Before a full valuation of a run (which finds every fate again if the
+// changed-part steps may have left some behind).
+void inc_before_full(pg_game *g, hipStream_t s) {
+  pg_game::Inc &x = g->inc;
+  if (!x.on) return;
+  inc_commit(g, s);
+  if (x.dirty || x.even) fates_reset(g, s);
+  x.even = false;
+  if (x.skip > 0) --x.skip;
+}
+
+void inc_after_full(pg_game *g, int32_t switches) {
+  pg_game::Inc &x = g->inc;
+  if (!x.on) return;
+  x.dirty = false;
+  x.d_valid = false;
+  x.a0 = 0;
+  x.grown = false;
+  x.pending = true;   // already in the play graph: applying them is harmless
+  x.cur = 0;
+  x.nsw = switches;
+}
+
+bool inc_dirty(const pg_game *g) { return g->inc.on && g->inc.dirty; }
+
+// A step that gave up: full valuations for a while.
+static void inc_backoff(pg_game *g) {
+  pg_game::Inc &x = g->inc;
+  x.back = x.back ? std::min(2 * x.back, 16) : 1;
+  x.skip = x.back;
+}
+
+// One step (device form) or a run of steps (block form) from the pending
+// decisions.
+pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
+                   int32_t max_inner, int32_t max_major, IncOut *out) {
+  pg_game::Inc &x = g->inc;
+  const IncP P = inc_params(g);
+  Prof *pf = &g->prof;
+  const int32_t N = P.N;
+  if (x.a0 > N) {   // no room for another step: forget the older changes
+    x.a0 = 0;
+    x.d_valid = false;
+  }
+  x.dirty = true;
+  if (g->timed && !g->ev_a) {
+    PG_HIP(hipEventCreate(&g->ev_a));
+    PG_HIP(hipEventCreate(&g->ev_b));
+  }
+  if (g->timed) PG_HIP(hipEventRecord(g->ev_a, s));
+  const bool block =
+      !x.grown && (x.nsw <= kBlockSwitches || N <= kBlockA);
+  x.grown = false;
+  *out = IncOut();
+  out->state = INC_MORE;
+  if (block) {
+    IncRun R;
+    R.epoch = x.epoch + 1;
+    R.a0 = x.a0;
+    R.nsw = x.nsw;
+    R.cur = x.cur;
+    R.a_cap = std::min(kBlockA, N);
+    R.val_cap = kBlockVals;
+    R.inner_cap = max_inner;
+    R.inner = x.inner;
+    R.major_cap = max_major;
+    R.major = x.major;
+    R.d_valid = x.d_valid;
+    R.with_even = with_even;
+    PG_LAUNCH(pf, K_INC_BLOCK, 0.0, k_inc_block, dim3(1), dim3(kIncThreads),
+              0, s, P, R, inc_dec(g, 0), inc_dec(g, 1), x.ic);
+  } else {
+    const int32_t epoch = ++x.epoch;
+    const unsigned gb =
+        std::min<unsigned>(kIncBlocks, grid_for(4 * (int64_t)x.nsw));
+    const dim3 grid(std::max(gb, 64u)), blk(kBlock);
+    const dim3 fgrid(std::min<unsigned>(2048, grid_for(x.nsw, kFindChunk)));
+    fill_i32(x.ic, 0, I_WORDS, s, pf);
+    PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_begin, dim3(grid_for(x.nsw)), blk, 0,
+              s, P, epoch, x.a0, inc_dec(g, x.cur), x.nsw, x.ic);
+    for (int r = 0; r < kFindRounds; ++r)
+      PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_find, fgrid, blk, 0, s, P, epoch,
+                x.a0, r, kFindLevels, (int)(r == kFindRounds - 1), x.ic);
+    PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0, 64,
+              0, 0, x.ic);
+    PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0, 256,
+              1, 1, x.ic);
+    PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_fate, grid, blk, 0, s, P, epoch,
+              x.a0, x.ic);
+    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide, grid, blk, 0, s, P, epoch, 1,
+              inc_dec(g, x.cur ^ 1), x.ic);
+  }
+  if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
+  PG_TRY(inc_read(g, s));
+  if (!g->timed ||
+      hipEventElapsedTime(&g->last_ms, g->ev_a, g->ev_b) != hipSuccess)
+    g->last_ms = 0.0f;
+  if (block) {
+    x.epoch = x.h[I_EPOCH];
+    x.a0 = x.h[I_A0];
+    x.cur = x.h[I_CUR];
+    x.nsw = x.h[I_NDEC];
+    x.inner = x.h[I_INNER];
+    x.major = x.h[I_MAJOR];
+    out->nval = x.h[I_NVAL];
+    out->odd = x.h[I_ODDSW];
+    out->even = x.h[I_EVENSW];
+    switch (x.h[I_STATE]) {
+      case IS_BR: out->state = INC_BR; break;
+      case IS_SOLVED: out->state = INC_SOLVED; break;
+      case IS_CAP:
+        if (x.inner == 0) out->state = INC_CAP;
+        break;
+      default:
+        if (out->nval >= kBlockVals) break;
+        // the pending step is too large for one block (or, in a game that
+        // always fits one, beyond another bound)
+        if (N > kBlockA) x.grown = true;
+        else inc_backoff(g);
+        break;
+    }
+  } else if (x.h[I_STOP]) {
+    inc_backoff(g);
+  } else {
+    x.back = 0;
+    x.a0 += x.h[I_NA];
+    x.cur ^= 1;
+    x.nsw = x.h[I_NDEC];
+    ++x.inner;
+    out->nval = 1;
+    out->odd = x.nsw;
+    if (x.nsw == 0) out->state = INC_BR;
+  }
+  return PG_OK;
+}
+
+// All_Even after a best response; its switches are pending afterwards.
+pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count) {
+  pg_game::Inc &x = g->inc;
+  const IncP P = inc_params(g);
+  Prof *pf = &g->prof;
+  const int64_t ne = g->n_aug - g->n_odd;
+  x.h[I_STOP] = 1;
+  if (x.d_valid && (int64_t)x.a0 * 8 <= g->n_aug) {
+    fill_i32(x.ic, 0, I_WORDS, s, pf);
+    const dim3 grid(std::max(
+        std::min<unsigned>(kIncBlocks, grid_for(4 * (int64_t)x.a0)), 64u));
+    PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_even_cand, grid, dim3(kBlock), 0, s,
+              P, ++x.epoch, x.a0, x.ic);
+    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide, grid, dim3(kBlock), 0, s,
+              P, x.epoch, 0, inc_dec(g, 0), x.ic);
+    PG_TRY(inc_read(g, s));
+  }
+  for (int pass = 0; x.h[I_STOP]; ++pass) {
+    if (pass > 0) {   // a comparison outgrew its bound: clean keys first
+      fates_reset(g, s);
+      PG_TRY(valuation_device(g, s, nullptr));
+      x.dirty = false;
+    }
+    fill_i32(x.ic, 0, I_WORDS, s, pf);
+    if (ne > 0)
+      PG_LAUNCH(pf, K_EVEN_SWITCH, 28.0 * ne + 8.0 * (g->m_aug - g->m_odd),
+                k_inc_even_all, dim3(grid_for(ne, kEvenBlock)),
+                dim3(kEvenBlock), 0, s, P, ne, g->even_ids, inc_dec(g, 0),
+                x.ic);
+    PG_TRY(inc_read(g, s));
+  }
+  x.pending = x.even = true;
+  x.grown = false;
+  x.cur = 0;
+  x.nsw = *count = x.h[I_NDEC];
+  x.a0 = 0;
+  x.d_valid = true;
+  return PG_OK;
+}
+
+}  // namespace pgk

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kTswMinBlock) void k_tsw_min(
     int64_t no, const int32_t *__restrict__ ids, const int32_t *__restrict__ bs,
     const int32_t *__restrict__ r, const int32_t *__restrict__ tz,
     const uint16_t *__restrict__ sz, const int32_t *__restrict__ key,
-    const int32_t *__restrict__ pri, int2 *sp, int32_t *ctr) {
+    const int32_t *__restrict__ pri, int2 *sp, int32_t *ctr, int2 *dec) {
   if (ctr[C_ABORT]) return;
   __shared__ unsigned long long best[kTswBucket];
   __shared__ int32_t curt[kTswBucket], curk[kTswBucket];
@@ -189,17 +189,41 @@ __global__ __launch_bounds__(kTswMinBlock) void k_tsw_min(
   }
   __syncthreads();
   int sw = 0;
-  for (int i = threadIdx.x; i < ns; i += kTswMinBlock) {
+  int32_t sv[kTswBucket / kTswMinBlock], stg[kTswBucket / kTswMinBlock];
+#pragma unroll
+  for (int q = 0; q < kTswBucket / kTswMinBlock; ++q) {
+    const int i = q * kTswMinBlock + threadIdx.x;
+    sv[q] = -1;
+    stg[q] = 0;
+    if (i >= ns) continue;
     const unsigned long long x = best[i];
     const int32_t kb = (int32_t)(x >> 32), bt = (int32_t)(uint32_t)x;
     int32_t kc = curk[i];
     if (kc < 0) kc = key[curt[i]];   // a current choice outside the row
     if (kb < kc) {
-      sp[ids[o0 + i]] = make_int2(bt, pri[bt]);
+      const int32_t v = ids[o0 + i];
+      sp[v] = make_int2(bt, pri[bt]);
+      sv[q] = v;
+      stg[q] = bt;
       ++sw;
     }
   }
-  add_block(&ctr[C_DIST_SW], sw);
+  // the switch list: places from an LDS count, the block's from one device
+  // atomic
+  __shared__ int32_t s_n, s_base;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  int32_t at = 0;
+  if (sw) at = atomicAdd(&s_n, sw);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_n) {
+    s_base = atomicAdd(&ctr[C_NDEC], s_n);
+    atomicAdd(&ctr[C_DIST_SW + (blockIdx.x % kDistSlots) * kDistStride], s_n);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kTswBucket / kTswMinBlock; ++q)
+    if (sv[q] >= 0) dec[s_base + at++] = make_int2(sv[q], stg[q]);
 }
 
 // ---- host side -------------------------------------------------------------
@@ -313,7 +337,7 @@ void enqueue_tsw_odd(pg_game *g, hipStream_t s) {
   // figure: the step's algorithmic bytes do not depend on the layout)
   PG_LAUNCH(pf, K_ODD_SWITCH, 28.0 * no, k_tsw_min, dim3((unsigned)g->tsw_nb),
             dim3(kTswMinBlock), 0, s, no, g->odd_ids, g->tsw_bs, g->tsw_r,
-            g->tsw_tz, g->tsw_sz, g->key, g->pri, g->sp, g->ctr);
+            g->tsw_tz, g->tsw_sz, g->key, g->pri, g->sp, g->ctr, g->elem);
 }
 
 }  // namespace pgk

@@ -721,10 +721,11 @@ __global__ __launch_bounds__(kBlock) void k_odd_switch(
     int32_t N, int64_t count, const int32_t *__restrict__ ids,
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
     const int32_t *__restrict__ key, const int32_t *__restrict__ pri, int2 *sp,
-    int32_t *ctr) {
+    int32_t *ctr, int2 *dec) {
   if (ctr[C_ABORT]) return;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool sw = false;
+  int32_t swv = 0, swt = 0;
   const int2 me = t < count ? sp[ids[t]] : make_int2(0, kTopMark);
   // a vertex known to stay top has only top successors: no switch
   if (me.y != kTopMark) {
@@ -753,9 +754,12 @@ __global__ __launch_bounds__(kBlock) void k_odd_switch(
     if (kb < kc) {
       sp[v] = make_int2(best, pri[best]);
       sw = true;
+      swv = v;
+      swt = best;
     }
   }
   count_block(&ctr[C_DIST_SW], sw);
+  if (dec) list_block(&ctr[C_NDEC], dec, sw, swv, swt);
 }
 
 // All_Even, greedy all-switches (section 3): options are the sink (first),
@@ -1058,7 +1062,8 @@ static void enqueue_switch(pg_game *g, bool odd, hipStream_t s, bool fresh) {
     if (cnt > 0)
       PG_LAUNCH(pf, K_ODD_SWITCH, 28.0 * cnt + 8.0 * g->m_odd, k_odd_switch,
                 dim3(grid_for(cnt)), dim3(kBlock), 0, s, N, cnt, g->odd_ids,
-                g->off, g->tgt, g->key, g->pri, g->sp, g->ctr);
+                g->off, g->tgt, g->key, g->pri, g->sp, g->ctr,
+                cnt <= kIncRowOdd ? g->elem : (int2 *)nullptr);
   } else {
     const int64_t cnt = N - g->n_odd;
     if (cnt > 0)
