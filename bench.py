@@ -89,8 +89,8 @@ TRAFFIC_FILES = {"c2": "traffic_random10M.json"}
 # the sources of everything a single rank-valuation game's load and solve
 # launch (batches, count valuations and PG_ODD_REGION live in other files)
 SINGLE_GAME_SOURCES = ["pg_api.hip", "pg_common.h", "pg_inc.hip",
-                       "pg_prims.hip", "pg_switch.hip", "pg_tune.hip",
-                       "pg_val.hip"]
+                       "pg_prims.hip", "pg_small.hip", "pg_switch.hip",
+                       "pg_tune.hip", "pg_val.hip"]
 
 
 def sources_sha256() -> str:
@@ -255,7 +255,8 @@ KERNEL_KINDS = {
     "k_inc_begin": "inc_find", "k_inc_find": "inc_find",
     "k_inc_even_cand": "inc_find", "k_inc_walk": "inc_walk",
     "k_inc_fate": "inc_walk", "k_inc_decide": "inc_decide",
-    "k_inc_block": "inc_block", "k_inc_even_all": "even_switch",
+    "k_inc_block": "inc_block", "k_small_run": "small",
+    "k_small_value": "small", "k_inc_even_all": "even_switch",
     "k_sum_dist": "other", "k_rs_upsweep": "sort_hist",
     "k_rs_downsweep": "sort_pass",
 }

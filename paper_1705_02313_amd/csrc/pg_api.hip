@@ -1142,12 +1142,15 @@ struct Run {
   Trace *tr = nullptr;
   int64_t n_major = 0, n_val = 0, n_odd = 0, n_even = 0;
   double iter_ms = 0.0;
+  bool keys = false;   // g->key holds the last valuation's ranks
 };
 
 pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
   const int32_t N = (int32_t)g->n_aug;
   // a trace reports every valuation's ranks
-  const bool inc = !(r->tr && r->tr->o->trace_cap > 0) && inc_prepare(g, s);
+  const bool traced = r->tr && r->tr->o->trace_cap > 0;
+  bool small = g->small && !traced;
+  bool inc = !traced && !small && inc_prepare(g, s);
   if (!inc) g->inc.on = false;
   int32_t &inner = g->inc.inner, &major = g->inc.major;
   major = 0;
@@ -1171,10 +1174,27 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
         inc_commit(g, s);
         return pg_fail(PG_EITERLIMIT, "best response: valuation cap reached");
       }
-      if (inc && inc_ready(g)) {
+      if (small) {
+        IncOut o;
+        bool deep = false;
+        PG_TRY(small_step(g, s, r->br_only, r->reset, r->max_inner,
+                          r->max_major, &deep, &o));
+        r->keys = false;
+        r->iter_ms += g->last_ms;
+        r->n_val += o.nval;
+        r->n_odd += o.odd;
+        r->n_even += o.even;
+        end = o.state;
+        if (deep) {   // the general path goes on from here
+          small = false;
+          inc = inc_prepare(g, s);
+          fates_reset(g, s);
+        }
+      } else if (inc && inc_ready(g)) {
         IncOut o;
         PG_TRY(inc_step(g, s, !r->reset && !r->br_only, r->max_inner,
                         r->max_major, &o));
+        r->keys = false;
         r->iter_ms += g->last_ms;
         r->n_val += o.nval;
         r->n_odd += o.odd;
@@ -1186,6 +1206,7 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
         inc_before_full(g, s);
         PG_TRY(iteration_device(g, s, &c, &nf));
         inc_after_full(g, c);
+        r->keys = true;
         r->iter_ms += g->last_ms;
         if (r->tr) r->tr->record(g, s, c, nf);
         ++inner;
@@ -1268,6 +1289,11 @@ pg_status load_game(int64_t n, int64_t m, const void *offsets,
   g->host_rl = (flags & PG_HOST_REDUCED_LIST) && !g->dense;
   if (st == PG_OK && !g->dense) apply_tuning(g, tuning_for(g->n_aug));
   g->mark_top = true;
+  // the switches that ask for a form of the general path keep it
+  g->small = st == PG_OK && !g->dense && g->relabeled &&
+             !(flags & (PG_CAREFUL_WALKS | PG_NO_GRAPH | PG_HOST_REDUCED_LIST |
+                        PG_SWITCH_ROWS | PG_SWITCH_BUCKETS)) &&
+             small_fits(g->n_aug, g->m_aug);
   return st;
 }
 
@@ -1618,6 +1644,26 @@ pg_status pg_valuation(pg_game *g, const int32_t *sigma, const int32_t *tau,
   PoolScope cache(game_cache(g->device));
   hipStream_t s = (hipStream_t)hip_stream;
   const bool dev = flags & PG_PTR_DEVICE;
+  if (g->small) {
+    const int64_t N = g->n_aug;
+    const int32_t *ds = sigma, *dt = tau;
+    int32_t *dk = key;
+    if (!dev) {
+      PG_TRY(copy_in(g->wl0, sigma, sizeof(int32_t) * N, false, s));
+      PG_TRY(copy_in(g->wl1, tau, sizeof(int32_t) * N, false, s));
+      ds = g->wl0;
+      dt = g->wl1;
+      dk = (int32_t *)g->elem;
+    }
+    bool deep = false;
+    PG_TRY(small_valuation(g, ds, dt, dk, s, &deep, n_finite));
+    if (!deep) {
+      if (dev) return PG_OK;
+      PG_TRY(copy_out(key, dk, sizeof(int32_t) * (N + 1), false, s));
+      PG_HIP(hipStreamSynchronize(s));
+      return PG_OK;
+    }
+  }
   PG_TRY(import_strats(g, sigma, tau, dev, s));
   valuation_reset(g, s);
   PG_TRY(valuation_device(g, s, n_finite));
@@ -1669,12 +1715,19 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
   const pg_status st = run_si(g, &r, s);
   if (n_valuations) *n_valuations = (int32_t)r.n_val;
   if (st != PG_OK) return st;
-  if (key && inc_dirty(g)) {   // the ranks of the vertices changed last
+  bool deep = true;
+  if (key && !r.keys && g->small) {
+    int32_t *dk = dev ? key : (int32_t *)g->elem;
+    PG_TRY(small_valuation(g, nullptr, nullptr, dk, s, &deep, nullptr));
+    if (!deep && !dev)
+      PG_TRY(copy_out(key, dk, sizeof(int32_t) * (g->n_aug + 1), false, s));
+  }
+  if (key && !r.keys && deep) {   // the ranks of the vertices changed last
     fates_reset(g, s);
     PG_TRY(valuation_device(g, s, nullptr));
   }
   PG_TRY(export_strats(g, nullptr, tau, dev, s, false));
-  if (key) PG_TRY(export_keys(g, key, dev, s));
+  if (key && deep) PG_TRY(export_keys(g, key, dev, s));
   PG_HIP(hipStreamSynchronize(s));
   return PG_OK;
 }
@@ -1732,6 +1785,9 @@ pg_status pg_solve_noalloc(int64_t n, int64_t m, const void *offsets,
   g.timed = false;
   pg_status st = load_game(n, m, offsets, targets, owner, priority,
                            flags | PG_NO_GRAPH | PG_SWITCH_ROWS, s, &g);
+  g.small = st == PG_OK && !g.dense && g.relabeled &&
+            !(flags & (PG_CAREFUL_WALKS | PG_NO_GRAPH | PG_SWITCH_ROWS)) &&
+            small_fits(g.n_aug, g.m_aug);
   if (st == PG_OK) st = solve_game(&g, opts, winner, sigma, tau, stats, s);
   // the scratch is free again once the stream has drained
   (void)hipStreamSynchronize(s);

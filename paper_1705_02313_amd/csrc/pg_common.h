@@ -77,7 +77,7 @@ enum KId : int {
   K_SORT_SPLIT, K_SORT_HIST, K_SCAN, K_SORT_PASS, K_LINK_INFO, K_LINK_BUILD,
   K_LR_SUM1, K_LR_SUMK, K_LR_TOP, K_LR_DISTK, K_LR_EMIT1, K_ODD_SWITCH,
   K_EVEN_SWITCH, K_ODD_STAGE, K_INC_FIND, K_INC_WALK, K_INC_DECIDE,
-  K_INC_BLOCK, K_OTHER, K_COUNT
+  K_INC_BLOCK, K_SMALL, K_OTHER, K_COUNT
 };
 extern const char *const kKernelNames[K_COUNT];
 
@@ -280,6 +280,9 @@ struct pg_game {
   int4 *elem4 = nullptr;      // [2*n_aug+2] {next, vertex | up bit, column}
   int32_t *vsum[pgk::kMaxLevels] = {};   // per level: dw ints per splitter
   int32_t *vbase[pgk::kMaxLevels] = {};
+
+  // small games run whole in one block (pg_small.hip)
+  bool small = false;
 
   // valuations by their changed part (pg_inc.hip)
   struct Inc {
@@ -576,6 +579,24 @@ struct IncOut {
 pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
                    int32_t max_inner, int32_t max_major, IncOut *out);
 pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count);
+}  // namespace pgk
+
+// ---- small games (pg_small.hip) ---------------------------------------------
+namespace pgk {
+constexpr int64_t kSmallN = 6144;   // most vertices of a small game
+// N vertices and M edges fit one block's LDS
+bool small_fits(int64_t N, int64_t M);
+// Algorithm 1 from the strategies in g->sp (g->inc.inner and major count on)
+// to the end of what a cap or the launch's budget allows; *deep: the general
+// path must go on (from the same strategies).
+pg_status small_step(pg_game *g, hipStream_t s, bool br_only, bool reset,
+                     int32_t max_inner, int32_t max_major, bool *deep,
+                     IncOut *out);
+// pg_valuation on device arrays in the caller's ids (null sigma: of the
+// strategies in g->sp); *deep: nothing written
+pg_status small_valuation(pg_game *g, const int32_t *sigma, const int32_t *tau,
+                          int32_t *key, hipStream_t s, bool *deep,
+                          int64_t *n_finite);
 }  // namespace pgk
 
 // ---- count valuations (pg_count.hip) ---------------------------------------

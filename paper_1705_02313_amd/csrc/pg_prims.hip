@@ -11,7 +11,7 @@ const char *const kKernelNames[K_COUNT] = {
     "sort_split", "sort_hist", "scan",       "sort_pass",  "link_info",
     "link_build", "lr_sum1",   "lr_sumk",    "lr_top",     "lr_distk",
     "lr_emit1",   "odd_switch", "even_switch", "odd_stage", "inc_find",
-    "inc_walk",   "inc_decide", "inc_block",  "other"};
+    "inc_walk",   "inc_decide", "inc_block",  "small",      "other"};
 
 hipEvent_t Prof::get() {
   if (!pool.empty()) {
