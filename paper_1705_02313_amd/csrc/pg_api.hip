@@ -642,8 +642,8 @@ pg_status sync_ctr(pg_game *g, hipStream_t s) {
   return PG_OK;
 }
 
-void free_game(pg_game *g) {
-  if (!g) return;
+// Returns the game's memory, graphs and events.
+static void drop_buffers(pg_game *g) {
   void *ptrs[] = {g->off,      g->tgt,      g->owner,    g->pri,
                   g->perm,     g->rvpos,    g->odd_ids,  g->even_ids,
                   g->sp,       g->key,      g->ng,       g->cand,
@@ -672,6 +672,11 @@ void free_game(pg_game *g) {
   if (g->ev_a) (void)hipEventDestroy(g->ev_a);
   if (g->ev_b) (void)hipEventDestroy(g->ev_b);
   g->prof.release();
+}
+
+void free_game(pg_game *g) {
+  if (!g) return;
+  drop_buffers(g);
   delete g;
 }
 
@@ -709,7 +714,7 @@ pg_status alloc_state(pg_game *g, int64_t cap) {
   PG_TRY(dev_alloc(&g->kids, N));
   PG_TRY(dev_alloc(&g->fh, N + 1));
   PG_TRY(dev_alloc(&g->pos, N + 1));
-  fill_i32(g->pos, 0, N + 1, 0);
+  if (g->dense) fill_i32(g->pos, 0, N + 1, 0);
   PG_TRY(dev_alloc(&g->elem, 2 * N + 2));
   PG_TRY(dev_alloc(&g->aux, 2 * N + 2));
   // sublist levels for the longest possible Euler list (down to one
@@ -1188,7 +1193,7 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
         if (deep) {   // the general path goes on from here
           small = false;
           inc = inc_prepare(g, s);
-          fates_reset(g, s);
+          valuation_reset(g, s);
         }
       } else if (inc && inc_ready(g)) {
         IncOut o;
@@ -1256,11 +1261,75 @@ pg_status check_load_args(int64_t n, int64_t m, const void *offsets,
   return PG_OK;
 }
 
+// The caller's flags that ask for a form of the general path; PG_ODD_REGION
+// and PG_COUNT_VALUATION games load there too.
+constexpr uint32_t kGeneralFlags =
+    PG_CAREFUL_WALKS | PG_NO_GRAPH | PG_HOST_REDUCED_LIST | PG_SWITCH_ROWS |
+    PG_SWITCH_BUCKETS;
+constexpr uint32_t kGeneralLoad =
+    kGeneralFlags | PG_ODD_REGION | PG_COUNT_VALUATION;
+
+// The small-game load: host arrays are copied to the device first.
+pg_status load_small(int64_t n, int64_t m, const void *offsets,
+                     const int32_t *targets, const uint8_t *owner,
+                     const int32_t *priority, uint32_t flags, hipStream_t s,
+                     pg_game *g, bool *done) {
+  g->n = n;
+  g->m = m;
+  PG_TRY(host_alloc((void **)&g->hctr, sizeof(int32_t) * C_COUNT));
+  PG_TRY(dev_alloc(&g->ctr, C_TOTAL));
+  fill_i32(g->ctr, 0, C_TOTAL, s);
+  struct Tmp {   // in use until the load has synchronised
+    hipStream_t s;
+    std::vector<void *> p;
+    ~Tmp() {
+      if (!p.empty()) (void)hipStreamSynchronize(s);
+      for (void *x : p) dev_free(x);
+    }
+  } tmp{s, {}};
+  if (!(flags & PG_PTR_DEVICE)) {
+    const size_t ob = (flags & PG_OFFSETS_I32) ? 4 : 8;
+    auto stage = [&](const void *src, size_t bytes, const void **out) {
+      uint8_t *d = nullptr;
+      PG_TRY(dev_alloc(&d, (int64_t)bytes));
+      tmp.p.push_back(d);
+      *out = d;
+      return copy_in(d, src, bytes, false, s);
+    };
+    PG_TRY(stage(offsets, ob * (n + 1), &offsets));
+    PG_TRY(stage(targets, 4 * m, (const void **)&targets));
+    PG_TRY(stage(owner, n, (const void **)&owner));
+    PG_TRY(stage(priority, 4 * n, (const void **)&priority));
+  }
+  return small_load(g, n, m, offsets, targets, owner, priority, flags, s,
+                    done);
+}
+
 // pg_load_csr's work on g (g->device set), allocating from the current pool.
+// asked: the caller's own flags (pg_solve_noalloc adds some).
 pg_status load_game(int64_t n, int64_t m, const void *offsets,
                     const int32_t *targets, const uint8_t *owner,
                     const int32_t *priority, uint32_t flags, hipStream_t s,
-                    pg_game *g) {
+                    pg_game *g, uint32_t asked) {
+  if (small_load_fits(n, m) && !(asked & kGeneralLoad)) {
+    bool done = false;
+    PG_TRY(load_small(n, m, offsets, targets, owner, priority, flags, s, g,
+                      &done));
+    if (done) {
+      g->use_graph = !(flags & PG_NO_GRAPH);
+      apply_tuning(g, tuning_for(g->n_aug));
+      g->mark_top = true;
+      g->small = small_fits(g->n_aug, g->m_aug);
+      return PG_OK;
+    }
+    // malformed, or priorities that repeat
+    drop_buffers(g);
+    const int device = g->device;
+    const bool timed = g->timed;
+    *g = pg_game();
+    g->device = device;
+    g->timed = timed;
+  }
   // count valuations when asked for or when the priorities repeat
   pg_status st =
       load_modified(n, m, offsets, targets, owner, priority, flags, s, g,
@@ -1289,11 +1358,8 @@ pg_status load_game(int64_t n, int64_t m, const void *offsets,
   g->host_rl = (flags & PG_HOST_REDUCED_LIST) && !g->dense;
   if (st == PG_OK && !g->dense) apply_tuning(g, tuning_for(g->n_aug));
   g->mark_top = true;
-  // the switches that ask for a form of the general path keep it
   g->small = st == PG_OK && !g->dense && g->relabeled &&
-             !(flags & (PG_CAREFUL_WALKS | PG_NO_GRAPH | PG_HOST_REDUCED_LIST |
-                        PG_SWITCH_ROWS | PG_SWITCH_BUCKETS)) &&
-             small_fits(g->n_aug, g->m_aug);
+             !(asked & kGeneralFlags) && small_fits(g->n_aug, g->m_aug);
   return st;
 }
 
@@ -1380,7 +1446,7 @@ pg_status solve_game(pg_game *g, const pg_solve_opts *opts, uint8_t *winner,
   } else if (o.init_sigma || o.init_tau) {
     PG_TRY(import_strats(g, o.init_sigma, o.init_tau, dev, s));
   }
-  valuation_reset(g, s);
+  if (!g->small || o.trace_cap > 0) valuation_reset(g, s);
   Trace tr;
   tr.o = &o;
   struct HashBuf {
@@ -1460,7 +1526,8 @@ pg_status solve_game(pg_game *g, const pg_solve_opts *opts, uint8_t *winner,
     hipLaunchKernelGGL(k_winner, dim3(grid_for(g->n)), dim3(kBlock), 0, s,
                        g->rs, io_rvpos(g), dw, g->n);
     if (!dev) PG_TRY(copy_out(winner, dw, g->n, false, s));
-    PG_HIP(hipStreamSynchronize(s));
+    // (host copies of the strategies use the staging buffers again)
+    if (!dev || (!sigma && !tau)) PG_HIP(hipStreamSynchronize(s));
   }
   PG_TRY(strats_out(report));
   const auto t1 = std::chrono::steady_clock::now();
@@ -1532,7 +1599,7 @@ pg_status pg_load_csr(int64_t n, int64_t m, const void *offsets,
   hipStream_t s = (hipStream_t)hip_stream;
   PoolScope cache(game_cache(g->device));
   const pg_status st = load_game(n, m, offsets, targets, owner, priority,
-                                 flags, s, g);
+                                 flags, s, g, flags);
   if (st != PG_OK) {
     (void)hipStreamSynchronize(s);
     free_game(g);
@@ -1708,7 +1775,7 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
   hipStream_t s = (hipStream_t)hip_stream;
   const bool dev = flags & PG_PTR_DEVICE;
   PG_TRY(import_strats(g, sigma, tau, dev, s));
-  valuation_reset(g, s);
+  if (!g->small) valuation_reset(g, s);
   Run r;
   r.max_inner = max_inner;
   r.br_only = true;
@@ -1784,10 +1851,7 @@ pg_status pg_solve_noalloc(int64_t n, int64_t m, const void *offsets,
   g.device = device;
   g.timed = false;
   pg_status st = load_game(n, m, offsets, targets, owner, priority,
-                           flags | PG_NO_GRAPH | PG_SWITCH_ROWS, s, &g);
-  g.small = st == PG_OK && !g.dense && g.relabeled &&
-            !(flags & (PG_CAREFUL_WALKS | PG_NO_GRAPH | PG_SWITCH_ROWS)) &&
-            small_fits(g.n_aug, g.m_aug);
+                           flags | PG_NO_GRAPH | PG_SWITCH_ROWS, s, &g, flags);
   if (st == PG_OK) st = solve_game(&g, opts, winner, sigma, tau, stats, s);
   // the scratch is free again once the stream has drained
   (void)hipStreamSynchronize(s);

@@ -584,6 +584,14 @@ pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count);
 // ---- small games (pg_small.hip) ---------------------------------------------
 namespace pgk {
 constexpr int64_t kSmallN = 6144;   // most vertices of a small game
+// A game of n vertices and m edges (device arrays) loaded in one launch;
+// g's counters are allocated.  *done = false: not loaded (malformed or
+// repeated priorities), the general path decides, with g's buffers dropped.
+bool small_load_fits(int64_t n, int64_t m);
+pg_status small_load(pg_game *g, int64_t n, int64_t m, const void *offsets,
+                     const int32_t *targets, const uint8_t *owner,
+                     const int32_t *priority, uint32_t flags, hipStream_t s,
+                     bool *done);
 // N vertices and M edges fit one block's LDS
 bool small_fits(int64_t N, int64_t M);
 // Algorithm 1 from the strategies in g->sp (g->inc.inner and major count on)

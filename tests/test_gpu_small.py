@@ -54,6 +54,9 @@ SIZES = [(2, 1, 1), (3, 2, 2), (63, 2, 4), (770, 2, 5), (1024, 2, 5),
 def test_solves(n, dmin, dmax, device):
     g = synth.random_game(n, dmin, dmax, n)
     with Game.from_dict(g, device=device) as d:
+        aug, ex = orc.preprocess(g), d.export()
+        for k in ("offsets", "targets", "owner", "pri"):
+            np.testing.assert_array_equal(ex[k], aug[k])
         _same(d.solve(), orc.solve(g))
         _same(d.solve(best_response=PG_BR_SI_RESET), orc.solve(g, reset=True))
     _same(solve_noalloc(g, device=device), orc.solve(g))
@@ -105,6 +108,21 @@ def test_best_responses_and_caps():
                 tau2, key2, _ = e.best_response(a["sigma"], a["tau"])
             np.testing.assert_array_equal(to_np(tau), to_np(tau2))
             np.testing.assert_array_equal(to_np(key), to_np(key2))
+
+
+def test_loads_refused_or_left_to_the_general_path():
+    g = synth.random_game(50, 2, 4, 5)
+    for k, i, x in (("targets", 7, 50), ("owner", 3, 2), ("pri", 9, -1),
+                    ("offsets", 4, 0), ("pri", 0, 2**31 - 1)):
+        h = {q: np.array(a) for q, a in g.items()}
+        h[k][i] = x
+        with pytest.raises(PgError) as e:
+            Game.from_dict(h)
+        assert e.value.status == PG_EINVAL
+    h = dict(g, pri=g["pri"] // 2 * 2)   # repeated: count valuations
+    with Game.from_dict(h) as d:
+        assert d.d > 0
+        d.solve()
 
 
 def test_refused_strategies():
