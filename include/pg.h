@@ -143,8 +143,8 @@ enum {
  * rounds directly: slower, same results; it exists to test that path.
  *
  * A valuation of pg_solve or pg_best_response that follows few switches is
- * computed by its changed part only (rank valuations; not with a trace,
- * PG_CAREFUL_WALKS or PG_HOST_REDUCED_LIST): same results.  The first such
+ * computed by its changed part only (not with a trace, PG_CAREFUL_WALKS or
+ * PG_HOST_REDUCED_LIST): same results.  The first such
  * call lays out the game's in-edges for it (4 bytes per edge, 12 per
  * vertex); without room for them every valuation is a full one.
  *

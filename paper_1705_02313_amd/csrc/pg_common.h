@@ -553,9 +553,9 @@ pg_status iteration_device(pg_game *g, hipStream_t s, int32_t *count,
 
 // ---- valuations by their changed part (pg_inc.hip) -------------------------
 namespace pgk {
-// Rows read by All_Odd's row form list its switches only up to this many Odd
-// vertices (one counter takes an atomic per block).
-constexpr int64_t kIncRowOdd = int64_t(1) << 20;
+// All_Odd's row form lists its switches only up to this many Odd vertices
+// (one counter takes an atomic per block).
+constexpr int64_t kIncRowOdd = int64_t(1) << 23;
 bool inc_eligible(const pg_game *g);
 // Start of a run: builds the in-edge lists if they are not there; false
 // when the game takes full valuations only.

@@ -38,7 +38,7 @@
 // decides by the parity of its priority); top is above every count vector.
 #include <algorithm>
 
-#include "pg_common.h"
+#include "pg_rows.h"
 
 namespace pgk {
 
@@ -180,35 +180,6 @@ __global__ void k_cnt_sink_chain(const uint32_t *__restrict__ sink_flag,
 // ---------------------------------------------------------------------------
 // vector list ranking
 // ---------------------------------------------------------------------------
-// adds s at column col without indexing a register array at run time
-template <int D>
-__device__ __forceinline__ void add_unit(int32_t (&a)[D], int col,
-                                         int32_t s) {
-#pragma unroll
-  for (int i = 0; i < D; ++i) a[i] += (i == col) ? s : 0;
-}
-
-template <int D>
-__device__ __forceinline__ void load_vec(const int32_t *p, int32_t (&a)[D]) {
-  const int4 *q = reinterpret_cast<const int4 *>(p);
-#pragma unroll
-  for (int i = 0; i < D / 4; ++i) {
-    const int4 x = q[i];
-    a[4 * i] = x.x;
-    a[4 * i + 1] = x.y;
-    a[4 * i + 2] = x.z;
-    a[4 * i + 3] = x.w;
-  }
-}
-
-template <int D>
-__device__ __forceinline__ void store_vec(int32_t *p, const int32_t (&a)[D]) {
-  int4 *q = reinterpret_cast<int4 *>(p);
-#pragma unroll
-  for (int i = 0; i < D / 4; ++i)
-    q[i] = make_int4(a[4 * i], a[4 * i + 1], a[4 * i + 2], a[4 * i + 3]);
-}
-
 // Level 1: each splitter (element index a multiple of the stride s0, a
 // power of two; element 0, the head, is one) sums the weights of its
 // sublist.  At the edge leaving v it writes the sum so far (v's prefix
@@ -408,92 +379,30 @@ __global__ __launch_bounds__(kBlock) void k_vlr_emit1(
 // ---------------------------------------------------------------------------
 // switching on count valuations
 // ---------------------------------------------------------------------------
-// -1: a below b, 0: equal, 1: above.  Top equals top and is above every
-// count vector; otherwise the largest differing column decides: a larger
-// count is better at an even priority, worse at an odd one.
-template <int D>
-__device__ __forceinline__ int vcmp(bool ta, const int32_t (&a)[D], bool tb,
-                                    const int32_t (&b)[D], uint32_t odd_cols) {
-  if (ta || tb) return ta == tb ? 0 : (ta ? 1 : -1);
-  int r = 0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    if (a[i] != b[i]) {
-      const bool even = !((odd_cols >> i) & 1u);
-      r = ((a[i] < b[i]) == even) ? -1 : 1;
-    }
-  }
-  return r;
-}
-
-// the valuation of vertex u (u == N: the sink, the zero vector); returns
-// whether it is top (the marker -1 in the first column)
-template <int D>
-__device__ __forceinline__ bool load_val(const int32_t *cnt, int32_t u,
-                                         int32_t (&a)[D]) {
-  load_vec<D>(cnt + (int64_t)u * D, a);
-  return a[0] < 0;
-}
-
-// All_Odd (section 4): the first successor of least valuation, if strictly
-// below the current choice.
+// All_Odd over the Odd vertices; the switches are listed in `dec` (nullable).
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_cnt_odd_switch(
     int32_t N, int64_t count, const int32_t *__restrict__ ids,
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
     const int32_t *__restrict__ cnt, uint32_t odd_cols,
     const int32_t *__restrict__ pri, int2 *sp,
-    int32_t *ctr) {
+    int32_t *ctr, int2 *dec) {
   if (ctr[C_ABORT]) return;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool sw = false;
+  int32_t v = 0, best = 0;
   const int2 me = t < count ? sp[ids[t]] : make_int2(0, kTopMark);
   // a vertex known to stay top has only top successors: no switch
   if (me.y != kTopMark) {
-    const int32_t v = ids[t];
-    const int64_t e0 = off[v], e1 = off[v + 1];
-    // the current choice is normally in the row: its valuation comes with
-    // the row's loads (a strategy given at the C ABI may name another vertex)
-    const int32_t cur = me.x;
-    int32_t cv[D];
-    bool ct = false, have_c = false;
-    int32_t best = tgt[e0];
-    int32_t bv[D];
-    bool bt = load_val<D>(cnt, best, bv);
-    if (best == cur) {
-      ct = bt;
-      have_c = true;
-#pragma unroll
-      for (int i = 0; i < D; ++i) cv[i] = bv[i];
-    }
-    for (int64_t e = e0 + 1; e < e1; ++e) {
-      const int32_t u = tgt[e];
-      int32_t uv[D];
-      const bool ut = load_val<D>(cnt, u, uv);
-      if (u == cur) {
-        ct = ut;
-        have_c = true;
-#pragma unroll
-        for (int i = 0; i < D; ++i) cv[i] = uv[i];
-      }
-      if (vcmp<D>(ut, uv, bt, bv, odd_cols) < 0) {
-        best = u;
-        bt = ut;
-#pragma unroll
-        for (int i = 0; i < D; ++i) bv[i] = uv[i];
-      }
-    }
-    if (!have_c) ct = load_val<D>(cnt, cur, cv);
-    if (vcmp<D>(bt, bv, ct, cv, odd_cols) < 0) {
-      sp[v] = make_int2(best, pri[best]);
-      sw = true;
-    }
+    v = ids[t];
+    sw = cnt_decide_odd<D>(off, tgt, cnt, odd_cols, v, me, &best);
+    if (sw) sp[v] = make_int2(best, pri[best]);
   }
   count_block(&ctr[C_DIST_SW], sw);
+  if (dec) list_block(&ctr[C_NDEC], dec, sw, v, best);
 }
 
-// All_Even, greedy all-switches (section 3): the sink first, then the row;
-// the first option of greatest valuation, if strictly above the current one.
+// All_Even over the Even vertices.
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_cnt_even_switch(
     int32_t N, int64_t count, const int32_t *__restrict__ ids,
@@ -507,37 +416,9 @@ __global__ __launch_bounds__(kBlock) void k_cnt_even_switch(
   // a vertex known to stay top keeps its choice
   if (me.y != kTopMark) {
     const int32_t v = ids[t];
-    const int64_t e0 = off[v], e1 = off[v + 1];
-    // the current choice is the sink (the zero vector) or normally in the
-    // row (see All_Odd)
-    const int32_t cur = me.x;
-    int32_t cv[D] = {};
-    bool ct = false, have_c = cur == N;
     int32_t best = N;
-    int32_t bv[D] = {};
-    bool bt = false;
-    for (int64_t e = e0; e < e1; ++e) {
-      const int32_t u = tgt[e];
-      int32_t uv[D];
-      const bool ut = load_val<D>(cnt, u, uv);
-      if (u == cur) {
-        ct = ut;
-        have_c = true;
-#pragma unroll
-        for (int i = 0; i < D; ++i) cv[i] = uv[i];
-      }
-      if (vcmp<D>(ut, uv, bt, bv, odd_cols) > 0) {
-        best = u;
-        bt = ut;
-#pragma unroll
-        for (int i = 0; i < D; ++i) bv[i] = uv[i];
-      }
-    }
-    if (!have_c) ct = load_val<D>(cnt, cur, cv);
-    if (vcmp<D>(bt, bv, ct, cv, odd_cols) > 0) {
-      sp[v] = make_int2(best, best == N ? 2147483647 : pri[best]);
-      sw = true;
-    }
+    sw = cnt_decide_even<D>(N, off, tgt, cnt, odd_cols, v, me, &best);
+    if (sw) sp[v] = make_int2(best, best == N ? 2147483647 : pri[best]);
   }
   count_block(&ctr[C_DIST_SW], sw);
 }
@@ -814,7 +695,8 @@ static void enqueue_count_switch_t(pg_game *g, bool odd, hipStream_t s,
                 28.0 * cnt + (5.0 + 4.0 * D) * g->m_odd,
                 k_cnt_odd_switch<D>, dim3(grid_for(cnt)), dim3(kBlock), 0, s,
                 N, cnt, g->odd_ids, g->off, g->tgt, g->cnt,
-                g->odd_cols, g->pri, g->sp, g->ctr);
+                g->odd_cols, g->pri, g->sp, g->ctr,
+                cnt <= kIncRowOdd ? g->elem : (int2 *)nullptr);
   } else {
     const int64_t cnt = N - g->n_odd;
     if (cnt > 0)

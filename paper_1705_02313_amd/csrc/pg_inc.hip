@@ -1,4 +1,4 @@
-// Valuations by their changed part (rank valuations, single games).
+// Valuations by their changed part (single games).
 //
 // Along a run most valuations follow a handful of switches.  A switch at w
 // changes the play of exactly the vertices whose play passes w (with the
@@ -20,6 +20,11 @@
 // valuation lists the tree in (pg_val.hip), so the switches are the same.
 // A full valuation makes every key clean again.
 //
+// Count valuations take the same steps with rows instead of keys: a vertex
+// of A walks its play out of A, counting, and adds the row it arrives at, so
+// every row is up to date and comparisons are the rows' own (1M vertices, 4
+// priorities, solve from arrays: 24.4 -> 10.4 ms).
+//
 // Decisions go to a list of {vertex, new successor} pairs (`dec`) that the
 // next step applies, so a step that gives up (a hub with too many in-edges,
 // a chain or walk longer than its bound, a full list) has changed nothing a
@@ -38,7 +43,7 @@
 // 3.6 -> 1.6 ms at 1,000 vertices.
 #include <algorithm>
 
-#include "pg_common.h"
+#include "pg_rows.h"
 
 namespace pgk {
 
@@ -118,6 +123,10 @@ struct IncP {
   int32_t cl_cap;
   int32_t *f[2];           // find frontiers
   int32_t f_cap;
+  // count valuations (kernels with D > 0)
+  int32_t *cnt;
+  const uint8_t *pidx;
+  uint32_t odd_cols;
 };
 
 // 1, 0 or -1: Val(x) above, equal to or below Val(y), for finite x and y,
@@ -217,8 +226,25 @@ __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
   return odd ? c < 0 : c > 0;
 }
 
-// The ng of a vertex of A is open until its walk.
+// The rule of a game with rank keys (D = 0) or count rows of D ints.
+template <int D>
+__device__ __forceinline__ bool rule(const IncP &P, int32_t v, bool odd,
+                                     int32_t *to, bool *stop) {
+  if constexpr (D == 0) {
+    return inc_decide(P, v, odd, to, stop);
+  } else {
+    const int2 me = P.sp[v];
+    if (me.y == kTopMark) return false;   // known to stay top
+    return odd ? cnt_decide_odd<D>(P.off, P.tgt, P.cnt, P.odd_cols, v, me, to)
+               : cnt_decide_even<D>(P.N, P.off, P.tgt, P.cnt, P.odd_cols, v,
+                                    me, to);
+  }
+}
+
+// The ng of a vertex of A is open until its walk (count valuations walk
+// plays: their ng is found again by the next full valuation).
 __device__ __forceinline__ void inc_open(const IncP &P, int32_t v) {
+  if (P.cnt) return;
   P.ng[v] = -1;
   P.cand[v] = -1;
 }
@@ -323,6 +349,59 @@ __device__ __forceinline__ bool inc_fate(const IncP &P, int32_t epoch,
   if (!f) return false;
   P.rs[v] = (uint8_t)f;
   P.key[v] = f == 2 ? PG_KEY_TOP : kKeyDirty;
+  return true;
+}
+
+// The row and the fate of one vertex of A: along its play to a vertex outside
+// A (or the sink), whose row stands.  A play that stays in A circles (Brent's
+// detection) and is top; its cycle's largest priority must be even for an
+// admissible sigma (section 3).  False when the steps run out.
+template <int D>
+__device__ __forceinline__ bool inc_row(const IncP &P, int32_t epoch,
+                                        int32_t *err, int32_t v, int steps) {
+  const int32_t N = P.N;
+  int32_t acc[D] = {};
+  add_unit<D>(acc, P.pidx[v], 1);
+  int2 s = P.sp[v];
+  int32_t u = s.x, mark = v;
+  int lam = 1, power = 1, f = 0;
+  for (int k = 0; k < steps; ++k) {
+    if (s.y == kTopMark) {
+      f = 2;
+      break;
+    }
+    if (u == N || ld_relaxed(&P.mark[u]) != epoch) {
+      int32_t r[D];
+      f = load_val<D>(P.cnt, u, r) ? 2 : 1;
+#pragma unroll
+      for (int i = 0; i < D; ++i) acc[i] += r[i];
+      break;
+    }
+    if (u == mark) {
+      int32_t best = P.pri[u];
+      for (int32_t x = P.sp[u].x; x != u; x = P.sp[x].x)
+        best = max(best, P.pri[x]);
+      if (best & 1) atomicOr(err, ERR_INADMISSIBLE);
+      f = 2;
+      break;
+    }
+    if (lam == power) {
+      mark = u;
+      power <<= 1;
+      lam = 0;
+    }
+    ++lam;
+    add_unit<D>(acc, P.pidx[u], 1);
+    s = P.sp[u];
+    u = s.x;
+  }
+  if (!f) return false;
+  if (f == 2) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) acc[i] = i == 0 ? -1 : 0;
+  }
+  store_vec<D>(P.cnt + (int64_t)v * D, acc);
+  P.rs[v] = (uint8_t)f;
   return true;
 }
 
@@ -555,6 +634,29 @@ __global__ __launch_bounds__(kBlock) void k_inc_walk(IncP P, int32_t a0,
                      1);
 }
 
+// Count valuations: rows and fates; the second pass takes the vertices whose
+// steps ran out in the first (rs 0).
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_inc_rows(IncP P, int32_t epoch,
+                                                     int32_t a0, int steps,
+                                                     int pass, int last,
+                                                     int32_t *ic) {
+  if (ic[I_STOP] || (pass > 0 && !ic[I_NF + kIncRounds + pass])) return;
+  const int32_t n = ic[I_NA];
+  bool open = false;
+  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += gridDim.x * blockDim.x) {
+    const int32_t v = P.list[a0 + i];
+    if (pass > 0 && P.rs[v]) continue;
+    if (!inc_row<D>(P, epoch, &ic[I_ERR], v, steps)) {
+      P.rs[v] = 0;
+      open = true;
+    }
+  }
+  if (open) atomicOr(last ? &ic[I_STOP] : &ic[I_NF + kIncRounds + pass + 1],
+                     1);
+}
+
 __global__ __launch_bounds__(kBlock) void k_inc_fate(IncP P, int32_t epoch,
                                                      int32_t a0, int32_t *ic) {
   if (ic[I_STOP]) return;
@@ -567,6 +669,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_fate(IncP P, int32_t epoch,
 }
 
 // The rule for every candidate.
+template <int D>
 __global__ __launch_bounds__(kBlock) void k_inc_decide(IncP P, int32_t epoch,
                                                        int odd, int2 *dec,
                                                        int32_t *ic) {
@@ -581,7 +684,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_decide(IncP P, int32_t epoch,
     if (i < n) {
       v = P.cl[i];
       if (!odd || atomicExch(&P.cmark[v], epoch) != epoch)
-        sw = inc_decide(P, v, odd != 0, &to, &stop);
+        sw = rule<D>(P, v, odd != 0, &to, &stop);
     }
     const int32_t p = wave_place(&ic[I_NDEC], sw);
     if (sw) dec[p] = make_int2(v, to);
@@ -615,8 +718,9 @@ __global__ __launch_bounds__(kBlock) void k_inc_even_cand(IncP P,
 }
 
 // All_Even over every Even vertex, keys clean or dirty; decisions only.
-constexpr int kEvenBlock = 1024;
-__global__ __launch_bounds__(kEvenBlock) void k_inc_even_all(
+constexpr int even_block(int D) { return D >= 16 ? 256 : 1024; }
+template <int D>
+__global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
     IncP P, int64_t count, const int32_t *__restrict__ ids, int2 *dec,
     int32_t *ic) {
   __shared__ int32_t n, base;
@@ -627,7 +731,7 @@ __global__ __launch_bounds__(kEvenBlock) void k_inc_even_all(
   int32_t v = 0, to = 0;
   if (t < count) {
     v = ids[t];
-    sw = inc_decide(P, v, false, &to, &stop);
+    sw = rule<D>(P, v, false, &to, &stop);
   }
   const int32_t at = wave_place(&n, sw);
   __syncthreads();
@@ -654,7 +758,6 @@ __global__ __launch_bounds__(kBlock) void k_inc_commit(
 // is reached, or a step outgrows it.  Every dependent access costs a
 // round trip to the L2, so its steps are bound by the length of their
 // chains (the depth of A, the ng chains), not by their size.
-constexpr int kIncThreads = 1024;
 constexpr int32_t kBlockA = 4096;  // most vertices of its A (LDS)
 constexpr int kBlockEven = 8192;   // most changed vertices of its All_Even
 enum IncState : int {
@@ -675,10 +778,14 @@ struct IncRun {
   int32_t with_even;             // run All_Even and go on
 };
 
-__global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
-                                                           int2 *dec0,
-                                                           int2 *dec1,
-                                                           int32_t *ic) {
+// (wide count rows: fewer threads, so that the rows stay in registers)
+constexpr int inc_threads(int D) { return D >= 16 ? 512 : 1024; }
+template <int D>
+__global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
+                                                              int2 *dec0,
+                                                              int2 *dec1,
+                                                              int32_t *ic) {
+  constexpr int T = inc_threads(D);
   __shared__ int32_t la[kBlockA];   // A
   __shared__ uint2 lr[kBlockA];     // its in-edge ranges
   __shared__ int32_t s_na, s_nc, s_nd, s_stop, s_open, s_err;
@@ -697,7 +804,7 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
       s_nd = 0;
       s_stop = 0;
     }
-    for (int32_t i = tid; i < R.nsw; i += kIncThreads) {
+    for (int32_t i = tid; i < R.nsw; i += T) {
       const int2 d = din[i];
       inc_apply(P, epoch, d);
       la[i] = d.x;
@@ -707,8 +814,8 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
     // find, level by level: a level is a stretch of the list
     int32_t beg = 0, end = R.nsw;
     while (beg < end) {
-      const int L = find_lanes(end - beg, kIncThreads);
-      for (int32_t i0 = beg; i0 < end; i0 += kIncThreads / L) {
+      const int L = find_lanes(end - beg, T);
+      for (int32_t i0 = beg; i0 < end; i0 += T / L) {
         const int32_t i = i0 + tid / L;
         uint32_t e = 0, e1 = 0;
         int32_t w = -1;
@@ -746,16 +853,24 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
     // (every thread leaves the loop with the same beg and end)
     if (end > R.a_cap || s_nc > P.cl_cap || s_stop) break;
     const int32_t na = end;
-    for (int32_t i = tid; i < na; i += kIncThreads) P.list[R.a0 + i] = la[i];
+    for (int32_t i = tid; i < na; i += T) P.list[R.a0 + i] = la[i];
     // walks: passes until none is open
     bool failed = true;
-    for (int pass = 0; pass < 8; ++pass) {
+    for (int pass = 0; pass < (D == 0 ? 8 : 2); ++pass) {
       if (tid == 0) s_open = 0;
       __syncthreads();
-      for (int32_t i = tid; i < na; i += kIncThreads) {
+      for (int32_t i = tid; i < na; i += T) {
         const int32_t v = la[i];
-        if (ld_relaxed(&P.ng[v]) >= 0) continue;
-        if (!inc_walk(P, &s_err, v, 64)) s_open = 1;
+        if constexpr (D == 0) {
+          if (ld_relaxed(&P.ng[v]) >= 0) continue;
+          if (!inc_walk(P, &s_err, v, 64)) s_open = 1;
+        } else {
+          if (pass > 0 && P.rs[v]) continue;
+          if (!inc_row<D>(P, epoch, &s_err, v, pass ? 1024 : 64)) {
+            P.rs[v] = 0;
+            s_open = 1;
+          }
+        }
       }
       __syncthreads();
       const bool open = s_open != 0;
@@ -766,21 +881,22 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
       }
     }
     if (failed) break;
-    for (int32_t i = tid; i < na; i += kIncThreads)
-      if (!inc_fate(P, epoch, la[i])) s_stop = 1;
+    if constexpr (D == 0)
+      for (int32_t i = tid; i < na; i += T)
+        if (!inc_fate(P, epoch, la[i])) s_stop = 1;
     __syncthreads();
     const int32_t nc = s_nc;
     const bool bad = s_stop || s_err;
     __syncthreads();   // the next phase writes s_stop
     if (bad) break;
-    for (int32_t i0 = 0; i0 < nc; i0 += kIncThreads) {
+    for (int32_t i0 = 0; i0 < nc; i0 += T) {
       const int32_t i = i0 + tid;
       bool sw = false, stop = false;
       int32_t v = 0, to = 0;
       if (i < nc) {
         v = P.cl[i];
         if (atomicExch(&P.cmark[v], epoch) != epoch)
-          sw = inc_decide(P, v, true, &to, &stop);
+          sw = rule<D>(P, v, true, &to, &stop);
       }
       if (stop) s_stop = 1;
       const int32_t p = wave_place(&s_nd, sw);
@@ -814,7 +930,7 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
       s_nd = 0;
     }
     __syncthreads();
-    for (int32_t i0 = 0; i0 < R.a0; i0 += kIncThreads) {
+    for (int32_t i0 = 0; i0 < R.a0; i0 += T) {
       const int32_t i = i0 + tid;
       uint32_t e = 0, e1 = 0;
       if (i < R.a0) {
@@ -832,13 +948,13 @@ __global__ __launch_bounds__(kIncThreads) void k_inc_block(IncP P, IncRun R,
     }
     __syncthreads();
     const int32_t ne = s_nc;
-    for (int32_t i0 = 0; i0 < ne; i0 += kIncThreads) {
+    for (int32_t i0 = 0; i0 < ne; i0 += T) {
       const int32_t i = i0 + tid;
       bool sw = false, stop = false;
       int32_t v = 0, to = 0;
       if (i < ne) {
         v = P.cl[i];
-        sw = inc_decide(P, v, false, &to, &stop);
+        sw = rule<D>(P, v, false, &to, &stop);
       }
       if (stop) s_stop = 1;
       const int32_t p = wave_place(&s_nd, sw);
@@ -905,6 +1021,9 @@ static IncP inc_params(const pg_game *g) {
   P.ng = g->ng;
   P.cand = g->cand;
   P.rs = g->rs;
+  P.cnt = g->dense ? g->cnt : nullptr;
+  P.pidx = g->pidx;
+  P.odd_cols = g->odd_cols;
   P.mark = g->inc.mark;
   P.cmark = g->inc.cmark;
   // the Euler list's records (4 N ints) and the parent sort's keys (N each)
@@ -924,7 +1043,7 @@ static IncP inc_params(const pg_game *g) {
 static int2 *inc_dec(const pg_game *g, int i) { return g->elem + i * g->n_aug; }
 
 bool inc_eligible(const pg_game *g) {
-  return !g->dense && g->relabeled && !g->careful && !g->host_rl &&
+  return (g->dense || g->relabeled) && !g->careful && !g->host_rl &&
          g->n_aug >= 2 && g->m_aug < (int64_t(1) << 31) &&
          (g->tsw || g->n_odd <= kIncRowOdd);
 }
@@ -1047,7 +1166,8 @@ static void inc_backoff(pg_game *g) {
 
 // One step (device form) or a run of steps (block form) from the pending
 // decisions.
-pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
+template <int D>
+static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
                    int32_t max_inner, int32_t max_major, IncOut *out) {
   pg_game::Inc &x = g->inc;
   const IncP P = inc_params(g);
@@ -1082,8 +1202,8 @@ pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
     R.major = x.major;
     R.d_valid = x.d_valid;
     R.with_even = with_even;
-    PG_LAUNCH(pf, K_INC_BLOCK, 0.0, k_inc_block, dim3(1), dim3(kIncThreads),
-              0, s, P, R, inc_dec(g, 0), inc_dec(g, 1), x.ic);
+    PG_LAUNCH(pf, K_INC_BLOCK, 0.0, k_inc_block<D>, dim3(1),
+              dim3(inc_threads(D)), 0, s, P, R, inc_dec(g, 0), inc_dec(g, 1), x.ic);
   } else {
     const int32_t epoch = ++x.epoch;
     const unsigned gb =
@@ -1096,13 +1216,20 @@ pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
     for (int r = 0; r < kFindRounds; ++r)
       PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_find, fgrid, blk, 0, s, P, epoch,
                 x.a0, r, kFindLevels, (int)(r == kFindRounds - 1), x.ic);
-    PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0, 64,
-              0, 0, x.ic);
-    PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0, 256,
-              1, 1, x.ic);
-    PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_fate, grid, blk, 0, s, P, epoch,
-              x.a0, x.ic);
-    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide, grid, blk, 0, s, P, epoch, 1,
+    if constexpr (D == 0) {
+      PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0, 64,
+                0, 0, x.ic);
+      PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0,
+                256, 1, 1, x.ic);
+      PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_fate, grid, blk, 0, s, P, epoch,
+                x.a0, x.ic);
+    } else {
+      PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_rows<D>, grid, blk, 0, s, P, epoch,
+                x.a0, 64, 0, 0, x.ic);
+      PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_rows<D>, grid, blk, 0, s, P, epoch,
+                x.a0, 1024, 1, 1, x.ic);
+    }
+    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide<D>, grid, blk, 0, s, P, epoch, 1,
               inc_dec(g, x.cur ^ 1), x.ic);
   }
   if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
@@ -1150,7 +1277,8 @@ pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
 }
 
 // All_Even after a best response; its switches are pending afterwards.
-pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count) {
+template <int D>
+static pg_status inc_even_t(pg_game *g, hipStream_t s, int32_t *count) {
   pg_game::Inc &x = g->inc;
   const IncP P = inc_params(g);
   Prof *pf = &g->prof;
@@ -1162,7 +1290,7 @@ pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count) {
         std::min<unsigned>(kIncBlocks, grid_for(4 * (int64_t)x.a0)), 64u));
     PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_even_cand, grid, dim3(kBlock), 0, s,
               P, ++x.epoch, x.a0, x.ic);
-    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide, grid, dim3(kBlock), 0, s,
+    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide<D>, grid, dim3(kBlock), 0, s,
               P, x.epoch, 0, inc_dec(g, 0), x.ic);
     PG_TRY(inc_read(g, s));
   }
@@ -1175,8 +1303,8 @@ pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count) {
     fill_i32(x.ic, 0, I_WORDS, s, pf);
     if (ne > 0)
       PG_LAUNCH(pf, K_EVEN_SWITCH, 28.0 * ne + 8.0 * (g->m_aug - g->m_odd),
-                k_inc_even_all, dim3(grid_for(ne, kEvenBlock)),
-                dim3(kEvenBlock), 0, s, P, ne, g->even_ids, inc_dec(g, 0),
+                k_inc_even_all<D>, dim3(grid_for(ne, even_block(D))),
+                dim3(even_block(D)), 0, s, P, ne, g->even_ids, inc_dec(g, 0),
                 x.ic);
     PG_TRY(inc_read(g, s));
   }
@@ -1187,6 +1315,28 @@ pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count) {
   x.a0 = 0;
   x.d_valid = true;
   return PG_OK;
+}
+
+// The row width of a count game, 0 for rank keys.
+pg_status inc_step(pg_game *g, hipStream_t s, bool with_even,
+                   int32_t max_inner, int32_t max_major, IncOut *out) {
+  switch (g->dense ? g->dw : 0) {
+    case 0: return inc_step_t<0>(g, s, with_even, max_inner, max_major, out);
+    case 4: return inc_step_t<4>(g, s, with_even, max_inner, max_major, out);
+    case 8: return inc_step_t<8>(g, s, with_even, max_inner, max_major, out);
+    case 16: return inc_step_t<16>(g, s, with_even, max_inner, max_major, out);
+    default: return inc_step_t<32>(g, s, with_even, max_inner, max_major, out);
+  }
+}
+
+pg_status inc_even(pg_game *g, hipStream_t s, int32_t *count) {
+  switch (g->dense ? g->dw : 0) {
+    case 0: return inc_even_t<0>(g, s, count);
+    case 4: return inc_even_t<4>(g, s, count);
+    case 8: return inc_even_t<8>(g, s, count);
+    case 16: return inc_even_t<16>(g, s, count);
+    default: return inc_even_t<32>(g, s, count);
+  }
 }
 
 }  // namespace pgk

@@ -87,6 +87,24 @@ def test_runs_equal_the_oracle(name, switch):
         np.testing.assert_array_equal(to_np(key), to_np(k2))
 
 
+@pytest.mark.parametrize("d", [2, 4, 6, 12, 27])
+@pytest.mark.parametrize("name", ["one_block", "mid", "chain", "hub",
+                                  "doubled"])
+def test_count_runs_equal_the_oracle(name, d):
+    g = GAMES[name]()
+    rng = np.random.default_rng(d)
+    g["pri"] = rng.integers(0, d, g["n"]).astype(np.int32)
+    ref = orc.dense_solve(g)
+    with Game.from_dict(g) as h:
+        for _ in range(2):
+            out = h.solve()
+            for k in ("winner", "sigma"):
+                np.testing.assert_array_equal(to_np(out[k]), ref[k])
+            np.testing.assert_array_equal(to_np(out["tau"]), ref["tau_orig"])
+            for k in ("n_major", "n_valuations"):
+                assert out["stats"][k] == ref[k], k
+
+
 @pytest.mark.parametrize("name", ["one_block", "mid", "chain"])
 def test_caps_stop_at_the_same_strategies(name):
     g = GAMES[name]()
