@@ -433,7 +433,9 @@ pg_status pg_profile_read(const pg_game *game, int32_t kind, const char **name,
  *                  Queued games join the arena, first come first served, at
  *                  a step where they fit beside the games already in it.  A
  *                  game's memory comes from a pool that the batch keeps
- *                  until pg_batch_free.
+ *                  until pg_batch_free, which leaves a pool of at most 1
+ *                  GiB to the next batch on the device (two such pools at
+ *                  most; pg_release_cache hands them back).
  * pg_batch_submit_many  submits count games at once (arrays of their
  *                  arguments; flags shared): the same checks, preprocessing
  *                  and queueing as count pg_batch_submit calls in order, but
@@ -589,8 +591,8 @@ int32_t pg_tuning_table(pg_tuning *entries, int64_t *min_n_aug,
  * hipFree for each. */
 pg_status pg_free(pg_game *game);
 
-/* Hand the cached memory of freed games back to the HIP runtime (every
- * device).  Memory of games still loaded is not touched.  Small blocks are
+/* Hand the cached memory of freed games and batches back to the HIP runtime
+ * (every device).  Memory of games still loaded is not touched.  Small blocks are
  * carved from shared slabs of 32; a slab goes back once none of its blocks
  * belongs to a loaded game (its free blocks stay cached until then). */
 pg_status pg_release_cache(void);

@@ -585,6 +585,36 @@ DevPool *game_cache(int device) {
   return c;
 }
 
+static std::map<int, std::vector<DevPool *>> g_idle;
+
+DevPool *take_pool(int device) {
+  {
+    std::lock_guard<std::mutex> lock(g_cache_mu);
+    auto &idle = g_idle[device];
+    if (!idle.empty()) {
+      DevPool *p = idle.back();
+      idle.pop_back();
+      return p;
+    }
+  }
+  return new (std::nothrow) DevPool();
+}
+
+void give_pool(int device, DevPool *pool) {
+  if (!pool) return;
+  if (pool->held(false) <= kIdlePoolBytes &&
+      pool->held(true) <= kIdlePoolHost) {
+    std::lock_guard<std::mutex> lock(g_cache_mu);
+    auto &idle = g_idle[device];
+    if (idle.size() < kIdlePools) {
+      idle.push_back(pool);
+      return;
+    }
+  }
+  pool->clear();
+  delete pool;
+}
+
 static void trim_caches() {
   std::lock_guard<std::mutex> lock(g_cache_mu);
   int prev = -1;
@@ -593,7 +623,24 @@ static void trim_caches() {
     (void)hipSetDevice(kv.first);
     kv.second->trim();
   }
+  for (auto &kv : g_idle) {
+    (void)hipSetDevice(kv.first);
+    for (DevPool *p : kv.second) {
+      p->clear();
+      delete p;
+    }
+    kv.second.clear();
+  }
   if (prev >= 0) (void)hipSetDevice(prev);
+}
+
+size_t DevPool::held(bool host) const {
+  size_t b = 0;
+  for (const auto &kv : host ? host_size : dev_size)
+    if (!slab_of.count(kv.first)) b += kv.second;
+  for (const Slab &sl : slabs)
+    if (sl.base && sl.host == host) b += sl.block * kSlabBlocks;
+  return b;
 }
 
 void DevPool::clear() {

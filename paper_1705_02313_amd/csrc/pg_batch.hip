@@ -611,11 +611,59 @@ __global__ void k_bm_split(const BmOut *out, const unsigned long long *n_oddpri,
 }
 
 
+// Many copies in one launch (blockIdx.y: which): a poll of many games copies
+// three arrays each, and a copy of its own per array is a launch and a gap of
+// some 10 us against a few us of transfer (96 games of 500 to 50,000
+// vertices: pg_batch_poll_many 3.4 -> 0.8 ms a batch).  The destinations are device memory or
+// pinned host memory the device can write.
+struct CopyItem {
+  void *dst;
+  const void *src;
+  int64_t bytes;
+};
+__global__ __launch_bounds__(kBlock) void k_copy_many(const CopyItem *items) {
+  const CopyItem c = items[blockIdx.y];
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  const uintptr_t both = (uintptr_t)c.dst | (uintptr_t)c.src;
+  int64_t done = 0;
+  if ((both & 15) == 0) {
+    const int64_t n = c.bytes / 16;
+    for (int64_t i = t; i < n; i += step)
+      ((int4 *)c.dst)[i] = ((const int4 *)c.src)[i];
+    done = 16 * n;
+  } else if ((both & 3) == 0) {
+    const int64_t n = c.bytes / 4;
+    for (int64_t i = t; i < n; i += step)
+      ((int32_t *)c.dst)[i] = ((const int32_t *)c.src)[i];
+    done = 4 * n;
+  }
+  for (int64_t i = done + t; i < c.bytes; i += step)
+    ((uint8_t *)c.dst)[i] = ((const uint8_t *)c.src)[i];
+}
+
 }  // namespace pgk
 
 using namespace pgk;
 
 namespace {
+
+// The address at which the device writes the host range [p, p + bytes), or
+// null when the range is not pinned memory of one allocation.
+void *device_view(void *p, size_t bytes) {
+  hipPointerAttribute_t a{}, z{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+      hipPointerGetAttributes(&z, (char *)p + bytes - 1) != hipSuccess) {
+    (void)hipGetLastError();   // pageable memory
+    return nullptr;
+  }
+  if (a.type != hipMemoryTypeHost || z.type != hipMemoryTypeHost ||
+      !a.devicePointer || !z.devicePointer ||
+      (char *)z.devicePointer - (char *)a.devicePointer !=
+          (ptrdiff_t)(bytes - 1))
+    return nullptr;
+  return a.devicePointer;
+}
 
 enum BState { B_QUEUED = 0, B_LIVE = 1, B_DONE = 2 };
 
@@ -671,7 +719,8 @@ struct pg_batch {
   std::deque<BGame *> queue;
   std::vector<BGame *> built;      // games of the current arena, by slot
   std::vector<BGame *> grave;      // left the arena; freed at the next rebuild
-  DevPool pool;                    // memory of the submitted games
+  // memory of the submitted games, and of a small arena (take_pool)
+  DevPool *pool = nullptr;
   int64_t done_vertices = 0;       // arena vertices of finished games
   int64_t queued_steps = 0;        // steps taken while a fitting game waited
   // per-slot device state
@@ -722,15 +771,23 @@ void drop_step_graphs(pg_batch *b) {
   }
 }
 
+// An arena of up to this many vertices comes from the batch's pool (blocks
+// of power-of-two sizes, kept for the next batch); a larger one from the
+// runtime, exactly sized.
+constexpr int64_t kPoolArena = int64_t(4) << 20;
+
 pg_status batch_alloc(pg_batch *b) {
+  b->pool = take_pool(b->device);
+  if (!b->pool) return pg_fail(PG_ENOMEM, "host allocation failed");
+  PoolScope ps(b->cap_v <= kPoolArena && b->cap_e <= 8 * kPoolArena ? b->pool
+                                                                   : nullptr);
   pg_game *a = new (std::nothrow) pg_game();
   if (!a) return pg_fail(PG_ENOMEM, "host allocation failed");
   b->arena = a;
   a->device = b->device;
   a->relabeled = true;   // arena ids are signed-order positions
   PG_HIP(hipStreamCreateWithFlags(&b->sub_stream, hipStreamNonBlocking));
-  PG_HIP(hipHostMalloc((void **)&a->hctr, sizeof(int32_t) * C_COUNT,
-                       hipHostMallocDefault));
+  PG_TRY(host_alloc((void **)&a->hctr, sizeof(int32_t) * C_COUNT));
   PG_TRY(dev_alloc(&a->ctr, C_TOTAL));
   PG_TRY(dev_alloc(&a->off, b->cap_v + 1));
   PG_TRY(dev_alloc(&a->tgt, b->cap_e));
@@ -757,7 +814,7 @@ pg_status batch_alloc(pg_batch *b) {
   b->h_nmaj.resize(G);
   b->h_sw_odd.resize(G);
   b->h_sw_even.resize(G);
-  PG_HIP(hipHostMalloc((void **)&b->h_res, res_bytes(G), hipHostMallocDefault));
+  PG_TRY(host_alloc((void **)&b->h_res, res_bytes(G)));
   return PG_OK;
 }
 
@@ -767,22 +824,21 @@ void batch_release(pg_batch *b) {
     (void)hipStreamSynchronize(b->sub_stream);
     (void)hipStreamDestroy(b->sub_stream);
   }
-  {
-    PoolScope ps(&b->pool);
-    for (auto &kv : b->games) free_bgame(kv.second);
-    for (BGame *g : b->grave) free_bgame(g);
-  }
-  b->pool.clear();
+  // the pool goes on to another batch: nothing may still use its blocks
+  (void)hipDeviceSynchronize();
   drop_step_graphs(b);
-  if (b->h_res) (void)hipHostFree(b->h_res);
+  PoolScope ps(b->pool);
+  for (auto &kv : b->games) free_bgame(kv.second);
+  for (BGame *g : b->grave) free_bgame(g);
+  host_free(b->h_res);
   free_game(b->arena);
   void *ptrs[] = {b->d_desc,    b->d_estart,  b->d_pstart,
                   b->d_gid,
                   b->d_run,     b->d_pending, b->d_newly,   b->d_cnt_odd,
                   b->d_cnt_even, b->d_nval,   b->d_nmaj,    b->d_sw_odd,
                   b->d_sw_even, b->d_i32};
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
+  for (void *p : ptrs) dev_free(p);
+  give_pool(b->device, b->pool);
   delete b;
 }
 
@@ -796,7 +852,7 @@ pg_status rebuild(pg_batch *b, bool *built_any) {
   drop_step_graphs(b);   // the arena's sizes and slots change
   b->steps_in_layout = 0;
   {
-    PoolScope ps(&b->pool);
+    PoolScope ps(b->pool);
     for (BGame *g : b->grave) free_bgame(g);
   }
   b->grave.clear();
@@ -1421,7 +1477,7 @@ pg_status pg_batch_submit(pg_batch *b, int64_t n, int64_t m,
   if (flags & PG_ODD_REGION)
     return pg_fail(PG_EINVAL, "a batch does not take PG_ODD_REGION games");
   hipStream_t s = b->sub_stream;
-  PoolScope ps(&b->pool);   // the game's memory comes from the batch's pool
+  PoolScope ps(b->pool);   // the game's memory comes from the batch's pool
   BGame *bg = new (std::nothrow) BGame();
   if (!bg) return pg_fail(PG_ENOMEM, "host allocation failed");
   bg->g = new (std::nothrow) pg_game();
@@ -1581,7 +1637,7 @@ pg_status pg_batch_submit_many(pg_batch *b, int32_t count, const int64_t *n,
       status[q] = pg_fail(PG_EINVAL, "int32 offsets cannot address m edges");
     if (status[q] == PG_OK) idx.push_back(q);
   }
-  PoolScope ps(&b->pool);   // the games' memory comes from the batch's pool
+  PoolScope ps(b->pool);   // the games' memory comes from the batch's pool
   // chunks of at most 2^28 vertices, so that a chunk's modified games
   // (at most twice its vertices) keep 32-bit ids
   size_t at = 0;
@@ -1718,15 +1774,45 @@ pg_status pg_batch_poll_many(pg_batch *b, int32_t count,
     done[i] = gs[i]->state == B_DONE;
     if (stats) stats[i] = gs[i]->st;
   }
-  // every copy on the batch's stream, then one wait
+  // every copy on the batch's stream, then one wait; several to memory that
+  // the device can write are one launch
+  std::vector<CopyItem> items;
+  int64_t most = 0;
   for (int32_t i = 0; i < count; ++i) {
     if (!done[i]) continue;
     const BGame *g = gs[i];
     size_t wb, sb, tb;
     sizes(i, &wb, &sb, &tb);
-    if (wb) PG_TRY(copy_out(winner[i], g->res_winner, wb, dev, s));
-    if (sb) PG_TRY(copy_out(sigma[i], g->res_sigma, sb, dev, s));
-    if (tb) PG_TRY(copy_out(tau[i], g->res_tau, tb, dev, s));
+    if (wb) items.push_back({winner[i], g->res_winner, (int64_t)wb});
+    if (sb) items.push_back({sigma[i], g->res_sigma, (int64_t)sb});
+    if (tb) items.push_back({tau[i], g->res_tau, (int64_t)tb});
+  }
+  for (const CopyItem &c : items) most = std::max(most, c.bytes);
+  struct List {
+    CopyItem *p = nullptr;
+    ~List() { host_free(p); }
+  };
+  PoolScope pool(b->pool);
+  List list;
+  bool one = items.size() > 1 && items.size() <= 65535 &&
+             host_alloc((void **)&list.p, sizeof(CopyItem) * items.size()) ==
+                 PG_OK;
+  for (size_t k = 0; one && k < items.size(); ++k) {
+    list.p[k] = items[k];
+    if (!dev) {
+      list.p[k].dst = device_view(items[k].dst, (size_t)items[k].bytes);
+      one = list.p[k].dst != nullptr;
+    }
+  }
+  if (one) {
+    const unsigned gx =
+        std::min<unsigned>(64, grid_for((most + 15) / 16, 4 * kBlock));
+    hipLaunchKernelGGL(k_copy_many, dim3(gx, (unsigned)items.size()),
+                       dim3(kBlock), 0, s, list.p);
+    PG_HIP(hipGetLastError());
+  } else {
+    for (const CopyItem &c : items)
+      PG_TRY(copy_out(c.dst, c.src, (size_t)c.bytes, dev, s));
   }
   PG_HIP(hipStreamSynchronize(s));
   for (int32_t i = 0; i < count; ++i) {
@@ -1738,7 +1824,7 @@ pg_status pg_batch_poll_many(pg_batch *b, int32_t count,
     g->polled = true;
     if (!g->in_arena) {
       b->games.erase(g->ticket);
-      PoolScope ps(&b->pool);
+      PoolScope ps(b->pool);
       free_bgame(g);
     }  // else: still laid out in the arena; released at the next rebuild
   }

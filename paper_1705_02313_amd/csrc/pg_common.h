@@ -682,7 +682,17 @@ struct DevPool {
   bool release(void *p);   // false: not a block of this pool
   void clear();            // every block, in use or not
   void trim();             // the blocks not in use
+  size_t held(bool host) const;   // bytes asked of the runtime
 };
+// Pools of batches that were freed, for the next batch on the device: at
+// most kIdlePools per device, each of at most kIdlePoolBytes device and
+// kIdlePoolHost pinned bytes.  A pool belongs to one batch at a time; it is
+// handed over with nothing in use and the device drained.
+constexpr size_t kIdlePools = 2;
+constexpr size_t kIdlePoolBytes = size_t(1) << 30;
+constexpr size_t kIdlePoolHost = size_t(1) << 28;
+DevPool *take_pool(int device);             // an idle one, else a new one
+void give_pool(int device, DevPool *pool);  // kept, or cleared and deleted
 // The cache of the calling thread's current device that single games
 // allocate from and return their memory to (see pg_release_cache).
 DevPool *game_cache(int device);
