@@ -715,6 +715,7 @@ static void drop_buffers(pg_game *g) {
   host_free(g->hctr);
   host_free(g->h_rl);
   if (g->iter_exec) (void)hipGraphExecDestroy(g->iter_exec);
+  if (g->iter_coarse) (void)hipGraphExecDestroy(g->iter_coarse);
   if (g->cap_stream) (void)hipStreamDestroy(g->cap_stream);
   if (g->ev_a) (void)hipEventDestroy(g->ev_a);
   if (g->ev_b) (void)hipEventDestroy(g->ev_b);
@@ -1255,10 +1256,20 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
       } else {
         int32_t c = 0;
         int64_t nf = 0;
-        inc_before_full(g, s);
-        PG_TRY(iteration_device(g, s, &c, &nf));
-        inc_after_full(g, c);
-        r->keys = true;
+        bool done = false;
+        const bool coarse = inc_coarse(g);
+        inc_before_full(g, s, coarse);
+        if (coarse) {
+          PG_TRY(iteration_coarse(g, s, &c, &done));
+          if (!done) {   // chains too long: ranks for a while
+            inc_backoff(g);
+            fates_reset(g, s);
+            r->iter_ms += g->last_ms;
+          }
+        }
+        if (!done) PG_TRY(iteration_device(g, s, &c, &nf));
+        inc_after_full(g, c, !done);
+        r->keys = !done;
         r->iter_ms += g->last_ms;
         if (r->tr) r->tr->record(g, s, c, nf);
         ++inner;
@@ -1836,9 +1847,13 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
     if (!deep && !dev)
       PG_TRY(copy_out(key, dk, sizeof(int32_t) * (g->n_aug + 1), false, s));
   }
-  if (key && !r.keys && deep) {   // the ranks of the vertices changed last
-    fates_reset(g, s);
-    PG_TRY(valuation_device(g, s, nullptr));
+  if (key && !r.keys && deep) {
+    if (g->small) {   // the run may have left ng in its kernel
+      valuation_reset(g, s);
+      PG_TRY(valuation_device(g, s, nullptr));
+    } else {
+      PG_TRY(ranks_device(g, s));
+    }
   }
   PG_TRY(export_strats(g, nullptr, tau, dev, s, false));
   if (key && deep) PG_TRY(export_keys(g, key, dev, s));

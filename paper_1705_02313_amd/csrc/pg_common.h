@@ -18,9 +18,6 @@ constexpr int kBlock = 256;            // threads per block for flat kernels
 // sp[v].y (the priority of v's successor) of a vertex known to stay top for
 // the rest of a solve: its play, and every play through it, is infinite
 constexpr int32_t kTopMark = INT32_MIN;
-// key[v] of a vertex whose valuation changed since the last full valuation
-// (pg_inc.hip); no rank is negative
-constexpr int32_t kKeyDirty = -1;
 constexpr int kWave = 64;              // CDNA wavefront width
 constexpr int kMaxVertices = (1 << 30) - 2;
 
@@ -34,7 +31,8 @@ enum Counter : int {
   C_MISC = 4,         // scratch counter (preprocessing changes, odd count,
                       // open vertices of host-driven walk rounds)
   C_NINNER = 5,       // finite vertices whose parent is not the sink
-  C_NDEC = 6,         // entries of All_Odd's switch list (single rank games)
+  C_NDEC = 6,         // entries of All_Odd's switch list
+  C_NTIE = 7,         // vertices whose All_Odd the coarse keys leave open
   // Hot counts are spread over kDistSlots slots kDistStride ints apart (one
   // atomic per block into slot blockIdx % kDistSlots) and summed afterwards:
   // a single address hit by every block serialises.  The switch slots are
@@ -190,6 +188,7 @@ struct pg_game {
   bool use_graph = false;
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t iter_exec = nullptr;
+  hipGraphExec_t iter_coarse = nullptr;   // the same with coarse keys
   // All_Odd over the bucketed edge layout (pg_switch.hip): the Odd rows'
   // edges in target order (tsw_t) with each edge's slot in its chunk
   // (tsw_slot) and that slot's place in bucket order (tsw_g); per place the
@@ -296,7 +295,8 @@ struct pg_game {
     int32_t epoch = 0;           // number of the last step
     // the run in progress
     bool on = false;
-    bool dirty = false;     // keys dirty since the last full valuation
+    bool dirty = false;     // the fates are not the last exact valuation's
+    bool exact = false;     // g->key holds ranks, not coarse keys
     bool pending = false;   // nsw decisions in list `cur` to apply
     bool d_valid = false;   // the list's first a0 entries hold every change
                             // since the last All_Even
@@ -407,11 +407,11 @@ __device__ __forceinline__ void append_block(int32_t *cnt, int32_t *list,
   if (pred) list[(int64_t)slot * cap + s_base + off] = v;
 }
 
-// Appends {v, to} (where pred holds) to a list whose length counts at *cnt,
-// one device atomic per block.  Every thread of the block must call it.
-__device__ __forceinline__ void list_block(int32_t *cnt, int2 *list,
-                                           bool pred, int32_t v, int32_t to) {
+// Places (where pred holds) in a list whose length counts at *cnt, one
+// device atomic per block.  Every thread of the block must call it.
+__device__ __forceinline__ int32_t block_place(int32_t *cnt, bool pred) {
   __shared__ int32_t s_n, s_base;
+  __syncthreads();   // an earlier call's words
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
   const uint64_t b = __ballot(pred);
@@ -426,7 +426,38 @@ __device__ __forceinline__ void list_block(int32_t *cnt, int2 *list,
   __syncthreads();
   if (threadIdx.x == 0 && s_n) s_base = atomicAdd(cnt, s_n);
   __syncthreads();
-  if (pred) list[s_base + off] = make_int2(v, to);
+  return s_base + off;
+}
+
+// Appends {v, to} (where pred holds) likewise.
+__device__ __forceinline__ void list_block(int32_t *cnt, int2 *list,
+                                           bool pred, int32_t v, int32_t to) {
+  const int32_t at = block_place(cnt, pred);
+  if (pred) list[at] = make_int2(v, to);
+}
+
+// Wave-wide append: every lane of the wave calls it; lanes with pred get
+// consecutive places from *ctr.  One atomic per wave.
+__device__ __forceinline__ int32_t wave_place(int32_t *ctr, bool pred) {
+  const uint64_t b = __ballot(pred);
+  if (!b) return 0;
+  const int lane = threadIdx.x & (kWave - 1);
+  int32_t base = 0;
+  if (lane == 0) base = atomicAdd(ctr, (int32_t)__popcll(b));
+  base = __shfl(base, 0);
+  return base + (int32_t)__popcll(b & ((1ull << lane) - 1ull));
+}
+
+// Coarse keys: a finite vertex's key is that of the last vertex of its ng
+// chain before the sink (its root, a child of the sink in the ng tree).
+// Siblings are in signed-priority order, the order of a relabeled game's
+// ids, and the sink lies between its odd and its even children, so vertices
+// with different coarse keys compare as their ranks do.
+__device__ __host__ __forceinline__ int32_t coarse_key(int32_t root) {
+  return 2 * root + 1;
+}
+__device__ __host__ __forceinline__ int32_t coarse_sink(int32_t n_oddpri) {
+  return 2 * n_oddpri;
 }
 
 __device__ __forceinline__ int ld_relaxed(const int32_t *p) {
@@ -549,6 +580,13 @@ void fates_reset(pg_game *g, hipStream_t s);
 // iteration's device time between two HIP events on s.
 pg_status iteration_device(pg_game *g, hipStream_t s, int32_t *count,
                            int64_t *n_finite = nullptr);
+// The same on coarse keys (rank games, see coarse_key): no vertex is ranked,
+// ties are decided on the ng chains.  *done = false: a walk or an ng chain
+// outlasted its bound and nothing was switched.
+pg_status iteration_coarse(pg_game *g, hipStream_t s, int32_t *count,
+                           bool *done);
+// The ranks of the valuation whose ng and fates are in place.
+pg_status ranks_device(pg_game *g, hipStream_t s);
 }  // namespace pgk
 
 // ---- valuations by their changed part (pg_inc.hip) -------------------------
@@ -563,10 +601,16 @@ bool inc_prepare(pg_game *g, hipStream_t s);
 void inc_release(pg_game *g);
 // true when the pending switches are few enough for inc_step
 bool inc_ready(const pg_game *g);
-bool inc_dirty(const pg_game *g);
 void inc_commit(pg_game *g, hipStream_t s);
-void inc_before_full(pg_game *g, hipStream_t s);
-void inc_after_full(pg_game *g, int32_t switches);
+void inc_before_full(pg_game *g, hipStream_t s, bool coarse);
+void inc_after_full(pg_game *g, int32_t switches, bool exact);
+// a full valuation may use coarse keys / did not fit them
+bool inc_coarse(const pg_game *g);
+void inc_backoff(pg_game *g);
+// All_Odd's vertices left open by the coarse keys (after a coarse valuation)
+void enqueue_ties(pg_game *g, hipStream_t s);
+// room for the vertices left open (n_odd entries at most)
+int32_t *tie_list(const pg_game *g);
 enum IncEnd : int { INC_MORE = 0, INC_BR, INC_SOLVED, INC_CAP };
 struct IncOut {
   int state = INC_MORE;
@@ -629,7 +673,7 @@ bool tsw_fits(int device, int64_t n_odd, int64_t m_odd);
 pg_status tsw_build(pg_game *g, hipStream_t s);
 // frees the layout (after the stream has drained); the row form serves
 void tsw_release(pg_game *g);
-void enqueue_tsw_odd(pg_game *g, hipStream_t s);
+void enqueue_tsw_odd(pg_game *g, hipStream_t s, bool coarse);
 // Odd-row edges from which a single game takes the bucketed layout by
 // default (smaller games read rows directly)
 constexpr int64_t kTswMinEdges = int64_t(1) << 20;

@@ -10,15 +10,15 @@
 //           in-edges (u joins when its current successor is in A)
 //   walk    recomputes ng for the vertices of A only, jumping over everyone
 //           else's ng
-//   fate    follows their ng chains to the sink or to top
+//   fate    follows their ng chains to the sink or to top: fate and root
 //   decide  evaluates the switching rule for the vertices whose row holds a
 //           vertex of A: nobody else's options changed since it last did not
 //           switch
-// and the keys of A become kKeyDirty.  Two clean keys compare as before; a
-// comparison with a dirty vertex climbs the two ng chains to their meeting
-// point and decides there by signed priority, which is the order a full
-// valuation lists the tree in (pg_val.hip), so the switches are the same.
-// A full valuation makes every key clean again.
+// Nothing is ranked: keys are coarse (coarse_key), and a comparison of two
+// vertices with the same one climbs their ng chains to the meeting point and
+// decides there by signed priority, which is the order ranks list the tree
+// in (pg_val.hip), so the switches are the same.  Full valuations of a run
+// stop at the coarse keys too (pg_val.hip, enqueue_coarse).
 //
 // Count valuations take the same steps with rows instead of keys: a vertex
 // of A walks its play out of A, counting, and adds the row it arrives at, so
@@ -37,10 +37,11 @@
 // Every access is a random line, so a step costs its round trips (small A)
 // or its lines (large A), a full valuation the whole game's lines whatever
 // changed: on the 10M-vertex random game 12 of the 95 valuations stay full
-// (1.4 ms each), 38 take the device form (0.1-0.4 ms mostly) and 45 the
-// block form (25-40 us each).  Solves, load included: 146 -> 64 ms there,
-// 15.1 -> 9.8 ms at 1M vertices, 59.6 -> 19.6 ms on the 2M-vertex chain,
-// 3.6 -> 1.6 ms at 1,000 vertices.
+// (0.4-0.9 ms each with coarse keys, 1.4-2.1 ms with ranks), 38 take the
+// device form (0.1-0.4 ms mostly) and 45 the block form (25-40 us each).
+// Solves, load included, against full valuations with ranks throughout:
+// 150 -> 50 ms there, 15.1 -> 7.5 ms at 1M vertices, 58 -> 16 ms on the
+// 2M-vertex chain, 5.8 -> 2.8 ms at 40,000 vertices.
 #include <algorithm>
 
 #include "pg_rows.h"
@@ -65,7 +66,7 @@ constexpr int kIncRounds = 8;        // most find rounds of the device form
 constexpr int kFindRounds = 3;       // find rounds of the device form
 constexpr int kFindLevels = 128;     // levels of one round
 constexpr int kIncMaxDegree = 2048;  // in-edges of one vertex, else give up
-constexpr int kIncClimb = 512;       // ng steps of one comparison
+constexpr int kIncClimb = 1024;      // ng steps of one comparison
 constexpr int kIncFate = 1024;       // ng steps of one fate
 constexpr int kIncBlocks = 1024;
 
@@ -129,11 +130,11 @@ struct IncP {
   uint32_t odd_cols;
 };
 
-// 1, 0 or -1: Val(x) above, equal to or below Val(y), for finite x and y,
-// one of them dirty.  The ng chains meet at their least common ancestor; in
-// the tree's listing order a vertex lies above its odd and below its even
-// children's subtrees, and siblings are in signed-priority order, which is
-// the order of the (relabeled) ids.
+// 1, 0 or -1: Val(x) above, equal to or below Val(y), for finite x and y.
+// The ng chains meet at their least common ancestor; in the tree's listing
+// order a vertex lies above its odd and below its even children's subtrees,
+// and siblings are in signed-priority order, which is the order of the
+// (relabeled) ids.
 __device__ __forceinline__ int inc_climb(const IncP &P, int32_t x, int32_t y,
                                          bool *stop) {
   const int32_t N = P.N;
@@ -163,18 +164,17 @@ __device__ __forceinline__ int inc_climb(const IncP &P, int32_t x, int32_t y,
   return ca > cb ? 1 : -1;
 }
 
-// the same for any two vertices (or the sink) with their keys
+// the same for any two vertices (or the sink) with their coarse keys
 __device__ __forceinline__ int inc_cmp(const IncP &P, int32_t x, int32_t kx,
                                        int32_t y, int32_t ky, bool *stop) {
-  if (kx >= 0 && ky >= 0) return kx < ky ? -1 : kx > ky;
-  if (x == y) return 0;
-  if (kx == PG_KEY_TOP) return 1;
-  if (ky == PG_KEY_TOP) return -1;
+  if (kx != ky) return kx < ky ? -1 : 1;
+  if (x == y || kx == PG_KEY_TOP) return 0;
   return inc_climb(P, x, y, stop);
 }
 
 // All_Odd and All_Even (section 4, section 3) for one vertex: true when v
-// switches, to *to.  A row without a dirty vertex compares keys only.
+// switches, to *to.  Most rows are decided by the coarse keys; one whose
+// best key is met on two vertices is read again with comparisons.
 __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
                                            int32_t *to, bool *stop) {
   const int2 me = P.sp[v];
@@ -183,7 +183,7 @@ __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
   const int32_t cur = me.x;
   const int32_t kn = odd ? 0 : P.key[P.N];
   int32_t best = odd ? -1 : P.N, kb = kn, kc = kn;
-  bool have = !odd && cur == P.N, dirty = false;
+  bool have = !odd && cur == P.N, tie = false;
   for (int64_t q = e0; q < e1; q += 4) {
     int32_t u[4], k[4];
 #pragma unroll
@@ -193,7 +193,6 @@ __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (u[j] < 0) continue;
-      dirty |= k[j] < 0;
       if (u[j] == cur) {
         kc = k[j];
         have = true;
@@ -201,11 +200,15 @@ __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
       if (odd ? best < 0 || k[j] < kb : k[j] > kb) {
         best = u[j];
         kb = k[j];
+        tie = false;
+      } else {
+        tie |= k[j] == kb && u[j] != best;
       }
     }
   }
   if (!have) kc = P.key[cur];
-  if (!dirty && kc >= 0) {
+  // top never ties: the first top option is taken, a top minimum stays
+  if (kb == PG_KEY_TOP || !(tie || (kb == kc && best != cur))) {
     *to = best;
     return odd ? kb < kc : kb > kc;
   }
@@ -226,7 +229,7 @@ __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
   return odd ? c < 0 : c > 0;
 }
 
-// The rule of a game with rank keys (D = 0) or count rows of D ints.
+// The rule of a rank game (D = 0) or with count rows of D ints.
 template <int D>
 __device__ __forceinline__ bool rule(const IncP &P, int32_t v, bool odd,
                                      int32_t *to, bool *stop) {
@@ -255,18 +258,6 @@ __device__ __forceinline__ void inc_apply(const IncP &P, int32_t epoch,
   P.sp[d.x] = make_int2(d.y, d.y == P.N ? 2147483647 : P.pri[d.y]);
   P.mark[d.x] = epoch;
   inc_open(P, d.x);
-}
-
-// Wave-wide append: every lane of the wave calls it; lanes with pred get
-// consecutive places from *ctr.  One atomic per wave.
-__device__ __forceinline__ int32_t wave_place(int32_t *ctr, bool pred) {
-  const uint64_t b = __ballot(pred);
-  if (!b) return 0;
-  const int lane = threadIdx.x & (kWave - 1);
-  int32_t base = 0;
-  if (lane == 0) base = atomicAdd(ctr, (int32_t)__popcll(b));
-  base = __shfl(base, 0);
-  return base + (int32_t)__popcll(b & ((1ull << lane) - 1ull));
 }
 
 // The walk of one vertex of A (ng_walk of pg_val.hip on the changed part: an
@@ -328,27 +319,30 @@ __device__ __forceinline__ bool inc_walk(const IncP &P, int32_t *err,
   return res >= 0;
 }
 
-// The fate of one vertex of A: along its ng chain to the sink, to top or to
-// a vertex outside A, whose fate stands.
+// The fate and the coarse key of one vertex of A: along its ng chain to the
+// sink, to top or to a vertex outside A, whose own stand.
 __device__ __forceinline__ bool inc_fate(const IncP &P, int32_t epoch,
                                          int32_t v) {
   const int32_t N = P.N;
-  int32_t r = P.ng[v];
+  int32_t a = v, r = P.ng[v], k = PG_KEY_TOP;
   int f = 0;
   for (int s = 0; s < kIncFate; ++s) {
     if (r >= N) {
       f = r == N ? 1 : 2;
+      k = coarse_key(a);
       break;
     }
     if (P.mark[r] != epoch) {
       f = P.rs[r];
+      k = P.key[r];
       break;
     }
+    a = r;
     r = P.ng[r];
   }
   if (!f) return false;
   P.rs[v] = (uint8_t)f;
-  P.key[v] = f == 2 ? PG_KEY_TOP : kKeyDirty;
+  P.key[v] = f == 2 ? PG_KEY_TOP : k;
   return true;
 }
 
@@ -717,7 +711,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_even_cand(IncP P,
   }
 }
 
-// All_Even over every Even vertex, keys clean or dirty; decisions only.
+// All_Even over every Even vertex; decisions only.
 constexpr int even_block(int D) { return D >= 16 ? 256 : 1024; }
 template <int D>
 __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
@@ -739,6 +733,28 @@ __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
   __syncthreads();
   if (sw) dec[base + at] = make_int2(v, to);
   if (stop) atomicOr(&ic[I_STOP], 1);
+}
+
+// All_Odd for the vertices a coarse valuation left open: switched in place
+// and listed, like the others' switches.
+__global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
+                                                       int2 *dec) {
+  if (ctr[C_ABORT]) return;
+  const int32_t n = ctr[C_NTIE];
+  for (int32_t i0 = blockIdx.x * blockDim.x; i0 < n;
+       i0 += gridDim.x * blockDim.x) {
+    const int32_t i = i0 + threadIdx.x;
+    bool sw = false, stop = false;
+    int32_t v = 0, to = 0;
+    if (i < n) {
+      v = P.cl[i];
+      sw = inc_decide(P, v, true, &to, &stop);
+      if (sw) P.sp[v] = make_int2(to, P.pri[to]);
+    }
+    // (the walks bound every chain: no climb stops)
+    if (stop) atomicOr(&ctr[C_ERR], ERR_LISTWALK);
+    list_block(&ctr[C_NDEC], dec, sw, v, to);
+  }
 }
 
 // Applies decisions before a full valuation or an export.
@@ -1052,7 +1068,7 @@ bool inc_eligible(const pg_game *g) {
 // for them the game keeps full valuations.
 bool inc_prepare(pg_game *g, hipStream_t s) {
   pg_game::Inc &x = g->inc;
-  x.dirty = x.pending = x.d_valid = x.grown = x.even = false;
+  x.dirty = x.pending = x.d_valid = x.grown = x.even = x.exact = false;
   x.nsw = x.a0 = 0;
   x.skip = x.back = 0;
   x.on = false;
@@ -1127,26 +1143,43 @@ void inc_commit(pg_game *g, hipStream_t s) {
 
 bool inc_ready(const pg_game *g) {
   const pg_game::Inc &x = g->inc;
-  return x.on && x.pending && x.skip == 0 &&
+  return x.on && x.pending && x.skip == 0 && !x.exact &&
          ((int64_t)x.nsw * kIncSwitchShare <= g->n_aug ||
           g->n_aug <= kBlockA);
 }
 
-// Before a full valuation of a run (which finds every fate again if the
-// changed-part steps may have left some behind).
-void inc_before_full(pg_game *g, hipStream_t s) {
+// Coarse keys serve the rank games of a run until something outgrows them.
+bool inc_coarse(const pg_game *g) {
+  return g->inc.on && !g->dense && g->inc.skip == 0;
+}
+
+int32_t *tie_list(const pg_game *g) {
+  return inc_params(g).cl;
+}
+
+void enqueue_ties(pg_game *g, hipStream_t s) {
+  PG_LAUNCH(&g->prof, K_INC_DECIDE, 0.0, k_tie_decide, dim3(1024),
+            dim3(kBlock), 0, s, inc_params(g), g->ctr, inc_dec(g, 0));
+}
+
+// Before a full valuation of a run (an exact one finds every fate again
+// unless the last one was exact too, in the same inner loop).
+void inc_before_full(pg_game *g, hipStream_t s, bool coarse) {
   pg_game::Inc &x = g->inc;
   if (!x.on) return;
   inc_commit(g, s);
-  if (x.dirty || x.even) fates_reset(g, s);
+  if (!coarse) {
+    if (x.dirty || x.even) fates_reset(g, s);
+    if (x.skip > 0) --x.skip;
+  }
   x.even = false;
-  if (x.skip > 0) --x.skip;
 }
 
-void inc_after_full(pg_game *g, int32_t switches) {
+void inc_after_full(pg_game *g, int32_t switches, bool exact) {
   pg_game::Inc &x = g->inc;
   if (!x.on) return;
-  x.dirty = false;
+  x.dirty = !exact;
+  x.exact = exact && !g->dense;
   x.d_valid = false;
   x.a0 = 0;
   x.grown = false;
@@ -1155,10 +1188,8 @@ void inc_after_full(pg_game *g, int32_t switches) {
   x.nsw = switches;
 }
 
-bool inc_dirty(const pg_game *g) { return g->inc.on && g->inc.dirty; }
-
 // A step that gave up: full valuations for a while.
-static void inc_backoff(pg_game *g) {
+void inc_backoff(pg_game *g) {
   pg_game::Inc &x = g->inc;
   x.back = x.back ? std::min(2 * x.back, 16) : 1;
   x.skip = x.back;
@@ -1295,10 +1326,10 @@ static pg_status inc_even_t(pg_game *g, hipStream_t s, int32_t *count) {
     PG_TRY(inc_read(g, s));
   }
   for (int pass = 0; x.h[I_STOP]; ++pass) {
-    if (pass > 0) {   // a comparison outgrew its bound: clean keys first
-      fates_reset(g, s);
-      PG_TRY(valuation_device(g, s, nullptr));
+    if (pass > 0) {   // a comparison outgrew its bound: ranks instead
+      PG_TRY(ranks_device(g, s));
       x.dirty = false;
+      x.exact = true;
     }
     fill_i32(x.ic, 0, I_WORDS, s, pf);
     if (ne > 0)

@@ -18,9 +18,11 @@
 //           of its vertices with LDS atomics, finds the current choice's
 //           key among the same entries, and applies the rule.
 //
-// Finite keys are pairwise distinct, so the least (key, target) pair names
-// the row's first entry of least key; when the least key is top no switch
-// happens, whichever top entry it names.  The layout is three stable radix
+// Ranks are pairwise distinct, so the least (key, target) pair names the
+// row's first entry of least key; when the least key is top no switch
+// happens, whichever top entry it names.  With coarse keys a vertex whose
+// least key is met on two targets, or is its current choice's, goes to a
+// list of its own (enqueue_ties).  The layout is three stable radix
 // sorts at load: the edges by target; those by bucket, which gives each
 // edge's place in bucket order; the places by chunk, which gives each edge's
 // slot in its chunk.
@@ -33,10 +35,11 @@ namespace pgk {
 // buckets give longer runs per chunk in the stage's writes; on the
 // 10M-vertex random game stage + min went 91 + 72 -> 82 + 63 us per step
 // against 32768-edge chunks and 2048-vertex buckets of 256 threads (1M
-// vertices: 16 + 21 -> 12 + 15 us).  8192- and 6144-vertex buckets, or 512
+// vertices: 16 + 21 -> 12 + 15 us).  The coarse keys' ties (the returned
+// minimum, one array more) take the min step to 78 and 17 us.  8192- and 6144-vertex buckets, or 512
 // threads per min block, were slower.
 constexpr int kTswChunk = 16384;   // edges per stage block
-constexpr int kTswBucket = 4096;   // Odd vertices per min block
+constexpr int kTswBucket = 4096;   // Odd vertices per min block (20 B of LDS)
 
 // ---- layout (load time) ----------------------------------------------------
 
@@ -155,16 +158,19 @@ __global__ __launch_bounds__(kTswMinBlock) void k_tsw_min(
     int64_t no, const int32_t *__restrict__ ids, const int32_t *__restrict__ bs,
     const int32_t *__restrict__ r, const int32_t *__restrict__ tz,
     const uint16_t *__restrict__ sz, const int32_t *__restrict__ key,
-    const int32_t *__restrict__ pri, int2 *sp, int32_t *ctr, int2 *dec) {
+    const int32_t *__restrict__ pri, int2 *sp, int32_t *ctr, int2 *dec,
+    int32_t *ties) {
   if (ctr[C_ABORT]) return;
   __shared__ unsigned long long best[kTswBucket];
   __shared__ int32_t curt[kTswBucket], curk[kTswBucket];
+  __shared__ int32_t tied[kTswBucket];   // least key met on two targets
   const int64_t o0 = (int64_t)blockIdx.x * kTswBucket;
   const int ns = (int)min((int64_t)kTswBucket, no - o0);
   for (int i = threadIdx.x; i < ns; i += kTswMinBlock) {
     best[i] = ~0ull;
     curt[i] = sp[ids[o0 + i]].x;
     curk[i] = -1;   // keys are >= 0: not met yet
+    tied[i] = 2147483647;
   }
   __syncthreads();
   const int32_t p0 = bs[blockIdx.x], p1 = bs[blockIdx.x + 1];
@@ -181,15 +187,20 @@ __global__ __launch_bounds__(kTswMinBlock) void k_tsw_min(
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (t[u] < 0) continue;
-      atomicMin(&best[s[u]], ((unsigned long long)(uint32_t)k[u] << 32) |
-                                 (uint32_t)t[u]);
+      const unsigned long long was =
+          atomicMin(&best[s[u]], ((unsigned long long)(uint32_t)k[u] << 32) |
+                                     (uint32_t)t[u]);
+      // the least key in the end meets its first entry here
+      if ((int32_t)(was >> 32) == k[u] && (int32_t)(uint32_t)was != t[u])
+        atomicMin(&tied[s[u]], k[u]);
       // every entry naming the current choice carries the same key
       if (t[u] == curt[s[u]]) curk[s[u]] = k[u];
     }
   }
   __syncthreads();
-  int sw = 0;
+  int sw = 0, nt = 0;
   int32_t sv[kTswBucket / kTswMinBlock], stg[kTswBucket / kTswMinBlock];
+  // (ranks are distinct: only coarse keys tie; a top minimum never switches)
 #pragma unroll
   for (int q = 0; q < kTswBucket / kTswMinBlock; ++q) {
     const int i = q * kTswMinBlock + threadIdx.x;
@@ -200,30 +211,43 @@ __global__ __launch_bounds__(kTswMinBlock) void k_tsw_min(
     const int32_t kb = (int32_t)(x >> 32), bt = (int32_t)(uint32_t)x;
     int32_t kc = curk[i];
     if (kc < 0) kc = key[curt[i]];   // a current choice outside the row
-    if (kb < kc) {
-      const int32_t v = ids[o0 + i];
+    const int32_t v = ids[o0 + i];
+    if (ties && kb != PG_KEY_TOP &&
+        (tied[i] == kb || (kb == kc && bt != curt[i]))) {
+      sv[q] = v;
+      stg[q] = -1;
+      ++nt;
+    } else if (kb < kc) {
       sp[v] = make_int2(bt, pri[bt]);
       sv[q] = v;
       stg[q] = bt;
       ++sw;
     }
   }
-  // the switch list: places from an LDS count, the block's from one device
-  // atomic
-  __shared__ int32_t s_n, s_base;
-  if (threadIdx.x == 0) s_n = 0;
+  // the switch list and the ties: places from LDS counts, the block's from
+  // one device atomic each.  The words take over best[0..3], which threads 0
+  // to 3 are done with: the arrays are half of a CU's LDS exactly.
+  int32_t *words = reinterpret_cast<int32_t *>(best);
+  if (threadIdx.x < 4) words[2 * threadIdx.x] = 0;
   __syncthreads();
-  int32_t at = 0;
-  if (sw) at = atomicAdd(&s_n, sw);
+  int32_t at = 0, tat = 0;
+  if (sw) at = atomicAdd(&words[0], sw);
+  if (nt) tat = atomicAdd(&words[2], nt);
   __syncthreads();
-  if (threadIdx.x == 0 && s_n) {
-    s_base = atomicAdd(&ctr[C_NDEC], s_n);
-    atomicAdd(&ctr[C_DIST_SW + (blockIdx.x % kDistSlots) * kDistStride], s_n);
+  if (threadIdx.x == 0 && words[0]) {
+    words[4] = atomicAdd(&ctr[C_NDEC], words[0]);
+    atomicAdd(&ctr[C_DIST_SW + (blockIdx.x % kDistSlots) * kDistStride],
+              words[0]);
   }
+  if (threadIdx.x == kWave && words[2])
+    words[6] = atomicAdd(&ctr[C_NTIE], words[2]);
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kTswBucket / kTswMinBlock; ++q)
-    if (sv[q] >= 0) dec[s_base + at++] = make_int2(sv[q], stg[q]);
+  for (int q = 0; q < kTswBucket / kTswMinBlock; ++q) {
+    if (sv[q] < 0) continue;
+    if (stg[q] >= 0) dec[words[4] + at++] = make_int2(sv[q], stg[q]);
+    else ties[words[6] + tat++] = sv[q];
+  }
 }
 
 // ---- host side -------------------------------------------------------------
@@ -326,7 +350,7 @@ void tsw_release(pg_game *g) {
   g->tsw_nb = g->tsw_nc = 0;
 }
 
-void enqueue_tsw_odd(pg_game *g, hipStream_t s) {
+void enqueue_tsw_odd(pg_game *g, hipStream_t s, bool coarse) {
   Prof *pf = &g->prof;
   const int64_t m = g->m_odd, no = g->n_odd;
   // a target and its key per edge
@@ -337,7 +361,8 @@ void enqueue_tsw_odd(pg_game *g, hipStream_t s) {
   // figure: the step's algorithmic bytes do not depend on the layout)
   PG_LAUNCH(pf, K_ODD_SWITCH, 28.0 * no, k_tsw_min, dim3((unsigned)g->tsw_nb),
             dim3(kTswMinBlock), 0, s, no, g->odd_ids, g->tsw_bs, g->tsw_r,
-            g->tsw_tz, g->tsw_sz, g->key, g->pri, g->sp, g->ctr, g->elem);
+            g->tsw_tz, g->tsw_sz, g->key, g->pri, g->sp, g->ctr, g->elem,
+            coarse ? tie_list(g) : (int32_t *)nullptr);
 }
 
 }  // namespace pgk

@@ -56,6 +56,10 @@ void apply_tuning(pg_game *g, const pg_tuning &t) {
     (void)hipGraphExecDestroy(g->iter_exec);
     g->iter_exec = nullptr;
   }
+  if (g->iter_coarse) {
+    (void)hipGraphExecDestroy(g->iter_coarse);
+    g->iter_coarse = nullptr;
+  }
 }
 
 }  // namespace pgk

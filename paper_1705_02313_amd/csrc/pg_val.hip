@@ -107,7 +107,8 @@ __global__ __launch_bounds__(kBlock) void k_ng_full(
     // fate stays; every other fate is found again
     // (rcand needs no clearing: the root pass writes it for every vertex
     // it leaves undecided, and the rounds read it for those only)
-    if (rs[v] != 1) rs[v] = 0;
+    // (null: every fate is written by the coarse root pass)
+    if (rs && rs[v] != 1) rs[v] = 0;
     // sp[x] = {successor of x, priority of that successor}: the first
     // comparison needs no gather, each further step one
     const int pv = pri[v];
@@ -269,10 +270,13 @@ __global__ __launch_bounds__(kBlock) void k_root_full(
     fh[v] = make_uint2(0u, 0u);
     const int32_t p = ng[v];
     int32_t r = p;
+    const int known = rs[v];
     if (r < 0) {
       r = -2;                       // ng(v) itself is not resolved yet
-    } else if (rs[v] == 1 && r <= N) {
+    } else if (known == 1 && r <= N) {
       r = N;                        // known finite: no walk to the root
+    } else if (known == 2) {
+      r = N + 1;                    // known top (ranks_device)
     } else {
       for (int st = 0; st < steps; ++st) {
         if (r >= N) break;
@@ -361,6 +365,74 @@ __global__ __launch_bounds__(kBlock) void k_root_round_list(
   }
   if (last && open) atomicOr(&ctr[C_ABORT], 1);
   add_block(&ctr[C_DIST_NF], nfin);
+}
+
+// ---------------------------------------------------------------------------
+// coarse keys (see coarse_key): the root and the fate of every vertex
+//
+// All_Odd needs an order, not ranks, and most of its rows are decided by
+// the roots; the rest climb two ng chains (pg_inc.hip, k_tie_decide).  In
+// place of the sort, the Euler list, its ranking and the emission this is
+// one pass bound by the lines of the chains (k_coarse_full, 10M vertices:
+// 57-215 us) and 4-100 us of ties: a whole iteration takes 0.4-0.9 ms
+// there instead of 1.4-2.1 ms, and at 40,000-300,000 vertices, where the
+// list's 30 launches were the time, 60-80 us instead of 250 us.
+// ---------------------------------------------------------------------------
+// Full pass: along the ng chain.  A child of the sink -- 40 to 90 % of the
+// finite vertices on the random games -- needs no gather, the others one per
+// link.  An undecided vertex gets rs = 0 and keeps the last vertex reached
+// in rcand.
+__global__ __launch_bounds__(kBlock) void k_coarse_full(
+    int32_t N, int32_t n_oddpri, const int32_t *ng, uint8_t *rs,
+    int32_t *rcand, int32_t *key, int32_t *ctr, int steps, int32_t *wl,
+    int64_t wl_cap) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  bool open = false;
+  if (i == 0) key[N] = coarse_sink(n_oddpri);
+  if (i < N) {
+    const int32_t v = (int32_t)i;
+    int32_t a = v, r = ng[v];
+    for (int st = 0; st < steps && r >= 0 && r < N; ++st) {
+      a = r;
+      r = ng[r];
+    }
+    open = r < N;
+    rs[v] = open ? 0 : r == N ? 1 : 2;
+    if (open) rcand[v] = a;
+    else key[v] = r == N ? coarse_key(a) : PG_KEY_TOP;
+  }
+  append_block(&ctr[C_DIST_WLRT], wl, wl_cap, open, (int32_t)i);
+}
+
+// A round over the undecided vertices.  No vertex takes over another's
+// result: the rounds bound the length of every chain, and with it the climb
+// of every comparison.
+__global__ __launch_bounds__(kBlock) void k_coarse_round_list(
+    int32_t N, const int32_t *ng, uint8_t *rs, int32_t *rcand, int32_t *key,
+    int32_t *ctr, int last, int steps, const int32_t *__restrict__ wl,
+    int64_t wl_cap) {
+  const ListPart lp = list_part();
+  const int32_t len = ctr[C_DIST_WLRT + lp.slot * kDistStride];
+  const int32_t *lst = wl + (int64_t)lp.slot * wl_cap;
+  bool open = false;
+  for (int64_t k = (int64_t)lp.part * blockDim.x + threadIdx.x; k < len;
+       k += (int64_t)lp.parts * blockDim.x) {
+    const int32_t v = lst[k];
+    if (rs[v]) continue;
+    int32_t a = rcand[v], r = ng[a];
+    for (int st = 0; st < steps && r >= 0 && r < N; ++st) {
+      a = r;
+      r = ng[r];
+    }
+    if (r < N) {
+      rcand[v] = a;
+      open = true;
+    } else {
+      rs[v] = r == N ? 1 : 2;
+      key[v] = r == N ? coarse_key(a) : PG_KEY_TOP;
+    }
+  }
+  if (last && open) atomicOr(&ctr[C_ABORT], 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -721,10 +793,10 @@ __global__ __launch_bounds__(kBlock) void k_odd_switch(
     int32_t N, int64_t count, const int32_t *__restrict__ ids,
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
     const int32_t *__restrict__ key, const int32_t *__restrict__ pri, int2 *sp,
-    int32_t *ctr, int2 *dec) {
+    int32_t *ctr, int2 *dec, int32_t *ties) {
   if (ctr[C_ABORT]) return;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool sw = false;
+  bool sw = false, tie = false;   // (ranks are distinct: coarse keys tie)
   int32_t swv = 0, swt = 0;
   const int2 me = t < count ? sp[ids[t]] : make_int2(0, kTopMark);
   // a vertex known to stay top has only top successors: no switch
@@ -746,17 +818,30 @@ __global__ __launch_bounds__(kBlock) void k_odd_switch(
       for (int j = 0; j < kRowBatch; ++j) k[j] = (u[j] >= 0) ? key[u[j]] : 0;
 #pragma unroll
       for (int j = 0; j < kRowBatch; ++j) {
-        if (u[j] >= 0 && (best < 0 || k[j] < kb)) { kb = k[j]; best = u[j]; }
+        if (u[j] >= 0) {
+          if (best < 0 || k[j] < kb) {
+            kb = k[j];
+            best = u[j];
+            tie = false;
+          } else {
+            tie |= k[j] == kb && u[j] != best;
+          }
+        }
         if (u[j] == cur) { kc = k[j]; have_kc = true; }
       }
     }
     if (!have_kc) kc = key[cur];
-    if (kb < kc) {
+    swv = v;
+    tie = ties && kb != PG_KEY_TOP && (tie || (kb == kc && best != cur));
+    if (!tie && kb < kc) {
       sp[v] = make_int2(best, pri[best]);
       sw = true;
-      swv = v;
       swt = best;
     }
+  }
+  if (ties) {
+    const int32_t at = block_place(&ctr[C_NTIE], tie);
+    if (tie) ties[at] = swv;
   }
   count_block(&ctr[C_DIST_SW], sw);
   if (dec) list_block(&ctr[C_NDEC], dec, sw, swv, swt);
@@ -866,46 +951,86 @@ void valuation_reset(pg_game *g, hipStream_t s) {
   fates_reset(g, s);
 }
 
-// ng and root phases with a fixed number of rounds; nothing is read back.
-static void enqueue_walks(pg_game *g, hipStream_t s) {
-  const int32_t N = (int32_t)g->n_aug;
-  Prof *pf = &g->prof;
-  int32_t *ng = g->ng, *cand = g->cand;
-  const WalkBudget wb = walk_budget(g);
-  // the counters, and the parent sort's work buffer of a rank valuation
-  clear_valuation(g->ctr, g->dense ? nullptr : g->rs1, N, s, pf);
-  // own record 8, first successor record 8, result 4; state resets 5
-  const int wblk = walk_block(g);
-  PG_LAUNCH(pf, K_NG_WALK, 25.0 * N, k_ng_full, dim3(grid_for(N, wblk)),
-            dim3(wblk), 0, s, N, g->sp, g->pri, ng, cand, g->ctr,
-            wb.full, g->rs, (int32_t *)nullptr, g->wl_ng,
-            g->wl_cap);
-  // the rounds walk the listed vertices only: as many lists as the full
-  // passes fill, each with up to kListBlocks blocks
+// The grid of a list round: as many lists as the full passes fill, each with
+// up to kListBlocks blocks.
+static dim3 list_grid(int64_t N, int wblk) {
   const int64_t fblocks = grid_for(N, wblk);
-  const dim3 lgrid((unsigned)(
+  return dim3((unsigned)(
       fblocks <= kDistSlots
           ? fblocks
           : kDistSlots *
                 std::min<int64_t>(kListBlocks,
                                   (fblocks + kDistSlots - 1) / kDistSlots)));
+}
+
+// The ng phase with a fixed number of rounds over the listed vertices;
+// nothing is read back.  Without `fates` the root pass writes every fate.
+static void enqueue_ng(pg_game *g, hipStream_t s, bool fates) {
+  const int32_t N = (int32_t)g->n_aug;
+  Prof *pf = &g->prof;
+  int32_t *ng = g->ng, *cand = g->cand;
+  const WalkBudget wb = walk_budget(g);
+  // own record 8, first successor record 8, result 4; state resets 5
+  const int wblk = walk_block(g);
+  PG_LAUNCH(pf, K_NG_WALK, 25.0 * N, k_ng_full, dim3(grid_for(N, wblk)),
+            dim3(wblk), 0, s, N, g->sp, g->pri, ng, cand, g->ctr,
+            wb.full, fates ? g->rs : (uint8_t *)nullptr, (int32_t *)nullptr,
+            g->wl_ng, g->wl_cap);
   for (int r = 1; r <= wb.rounds; ++r)
-    PG_LAUNCH(pf, K_NG_ROUND, 0.0, k_ng_round_list, lgrid, dim3(kBlock), 0,
-              s, N, g->sp, g->pri, ng, cand, g->ctr, (int)(r == wb.rounds),
-              wb.walk, g->wl_ng, g->wl_cap);
+    PG_LAUNCH(pf, K_NG_ROUND, 0.0, k_ng_round_list, list_grid(N, wblk),
+              dim3(kBlock), 0, s, N, g->sp, g->pri, ng, cand, g->ctr,
+              (int)(r == wb.rounds), wb.walk, g->wl_ng, g->wl_cap);
+}
+
+// The root phase of an exact valuation, likewise.
+static void enqueue_root(pg_game *g, hipStream_t s) {
+  const int32_t N = (int32_t)g->n_aug;
+  Prof *pf = &g->prof;
+  const WalkBudget wb = walk_budget(g);
+  const int wblk = walk_block(g);
   // own ng 4, parent's ng 4, sort key 4, rs 1 (+ rvpos 4 unless
   // relabeled); resets 12
   const int32_t *rvpos = kernel_rvpos(g);
   PG_LAUNCH(pf, K_ROOT_WALK, (rvpos ? 29.0 : 25.0) * N, k_root_full,
-            dim3(grid_for(N, wblk)), dim3(wblk), 0, s, N, ng, g->rs,
+            dim3(grid_for(N, wblk)), dim3(wblk), 0, s, N, g->ng, g->rs,
             g->rcand, g->key, g->ctr, wb.full, g->fh, rvpos,
             g->sk0, (int32_t *)nullptr, g->wl_rt, g->wl_cap);
   for (int r = 1; r <= wb.rounds; ++r)
-    PG_LAUNCH(pf, K_ROOT_ROUND, 0.0, k_root_round_list, lgrid,
-              dim3(kBlock), 0, s, N, ng, g->rs, g->rcand, g->key, g->ctr,
+    PG_LAUNCH(pf, K_ROOT_ROUND, 0.0, k_root_round_list, list_grid(N, wblk),
+              dim3(kBlock), 0, s, N, g->ng, g->rs, g->rcand, g->key, g->ctr,
               (int)(r == wb.rounds), wb.walk, rvpos, g->sk0, g->wl_rt,
               g->wl_cap);
   sum_dist(g->ctr, C_DIST_NF, C_NFIN, s, pf);
+}
+
+// ng and root phases with a fixed number of rounds; nothing is read back.
+static void enqueue_walks(pg_game *g, hipStream_t s) {
+  // the counters, and the parent sort's work buffer of a rank valuation
+  clear_valuation(g->ctr, g->dense ? nullptr : g->rs1, (int32_t)g->n_aug, s,
+                  &g->prof);
+  enqueue_ng(g, s, true);
+  enqueue_root(g, s);
+}
+
+// The walks of a valuation with coarse keys.  Its chains are at most
+// walk_full + 2 * kCoarseRound long, so a climb takes no more than twice
+// that; longer ones raise C_ABORT.
+constexpr int kCoarseRound = 128;
+void enqueue_coarse(pg_game *g, hipStream_t s) {
+  const int32_t N = (int32_t)g->n_aug;
+  Prof *pf = &g->prof;
+  const WalkBudget wb = walk_budget(g);
+  const int wblk = walk_block(g);
+  clear_valuation(g->ctr, nullptr, N, s, pf);
+  enqueue_ng(g, s, false);
+  // own ng 4, the parent's 4, key 4, fate 1
+  PG_LAUNCH(pf, K_ROOT_WALK, 13.0 * N, k_coarse_full, dim3(grid_for(N, wblk)),
+            dim3(wblk), 0, s, N, g->n_oddpri, g->ng, g->rs, g->rcand, g->key,
+            g->ctr, wb.full, g->wl_rt, g->wl_cap);
+  for (int r = 1; r <= 2; ++r)
+    PG_LAUNCH(pf, K_ROOT_ROUND, 0.0, k_coarse_round_list, list_grid(N, wblk),
+              dim3(kBlock), 0, s, N, g->ng, g->rs, g->rcand, g->key, g->ctr,
+              (int)(r == 2), kCoarseRound, g->wl_rt, g->wl_cap);
 }
 
 // Clears the distributed counter at C_DIST_MISC and C_MISC, runs `launch`
@@ -1048,7 +1173,8 @@ static void enqueue_rank_emit(pg_game *g, hipStream_t s, bool device_reduced) {
 
 // fresh: the switch counters are still zero from the valuation's own
 // clearing (an iteration: walks, valuation, All_Odd in one sequence)
-static void enqueue_switch(pg_game *g, bool odd, hipStream_t s, bool fresh) {
+static void enqueue_switch(pg_game *g, bool odd, hipStream_t s, bool fresh,
+                           bool coarse = false) {
   const int32_t N = (int32_t)g->n_aug;
   Prof *pf = &g->prof;
   if (!fresh) fill_i32(g->ctr + C_DIST_SW, 0, kDistSlots * kDistStride, s, pf);
@@ -1056,14 +1182,15 @@ static void enqueue_switch(pg_game *g, bool odd, hipStream_t s, bool fresh) {
   // counted once; its key is one of the row's) -> 28; per edge: target 4
   // and its key 4
   if (odd && g->tsw) {
-    enqueue_tsw_odd(g, s);
+    enqueue_tsw_odd(g, s, coarse);
   } else if (odd) {
     const int64_t cnt = g->n_odd;
     if (cnt > 0)
       PG_LAUNCH(pf, K_ODD_SWITCH, 28.0 * cnt + 8.0 * g->m_odd, k_odd_switch,
                 dim3(grid_for(cnt)), dim3(kBlock), 0, s, N, cnt, g->odd_ids,
                 g->off, g->tgt, g->key, g->pri, g->sp, g->ctr,
-                cnt <= kIncRowOdd ? g->elem : (int2 *)nullptr);
+                cnt <= kIncRowOdd ? g->elem : (int2 *)nullptr,
+                coarse ? tie_list(g) : (int32_t *)nullptr);
   } else {
     const int64_t cnt = N - g->n_odd;
     if (cnt > 0)
@@ -1151,14 +1278,21 @@ static pg_status check_ctr(pg_game *g) {
 // host synchronisation on the common path.
 // Captures one best-response iteration (fixed sizes and buffers: every size
 // a kernel needs is read on the device) on a private stream, as a graph.
-static pg_status capture_iteration(pg_game *g, hipGraphExec_t *ex) {
+static pg_status capture_iteration(pg_game *g, hipGraphExec_t *ex,
+                                   bool coarse) {
   if (!g->cap_stream)
     PG_HIP(hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking));
   hipStream_t cs = g->cap_stream;
   PG_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  enqueue_walks(g, cs);
-  enqueue_values(g, cs);
-  enqueue_any_switch(g, true, cs, true);
+  if (coarse) {
+    enqueue_coarse(g, cs);
+    enqueue_switch(g, true, cs, true, true);
+    enqueue_ties(g, cs);
+  } else {
+    enqueue_walks(g, cs);
+    enqueue_values(g, cs);
+    enqueue_any_switch(g, true, cs, true);
+  }
   hipGraph_t gr = nullptr;
   hipError_t e = hipStreamEndCapture(cs, &gr);
   if (e == hipSuccess) e = hipGraphInstantiate(ex, gr, nullptr, nullptr, 0);
@@ -1184,7 +1318,7 @@ static pg_status run_valuation(pg_game *g, hipStream_t s, bool odd_switch,
   if (odd_switch && g->use_graph && !g->careful && !g->prof.on &&
       !g->host_rl) {
     hipGraphExec_t &ex = g->iter_exec;
-    if (!ex && capture_iteration(g, &ex) != PG_OK) {
+    if (!ex && capture_iteration(g, &ex, false) != PG_OK) {
       g->use_graph = false;  // capture refused: stay eager from now on
       (void)hipGetLastError();
     }
@@ -1249,6 +1383,53 @@ pg_status valuation_device(pg_game *g, hipStream_t s, int64_t *n_finite_out) {
 pg_status iteration_device(pg_game *g, hipStream_t s, int32_t *count,
                            int64_t *n_finite) {
   return run_valuation(g, s, true, count, n_finite);
+}
+
+pg_status iteration_coarse(pg_game *g, hipStream_t s, int32_t *count,
+                           bool *done) {
+  if (g->timed && !g->ev_a) {
+    PG_HIP(hipEventCreate(&g->ev_a));
+    PG_HIP(hipEventCreate(&g->ev_b));
+  }
+  if (g->timed) PG_HIP(hipEventRecord(g->ev_a, s));
+  hipGraphExec_t &ex = g->iter_coarse;
+  const bool graph = g->use_graph && !g->prof.on;
+  if (graph && !ex && capture_iteration(g, &ex, true) != PG_OK) {
+    g->use_graph = false;  // capture refused: stay eager from now on
+    (void)hipGetLastError();
+  }
+  if (graph && ex) {
+    PG_HIP(hipGraphLaunch(ex, s));
+  } else {
+    enqueue_coarse(g, s);
+    enqueue_switch(g, true, s, true, true);
+    enqueue_ties(g, s);
+  }
+  if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
+  PG_HIP(hipMemcpyAsync(g->hctr, g->ctr, sizeof(int32_t) * C_DIST_SW,
+                        hipMemcpyDeviceToHost, s));
+  PG_HIP(hipStreamSynchronize(s));
+  if (g->prof.on) g->prof.flush();
+  if (!g->timed ||
+      hipEventElapsedTime(&g->last_ms, g->ev_a, g->ev_b) != hipSuccess)
+    g->last_ms = 0.0f;
+  *done = !g->hctr[C_ABORT];
+  *count = g->hctr[C_NDEC];
+  return check_ctr(g);
+}
+
+pg_status ranks_device(pg_game *g, hipStream_t s) {
+  g->nlevels = plan_levels(g->n_aug, g->tune.stride0);
+  clear_valuation(g->ctr, g->rs1, (int32_t)g->n_aug, s, &g->prof);
+  enqueue_root(g, s);
+  enqueue_values(g, s);
+  PG_TRY(read_ctr(g, s));
+  if (g->hctr[C_ABORT]) {
+    fates_reset(g, s);
+    PG_TRY(redo_valuation(g, s));
+    PG_TRY(read_ctr(g, s));
+  }
+  return check_ctr(g);
 }
 
 void mark_top(pg_game *g, hipStream_t s) {

@@ -1,7 +1,8 @@
 """Valuations by their changed part (csrc/pg_inc.hip) against the oracle, at
 the sizes and shapes where the path changes: games that always fit one block
 and the first that do not, hubs beyond the in-degree bound, repeated edges,
-ng chains beyond the comparison's bound; and runs stopped by caps against the
+ng chains beyond the comparison's bound, games whose vertices share a few
+roots (their coarse keys tie); and runs stopped by caps against the
 same runs on full valuations (a trace asks for those).  Everything is exact.
 """
 from __future__ import annotations
@@ -50,6 +51,18 @@ def _rising(n, seed):
     return g
 
 
+def _stairs(n, seed, step):
+    """A chain whose priorities rise by stairs of `step` vertices: most
+    vertices share a few roots and the ng chains have about n / step links."""
+    g = synth.chain_game(n, seed)
+    rng = np.random.default_rng(seed)
+    pri = np.arange(n, dtype=np.int32)
+    for a in range(0, n, step):
+        rng.shuffle(pri[a:a + step])
+    g["pri"] = pri
+    return g
+
+
 GAMES = {
     "tiny": lambda: synth.random_game(3, 2, 2, 1),
     "one_block": lambda: synth.random_game(900, 2, 5, 2),
@@ -63,6 +76,8 @@ GAMES = {
     "doubled_small": lambda: _doubled(701, 9),
     "rising": lambda: _rising(3000, 10),
     "rising_large": lambda: _rising(12001, 11),
+    "stairs": lambda: _stairs(40009, 12, 600),
+    "stairs_wide": lambda: _stairs(40009, 13, 8000),
 }
 
 
