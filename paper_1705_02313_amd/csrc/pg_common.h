@@ -448,18 +448,6 @@ __device__ __forceinline__ int32_t wave_place(int32_t *ctr, bool pred) {
   return base + (int32_t)__popcll(b & ((1ull << lane) - 1ull));
 }
 
-// Coarse keys: a finite vertex's key is that of the last vertex of its ng
-// chain before the sink (its root, a child of the sink in the ng tree).
-// Siblings are in signed-priority order, the order of a relabeled game's
-// ids, and the sink lies between its odd and its even children, so vertices
-// with different coarse keys compare as their ranks do.
-__device__ __host__ __forceinline__ int32_t coarse_key(int32_t root) {
-  return 2 * root + 1;
-}
-__device__ __host__ __forceinline__ int32_t coarse_sink(int32_t n_oddpri) {
-  return 2 * n_oddpri;
-}
-
 __device__ __forceinline__ int ld_relaxed(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -560,6 +548,9 @@ pg_status valuation_device(pg_game *g, hipStream_t s, int64_t *n_finite_out);
 // The walks and the valuation of g->sp with no host synchronisation (for
 // graph capture); the counters are not read back.
 void enqueue_valuation(pg_game *g, hipStream_t s);
+// The walks of a valuation with coarse keys (pg_coarse.h).  Its ng chains
+// are bounded, and with them the climbs; longer ones raise C_ABORT.
+void enqueue_coarse(pg_game *g, hipStream_t s);
 // After a valuation whose bounded walks left vertices open (C_ABORT read
 // back into g->hctr): the host-driven walks and the valuation again.
 pg_status redo_valuation(pg_game *g, hipStream_t s);

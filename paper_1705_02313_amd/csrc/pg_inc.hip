@@ -44,6 +44,7 @@
 // 2M-vertex chain, 5.8 -> 2.8 ms at 40,000 vertices.
 #include <algorithm>
 
+#include "pg_coarse.h"
 #include "pg_rows.h"
 
 namespace pgk {
@@ -66,7 +67,6 @@ constexpr int kIncRounds = 8;        // most find rounds of the device form
 constexpr int kFindRounds = 3;       // find rounds of the device form
 constexpr int kFindLevels = 128;     // levels of one round
 constexpr int kIncMaxDegree = 2048;  // in-edges of one vertex, else give up
-constexpr int kIncClimb = 1024;      // ng steps of one comparison
 constexpr int kIncFate = 1024;       // ng steps of one fate
 constexpr int kIncBlocks = 1024;
 
@@ -130,103 +130,18 @@ struct IncP {
   uint32_t odd_cols;
 };
 
-// 1, 0 or -1: Val(x) above, equal to or below Val(y), for finite x and y.
-// The ng chains meet at their least common ancestor; in the tree's listing
-// order a vertex lies above its odd and below its even children's subtrees,
-// and siblings are in signed-priority order, which is the order of the
-// (relabeled) ids.
-__device__ __forceinline__ int inc_climb(const IncP &P, int32_t x, int32_t y,
-                                         bool *stop) {
-  const int32_t N = P.N;
-  int32_t a = x, b = y, ca = -1, cb = -1;
-  // a vertex's ng is fetched with its priority: one round trip a step
-  int32_t pa = a >= N ? 2147483647 : P.pri[a], na = a >= N ? N : P.ng[a];
-  int32_t pb = b >= N ? 2147483647 : P.pri[b], nb = b >= N ? N : P.ng[b];
-  for (int s = 0; a != b; ++s) {
-    if (s >= kIncClimb) {
-      *stop = true;
-      return 0;
-    }
-    if (pa < pb) {
-      ca = a;
-      a = na;
-      pa = a >= N ? 2147483647 : P.pri[a];
-      na = a >= N ? N : P.ng[a];
-    } else {
-      cb = b;
-      b = nb;
-      pb = b >= N ? 2147483647 : P.pri[b];
-      nb = b >= N ? N : P.ng[b];
-    }
-  }
-  if (ca < 0) return cb < 0 ? 0 : (cb >= P.n_oddpri ? -1 : 1);
-  if (cb < 0) return ca >= P.n_oddpri ? 1 : -1;
-  return ca > cb ? 1 : -1;
+__device__ __forceinline__ CoarseP coarse(const IncP &P) {
+  return CoarseP{P.N, P.n_oddpri, P.off, P.tgt, P.pri, P.ng, P.key};
 }
 
-// the same for any two vertices (or the sink) with their coarse keys
-__device__ __forceinline__ int inc_cmp(const IncP &P, int32_t x, int32_t kx,
-                                       int32_t y, int32_t ky, bool *stop) {
-  if (kx != ky) return kx < ky ? -1 : 1;
-  if (x == y || kx == PG_KEY_TOP) return 0;
-  return inc_climb(P, x, y, stop);
-}
-
-// All_Odd and All_Even (section 4, section 3) for one vertex: true when v
-// switches, to *to.  Most rows are decided by the coarse keys; one whose
-// best key is met on two vertices is read again with comparisons.
 __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
                                            int32_t *to, bool *stop) {
   const int2 me = P.sp[v];
   if (me.y == kTopMark) return false;   // known to stay top
-  const int64_t e0 = P.off[v], e1 = P.off[v + 1];
-  const int32_t cur = me.x;
-  const int32_t kn = odd ? 0 : P.key[P.N];
-  int32_t best = odd ? -1 : P.N, kb = kn, kc = kn;
-  bool have = !odd && cur == P.N, tie = false;
-  for (int64_t q = e0; q < e1; q += 4) {
-    int32_t u[4], k[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) u[j] = q + j < e1 ? P.tgt[q + j] : -1;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) k[j] = u[j] >= 0 ? P.key[u[j]] : 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (u[j] < 0) continue;
-      if (u[j] == cur) {
-        kc = k[j];
-        have = true;
-      }
-      if (odd ? best < 0 || k[j] < kb : k[j] > kb) {
-        best = u[j];
-        kb = k[j];
-        tie = false;
-      } else {
-        tie |= k[j] == kb && u[j] != best;
-      }
-    }
-  }
-  if (!have) kc = P.key[cur];
-  // top never ties: the first top option is taken, a top minimum stays
-  if (kb == PG_KEY_TOP || !(tie || (kb == kc && best != cur))) {
-    *to = best;
-    return odd ? kb < kc : kb > kc;
-  }
-  best = odd ? -1 : P.N;
-  kb = kn;
-  for (int64_t q = e0; q < e1; ++q) {
-    const int32_t u = P.tgt[q], k = P.key[u];
-    if (best >= 0) {
-      const int c = inc_cmp(P, u, k, best, kb, stop);
-      if (!(odd ? c < 0 : c > 0)) continue;
-    }
-    best = u;
-    kb = k;
-  }
-  if (best == cur) return false;
-  const int c = inc_cmp(P, best, kb, cur, kc, stop);
-  *to = best;
-  return odd ? c < 0 : c > 0;
+  const CoarseP C = coarse(P);
+  bool tie;
+  const bool sw = coarse_row(C, v, me.x, odd, to, &tie);
+  return tie ? coarse_exact(C, v, me.x, odd, to, stop) : sw;
 }
 
 // The rule of a rank game (D = 0) or with count rows of D ints.

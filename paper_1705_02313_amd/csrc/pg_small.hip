@@ -173,8 +173,8 @@ __device__ __forceinline__ bool small_walks(const Small &S, BlockSum &sum,
   return !sum(deep);
 }
 
-// 1, 0 or -1: Val(x) above, equal to or below Val(y) (as inc_climb of
-// pg_inc.hip); rx and ry are their roots.
+// 1, 0 or -1: Val(x) above, equal to or below Val(y) (as
+// coarse_climb of pg_coarse.h); rx and ry are their roots.
 __device__ __forceinline__ int small_cmp(const Small &S, int32_t x, int32_t rx,
                                          int32_t y, int32_t ry) {
   const int32_t N = S.N;

@@ -30,7 +30,7 @@
 //           at fixed element strides, every sublist summed by one thread, the
 //           reduced list ranked recursively and finally in LDS by pointer
 //           jumping, then each sublist is walked again to emit keys
-#include "pg_common.h"
+#include "pg_coarse.h"
 
 namespace pgk {
 

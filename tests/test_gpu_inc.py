@@ -12,8 +12,9 @@ import pytest
 
 from oracle import orc
 from paper_1705_02313_amd import synth
-from paper_1705_02313_amd.pg import Game
+from paper_1705_02313_amd.pg import Batch, Game
 from tests.helpers import to_np
+from tests.test_gpu_batch import _check, _drain
 
 pytestmark = pytest.mark.gpu
 
@@ -137,3 +138,16 @@ def test_caps_stop_at_the_same_strategies(name):
             for k in ("n_major", "n_valuations", "n_odd_switches",
                       "n_even_switches"):
                 assert a["stats"][k] == b["stats"][k], (cap, k)
+
+
+@pytest.mark.parametrize("names", [
+    ("stairs", "stairs_wide", "hub", "doubled", "chain", "tiny", "mid"),
+    ("rising", "mid", "stairs_wide"),   # chains too long: ranks in a layout
+])
+def test_batches_equal_the_oracle(names):
+    games = [GAMES[k]() for k in names]
+    with Batch(max_vertices=1 << 18, max_edges=1 << 20) as b:
+        tickets = [b.submit(g) for g in games]
+        out = _drain(b, list(tickets))
+    for g, t in zip(games, tickets):
+        _check(g, out[t])
