@@ -297,6 +297,7 @@ struct pg_game {
     bool on = false;
     bool dirty = false;     // the fates are not the last exact valuation's
     bool exact = false;     // g->key holds ranks, not coarse keys
+    bool queue = false;     // the find's queue is empty (-1 throughout)
     bool pending = false;   // nsw decisions in list `cur` to apply
     bool d_valid = false;   // the list's first a0 entries hold every change
                             // since the last All_Even

@@ -59,13 +59,14 @@ enum IncCounter : int {
   // block form only
   I_STATE = 5, I_NVAL = 6, I_ODDSW = 7, I_EVENSW = 8, I_MAJOR = 9,
   I_INNER = 10, I_A0 = 11, I_CUR = 12, I_EPOCH = 13,
-  I_NF = 16,      // frontier lengths, one per find round
-  I_WORDS = 64
+  I_OPEN = 16,    // passes after the first: vertices left for them
+  I_WORDS = 64,   // the part copied to the host
+  // the find's queue, a line each
+  I_TICKET = 64, I_QTAIL = 96, I_QDONE = 128,
+  I_ALL = 160
 };
 static_assert((int)I_ERR == (int)C_ERR, "the ng walk reports through ctr[0]");
-constexpr int kIncRounds = 8;        // most find rounds of the device form
-constexpr int kFindRounds = 3;       // find rounds of the device form
-constexpr int kFindLevels = 128;     // levels of one round
+constexpr int kFindLevels = 512;     // levels of a device form's find
 constexpr int kIncMaxDegree = 2048;  // in-edges of one vertex, else give up
 constexpr int kIncFate = 1024;       // ng steps of one fate
 constexpr int kIncBlocks = 1024;
@@ -122,8 +123,8 @@ struct IncP {
   int32_t list_cap;
   int32_t *cl;             // candidates (with repeats: cmark tells them)
   int32_t cl_cap;
-  int32_t *f[2];           // find frontiers
-  int32_t f_cap;
+  int32_t *q;              // the find's queue (kFindChunk-int chunks, -1)
+  int32_t q_cap;           // chunks
   // count valuations (kernels with D > 0)
   int32_t *cnt;
   const uint8_t *pidx;
@@ -317,7 +318,7 @@ __device__ __forceinline__ bool inc_row(const IncP &P, int32_t epoch,
 // ---------------------------------------------------------------------------
 // the device form: one step in a few kernels
 // ---------------------------------------------------------------------------
-// Applies the decisions: A and the first frontier start with them.
+// Applies the decisions: A starts with them.
 __global__ __launch_bounds__(kBlock) void k_inc_begin(
     IncP P, int32_t epoch, int32_t a0, const int2 *__restrict__ dec,
     int32_t nsw, int32_t *ic) {
@@ -326,12 +327,8 @@ __global__ __launch_bounds__(kBlock) void k_inc_begin(
     const int2 d = dec[i];
     inc_apply(P, epoch, d);
     P.list[a0 + i] = d.x;
-    P.f[0][i] = d.x;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ic[I_NA] = nsw;
-    ic[I_NF] = nsw;
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) ic[I_NA] = nsw;
 }
 
 // One in-edge x of w in A: its source joins A when w is its successor; true
@@ -378,25 +375,58 @@ __device__ __forceinline__ int find_lanes(int n, int T) {
   return n * 8 <= T ? 8 : n * 4 <= T ? 4 : n * 2 <= T ? 2 : 1;
 }
 
-// One find round: a block takes chunks of the frontier and follows the
-// in-edges breadth first by itself, its part of A and its candidates (the
-// Odd sources: they have an option in A) in LDS
-// (plays inside A are tens of vertices long: a kernel per level would be
-// mostly launches, and a place in a global list per level mostly atomics'
-// round trips).  A level too wide for the block, or past max_levels, goes to
-// the next round's frontier.
-constexpr int kFindChunk = 64, kFindA = 2048, kFindC = 2048;
-__global__ __launch_bounds__(kBlock) void k_inc_find(
-    IncP P, int32_t epoch, int32_t a0, int round, int max_levels, int last,
-    int32_t *ic) {
+// The find.  A block takes a chunk of A and follows the in-edges breadth
+// first by itself, its part of A and its candidates (the Odd sources: they
+// have an option in A) in LDS: plays inside A are tens of vertices long, so
+// a kernel per level would be mostly launches, and a place in a global list
+// per level mostly atomics' round trips.  A level costs a block two round
+// trips (3 us), and per 64 vertices the rate at which one CU fetches random
+// lines; trees are uneven (on the 10M-vertex game one switch can hold 200k
+// vertices in 90 levels), so a level beyond kFindKeep vertices hands the
+// rest on in chunks of a queue that idle blocks wait at.  Two blocks per CU
+// with the queue took the longest finds of that game from 3.1 and 2.0 to 1.3
+// and 0.77 ms (all 38: 11.4 -> 7.1 ms) against three launches that each
+// handed their widest levels to the next; what is left are the levels.
+// 256, 1024 and 2048 blocks were 0-4 % slower.
+//
+// Chunk t is A's own t-th stretch for t < S, else place t - S of the queue.
+// Blocks take tickets in order and wait for their chunk to come, or for all
+// S + tail chunks to be done.  A waiting block needs nothing but the blocks
+// that hold earlier tickets, and these run: no order of residency can stop
+// it.  A queue place holds -1 until its writer stores the value, and again
+// after its reader took it.
+constexpr int kFindChunk = 64, kFindA = 1024, kFindC = 2048;
+constexpr int kFindKeep = 128, kFindBlocks = 512;
+constexpr int kFindItems = kFindChunk - 1;   // of a queue chunk: word 0 is
+                                             // its level, -2 no item
+constexpr int kFindWait = 1 << 20;           // polls, then the step gives up
+
+// the next chunk, or -1: all done, or the step gave up
+__device__ __forceinline__ int32_t find_ticket(int32_t S, int32_t *ic) {
+  const int32_t t = atomicAdd(&ic[I_TICKET], 1);
+  if (t < S) return t;
+  for (int k = 0; k < kFindWait; ++k) {
+    // done first (never negative: the tail's address waits for it): when it
+    // has reached S + tail, no chunk was open then
+    const int32_t done = ld_relaxed(&ic[I_QDONE]);
+    const int32_t tail = ld_relaxed(&ic[I_QTAIL + (done < 0)]);
+    if (tail > t - S) return t;
+    if (done == S + tail || ld_relaxed(&ic[I_STOP])) return -1;
+    __builtin_amdgcn_s_sleep(8);
+  }
+  atomicOr(&ic[I_STOP], 1);
+  return -1;
+}
+
+__global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
+                                                     int32_t a0, int32_t nsw,
+                                                     int32_t *ic) {
   __shared__ int32_t la[kFindA], lc[kFindC];
   __shared__ uint2 lr[kFindA];   // in-edge ranges of la
-  __shared__ int32_t s_na, s_nc, s_base, s_stop;
-  if (ic[I_STOP]) return;
+  __shared__ int32_t s_na, s_nc, s_base, s_q, s_stop, s_t, s_level;
   const int tid = threadIdx.x;
-  const int32_t cnt = ic[I_NF + round];
-  const int32_t *fin = P.f[round & 1];
-  int32_t *fout = P.f[(round + 1) & 1];
+  const int lane = tid & (kWave - 1);
+  const int32_t S = (nsw + kFindChunk - 1) / kFindChunk;
   if (tid == 0) s_stop = 0;
   // entries [from, to) of an LDS list to a global one (all threads)
   auto flush = [&](const int32_t *l, int from, int to, int32_t *ctr,
@@ -412,25 +442,46 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(
     }
     __syncthreads();
   };
-  for (int32_t c0 = blockIdx.x * kFindChunk; c0 < cnt;
-       c0 += gridDim.x * kFindChunk) {
-    int beg = 0, end = min(kFindChunk, cnt - c0);
-    int flushed = end;   // the frontier is in A's list already
+  for (;;) {
     __syncthreads();
-    if (tid < end) {
-      const int32_t w = fin[c0 + tid];
-      la[tid] = w;
-      lr[tid] = make_uint2(P.in_off[w], P.in_off[w + 1]);
-    }
-    if (tid == 0) {
-      s_na = end;
-      s_nc = 0;
+    if (tid == 0) s_t = find_ticket(S, ic);
+    __syncthreads();
+    const int32_t t = s_t;
+    if (t < 0) break;
+    if (tid < kWave) {   // (a chunk is a wave)
+      int32_t w = -2, lev = 0;
+      if (t < S) {
+        if (t * kFindChunk + lane < nsw) w = P.list[a0 + t * kFindChunk + lane];
+      } else {
+        int32_t *q = P.q + (int64_t)(t - S) * kFindChunk + lane;
+        for (int k = 0; (w = ld_relaxed(q)) == -1; ++k)
+          if (k >= kFindWait || ld_relaxed(&ic[I_STOP])) {
+            w = -2;
+            s_stop = 1;
+            break;
+          }
+        st_relaxed(q, -1);
+        lev = __shfl(w, 0);
+        if (lane == 0) w = -2;
+      }
+      const uint64_t b = __ballot(w >= 0);
+      if (w >= 0) {
+        const int at = __popcll(b & ((1ull << lane) - 1ull));
+        la[at] = w;
+        lr[at] = make_uint2(P.in_off[w], P.in_off[w + 1]);
+      }
+      if (lane == 0) {
+        s_na = __popcll(b);
+        s_nc = 0;
+        s_level = lev;
+      }
     }
     __syncthreads();
-    for (int level = 0; beg < end; ++level) {
-      if (level >= max_levels || end - beg > kFindA / 2) {
-        flush(la, beg, end, &ic[I_NF + round + 1], fout, P.f_cap);
-        if (last && tid == 0) s_stop = 1;
+    int beg = 0, end = s_na, level = s_level;
+    int flushed = end;   // the chunk is in A's list already
+    for (; beg < end; ++level) {
+      if (level >= kFindLevels) {
+        s_stop = 1;
         break;
       }
       const int L = find_lanes(end - beg, kBlock);
@@ -468,14 +519,27 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(
             if (oc && at < P.cl_cap) P.cl[at] = u;
             else if (oc) s_stop = 1;
           }
-          if (__ballot(oa)) {
+          const uint64_t bo = __ballot(oa);
+          if (bo) {   // one or two chunks of the wave's own
             const int32_t at = wave_place(&ic[I_NA], oa);
-            const int32_t af = wave_place(&ic[I_NF + round + 1], oa);
-            if (oa && last) s_stop = 1;
-            if (oa && (a0 + at >= P.list_cap || af >= P.f_cap)) s_stop = 1;
-            else if (oa) {
-              P.list[a0 + at] = u;
-              fout[af] = u;
+            if (oa && a0 + at >= P.list_cap) s_stop = 1;
+            else if (oa) P.list[a0 + at] = u;
+            const int n = __popcll(bo), nq = (n + kFindItems - 1) / kFindItems;
+            int32_t q0 = 0;
+            if (lane == 0) q0 = atomicAdd(&ic[I_QTAIL], nq);
+            q0 = __shfl(q0, 0);
+            if (q0 + nq > P.q_cap) {
+              if (lane == 0) atomicOr(&ic[I_STOP], 1);
+            } else {
+              int32_t *q = P.q + (int64_t)q0 * kFindChunk;
+              for (int k = 0; k < nq; ++k)
+                if (lane == 0 || k * kFindItems + lane - 1 >= n)
+                  st_relaxed(q + k * kFindChunk + lane,
+                             lane == 0 ? level + 1 : -2);
+              const int r = __popcll(bo & ((1ull << lane) - 1ull));
+              if (oa)
+                st_relaxed(q + r / kFindItems * kFindChunk + 1 +
+                               r % kFindItems, u);
             }
           }
         }
@@ -489,48 +553,64 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(
         flush(lc, 0, nc, &ic[I_NC], P.cl, P.cl_cap);
         if (tid == 0) s_nc = 0;
       }
-      if (end > kFindA / 2) {
-        // the level moves to the front of the list
+      if (end - beg > kFindKeep || end > kFindA / 2) {
         flush(la, flushed, end, &ic[I_NA], P.list + a0, P.list_cap - a0);
-        const int n = end - beg;
-        if (n <= kFindA / 2) {
-          int32_t t[kFindA / 2 / kBlock];
-          uint2 tr[kFindA / 2 / kBlock];
-#pragma unroll
-          for (int k = 0; k < kFindA / 2 / kBlock; ++k) {
-            const int i = k * kBlock + tid;
-            t[k] = i < n ? la[beg + i] : 0;
-            tr[k] = i < n ? lr[beg + i] : make_uint2(0u, 0u);
+        if (end - beg > kFindKeep) {
+          // all but the first kFindChunk to 126 go to the queue
+          const int nq = (end - beg - kFindChunk) / kFindItems;
+          if (tid == 0) {
+            s_q = atomicAdd(&ic[I_QTAIL], nq);
+            if (s_q + nq > P.q_cap) atomicOr(&ic[I_STOP], 1);
           }
           __syncthreads();
-#pragma unroll
-          for (int k = 0; k < kFindA / 2 / kBlock; ++k) {
-            const int i = k * kBlock + tid;
-            if (i < n) {
-              la[i] = t[k];
-              lr[i] = tr[k];
+          const int from = end - nq * kFindItems;
+          if (s_q + nq > P.q_cap) {
+            s_stop = 1;
+          } else {
+            for (int i = tid; i < nq * kFindChunk; i += kBlock) {
+              const int k = i / kFindChunk, j = i % kFindChunk;
+              st_relaxed(P.q + (int64_t)s_q * kFindChunk + i,
+                         j == 0 ? level + 1
+                                : la[from + k * kFindItems + j - 1]);
             }
           }
-          beg = 0;
-          end = n;
-          if (tid == 0) s_na = n;
+          end = from;
         }
-        flushed = end;
+        // the level moves to the front of the list
+        const int n = end - beg;   // at most kFindKeep
+        int32_t mv = 0;
+        uint2 mr = make_uint2(0u, 0u);
+        if (tid < n) {
+          mv = la[beg + tid];
+          mr = lr[beg + tid];
+        }
+        __syncthreads();
+        if (tid < n) {
+          la[tid] = mv;
+          lr[tid] = mr;
+        }
+        beg = 0;
+        end = flushed = n;
+        if (tid == 0) s_na = n;
       }
       __syncthreads();
     }
     flush(la, flushed, end, &ic[I_NA], P.list + a0, P.list_cap - a0);
     __syncthreads();
     flush(lc, 0, min(s_nc, kFindC), &ic[I_NC], P.cl, P.cl_cap);
+    __syncthreads();
+    if (tid == 0) {
+      if (s_stop) atomicOr(&ic[I_STOP], 1);
+      atomicAdd(&ic[I_QDONE], 1);
+    }
   }
-  __syncthreads();
-  if (tid == 0 && s_stop) atomicOr(&ic[I_STOP], 1);
 }
+static_assert(kFindChunk == kWave && kFindKeep <= kBlock, "k_inc_find");
 
 __global__ __launch_bounds__(kBlock) void k_inc_walk(IncP P, int32_t a0,
                                                      int steps, int pass,
                                                      int last, int32_t *ic) {
-  if (ic[I_STOP] || (pass > 0 && !ic[I_NF + kIncRounds + pass])) return;
+  if (ic[I_STOP] || (pass > 0 && !ic[I_OPEN + pass])) return;
   const int32_t n = ic[I_NA];
   bool open = false;
   for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -539,7 +619,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_walk(IncP P, int32_t a0,
     if (pass > 0 && ld_relaxed(&P.ng[v]) >= 0) continue;
     open |= !inc_walk(P, &ic[I_ERR], v, steps);
   }
-  if (open) atomicOr(last ? &ic[I_STOP] : &ic[I_NF + kIncRounds + pass + 1],
+  if (open) atomicOr(last ? &ic[I_STOP] : &ic[I_OPEN + pass + 1],
                      1);
 }
 
@@ -550,7 +630,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_rows(IncP P, int32_t epoch,
                                                      int32_t a0, int steps,
                                                      int pass, int last,
                                                      int32_t *ic) {
-  if (ic[I_STOP] || (pass > 0 && !ic[I_NF + kIncRounds + pass])) return;
+  if (ic[I_STOP] || (pass > 0 && !ic[I_OPEN + pass])) return;
   const int32_t n = ic[I_NA];
   bool open = false;
   for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -562,7 +642,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_rows(IncP P, int32_t epoch,
       open = true;
     }
   }
-  if (open) atomicOr(last ? &ic[I_STOP] : &ic[I_NF + kIncRounds + pass + 1],
+  if (open) atomicOr(last ? &ic[I_STOP] : &ic[I_OPEN + pass + 1],
                      1);
 }
 
@@ -957,15 +1037,14 @@ static IncP inc_params(const pg_game *g) {
   P.odd_cols = g->odd_cols;
   P.mark = g->inc.mark;
   P.cmark = g->inc.cmark;
-  // the Euler list's records (4 N ints) and the parent sort's keys (N each)
+  // the Euler list's records (4 N ints) and the parent sort's keys (N)
   // are free between full valuations
   P.list = reinterpret_cast<int32_t *>(g->aux);
   P.list_cap = 2 * N;
   P.cl = P.list + 2 * (int64_t)N;
   P.cl_cap = 2 * N;
-  P.f[0] = reinterpret_cast<int32_t *>(g->sk0);
-  P.f[1] = reinterpret_cast<int32_t *>(g->sk1);
-  P.f_cap = N;
+  P.q = reinterpret_cast<int32_t *>(g->sk0);
+  P.q_cap = N / kFindChunk;
   return P;
 }
 
@@ -984,6 +1063,7 @@ bool inc_eligible(const pg_game *g) {
 bool inc_prepare(pg_game *g, hipStream_t s) {
   pg_game::Inc &x = g->inc;
   x.dirty = x.pending = x.d_valid = x.grown = x.even = x.exact = false;
+  x.queue = false;
   x.nsw = x.a0 = 0;
   x.skip = x.back = 0;
   x.on = false;
@@ -994,7 +1074,7 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     if (st == PG_OK) st = dev_alloc(&x.in, M);
     if (st == PG_OK) st = dev_alloc(&x.mark, N);
     if (st == PG_OK) st = dev_alloc(&x.cmark, N);
-    if (st == PG_OK) st = dev_alloc(&x.ic, I_WORDS);
+    if (st == PG_OK) st = dev_alloc(&x.ic, I_ALL);
     if (st == PG_OK)
       st = host_alloc((void **)&x.h, sizeof(int32_t) * I_WORDS);
     if (st != PG_OK) {
@@ -1095,6 +1175,7 @@ void inc_after_full(pg_game *g, int32_t switches, bool exact) {
   if (!x.on) return;
   x.dirty = !exact;
   x.exact = exact && !g->dense;
+  if (exact) x.queue = false;
   x.d_valid = false;
   x.a0 = 0;
   x.grown = false;
@@ -1155,13 +1236,13 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     const unsigned gb =
         std::min<unsigned>(kIncBlocks, grid_for(4 * (int64_t)x.nsw));
     const dim3 grid(std::max(gb, 64u)), blk(kBlock);
-    const dim3 fgrid(std::min<unsigned>(2048, grid_for(x.nsw, kFindChunk)));
-    fill_i32(x.ic, 0, I_WORDS, s, pf);
+    if (!x.queue) fill_i32(P.q, -1, N, s, pf);
+    x.queue = true;
+    fill_i32(x.ic, 0, I_ALL, s, pf);
     PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_begin, dim3(grid_for(x.nsw)), blk, 0,
               s, P, epoch, x.a0, inc_dec(g, x.cur), x.nsw, x.ic);
-    for (int r = 0; r < kFindRounds; ++r)
-      PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_find, fgrid, blk, 0, s, P, epoch,
-                x.a0, r, kFindLevels, (int)(r == kFindRounds - 1), x.ic);
+    PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_find, dim3(kFindBlocks), blk, 0, s,
+              P, epoch, x.a0, x.nsw, x.ic);
     if constexpr (D == 0) {
       PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0, 64,
                 0, 0, x.ic);
@@ -1208,6 +1289,7 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
         break;
     }
   } else if (x.h[I_STOP]) {
+    x.queue = false;
     inc_backoff(g);
   } else {
     x.back = 0;
@@ -1243,7 +1325,7 @@ static pg_status inc_even_t(pg_game *g, hipStream_t s, int32_t *count) {
   for (int pass = 0; x.h[I_STOP]; ++pass) {
     if (pass > 0) {   // a comparison outgrew its bound: ranks instead
       PG_TRY(ranks_device(g, s));
-      x.dirty = false;
+      x.dirty = x.queue = false;
       x.exact = true;
     }
     fill_i32(x.ic, 0, I_WORDS, s, pf);
