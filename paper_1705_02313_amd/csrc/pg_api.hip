@@ -674,6 +674,12 @@ void host_free(void *p) {
   (void)hipHostFree(p);
 }
 
+bool host_pinned(const void *p) {
+  const uint8_t *q = (const uint8_t *)p;
+  return !(tl_pool && q >= tl_pool->bump_host &&
+           q < tl_pool->bump_host + tl_pool->bump_hcap);
+}
+
 pg_status host_alloc(void **p, size_t bytes) {
   if (tl_pool) return tl_pool->alloc(p, bytes, true);
   PG_HIP(hipHostMalloc(p, bytes, hipHostMallocDefault));
@@ -681,8 +687,7 @@ pg_status host_alloc(void **p, size_t bytes) {
 }
 
 pg_status sync_ctr(pg_game *g, hipStream_t s) {
-  PG_HIP(hipMemcpyAsync(g->hctr, g->ctr, sizeof(int32_t) * C_COUNT,
-                        hipMemcpyDeviceToHost, s));
+  publish(g->hctr, g->ctr, C_COUNT, s);
   PG_HIP(hipStreamSynchronize(s));
   fold_switches(g->hctr);
   if (g->prof.on) g->prof.flush();
@@ -954,12 +959,10 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
     PG_TRY(dev_alloc((uint8_t **)&stmp, (int64_t)need + 16));
     tmp.p.push_back(stmp);
     scan_excl_u32(xp, did, n, stmp, s);
-    uint32_t last[2] = {0, 0};
-    PG_HIP(hipMemcpyAsync(&last[0], did + (n - 1), 4, hipMemcpyDeviceToHost,
-                          s));
-    PG_HIP(hipMemcpyAsync(&last[1], xp + (n - 1), 4, hipMemcpyDeviceToHost, s));
+    publish(g->hctr, (const int32_t *)did + (n - 1), 1, s);
+    publish(g->hctr + 1, (const int32_t *)xp + (n - 1), 1, s);
     PG_HIP(hipStreamSynchronize(s));
-    nxp = (int64_t)last[0] + last[1];
+    nxp = (int64_t)g->hctr[0] + g->hctr[1];
   }
   g->n_aug = n + nxp;
   g->m_aug = m + nxp;
@@ -1075,21 +1078,17 @@ pg_status finalize_state(pg_game *g, hipStream_t s, bool init_sp,
   hipLaunchKernelGGL(k_odd_flags, dim3(grid_for(N)), dim3(kBlock), 0, s,
                      g->owner, flags, N);
   scan_excl_u32(flags, oscan, N, g->scan_tmp, s);
-  uint32_t last[2] = {0, 0};
-  PG_HIP(hipMemcpyAsync(&last[0], oscan + (N - 1), 4, hipMemcpyDeviceToHost,
-                        s));
-  PG_HIP(hipMemcpyAsync(&last[1], flags + (N - 1), 4, hipMemcpyDeviceToHost,
-                        s));
+  publish(g->hctr, (const int32_t *)oscan + (N - 1), 1, s);
+  publish(g->hctr + 1, (const int32_t *)flags + (N - 1), 1, s);
   fill_i32((int32_t *)g->u64tmp, 0, 2, s);
   hipLaunchKernelGGL(k_count_odd_edges, dim3(1024), dim3(kBlock), 0, s,
                      g->off, g->owner, N, g->u64tmp);
-  unsigned long long me = 0;
-  PG_HIP(hipMemcpyAsync(&me, g->u64tmp, sizeof(me), hipMemcpyDeviceToHost, s));
+  publish(g->hctr + 2, (const int32_t *)g->u64tmp, 2, s);
   hipLaunchKernelGGL(k_split_players, dim3(grid_for(N)), dim3(kBlock), 0, s,
                      g->owner, oscan, g->odd_ids, g->even_ids, N);
   PG_HIP(hipStreamSynchronize(s));
-  g->n_odd = (int64_t)last[0] + last[1];
-  g->m_odd = (int64_t)me;
+  g->n_odd = (int64_t)g->hctr[0] + g->hctr[1];
+  g->m_odd = (int64_t)(uint32_t)g->hctr[2] | ((int64_t)g->hctr[3] << 32);
   return PG_OK;
 }
 

@@ -319,6 +319,27 @@ __global__ void k_batch_ctl2(int G, uint8_t *run, uint8_t *pending,
 }
 
 
+// A step's results per slot and the counters into pinned memory: one launch
+// in place of six copies of some hundred bytes (see publish).
+__global__ void k_batch_publish(int G, const uint8_t *newly,
+                                const int32_t *nval, const int32_t *nmaj,
+                                const int64_t *sw_odd, const int64_t *sw_even,
+                                uint8_t *h_newly, int32_t *h_nval,
+                                int32_t *h_nmaj, int64_t *h_sw_odd,
+                                int64_t *h_sw_even, const int32_t *ctr,
+                                int32_t *h_ctr) {
+  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < G;
+       s += gridDim.x * blockDim.x) {
+    h_newly[s] = newly[s];
+    h_nval[s] = nval[s];
+    h_nmaj[s] = nmaj[s];
+    h_sw_odd[s] = sw_odd[s];
+    h_sw_even[s] = sw_even[s];
+  }
+  if (blockIdx.x == 0 && threadIdx.x < C_DIST_SW)
+    h_ctr[threadIdx.x] = ctr[threadIdx.x];
+}
+
 // ---------------------------------------------------------------------------
 // Submissions in bulk: the games of one pg_batch_submit_many call are
 // validated and preprocessed together over their disjoint union.  Game g's
@@ -996,17 +1017,13 @@ void enqueue_step_rest(pg_batch *b, hipStream_t s) {
                      b->d_desc, b->d_gid, b->d_newly, a->sp, a->key, a->owner,
                      N, (int64_t)a->n_oddpri, a->ctr);
   uint8_t *r = b->h_res;
-  (void)hipMemcpyAsync(r, b->d_newly, G, hipMemcpyDeviceToHost, s);
-  (void)hipMemcpyAsync(r + res_off_nval(G), b->d_nval, 4 * (size_t)G,
-                       hipMemcpyDeviceToHost, s);
-  (void)hipMemcpyAsync(r + res_off_nmaj(G), b->d_nmaj, 4 * (size_t)G,
-                       hipMemcpyDeviceToHost, s);
-  (void)hipMemcpyAsync(r + res_off_swodd(G), b->d_sw_odd, 8 * (size_t)G,
-                       hipMemcpyDeviceToHost, s);
-  (void)hipMemcpyAsync(r + res_off_sweven(G), b->d_sw_even, 8 * (size_t)G,
-                       hipMemcpyDeviceToHost, s);
-  (void)hipMemcpyAsync(a->hctr, a->ctr, sizeof(int32_t) * C_COUNT,
-                       hipMemcpyDeviceToHost, s);
+  hipLaunchKernelGGL(k_batch_publish, dim3(std::min(64u, (unsigned)grid_for(G))),
+                     dim3(kBlock), 0, s, G,
+                     b->d_newly, b->d_nval, b->d_nmaj, b->d_sw_odd,
+                     b->d_sw_even, r, (int32_t *)(r + res_off_nval(G)),
+                     (int32_t *)(r + res_off_nmaj(G)),
+                     (int64_t *)(r + res_off_swodd(G)),
+                     (int64_t *)(r + res_off_sweven(G)), a->ctr, a->hctr);
 }
 
 // One step of every live game: replayed from the graph of the current

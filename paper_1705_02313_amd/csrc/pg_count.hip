@@ -737,8 +737,7 @@ static pg_status bf_best_response_t(pg_game *g, hipStream_t s,
               k_bf_round<D>, dim3(grid_for(N)), dim3(kBlock), 0, s, N, g->off,
               g->tgt, g->owner, g->pidx, g->sp, g->cnt, g->cnt2, g->odd_cols,
               g->ctr);
-    PG_HIP(hipMemcpyAsync(g->hctr, g->ctr, sizeof(int32_t) * C_COUNT,
-                          hipMemcpyDeviceToHost, s));
+    publish(g->hctr, g->ctr, C_COUNT, s);
     PG_HIP(hipStreamSynchronize(s));
     fold_switches(g->hctr);
     if (g->prof.on) g->prof.flush();

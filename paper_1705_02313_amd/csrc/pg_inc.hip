@@ -1114,9 +1114,9 @@ void inc_release(pg_game *g) {
   x = pg_game::Inc();
 }
 
-static pg_status inc_read(pg_game *g, hipStream_t s) {
-  PG_HIP(hipMemcpyAsync(g->inc.h, g->inc.ic, sizeof(int32_t) * I_WORDS,
-                        hipMemcpyDeviceToHost, s));
+// direct: the kernel wrote its results to the host's words itself
+static pg_status inc_read(pg_game *g, hipStream_t s, bool direct = false) {
+  if (!direct) publish(g->inc.h, g->inc.ic, I_WORDS, s);
   PG_HIP(hipStreamSynchronize(s));
   if (g->prof.on) g->prof.flush();
   if (g->inc.h[I_ERR] & ERR_INADMISSIBLE)
@@ -1230,7 +1230,8 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     R.d_valid = x.d_valid;
     R.with_even = with_even;
     PG_LAUNCH(pf, K_INC_BLOCK, 0.0, k_inc_block<D>, dim3(1),
-              dim3(inc_threads(D)), 0, s, P, R, inc_dec(g, 0), inc_dec(g, 1), x.ic);
+              dim3(inc_threads(D)), 0, s, P, R, inc_dec(g, 0), inc_dec(g, 1),
+              host_pinned(x.h) ? x.h : x.ic);
   } else {
     const int32_t epoch = ++x.epoch;
     const unsigned gb =
@@ -1260,7 +1261,7 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
               inc_dec(g, x.cur ^ 1), x.ic);
   }
   if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
-  PG_TRY(inc_read(g, s));
+  PG_TRY(inc_read(g, s, block && host_pinned(x.h)));
   if (!g->timed ||
       hipEventElapsedTime(&g->last_ms, g->ev_a, g->ev_b) != hipSuccess)
     g->last_ms = 0.0f;

@@ -318,15 +318,14 @@ struct ListBufs {
 
 // keeps the flagged entries of l->a (cnt of them; all ids 0..cnt-1 when
 // `ids`) in order in l->b, swaps the two and queues the new count into
-// *host (valid after the next synchronisation)
+// *host (of host_alloc; valid after the next synchronisation)
 void list_keep(ListBufs *l, int64_t cnt, bool ids, hipStream_t s,
                int32_t *host) {
   scan_excl_u32(l->flag, l->pos, cnt, l->stmp, s);
   hipLaunchKernelGGL(k_or_scatter, dim3(grid_for(cnt)), dim3(kBlock), 0, s,
                      ids ? nullptr : l->a, cnt, l->flag, l->pos, l->b,
                      l->dcnt);
-  (void)hipMemcpyAsync(host, l->dcnt, sizeof(int32_t), hipMemcpyDeviceToHost,
-                       s);
+  publish(host, l->dcnt, 1, s);
   std::swap(l->a, l->b);
 }
 
@@ -339,14 +338,14 @@ pg_status fixpoint_list(pg_game *g, hipStream_t s, int64_t bound,
       return pg_fail(PG_EINTERNAL, "odd-region fixpoint did not converge");
     fill_i32(g->ctr + C_MISC, 0, 1, s);
     for (int k = 0; k < 4; ++k) sweep(l->a, *cnt, g->ctr + C_MISC);
-    int32_t h[2] = {0, *cnt};
+    int32_t *h = g->hctr;
+    h[1] = *cnt;
     if (done) {
       hipLaunchKernelGGL(k_or_undecided, dim3(grid_for(*cnt)), dim3(kBlock),
                          0, s, l->a, *cnt, done, l->flag);
       list_keep(l, *cnt, false, s, &h[1]);
     }
-    PG_HIP(hipMemcpyAsync(&h[0], g->ctr + C_MISC, sizeof(int32_t),
-                          hipMemcpyDeviceToHost, s));
+    publish(&h[0], g->ctr + C_MISC, 1, s);
     PG_HIP(hipStreamSynchronize(s));
     *cnt = h[1];
     if (h[0] == 0) break;
@@ -403,8 +402,9 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
                     int32_t *cnt) -> pg_status {
     hipLaunchKernelGGL(k_or_select, dim3(gn), dim3(kBlock), 0, s, n, a, b,
                        mode, L.flag);
-    list_keep(&L, n, true, s, cnt);
+    list_keep(&L, n, true, s, g->hctr);
     PG_HIP(hipStreamSynchronize(s));
+    *cnt = g->hctr[0];
     return PG_OK;
   };
   PG_HIP(hipMemcpyAsync(alive, inx, n, hipMemcpyDeviceToDevice, s));
@@ -436,10 +436,9 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
                        cnt, off, tgt, col, reach, nontriv);
     hipLaunchKernelGGL(k_or_peel, dim3(gc), dim3(kBlock), 0, s, L.a, cnt,
                        alive, col, reach, nontriv, seed, L.flag);
-    int32_t next = 0;
-    list_keep(&L, cnt, false, s, &next);
+    list_keep(&L, cnt, false, s, g->hctr);
     PG_HIP(hipStreamSynchronize(s));
-    cnt = next;
+    cnt = g->hctr[0];
   }
   // R = what reaches the seed inside X (over X minus R); A = Odd's attractor
   // of R (over the vertices outside A), both in place

@@ -90,6 +90,18 @@ static unsigned capped_grid(int64_t n) {
   return g > 65536u ? 65536u : g;
 }
 
+__global__ void k_publish(int32_t *host, const int32_t *src, int n) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) host[i] = src[i];
+}
+
+void publish(int32_t *host, const int32_t *src, int n, hipStream_t s) {
+  if (host_pinned(host))
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, s, host, src, n);
+  else
+    (void)hipMemcpyAsync(host, src, sizeof(int32_t) * n,
+                         hipMemcpyDeviceToHost, s);
+}
+
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s, Prof *prof) {
   if (n <= 0) return;
   PG_LAUNCH(prof, K_FILL, 4.0 * n, k_fill_i32, dim3(capped_grid(n)),

@@ -35,7 +35,7 @@ constexpr size_t kSmallLds = 150 * 1024;  // dynamic LDS of a block at most
 constexpr uint32_t kOpen = 0x8000u;       // ng entry: still walking, low bits
                                           // its candidate
 
-// words of g->ctr a small kernel reports in (below C_DIST_SW)
+// words of g->hctr (g->ctr when that is not pinned) a small kernel reports in
 enum SmallCounter : int {
   S_STATE = 8, S_NVAL, S_ODDSW, S_EVENSW, S_MAJOR, S_INNER, S_NFIN, S_END
 };
@@ -771,13 +771,12 @@ static SmallGame small_game(const pg_game *g) {
   G.even_ids = g->even_ids;
   G.sp = g->sp;
   G.rs = g->rs;
-  G.ctr = g->ctr;
+  G.ctr = host_pinned(g->hctr) ? g->hctr : g->ctr;
   return G;
 }
 
 static pg_status small_read(pg_game *g, hipStream_t s) {
-  PG_HIP(hipMemcpyAsync(g->hctr, g->ctr, sizeof(int32_t) * S_END,
-                        hipMemcpyDeviceToHost, s));
+  if (!host_pinned(g->hctr)) publish(g->hctr, g->ctr, S_END, s);
   PG_HIP(hipStreamSynchronize(s));
   if (g->prof.on) g->prof.flush();
   if (g->hctr[C_ERR] & ERR_INVAL)
@@ -826,13 +825,12 @@ pg_status small_load(pg_game *g, int64_t n, int64_t m, const void *offsets,
   L.even_ids = g->even_ids;
   L.owner2 = g->owner;
   L.sp = g->sp;
-  L.ctr = g->ctr;
+  L.ctr = host_pinned(g->hctr) ? g->hctr : g->ctr;
   auto a = [](size_t b) { return (b + 15) & ~size_t(15); };
   hipLaunchKernelGGL(k_small_load, dim3(1), dim3(kSmallThreads),
                      2 * a(2 * n) + 2 * a(n) + 8 * (size_t)L.sort_n, s, L);
   PG_HIP(hipGetLastError());
-  PG_HIP(hipMemcpyAsync(g->hctr, g->ctr, sizeof(int32_t) * L_END,
-                        hipMemcpyDeviceToHost, s));
+  if (!host_pinned(g->hctr)) publish(g->hctr, g->ctr, L_END, s);
   PG_HIP(hipStreamSynchronize(s));
   if (!g->hctr[L_STATE]) return PG_OK;
   *done = true;

@@ -920,8 +920,7 @@ static int walk_block(const pg_game *g) {
 constexpr int kMaxRounds = 64;    // rounds of the careful path before failing
 
 static pg_status read_ctr(pg_game *g, hipStream_t s) {
-  PG_HIP(hipMemcpyAsync(g->hctr, g->ctr, sizeof(int32_t) * C_COUNT,
-                        hipMemcpyDeviceToHost, s));
+  publish(g->hctr, g->ctr, C_COUNT, s);
   PG_HIP(hipStreamSynchronize(s));
   fold_switches(g->hctr);
   if (g->prof.on) {
@@ -1406,8 +1405,7 @@ pg_status iteration_coarse(pg_game *g, hipStream_t s, int32_t *count,
     enqueue_ties(g, s);
   }
   if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
-  PG_HIP(hipMemcpyAsync(g->hctr, g->ctr, sizeof(int32_t) * C_DIST_SW,
-                        hipMemcpyDeviceToHost, s));
+  publish(g->hctr, g->ctr, C_DIST_SW, s);
   PG_HIP(hipStreamSynchronize(s));
   if (g->prof.on) g->prof.flush();
   if (!g->timed ||
