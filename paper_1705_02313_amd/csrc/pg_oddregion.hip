@@ -9,11 +9,13 @@
 //   X  the vertices from which Odd avoids every Even vertex forever (the
 //      load's fixpoint rounds, inx)
 //   R  the vertices of X from which Odd, moving inside X, reaches a cycle
-//      whose largest priority is odd: strongly connected components of X
-//      are peeled by colouring rounds -- every vertex takes the largest
-//      (priority, id) that reaches it inside the live part of X (forward
-//      max-propagation), a colour's root with the vertices of its colour
-//      that reach the root is the root's component; a component with an
+//      whose largest priority is odd: rounds drop what no live vertex leads
+//      to (it is on no cycle; in a random game that is two fifths of X, and
+//      most of the rest is one component), then peel strongly connected
+//      components of the live part by colouring -- every vertex takes the
+//      largest (priority, id) that reaches it inside the live part of X
+//      (forward max-propagation), a colour's root with the vertices of its
+//      colour that reach the root is the root's component; a component with an
 //      edge and an odd root goes to R's seed, a root of an even-rooted or
 //      edgeless component is dropped (the rest of its component is coloured
 //      again in the next round); then everything in X that reaches the seed
@@ -31,6 +33,9 @@
 namespace pgk {
 
 namespace {
+
+// A sweep stops at once when the one before it changed nothing (`before`,
+// null for a group's first).
 
 // raises *flag when pred holds in a lane of the wave: one atomic per wave
 // at most, and none once the flag reads raised (a million waves' atomics on
@@ -90,22 +95,97 @@ __global__ void k_or_color_init(const int32_t *lst, int32_t cnt,
   nontriv[v] = 0;
 }
 
+// Topological peeling of the live part: deg[w] = live v -> w, counted over
+// the list; the vertices without any are removed, and then whoever they
+// leave without any.
+__global__ void k_or_indeg(const int32_t *lst, int32_t cnt,
+                           const int64_t *off, const int32_t *tgt,
+                           const uint8_t *alive, int32_t *deg) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= cnt) return;
+  const int32_t v = lst[i];
+  for (int64_t e = off[v]; e < off[v + 1]; ++e)
+    if (alive[tgt[e]]) atomicAdd(&deg[tgt[e]], 1);
+}
+
+__global__ void k_or_sources(const int32_t *lst, int32_t cnt,
+                             const int32_t *deg, int32_t *out, int32_t *n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool src = i < cnt && deg[lst[i]] == 0;
+  const int32_t at = block_place(n, src);
+  if (src) out[at] = lst[i];
+}
+
+// Removes the n vertices of `in` and what follows.  A thread keeps what it
+// frees on a stack of its own: the trees that hang into a component are
+// lopsided and deep, and a launch per layer would be mostly launches.  What
+// exceeds the stack or kTrimSteps goes to `out`, the next launch's list.
+// (1M-vertex random game, X 359k: 147k removed in 90 us, and the colouring
+// that follows runs on 212k vertices whose largest colour is their own.)
+constexpr int kTrimStack = 16, kTrimSteps = 1024;
+__global__ __launch_bounds__(kBlock) void k_or_trim(
+    const int32_t *in, int32_t n, const int64_t *off, const int32_t *tgt,
+    uint8_t *alive, int32_t *deg, int32_t *out, int32_t *nout) {
+  __shared__ int32_t stack[kTrimStack][kBlock];
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int tid = threadIdx.x;
+  int top = 0;
+  int32_t u = in[i];
+  for (int step = 0;; ++step) {
+    if (step == kTrimSteps) {
+      out[atomicAdd(nout, 1)] = u;
+      while (top > 0) out[atomicAdd(nout, 1)] = stack[--top][tid];
+      break;
+    }
+    alive[u] = 0;
+    int32_t next = -1;
+    for (int64_t e = off[u]; e < off[u + 1]; ++e) {
+      const int32_t w = tgt[e];
+      // (a vertex with a live predecessor is alive itself: nobody but the
+      // last predecessor's remover removes it)
+      if (alive[w] && atomicSub(&deg[w], 1) == 1) {
+        if (next < 0) next = w;
+        else if (top < kTrimStack) stack[top++][tid] = w;
+        else out[atomicAdd(nout, 1)] = w;
+      }
+    }
+    if (next < 0) {
+      if (top == 0) break;
+      next = stack[--top][tid];
+    }
+    u = next;
+  }
+}
+
+// keep flags for the live entries of lst
+__global__ void k_or_live(const int32_t *lst, int32_t cnt,
+                          const uint8_t *alive, uint32_t *flag) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < cnt) flag[i] = alive[lst[i]] ? 1u : 0u;
+}
+
 // col[w] = max over live v -> w of col[v]: one relaxation sweep.  A thread
 // that raises a successor's colour goes on pushing from the first one it
-// raised, up to kChase steps, so a colour runs down a chain of live
-// vertices within one sweep instead of one link per sweep.
-constexpr int kChase = 64;
+// raised, up to `chase` steps, so a colour runs down a chain of live
+// vertices within one sweep instead of one link per sweep.  Inside a wide
+// component that chases colours which a larger one soon replaces (1M-vertex
+// random game: first sweeps of 380, 350, 295, 154 us with 64 steps, eight of
+// 62 us with 4 and then 340 us with 64; two groups without a chase took 470
+// and then 490 us), so a round's first group takes kChaseWide steps.
+constexpr int kChase = 64, kChaseWide = 4;
 
 __global__ void k_or_color_sweep(const int32_t *lst, int32_t cnt,
                                  const int64_t *off, const int32_t *tgt,
                                  const uint8_t *alive,
-                                 unsigned long long *col, int32_t *changed) {
+                                 unsigned long long *col, int chase, const int32_t *before, int32_t *changed) {
+  if (before && !*before) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool ch = false;
   if (i < cnt) {
     int32_t u = lst[i];
     unsigned long long c = col[u];
-    for (int step = 0; step < kChase; ++step) {
+    for (int step = 0; step < chase; ++step) {
       int32_t nx = -1;
       unsigned long long cn = 0;
       for (int64_t e = off[u]; e < off[u + 1]; ++e) {
@@ -145,7 +225,8 @@ __global__ void k_or_reach_sweep(const int32_t *lst, int32_t cnt,
                                  const int64_t *off, const int32_t *tgt,
                                  const uint8_t *alive,
                                  const unsigned long long *col, uint8_t *reach,
-                                 int32_t *changed) {
+                                 const int32_t *before, int32_t *changed) {
+  if (before && !*before) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool ch = false;
   if (i < cnt) {
@@ -154,7 +235,8 @@ __global__ void k_or_reach_sweep(const int32_t *lst, int32_t cnt,
       const unsigned long long c = col[v];
       for (int64_t e = off[v]; e < off[v + 1]; ++e) {
         const int32_t w = tgt[e];
-        if (alive[w] && col[w] == c && reach[w]) {
+        // (reach first: its bytes stay in the L2 and few are set)
+        if (reach[w] && alive[w] && col[w] == c) {
           reach[v] = 1;
           ch = true;
           break;
@@ -217,7 +299,8 @@ __global__ void k_or_peel(const int32_t *lst, int32_t cnt, uint8_t *alive,
 // R: v in X with a successor in R (inside X); lst holds X minus R
 __global__ void k_or_back(const int32_t *lst, int32_t cnt, const int64_t *off,
                           const int32_t *tgt, const uint8_t *inx, uint8_t *R,
-                          int32_t *changed) {
+                          const int32_t *before, int32_t *changed) {
+  if (before && !*before) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool ch = false;
   if (i < cnt) {
@@ -240,7 +323,8 @@ __global__ void k_or_back(const int32_t *lst, int32_t cnt, const int64_t *off,
 // every successor in A; lst holds vertices outside A
 __global__ void k_or_attr(const int32_t *lst, int32_t cnt, const int64_t *off,
                           const int32_t *tgt, const uint8_t *owner,
-                          uint8_t *A, int32_t *changed) {
+                          uint8_t *A, const int32_t *before, int32_t *changed) {
+  if (before && !*before) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool ch = false;
   if (i < cnt) {
@@ -304,15 +388,16 @@ __global__ void k_or_newmap(const uint8_t *A, const uint32_t *newid,
   if (v < n) newmap[v] = A[v] ? -1 : (int32_t)newid[v];
 }
 
-// Runs `sweep` over the list (*lst, cnt entries) in groups of four, one
+// Runs `sweep` over the list (*lst, cnt entries) in groups of kGroup, one
 // synchronisation each, until a group changes nothing or the list is empty.
 // With `done`, the entries decided (done[v] != 0) leave the list after each
 // group (compacted into *spare, then the two swap).  Fails after `bound`
 // groups.
+constexpr int kGroup = 8;
 struct ListBufs {
   int32_t *a, *b;      // the list and its spare
   uint32_t *flag, *pos;
-  int32_t *dcnt;
+  int32_t *dcnt;       // a count, then a group's change flags
   void *stmp;          // scan scratch
 };
 
@@ -336,8 +421,10 @@ pg_status fixpoint_list(pg_game *g, hipStream_t s, int64_t bound,
   for (int64_t round = 0; *cnt > 0; ++round) {
     if (round > bound)
       return pg_fail(PG_EINTERNAL, "odd-region fixpoint did not converge");
-    fill_i32(g->ctr + C_MISC, 0, 1, s);
-    for (int k = 0; k < 4; ++k) sweep(l->a, *cnt, g->ctr + C_MISC);
+    int32_t *ch = l->dcnt + 1;
+    fill_i32(ch, 0, kGroup, s);
+    for (int k = 0; k < kGroup; ++k)
+      sweep(l->a, *cnt, round, k ? ch + k - 1 : nullptr, ch + k);
     int32_t *h = g->hctr;
     h[1] = *cnt;
     if (done) {
@@ -345,7 +432,7 @@ pg_status fixpoint_list(pg_game *g, hipStream_t s, int64_t bound,
                          0, s, l->a, *cnt, done, l->flag);
       list_keep(l, *cnt, false, s, &h[1]);
     }
-    publish(&h[0], g->ctr + C_MISC, 1, s);
+    publish(&h[0], ch + kGroup - 1, 1, s);
     PG_HIP(hipStreamSynchronize(s));
     *cnt = h[1];
     if (h[0] == 0) break;
@@ -390,7 +477,7 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
   tmp.p.push_back(L.flag);
   PG_TRY(dev_alloc(&L.pos, n));
   tmp.p.push_back(L.pos);
-  PG_TRY(dev_alloc(&L.dcnt, 1));
+  PG_TRY(dev_alloc(&L.dcnt, 1 + kGroup));
   tmp.p.push_back(L.dcnt);
   {
     const size_t need = scan_excl_u32(nullptr, nullptr, n, nullptr, s);
@@ -407,6 +494,38 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
     *cnt = g->hctr[0];
     return PG_OK;
   };
+  // removes from the list what is on no cycle of live vertices (L.b, L.pos
+  // and col hold the removers' lists and degrees meanwhile)
+  auto trim = [&](int32_t *cnt) -> pg_status {
+    int32_t *deg = (int32_t *)col, *in = L.b, *out = (int32_t *)L.pos;
+    fill_i32(deg, 0, n, s);
+    fill_i32(L.dcnt, 0, 2, s);
+    hipLaunchKernelGGL(k_or_indeg, dim3(grid_for(*cnt)), dim3(kBlock), 0, s,
+                       L.a, *cnt, off, tgt, alive, deg);
+    hipLaunchKernelGGL(k_or_sources, dim3(grid_for(*cnt)), dim3(kBlock), 0, s,
+                       L.a, *cnt, deg, in, L.dcnt);
+    publish(g->hctr, L.dcnt, 1, s);
+    PG_HIP(hipStreamSynchronize(s));
+    const bool any = g->hctr[0] > 0;
+    for (int64_t round = 0; g->hctr[0] > 0; ++round) {
+      if (round > n)
+        return pg_fail(PG_EINTERNAL, "odd-region trimming did not converge");
+      const int32_t ni = g->hctr[0];
+      fill_i32(L.dcnt, 0, 1, s);
+      hipLaunchKernelGGL(k_or_trim, dim3(grid_for(ni)), dim3(kBlock), 0, s, in,
+                         ni, off, tgt, alive, deg, out, L.dcnt);
+      publish(g->hctr, L.dcnt, 1, s);
+      PG_HIP(hipStreamSynchronize(s));
+      std::swap(in, out);
+    }
+    if (!any) return PG_OK;
+    hipLaunchKernelGGL(k_or_live, dim3(grid_for(*cnt)), dim3(kBlock), 0, s,
+                       L.a, *cnt, alive, L.flag);
+    list_keep(&L, *cnt, false, s, g->hctr);
+    PG_HIP(hipStreamSynchronize(s));
+    *cnt = g->hctr[0];
+    return PG_OK;
+  };
   PG_HIP(hipMemcpyAsync(alive, inx, n, hipMemcpyDeviceToDevice, s));
   fill_u8(seed, 0, n, s);
   const int64_t bound = n + 64;
@@ -417,20 +536,24 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
   for (int64_t round = 0; cnt > 0; ++round) {
     if (round > n + 1)
       return pg_fail(PG_EINTERNAL, "odd-region peeling did not converge");
+    PG_TRY(trim(&cnt));
+    if (cnt == 0) break;
     const unsigned gc = grid_for(cnt);
     hipLaunchKernelGGL(k_or_color_init, dim3(gc), dim3(kBlock), 0, s, L.a,
                        cnt, pri, col, reach, nontriv);
     PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, nullptr,
-                         [&](const int32_t *l, int32_t c, int32_t *ch) {
+                         [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
+                             int32_t *ch) {
       hipLaunchKernelGGL(k_or_color_sweep, dim3(grid_for(c)), dim3(kBlock), 0,
-                         s, l, c, off, tgt, alive, col, ch);
+                         s, l, c, off, tgt, alive, col, round ? kChase : kChaseWide, b4, ch);
     }));
     hipLaunchKernelGGL(k_or_reach_init, dim3(gc), dim3(kBlock), 0, s, L.a,
                        cnt, col, reach);
     PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, nullptr,
-                         [&](const int32_t *l, int32_t c, int32_t *ch) {
+                         [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
+                             int32_t *ch) {
       hipLaunchKernelGGL(k_or_reach_sweep, dim3(grid_for(c)), dim3(kBlock), 0,
-                         s, l, c, off, tgt, alive, col, reach, ch);
+                         s, l, c, off, tgt, alive, col, reach, b4, ch);
     }));
     hipLaunchKernelGGL(k_or_nontrivial, dim3(gc), dim3(kBlock), 0, s, L.a,
                        cnt, off, tgt, col, reach, nontriv);
@@ -444,15 +567,17 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
   // of R (over the vertices outside A), both in place
   PG_TRY(select(inx, seed, 1, &cnt));
   PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, seed,
-                       [&](const int32_t *l, int32_t c, int32_t *ch) {
+                       [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
+                             int32_t *ch) {
     hipLaunchKernelGGL(k_or_back, dim3(grid_for(c)), dim3(kBlock), 0, s, l, c,
-                       off, tgt, inx, seed, ch);
+                       off, tgt, inx, seed, b4, ch);
   }));
   PG_TRY(select(seed, nullptr, 2, &cnt));
   PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, seed,
-                       [&](const int32_t *l, int32_t c, int32_t *ch) {
+                       [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
+                             int32_t *ch) {
     hipLaunchKernelGGL(k_or_attr, dim3(grid_for(c)), dim3(kBlock), 0, s, l, c,
-                       off, tgt, owner, seed, ch);
+                       off, tgt, owner, seed, b4, ch);
   }));
   uint8_t *A = seed;
   // the game on the vertices kept, rows in their order
