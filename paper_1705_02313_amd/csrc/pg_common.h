@@ -288,6 +288,7 @@ struct pg_game {
     int state = 0;               // 0 not built, 1 built, -1 no memory
     uint32_t *in_off = nullptr;  // [n_aug+1] in-edge lists (at the first solve)
     uint32_t *in = nullptr;      // [m_aug] source, its owner in bit 31
+    uint2 *pairs = nullptr;      // building them (until the first valuation)
     int32_t *mark = nullptr;     // [n_aug] last step that changed the vertex
     int32_t *cmark = nullptr;    // [n_aug] last step it was a candidate of
     int32_t *ic = nullptr;       // a step's counters

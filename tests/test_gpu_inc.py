@@ -71,6 +71,7 @@ GAMES = {
     "block_edge_above": lambda: synth.random_game(3150, 2, 5, 3),
     "mid": lambda: synth.random_game(20011, 2, 8, 4),
     "large": lambda: synth.random_game(150001, 2, 5, 5),
+    "large_hub": lambda: _hub(140003, 14),
     "chain": lambda: synth.chain_game(60013, 6),
     "hub": lambda: _hub(20000, 7),
     "doubled": lambda: _doubled(6001, 8),
