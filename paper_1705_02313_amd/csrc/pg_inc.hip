@@ -1109,10 +1109,15 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// A step starts when at most one vertex in kIncSwitchShare switched (A is
-// two to six times the switched vertices on the workloads), in the block
-// form up to kBlockSwitches of them.
-constexpr int64_t kIncSwitchShare = 24;
+// A step starts when at most one vertex in kIncSwitchShare switched, in the
+// block form up to kBlockSwitches of them.  A is two to six times the
+// switched vertices on the workloads, and its find follows plays of up to
+// hundreds of vertices, level by level, where a full valuation with coarse
+// keys takes 0.06 ms (40,000 vertices) to 0.8 ms (10M): one in 100 against
+// one in 24 made solves 3-6 % faster, with the Odd region 20 %; one in 150
+// and one in 400 were 2 % slower than that on some and faster on others.
+// Full count valuations cost four times as much.
+constexpr int64_t kIncSwitchShare = 100, kIncSwitchShareCounts = 24;
 constexpr int32_t kBlockSwitches = 512;
 constexpr int32_t kBlockVals = 64;
 
@@ -1274,7 +1279,8 @@ void inc_commit(pg_game *g, hipStream_t s) {
 bool inc_ready(const pg_game *g) {
   const pg_game::Inc &x = g->inc;
   return x.on && x.pending && x.skip == 0 && !x.exact &&
-         ((int64_t)x.nsw * kIncSwitchShare <= g->n_aug ||
+         ((int64_t)x.nsw * (g->dense ? kIncSwitchShareCounts
+                                     : kIncSwitchShare) <= g->n_aug ||
           g->n_aug <= kBlockA);
 }
 
