@@ -724,7 +724,7 @@ def main():
     load_s = [r["load"] for r in runs]
 
     # Roofline of the best-response iteration (one replay of its HIP graph)
-    # from the timed steps: the library records HIP events on the solve's
+    # from the timed steps: the library reads the device's clock on the solve's
     # stream around every iteration (pg_stats.iteration_ms, summed).
     n_aug, m_aug = runs[0]["aug"][0], runs[0]["aug"][1]
     b_min = method_min_bytes(n_aug, m_aug,

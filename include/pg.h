@@ -345,10 +345,11 @@ typedef struct pg_stats {
     int64_t n_even_switches;/* vertices switched by All_Even, summed         */
     double seconds;         /* wall time of the solve on the host clock      */
     double iteration_ms;    /* device time of the best-response iterations,
-                               summed (HIP events on the call's stream
-                               around each, or around several of them and
-                               the All_Even steps between where they run in
-                               one kernel; 0 for Bellman-Ford and batches)  */
+                               summed (the device's clock, from each one's
+                               first kernel past its last, or over several of
+                               them and the All_Even steps between where they
+                               run in one kernel; 0 for Bellman-Ford and
+                               batches)                                     */
     int64_t n_traced;       /* entries written to the trace arrays           */
 } pg_stats;
 

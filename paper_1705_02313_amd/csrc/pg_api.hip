@@ -680,6 +680,16 @@ bool host_pinned(const void *p) {
            q < tl_pool->bump_host + tl_pool->bump_hcap);
 }
 
+float clock_ms(pg_game *g, int32_t begin, int32_t end) {
+  if (!g->timed) return 0.0f;
+  if (g->clock_khz == 0 &&
+      hipDeviceGetAttribute(&g->clock_khz, hipDeviceAttributeWallClockRate,
+                            g->device) != hipSuccess)
+    g->clock_khz = -1;
+  if (g->clock_khz <= 0) return 0.0f;
+  return (float)((uint32_t)end - (uint32_t)begin) / (float)g->clock_khz;
+}
+
 pg_status host_alloc(void **p, size_t bytes) {
   if (tl_pool) return tl_pool->alloc(p, bytes, true);
   PG_HIP(hipHostMalloc(p, bytes, hipHostMallocDefault));
@@ -722,8 +732,6 @@ static void drop_buffers(pg_game *g) {
   if (g->iter_exec) (void)hipGraphExecDestroy(g->iter_exec);
   if (g->iter_coarse) (void)hipGraphExecDestroy(g->iter_coarse);
   if (g->cap_stream) (void)hipStreamDestroy(g->cap_stream);
-  if (g->ev_a) (void)hipEventDestroy(g->ev_a);
-  if (g->ev_b) (void)hipEventDestroy(g->ev_b);
   g->prof.release();
 }
 

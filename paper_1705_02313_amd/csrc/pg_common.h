@@ -33,6 +33,8 @@ enum Counter : int {
   C_NINNER = 5,       // finite vertices whose parent is not the sink
   C_NDEC = 6,         // entries of All_Odd's switch list
   C_NTIE = 7,         // vertices whose All_Odd the coarse keys leave open
+  C_CLOCK = 8,        // a valuation's start (clock32)
+  C_CLOCK_END = 9,    // and its end (in the host's copy)
   // Hot counts are spread over kDistSlots slots kDistStride ints apart (one
   // atomic per block into slot blockIdx % kDistSlots) and summed afterwards:
   // a single address hit by every block serialises.  The switch slots are
@@ -321,7 +323,7 @@ struct pg_game {
   bool timed = true;
   // HIP events around each best-response iteration on the call's stream
   // (created at first use); the last iteration's device time
-  hipEvent_t ev_a = nullptr, ev_b = nullptr;
+  int clock_khz = 0;        // the device's wall clock (at its first use)
   float last_ms = 0.0f;
 };
 
@@ -407,6 +409,14 @@ __device__ __forceinline__ void append_block(int32_t *cnt, int32_t *list,
     s_base = atomicAdd(&cnt[slot * kDistStride], s_n);
   __syncthreads();
   if (pred) list[(int64_t)slot * cap + s_base + off] = v;
+}
+
+// The device's wall clock, its low 32 bits: a step's first kernel stores it
+// and publish stores it again, in place of two events around the step (their
+// packets and the query of their times were 3-4 % of a solve of 1,000 to 1M
+// vertices).  At 100 MHz the difference holds 42 s.
+__device__ __forceinline__ int32_t clock32() {
+  return (int32_t)(uint32_t)wall_clock64();
 }
 
 // Places (where pred holds) in a list whose length counts at *cnt, one
@@ -746,11 +756,15 @@ pg_status host_alloc(void **p, size_t bytes);
 // Whether host_alloc's memory p is pinned and so has the same address on the
 // device: all of it but the static host words of pg_solve_noalloc.
 bool host_pinned(const void *p);
+// the time between two clock32 values, for a game that is timed
+float clock_ms(pg_game *g, int32_t begin, int32_t end);
 // n ints of device memory to host_alloc's memory, there after the stream's
 // next synchronisation.  A copy of a few words takes 3.5 us after a gap of
 // 4 to 8 us; a kernel that writes them follows the one before at once
 // (solves of 1,000 to 2M vertices 1-4 % faster, with the Odd region 7 %).
-void publish(int32_t *host, const int32_t *src, int n, hipStream_t s);
+// end >= 0: host[end] receives the time of the copy (clock32).
+void publish(int32_t *host, const int32_t *src, int n, hipStream_t s,
+             int end = -1);
 }  // namespace pgk
 
 // ---- loading helpers shared by single games and batches (pg_api.hip) ------

@@ -60,6 +60,7 @@ enum IncCounter : int {
   I_STATE = 5, I_NVAL = 6, I_ODDSW = 7, I_EVENSW = 8, I_MAJOR = 9,
   I_INNER = 10, I_A0 = 11, I_CUR = 12, I_EPOCH = 13,
   I_OPEN = 16,    // passes after the first: vertices left for them
+  I_CLOCK = 32, I_CLOCK_END = 33,   // a step's start and end (clock32)
   I_WORDS = 64,   // the part copied to the host
   // the find's queue, a line each
   I_TICKET = 64, I_QTAIL = 96, I_QDONE = 128,
@@ -427,7 +428,10 @@ __global__ __launch_bounds__(kBlock) void k_inc_begin(
     inc_apply(P, epoch, d);
     P.list[a0 + i] = d.x;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) ic[I_NA] = nsw;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ic[I_CLOCK] = clock32();
+    ic[I_NA] = nsw;
+  }
 }
 
 // One in-edge x of w in A: its source joins A when w is its successor; true
@@ -901,7 +905,10 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
   __shared__ int32_t s_na, s_nc, s_nd, s_stop, s_open, s_err;
   const int tid = threadIdx.x;
   int32_t nval = 0, oddsw = 0, evensw = 0, state = IS_GROWN;
-  if (tid == 0) s_err = 0;
+  if (tid == 0) {
+    ic[I_CLOCK] = clock32();
+    s_err = 0;
+  }
   for (;;) {
     if (nval >= R.val_cap) break;
     const int2 *din = R.cur ? dec1 : dec0;
@@ -1103,6 +1110,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
     ic[I_CUR] = R.cur;
     ic[I_NDEC] = R.nsw;
     ic[I_EPOCH] = R.epoch;
+    ic[I_CLOCK_END] = clock32();
   }
 }
 
@@ -1256,7 +1264,7 @@ void inc_release(pg_game *g) {
 
 // direct: the kernel wrote its results to the host's words itself
 static pg_status inc_read(pg_game *g, hipStream_t s, bool direct = false) {
-  if (!direct) publish(g->inc.h, g->inc.ic, I_WORDS, s);
+  if (!direct) publish(g->inc.h, g->inc.ic, I_WORDS, s, I_CLOCK_END);
   PG_HIP(hipStreamSynchronize(s));
   if (g->prof.on) g->prof.flush();
   if (g->inc.h[I_ERR] & ERR_INADMISSIBLE)
@@ -1348,11 +1356,6 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     x.d_valid = false;
   }
   x.dirty = true;
-  if (g->timed && !g->ev_a) {
-    PG_HIP(hipEventCreate(&g->ev_a));
-    PG_HIP(hipEventCreate(&g->ev_b));
-  }
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_a, s));
   const bool block =
       !x.grown && (x.nsw <= kBlockSwitches || N <= kBlockA);
   x.grown = false;
@@ -1403,11 +1406,8 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide<D>, grid, blk, 0, s, P, epoch, 1,
               inc_dec(g, x.cur ^ 1), x.ic);
   }
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
   PG_TRY(inc_read(g, s, block && host_pinned(x.h)));
-  if (!g->timed ||
-      hipEventElapsedTime(&g->last_ms, g->ev_a, g->ev_b) != hipSuccess)
-    g->last_ms = 0.0f;
+  g->last_ms = clock_ms(g, x.h[I_CLOCK], x.h[I_CLOCK_END]);
   if (block) {
     x.epoch = x.h[I_EPOCH];
     x.a0 = x.h[I_A0];

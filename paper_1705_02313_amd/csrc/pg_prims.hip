@@ -90,13 +90,17 @@ static unsigned capped_grid(int64_t n) {
   return g > 65536u ? 65536u : g;
 }
 
-__global__ void k_publish(int32_t *host, const int32_t *src, int n) {
+__global__ void k_publish(int32_t *host, const int32_t *src, int n, int end) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) host[i] = src[i];
+  if (end >= 0 && threadIdx.x == (unsigned)end % blockDim.x)
+    host[end] = clock32();
 }
 
-void publish(int32_t *host, const int32_t *src, int n, hipStream_t s) {
+void publish(int32_t *host, const int32_t *src, int n, hipStream_t s,
+             int end) {
   if (host_pinned(host))
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, s, host, src, n);
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, s, host, src, n,
+                       end);
   else
     (void)hipMemcpyAsync(host, src, sizeof(int32_t) * n,
                          hipMemcpyDeviceToHost, s);

@@ -37,7 +37,8 @@ constexpr uint32_t kOpen = 0x8000u;       // ng entry: still walking, low bits
 
 // words of g->hctr (g->ctr when that is not pinned) a small kernel reports in
 enum SmallCounter : int {
-  S_STATE = 8, S_NVAL, S_ODDSW, S_EVENSW, S_MAJOR, S_INNER, S_NFIN, S_END
+  S_STATE = 8, S_NVAL, S_ODDSW, S_EVENSW, S_MAJOR, S_INNER, S_NFIN,
+  S_CLOCK, S_CLOCK_END, S_END
 };
 static_assert((int)S_END <= (int)C_DIST_SW, "the small kernels' words");
 enum SmallState : int {
@@ -224,6 +225,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(SmallGame G,
   extern __shared__ __align__(16) char lds[];
   __shared__ int32_t s_err, s_sum[3];
   const int tid = threadIdx.x;
+  if (tid == 0) G.ctr[S_CLOCK] = clock32();
   const int32_t N = G.N;
   char *p = lds;
   Small S;
@@ -328,6 +330,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_run(SmallGame G,
     G.ctr[S_EVENSW] = evensw;
     G.ctr[S_MAJOR] = R.major;
     G.ctr[S_INNER] = R.inner;
+    G.ctr[S_CLOCK_END] = clock32();
   }
 }
 
@@ -857,18 +860,10 @@ pg_status small_step(pg_game *g, hipStream_t s, bool br_only, bool reset,
   R.br_only = br_only;
   R.reset = reset;
   R.val_cap = 512;
-  if (g->timed && !g->ev_a) {
-    PG_HIP(hipEventCreate(&g->ev_a));
-    PG_HIP(hipEventCreate(&g->ev_b));
-  }
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_a, s));
   PG_LAUNCH(&g->prof, K_SMALL, 0.0, k_small_run, dim3(1), dim3(kSmallThreads),
             run_lds(g->n_aug, g->m_aug), s, small_game(g), R);
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
   PG_TRY(small_read(g, s));
-  if (!g->timed ||
-      hipEventElapsedTime(&g->last_ms, g->ev_a, g->ev_b) != hipSuccess)
-    g->last_ms = 0.0f;
+  g->last_ms = clock_ms(g, g->hctr[S_CLOCK], g->hctr[S_CLOCK_END]);
   *out = IncOut();
   out->nval = g->hctr[S_NVAL];
   out->odd = g->hctr[S_ODDSW];

@@ -99,6 +99,7 @@ __global__ __launch_bounds__(kBlock) void k_ng_full(
     int32_t *ng, int32_t *cand, int32_t *ctr, int steps, uint8_t *rs,
     int32_t *dist, int32_t *wl, int64_t wl_cap) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) ctr[C_CLOCK] = clock32();
   bool pending = false;
   if (i < N) {
     const int32_t v = (int32_t)i;
@@ -920,7 +921,7 @@ static int walk_block(const pg_game *g) {
 constexpr int kMaxRounds = 64;    // rounds of the careful path before failing
 
 static pg_status read_ctr(pg_game *g, hipStream_t s) {
-  publish(g->hctr, g->ctr, C_COUNT, s);
+  publish(g->hctr, g->ctr, C_COUNT, s, C_CLOCK_END);
   PG_HIP(hipStreamSynchronize(s));
   fold_switches(g->hctr);
   if (g->prof.on) {
@@ -1308,11 +1309,6 @@ static pg_status run_valuation(pg_game *g, hipStream_t s, bool odd_switch,
                                int32_t *count, int64_t *n_finite) {
   g->nlevels = g->dense ? count_levels(g->n_aug, g->dw)
                         : plan_levels(g->n_aug, g->tune.stride0);
-  if (g->timed && !g->ev_a) {
-    PG_HIP(hipEventCreate(&g->ev_a));
-    PG_HIP(hipEventCreate(&g->ev_b));
-  }
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_a, s));
   bool replayed = false;
   if (odd_switch && g->use_graph && !g->careful && !g->prof.on &&
       !g->host_rl) {
@@ -1334,10 +1330,11 @@ static pg_status run_valuation(pg_game *g, hipStream_t s, bool odd_switch,
       enqueue_any_switch(g, true, s, true);
     }
   }
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
   pg_status st = read_ctr(g, s);
   if (st != PG_OK) return st;
+  float ms = 0.0f;
   if (g->hctr[C_ABORT]) {
+    ms = clock_ms(g, g->hctr[C_CLOCK], g->hctr[C_CLOCK_END]);
     // a walk outlasted the fixed rounds: finish on the host-driven path and
     // redo everything after the walks (the gated kernels did nothing)
     st = careful_walks(g, s);
@@ -1347,13 +1344,10 @@ static pg_status run_valuation(pg_game *g, hipStream_t s, bool odd_switch,
     if (odd_switch) {
       enqueue_any_switch(g, true, s, true);
     }
-    if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
     st = read_ctr(g, s);
     if (st != PG_OK) return st;
   }
-  if (!g->timed ||
-      hipEventElapsedTime(&g->last_ms, g->ev_a, g->ev_b) != hipSuccess)
-    g->last_ms = 0.0f;
+  g->last_ms = ms + clock_ms(g, g->hctr[C_CLOCK], g->hctr[C_CLOCK_END]);
   st = check_ctr(g);
   if (st != PG_OK) return st;
   if (count) *count = g->hctr[C_SWITCH];
@@ -1386,11 +1380,6 @@ pg_status iteration_device(pg_game *g, hipStream_t s, int32_t *count,
 
 pg_status iteration_coarse(pg_game *g, hipStream_t s, int32_t *count,
                            bool *done) {
-  if (g->timed && !g->ev_a) {
-    PG_HIP(hipEventCreate(&g->ev_a));
-    PG_HIP(hipEventCreate(&g->ev_b));
-  }
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_a, s));
   hipGraphExec_t &ex = g->iter_coarse;
   const bool graph = g->use_graph && !g->prof.on;
   if (graph && !ex && capture_iteration(g, &ex, true) != PG_OK) {
@@ -1404,13 +1393,10 @@ pg_status iteration_coarse(pg_game *g, hipStream_t s, int32_t *count,
     enqueue_switch(g, true, s, true, true);
     enqueue_ties(g, s);
   }
-  if (g->timed) PG_HIP(hipEventRecord(g->ev_b, s));
-  publish(g->hctr, g->ctr, C_DIST_SW, s);
+  publish(g->hctr, g->ctr, C_DIST_SW, s, C_CLOCK_END);
   PG_HIP(hipStreamSynchronize(s));
   if (g->prof.on) g->prof.flush();
-  if (!g->timed ||
-      hipEventElapsedTime(&g->last_ms, g->ev_a, g->ev_b) != hipSuccess)
-    g->last_ms = 0.0f;
+  g->last_ms = clock_ms(g, g->hctr[C_CLOCK], g->hctr[C_CLOCK_END]);
   *done = !g->hctr[C_ABORT];
   *count = g->hctr[C_NDEC];
   return check_ctr(g);
