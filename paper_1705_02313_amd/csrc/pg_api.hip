@@ -72,11 +72,29 @@ __global__ void k_dup_bits(const int32_t *pri, int64_t n, uint32_t *bits,
   if (atomicOr(&bits[p >> 5], b) & b) *flag = 1;
 }
 
-__global__ void k_check_vertices(const uint8_t *owner, const int32_t *pri,
-                                 int64_t n, int32_t *ctr) {
-  int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  if (owner[v] > 1 || pri[v] < 0) atomicOr(&ctr[C_ERR], ERR_INVAL);
+// Owners and priorities, and the largest priority: few blocks, one atomic
+// each (512 blocks with one per wave took 26 us whatever the size).
+__global__ __launch_bounds__(kBlock) void k_check_vertices(
+    const uint8_t *owner, const int32_t *pri, int64_t n, int32_t *ctr) {
+  __shared__ int32_t part[kBlock / kWave];
+  int32_t mx = 0;
+  bool bad = false;
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
+       v += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t p = pri[v];
+    bad |= owner[v] > 1 || p < 0;
+    mx = p > mx ? p : mx;
+  }
+  if (bad) atomicOr(&ctr[C_ERR], ERR_INVAL);
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    const int32_t y = __shfl_down(mx, o, kWave);
+    mx = y > mx ? y : mx;
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = mx;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < kBlock / kWave; ++w) mx = part[w] > mx ? part[w] : mx;
+  atomicMax(&ctr[C_MAXPRI], mx);
 }
 
 // ---------------------------------------------------------------------------
@@ -132,6 +150,92 @@ __global__ void k_x_round(const int64_t *__restrict__ off,
     atomicOr(&ctr[C_MISC], 1);
 }
 
+// X by witnesses (single games): a member's witness is a successor in X; a
+// sweep looks whether it is still there and reads the row again only if not.
+// X is a bit per vertex: the witnesses' bits are random reads, and 10M bits
+// stay in an L2 where bytes do not (sweeps of 10M vertices, once few leave:
+// 85 -> 22 us; with them X', the modified game's build and three
+// synchronisations less the load's part up to the dummies went from 3.3 to
+// 2.0 ms).  A wave owns the word of its 64 vertices.  A bit read too early
+// (another XCD's change of the same sweep) is read again by the next sweep,
+// which runs because that change raised the flag.
+__device__ __forceinline__ bool bit_of(const uint64_t *bits, int32_t v) {
+  return (bits[v >> 6] >> (v & 63)) & 1ull;
+}
+
+__global__ __launch_bounds__(kBlock) void k_xb_first(
+    const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
+    const uint8_t *__restrict__ owner, int64_t n, int32_t *wit,
+    uint64_t *bits) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int32_t w = -1;
+  if (v < n && owner[v] == 1)
+    for (int64_t e = off[v], end = off[v + 1]; e < end; ++e)
+      if (owner[tgt[e]] == 1) {
+        w = tgt[e];
+        break;
+      }
+  if (v < n) wit[v] = w;
+  const uint64_t b = __ballot(w >= 0);
+  if ((threadIdx.x & (kWave - 1)) == 0 && v < n) bits[v >> 6] = b;
+}
+
+// before: the flag of the sweep before (null for a group's first)
+__global__ __launch_bounds__(kBlock) void k_xb_sweep(
+    const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
+    int64_t n, int32_t *wit, uint64_t *bits, const int32_t *before,
+    int32_t *changed) {
+  if (before && !*before) return;
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  bool drop = false;
+  if (v < n) {
+    const int32_t w = wit[v];
+    if (w >= 0 && !bit_of(bits, w)) {
+      int32_t nw = -1;
+      for (int64_t e = off[v], end = off[v + 1]; e < end; ++e)
+        if (bit_of(bits, tgt[e])) {
+          nw = tgt[e];
+          break;
+        }
+      wit[v] = nw;
+      drop = nw < 0;
+    }
+  }
+  const uint64_t b = __ballot(drop);
+  if (b && (threadIdx.x & (kWave - 1)) == 0) {
+    bits[v >> 6] &= ~b;
+    if (ld_flag(changed) == 0) atomicOr(changed, 1);
+  }
+}
+
+__global__ void k_xb_bytes(const int32_t *wit, int64_t n, uint8_t *inx) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v < n) inx[v] = wit[v] >= 0;
+}
+
+// X' as bytes (bits would be atomics, on one word for neighbours' successors:
+// 80 us on the 2M chain, 12 with bytes), then as bits with their number per
+// word
+__global__ __launch_bounds__(kBlock) void k_xb_mark(
+    const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
+    const uint64_t *__restrict__ bits, uint8_t *mark, int64_t n) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= n || !bit_of(bits, (int32_t)v)) return;
+  for (int64_t e = off[v], end = off[v + 1]; e < end; ++e)
+    if (bit_of(bits, tgt[e])) mark[tgt[e]] = 1;
+}
+
+__global__ __launch_bounds__(kBlock) void k_xb_count(const uint8_t *mark,
+                                                     int64_t n, uint64_t *xp,
+                                                     uint32_t *cnt) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint64_t b = __ballot(v < n && mark[v]);
+  if ((threadIdx.x & (kWave - 1)) == 0 && v < n) {
+    xp[v >> 6] = b;
+    cnt[v >> 6] = (uint32_t)__popcll(b);
+  }
+}
+
 // X': members of X with a predecessor in X
 __global__ void k_xp_mark(const int64_t *__restrict__ off,
                           const int32_t *__restrict__ tgt,
@@ -145,6 +249,13 @@ __global__ void k_xp_mark(const int64_t *__restrict__ off,
   }
 }
 
+// the number of members of X' before w (base: before its word)
+__device__ __forceinline__ int64_t xb_rank(const uint64_t *xp,
+                                           const uint32_t *base, int32_t w) {
+  return (int64_t)base[w >> 6] +
+         __popcll(xp[w >> 6] & ((1ull << (w & 63)) - 1ull));
+}
+
 // The modified game: rows of original vertices keep their length, edges
 // between members of X go through the dummy of their target; the dummy of the
 // i-th member w of X' is vertex n + i, Even, priority i, row [w].  Original
@@ -154,26 +265,26 @@ __global__ void k_aug_build(int64_t n, int64_t m, int64_t K, int dense,
                             const int32_t *__restrict__ tgt,
                             const uint8_t *__restrict__ owner,
                             const int32_t *__restrict__ pri,
-                            const uint8_t *__restrict__ inx,
-                            const uint32_t *__restrict__ xp,
-                            const uint32_t *__restrict__ did, int64_t *off2,
+                            const uint64_t *__restrict__ inx,
+                            const uint64_t *__restrict__ xp,
+                            const uint32_t *__restrict__ base, int64_t *off2,
                             int32_t *tgt2, uint8_t *owner2, int32_t *pri2,
                             int32_t *ctr) {
   int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
   off2[v] = off[v];
   if (v == n - 1) off2[n] = off[n];
-  const bool vx = inx[v] != 0;
+  const bool vx = bit_of(inx, (int32_t)v);
   for (int64_t e = off[v], end = off[v + 1]; e < end; ++e) {
     const int32_t w = tgt[e];
-    tgt2[e] = (vx && inx[w]) ? (int32_t)(n + did[w]) : w;
+    tgt2[e] = (vx && bit_of(inx, w)) ? (int32_t)(n + xb_rank(xp, base, w)) : w;
   }
   owner2[v] = owner[v];
   const int64_t p = (int64_t)pri[v] + K;
   if (p > 2147483647LL) atomicOr(&ctr[C_ERR], ERR_INVAL);
   pri2[v] = (int32_t)p;
-  if (xp[v]) {
-    const int64_t i = did[v];
+  if (bit_of(xp, (int32_t)v)) {
+    const int64_t i = xb_rank(xp, base, (int32_t)v);
     owner2[n + i] = 0;
     pri2[n + i] = dense ? 0 : (int32_t)i;
     tgt2[m + i] = (int32_t)v;
@@ -864,8 +975,8 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
                      off_in, n, m, g->ctr);
   hipLaunchKernelGGL(k_check_targets, dim3(grid_for(m)), dim3(kBlock), 0, s,
                      tgt_in, m, n, g->ctr);
-  hipLaunchKernelGGL(k_check_vertices, dim3(grid_for(n)), dim3(kBlock), 0, s,
-                     own_in, pri_in, n, g->ctr);
+  hipLaunchKernelGGL(k_check_vertices, dim3(std::min(512u, grid_for(n))),
+                     dim3(kBlock), 0, s, own_in, pri_in, n, g->ctr);
   PG_TRY(sync_ctr(g, s));
   if (g->hctr[C_ERR] & ERR_OFFSETS)
     return pg_fail(PG_EINVAL,
@@ -883,12 +994,8 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
     // value when the largest is below 32 n (each word then serves a few
     // scattered vertices), else a sort of the priorities and a look at
     // neighbours
-    fill_i32(g->ctr + C_MISC, -1, 1, s);
-    hipLaunchKernelGGL(k_max_i32, dim3(512), dim3(kBlock), 0, s, pri_in, n,
-                       g->ctr + C_MISC);
-    PG_TRY(sync_ctr(g, s));
-    const int64_t maxpri = g->hctr[C_MISC];
-    fill_i32(g->ctr + C_MISC, 0, 1, s);
+    // (read with the next synchronisation's counters)
+    const int64_t maxpri = g->hctr[C_MAXPRI];
     if (maxpri + 1 < n) {
       g->dense = true;
     } else if (maxpri < 32 * n) {
@@ -898,9 +1005,7 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
       tmp.p.push_back(bits);
       fill_i32((int32_t *)bits, 0, words, s);
       hipLaunchKernelGGL(k_dup_bits, dim3(grid_for(n)), dim3(kBlock), 0, s,
-                         pri_in, n, bits, g->ctr + C_MISC);
-      PG_TRY(sync_ctr(g, s));
-      g->dense = g->hctr[C_MISC] != 0;
+                         pri_in, n, bits, g->ctr + C_DUP);
     } else {
       uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr;
       uint32_t *tc = nullptr;
@@ -922,56 +1027,89 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
       const int w = radix_sort(k0, v0, k1, v1, n, 32, tc, st, s, nullptr,
                                nullptr, true);
       hipLaunchKernelGGL(k_dup_check, dim3(grid_for(n)), dim3(kBlock), 0, s,
-                         w ? k1 : k0, n, g->ctr + C_MISC);
-      PG_TRY(sync_ctr(g, s));
-      g->dense = g->hctr[C_MISC] != 0;
+                         w ? k1 : k0, n, g->ctr + C_DUP);
     }
   }
-  const bool dense = g->dense;
 
   int64_t nxp = 0;
-  uint8_t *inx = nullptr;
-  uint32_t *xp = nullptr, *did = nullptr;
+  uint64_t *xb = nullptr, *xp = nullptr;
+  uint32_t *xbase = nullptr;
   if (!(flags & PG_NO_PREPROCESS)) {
-    PG_TRY(dev_alloc(&inx, n));
-    tmp.p.push_back(inx);
-    PG_TRY(dev_alloc(&xp, n));
+    const int64_t nw = (n + 63) / 64;
+    int32_t *wit = nullptr;
+    uint32_t *cnt = nullptr;
+    PG_TRY(dev_alloc(&wit, n));
+    tmp.p.push_back(wit);
+    PG_TRY(dev_alloc(&xb, nw));
+    tmp.p.push_back(xb);
+    PG_TRY(dev_alloc(&xp, nw));
     tmp.p.push_back(xp);
-    PG_TRY(dev_alloc(&did, n));
-    tmp.p.push_back(did);
-    hipLaunchKernelGGL(k_x_init, dim3(grid_for(n)), dim3(kBlock), 0, s, own_in,
-                       inx, n);
-    // xp holds the rounds' row witnesses until X is known
-    fill_i32((int32_t *)xp, 0, n, s);
-    for (int64_t round = 0;; round += 4) {
-      if (round > 4 * n + 64)
-        return pg_fail(PG_EINTERNAL, "preprocessing did not converge");
-      fill_i32(g->ctr + C_MISC, 0, 1, s);
-      for (int k = 0; k < 4; ++k)
-        hipLaunchKernelGGL(k_x_round, dim3(grid_for(n)), dim3(kBlock), 0, s,
-                           off_in, tgt_in, inx, xp, n, g->ctr);
-      PG_TRY(sync_ctr(g, s));
-      if (g->hctr[C_MISC] == 0) break;
-    }
-    if (flags & PG_ODD_REGION) {
-      // no dummies: the game without Odd's own winning region instead
-      g->odd_region = true;
-      return odd_region_reduce(g, s, n, m, off_in, tgt_in, own_in, pri_in,
-                               inx);
-    }
-    fill_i32((int32_t *)xp, 0, n, s);
-    hipLaunchKernelGGL(k_xp_mark, dim3(grid_for(n)), dim3(kBlock), 0, s,
-                       off_in, tgt_in, inx, xp, n);
-    size_t need = scan_excl_u32(nullptr, nullptr, n, nullptr, s);
+    PG_TRY(dev_alloc(&cnt, nw));
+    tmp.p.push_back(cnt);
+    PG_TRY(dev_alloc(&xbase, nw));
+    tmp.p.push_back(xbase);
+    const size_t need = scan_excl_u32(nullptr, nullptr, nw, nullptr, s);
     void *stmp = nullptr;
     PG_TRY(dev_alloc((uint8_t **)&stmp, (int64_t)need + 16));
     tmp.p.push_back(stmp);
-    scan_excl_u32(xp, did, n, stmp, s);
-    publish(g->hctr, (const int32_t *)did + (n - 1), 1, s);
-    publish(g->hctr + 1, (const int32_t *)xp + (n - 1), 1, s);
-    PG_HIP(hipStreamSynchronize(s));
-    nxp = (int64_t)g->hctr[0] + g->hctr[1];
+    hipLaunchKernelGGL(k_xb_first, dim3(grid_for(n)), dim3(kBlock), 0, s,
+                       off_in, tgt_in, own_in, n, wit, xb);
+    const bool region = flags & PG_ODD_REGION;
+    uint8_t *mark = nullptr;
+    PG_TRY(dev_alloc(&mark, n));
+    tmp.p.push_back(mark);
+    int32_t *h = g->hctr + C_DIST_SW;
+    auto find_xp = [&]() {
+      fill_u8(mark, 0, n, s);
+      hipLaunchKernelGGL(k_xb_mark, dim3(grid_for(n)), dim3(kBlock), 0, s,
+                         off_in, tgt_in, xb, mark, n);
+      hipLaunchKernelGGL(k_xb_count, dim3(grid_for(n)), dim3(kBlock), 0, s,
+                         mark, n, xp, cnt);
+      scan_excl_u32(cnt, xbase, nw, stmp, s);
+      publish(h, (const int32_t *)xbase + (nw - 1), 1, s);
+      publish(h + 1, (const int32_t *)cnt + (nw - 1), 1, s);
+    };
+    // groups of sweeps with one synchronisation each, the first one's with
+    // X' as if it had found X (random games below 1M vertices take 6 to 8
+    // sweeps, 10M vertices 15, the 2M chain 40)
+    const int group = n < 1000000 ? kXGroup / 2 : kXGroup;
+    int64_t round = 0;
+    for (;; round += group) {
+      if (round > n + kXGroup)
+        return pg_fail(PG_EINTERNAL, "preprocessing did not converge");
+      int32_t *ch = g->ctr + C_XN;
+      if (round > 0) fill_i32(ch, 0, kXGroup, s);
+      for (int k = 0; k < group; ++k)
+        hipLaunchKernelGGL(k_xb_sweep, dim3(grid_for(n)), dim3(kBlock), 0, s,
+                           off_in, tgt_in, n, wit, xb, k ? ch + k - 1 : nullptr,
+                           ch + k);
+      if (round == 0 && !region) find_xp();
+      publish(g->hctr, g->ctr, C_DIST_SW, s);
+      PG_HIP(hipStreamSynchronize(s));
+      if (!g->hctr[C_XN + group - 1]) break;
+    }
+    if (round > 0 && !region) {
+      find_xp();
+      PG_HIP(hipStreamSynchronize(s));
+    }
+    if (region) {
+      // no dummies: the game without Odd's own winning region instead
+      if (mode == kLoadAuto && g->hctr[C_DUP]) g->dense = true;
+      g->odd_region = true;
+      uint8_t *inx = nullptr;
+      PG_TRY(dev_alloc(&inx, n));
+      tmp.p.push_back(inx);
+      hipLaunchKernelGGL(k_xb_bytes, dim3(grid_for(n)), dim3(kBlock), 0, s,
+                         wit, n, inx);
+      return odd_region_reduce(g, s, n, m, off_in, tgt_in, own_in, pri_in,
+                               inx);
+    }
+    nxp = (int64_t)h[0] + h[1];
+  } else {
+    PG_TRY(sync_ctr(g, s));
   }
+  if (mode == kLoadAuto && g->hctr[C_DUP]) g->dense = true;
+  const bool dense = g->dense;
   g->n_aug = n + nxp;
   g->m_aug = m + nxp;
   if (g->n_aug > kMaxVertices)
@@ -992,8 +1130,8 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
   } else {
     const int64_t K = dense ? (nxp > 0 ? 2 : 0) : nxp + (nxp & 1);
     hipLaunchKernelGGL(k_aug_build, dim3(grid_for(n)), dim3(kBlock), 0, s, n,
-                       m, K, (int)dense, off_in, tgt_in, own_in, pri_in, inx,
-                       xp, did, g->off, g->tgt, g->owner, g->pri, g->ctr);
+                       m, K, (int)dense, off_in, tgt_in, own_in, pri_in, xb,
+                       xp, xbase, g->off, g->tgt, g->owner, g->pri, g->ctr);
   }
   // a priority above INT32_MAX (ERR_INVAL) is reported at the caller's
   // next synchronisation: the wrapped values only make later keys wrong

@@ -35,6 +35,9 @@ enum Counter : int {
   C_NTIE = 7,         // vertices whose All_Odd the coarse keys leave open
   C_CLOCK = 8,        // a valuation's start (clock32)
   C_CLOCK_END = 9,    // and its end (in the host's copy)
+  C_DUP = 10,         // loading: a priority repeats
+  C_MAXPRI = 11,      // the largest priority
+  C_XN = 16,          // X's sweeps: a change in each (kXGroup)
   // Hot counts are spread over kDistSlots slots kDistStride ints apart (one
   // atomic per block into slot blockIdx % kDistSlots) and summed afterwards:
   // a single address hit by every block serialises.  The switch slots are
@@ -50,6 +53,7 @@ enum Counter : int {
   C_DIST_WLRT = C_COUNT + 3072,
   C_TOTAL = C_COUNT + 4096
 };
+constexpr int kXGroup = 16;
 constexpr int kDistSlots = 64;
 constexpr int kDistStride = 16;
 
