@@ -963,6 +963,13 @@ static dim3 list_grid(int64_t N, int wblk) {
                                   (fblocks + kDistSlots - 1) / kDistSlots)));
 }
 
+// A round lasts as long as its longest walk, and some vertex nearly always
+// needs all the steps it may take (70 us for 128 in a batch of 96 games);
+// after a short round the others' results carry it on in a few jumps (20 us
+// for 32 and 5 for the next round: 205 -> 160 us a step of that batch).
+// Valuations whose walks are short anyway pay a launch of 4 us.
+constexpr int kShortRound = 32;
+
 // The ng phase with a fixed number of rounds over the listed vertices;
 // nothing is read back.  Without `fates` the root pass writes every fate.
 static void enqueue_ng(pg_game *g, hipStream_t s, bool fates) {
@@ -976,6 +983,10 @@ static void enqueue_ng(pg_game *g, hipStream_t s, bool fates) {
             dim3(wblk), 0, s, N, g->sp, g->pri, ng, cand, g->ctr,
             wb.full, fates ? g->rs : (uint8_t *)nullptr, (int32_t *)nullptr,
             g->wl_ng, g->wl_cap);
+  if (wb.walk > kShortRound)
+    PG_LAUNCH(pf, K_NG_ROUND, 0.0, k_ng_round_list, list_grid(N, wblk),
+              dim3(kBlock), 0, s, N, g->sp, g->pri, ng, cand, g->ctr, 0,
+              kShortRound, g->wl_ng, g->wl_cap);
   for (int r = 1; r <= wb.rounds; ++r)
     PG_LAUNCH(pf, K_NG_ROUND, 0.0, k_ng_round_list, list_grid(N, wblk),
               dim3(kBlock), 0, s, N, g->sp, g->pri, ng, cand, g->ctr,
