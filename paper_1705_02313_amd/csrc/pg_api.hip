@@ -1386,7 +1386,7 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
         if (deep) {   // the general path goes on from here
           small = false;
           inc = inc_prepare(g, s);
-          valuation_reset(g, s);
+          fates_reset(g, s);
         }
       } else if (inc && inc_ready(g)) {
         IncOut o;
@@ -1649,7 +1649,7 @@ pg_status solve_game(pg_game *g, const pg_solve_opts *opts, uint8_t *winner,
   } else if (o.init_sigma || o.init_tau) {
     PG_TRY(import_strats(g, o.init_sigma, o.init_tau, dev, s));
   }
-  if (!g->small || o.trace_cap > 0) valuation_reset(g, s);
+  if (!g->small || o.trace_cap > 0) fates_reset(g, s);
   Trace tr;
   tr.o = &o;
   struct HashBuf {
@@ -1935,7 +1935,7 @@ pg_status pg_valuation(pg_game *g, const int32_t *sigma, const int32_t *tau,
     }
   }
   PG_TRY(import_strats(g, sigma, tau, dev, s));
-  valuation_reset(g, s);
+  fates_reset(g, s);
   PG_TRY(valuation_device(g, s, n_finite));
   PG_TRY(export_keys(g, key, dev, s));
   PG_TRY(sync_ctr(g, s));
@@ -1957,7 +1957,7 @@ pg_status pg_valuation_counts(pg_game *g, const int32_t *sigma,
   hipStream_t s = (hipStream_t)hip_stream;
   const bool dev = flags & PG_PTR_DEVICE;
   PG_TRY(import_strats(g, sigma, tau, dev, s));
-  valuation_reset(g, s);
+  fates_reset(g, s);
   PG_TRY(valuation_device(g, s, n_finite));
   PG_TRY(export_counts(g, counts, top, dev, s));
   return PG_OK;
@@ -1978,7 +1978,7 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
   hipStream_t s = (hipStream_t)hip_stream;
   const bool dev = flags & PG_PTR_DEVICE;
   PG_TRY(import_strats(g, sigma, tau, dev, s));
-  if (!g->small) valuation_reset(g, s);
+  if (!g->small) fates_reset(g, s);
   Run r;
   r.max_inner = max_inner;
   r.br_only = true;
@@ -1994,7 +1994,7 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
   }
   if (key && !r.keys && deep) {
     if (g->small) {   // the run may have left ng in its kernel
-      valuation_reset(g, s);
+      fates_reset(g, s);
       PG_TRY(valuation_device(g, s, nullptr));
     } else {
       PG_TRY(ranks_device(g, s));

@@ -982,7 +982,7 @@ pg_status rebuild(pg_batch *b, bool *built_any) {
                         hipMemcpyHostToDevice, s));
   PG_HIP(hipMemcpyAsync(b->d_sw_even, b->h_sw_even.data(), 8 * (size_t)G,
                         hipMemcpyHostToDevice, s));
-  valuation_reset(a, s);
+  fates_reset(a, s);
   return PG_OK;
 }
 

@@ -557,8 +557,6 @@ pg_tuning tuning_for(int64_t n_aug);
 bool tuning_valid(const pg_tuning &t);
 // Applies t to g (rank valuations); drops captured iteration graphs.
 void apply_tuning(pg_game *g, const pg_tuning &t);
-// Clears the walk state; call once before a sequence of valuations.
-void valuation_reset(pg_game *g, hipStream_t s);
 // One valuation of the play graph held in g->sp; writes g->key.
 pg_status valuation_device(pg_game *g, hipStream_t s, int64_t *n_finite_out);
 // The walks and the valuation of g->sp with no host synchronisation (for
@@ -577,9 +575,9 @@ pg_status switch_device(pg_game *g, bool odd, hipStream_t s, int32_t *count);
 // marks the vertices whose valuation (the best response's) is top, for
 // later walks to stop at (g->mark_top games; see k_mark_top)
 void mark_top(pg_game *g, hipStream_t s);
-// forgets every vertex's fate: at the start of a solve and after each Even
-// switch step (a valuation keeps the finite fates of the previous one of
-// the same inner loop; valuation_reset includes this)
+// forgets every vertex's fate: before a sequence of valuations and after
+// each Even switch step (a valuation keeps the finite fates of the previous
+// one of the same inner loop)
 void fates_reset(pg_game *g, hipStream_t s);
 // One best-response iteration (valuation, then All_Odd) with a single
 // host synchronisation; returns the number of Odd switches and (nullable)

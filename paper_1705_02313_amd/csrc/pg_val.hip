@@ -944,12 +944,6 @@ void fates_reset(pg_game *g, hipStream_t s) {
   fill_u8(g->rs, 0, g->n_aug + 1, s, &g->prof);
 }
 
-void valuation_reset(pg_game *g, hipStream_t s) {
-  const int64_t N = g->n_aug;
-  fill_i32(g->ng, -1, N, s, &g->prof);
-  fill_i32(g->cand, -1, N, s, &g->prof);
-  fates_reset(g, s);
-}
 
 // The grid of a list round: as many lists as the full passes fill, each with
 // up to kListBlocks blocks.
