@@ -23,7 +23,7 @@
 // Count valuations take the same steps with rows instead of keys: a vertex
 // of A walks its play out of A, counting, and adds the row it arrives at, so
 // every row is up to date and comparisons are the rows' own (1M vertices, 4
-// priorities, solve from arrays: 24.4 -> 10.4 ms).
+// priorities, solve from arrays: 23.4 -> 9.4 ms).
 //
 // Decisions go to a list of {vertex, new successor} pairs (`dec`) that the
 // next step applies, so a step that gives up (a hub with too many in-edges,
@@ -36,12 +36,12 @@
 //
 // Every access is a random line, so a step costs its round trips (small A)
 // or its lines (large A), a full valuation the whole game's lines whatever
-// changed: on the 10M-vertex random game 12 of the 95 valuations stay full
-// (0.4-0.9 ms each with coarse keys, 1.4-2.1 ms with ranks), 38 take the
+// changed: on the 10M-vertex random game 18 of the 95 valuations stay full
+// (0.4-0.9 ms each with coarse keys, 1.4-2.1 ms with ranks), 32 take the
 // device form (0.1-0.4 ms mostly) and 45 the block form (25-40 us each).
 // Solves, load included, against full valuations with ranks throughout:
-// 150 -> 50 ms there, 15.1 -> 7.5 ms at 1M vertices, 58 -> 16 ms on the
-// 2M-vertex chain, 5.8 -> 2.8 ms at 40,000 vertices.
+// 153 -> 36 ms there, 15.5 -> 5.6 ms at 1M vertices, 58 -> 14 ms on the
+// 2M-vertex chain, 5.9 -> 2.4 ms at 40,000 vertices.
 #include <algorithm>
 
 #include "pg_coarse.h"
