@@ -498,6 +498,12 @@ __device__ __forceinline__ int find_lanes(int n, int T) {
 // that hold earlier tickets, and these run: no order of residency can stop
 // it.  A queue place holds -1 until its writer stores the value, and again
 // after its reader took it.
+//
+// The tail counts the places asked for, not those that are there: a wave past
+// the LDS lists takes a chunk for the few sources it has just found, so a
+// hub's in-edges can ask for more than the q_cap chunks that every vertex of
+// the game once would need.  Whoever asks beyond them sets I_STOP, and no
+// ticket names a place at or past q_cap.
 constexpr int kFindChunk = 64, kFindA = 1024, kFindC = 2048;
 constexpr int kFindKeep = 128, kFindBlocks = 512;
 constexpr int kFindItems = kFindChunk - 1;   // of a queue chunk: word 0 is
@@ -505,16 +511,19 @@ constexpr int kFindItems = kFindChunk - 1;   // of a queue chunk: word 0 is
 constexpr int kFindWait = 1 << 20;           // polls, then the step gives up
 
 // the next chunk, or -1: all done, or the step gave up
-__device__ __forceinline__ int32_t find_ticket(int32_t S, int32_t *ic) {
+__device__ __forceinline__ int32_t find_ticket(int32_t S, int32_t q_cap,
+                                               int32_t *ic) {
   const int32_t t = atomicAdd(&ic[I_TICKET], 1);
   if (t < S) return t;
+  if (t - S >= q_cap) return -1;
   for (int k = 0; k < kFindWait; ++k) {
+    if (ld_relaxed(&ic[I_STOP])) return -1;
     // done first (never negative: the tail's address waits for it): when it
     // has reached S + tail, no chunk was open then
     const int32_t done = ld_relaxed(&ic[I_QDONE]);
     const int32_t tail = ld_relaxed(&ic[I_QTAIL + (done < 0)]);
     if (tail > t - S) return t;
-    if (done == S + tail || ld_relaxed(&ic[I_STOP])) return -1;
+    if (done == S + tail) return -1;
     __builtin_amdgcn_s_sleep(8);
   }
   atomicOr(&ic[I_STOP], 1);
@@ -547,7 +556,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
   };
   for (;;) {
     __syncthreads();
-    if (tid == 0) s_t = find_ticket(S, ic);
+    if (tid == 0) s_t = find_ticket(S, P.q_cap, ic);
     __syncthreads();
     const int32_t t = s_t;
     if (t < 0) break;
