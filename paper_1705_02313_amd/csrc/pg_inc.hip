@@ -71,6 +71,8 @@ constexpr int kFindLevels = 512;     // levels of a device form's find
 constexpr int kIncMaxDegree = 2048;  // in-edges of one vertex, else give up
 constexpr int kIncFate = 1024;       // ng steps of one fate
 constexpr int kIncBlocks = 1024;
+constexpr int32_t kEpochMax = 1 << 30;   // the marks are cleared at the start
+                                         // of a run past it
 
 // ---------------------------------------------------------------------------
 // the in-edge lists
@@ -1254,7 +1256,7 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     fill_i32(x.cmark, 0, N, s);
     x.epoch = 0;
     x.state = 1;
-  } else if (x.epoch > (1 << 30)) {
+  } else if (x.epoch >= kEpochMax) {
     fill_i32(x.mark, 0, N, s);
     fill_i32(x.cmark, 0, N, s);
     x.epoch = 0;
@@ -1415,10 +1417,13 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide<D>, grid, blk, 0, s, P, epoch, 1,
               inc_dec(g, x.cur ^ 1), x.ic);
   }
-  PG_TRY(inc_read(g, s, block && host_pinned(x.h)));
+  const pg_status st = inc_read(g, s, block && host_pinned(x.h));
+  // a refused run's epochs are used all the same: its marks stay
+  if (st != PG_OK && st != PG_EINADMISSIBLE) x.epoch = kEpochMax;
+  else if (block) x.epoch = x.h[I_EPOCH];
+  if (st != PG_OK) return st;
   g->last_ms = clock_ms(g, x.h[I_CLOCK], x.h[I_CLOCK_END]);
   if (block) {
-    x.epoch = x.h[I_EPOCH];
     x.a0 = x.h[I_A0];
     x.cur = x.h[I_CUR];
     x.nsw = x.h[I_NDEC];
