@@ -144,7 +144,8 @@ enum {
  *
  * A valuation of pg_solve or pg_best_response that follows few switches is
  * computed by its changed part only (not with a trace, PG_CAREFUL_WALKS or
- * PG_HOST_REDUCED_LIST): same results.  The first such
+ * PG_HOST_REDUCED_LIST, nor while a strategy given by the caller names a
+ * vertex outside its row): same results.  The first such
  * call lays out the game's in-edges for it (4 bytes per edge, 12 per
  * vertex); without room for them every valuation is a full one.
  *
@@ -223,7 +224,8 @@ pg_status pg_initial_strategies(pg_game *game, int32_t *sigma, int32_t *tau,
  *   sigma   n_aug entries; for Even vertices a successor id or PG_SINK
  *   tau     n_aug entries; for Odd vertices a successor id
  *           (entries of the other player are ignored; every chosen successor
- *           must be an edge of the modified game -- this is not checked)
+ *           must be an edge of the modified game -- an id out of range is
+ *           PG_EINVAL, any other vertex is followed as it is given)
  *   key     n_aug+1 outputs: for a vertex whose play reaches the sink, the
  *           rank of its valuation among all such vertices and the sink
  *           (0 = smallest in the paper's order); PG_KEY_TOP for an infinite

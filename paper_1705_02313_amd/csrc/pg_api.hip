@@ -1337,6 +1337,7 @@ struct Trace {
 struct Run {
   int32_t max_major = 0, max_inner = 0;
   bool reset = false, br_only = false;
+  bool given = false;   // the caller's strategies: any vertices may be named
   Trace *tr = nullptr;
   int64_t n_major = 0, n_val = 0, n_odd = 0, n_even = 0;
   double iter_ms = 0.0;
@@ -1350,6 +1351,7 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
   bool small = g->small && !traced;
   bool inc = !traced && !small && inc_prepare(g, s);
   if (!inc) g->inc.on = false;
+  if (r->given) inc_check_rows(g, s);
   int32_t &inner = g->inc.inner, &major = g->inc.major;
   major = 0;
   for (;;) {
@@ -1386,6 +1388,7 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
         if (deep) {   // the general path goes on from here
           small = false;
           inc = inc_prepare(g, s);
+          if (r->given) inc_check_rows(g, s);
           fates_reset(g, s);
         }
       } else if (inc && inc_ready(g)) {
@@ -1413,7 +1416,7 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
           }
         }
         if (!done) PG_TRY(iteration_device(g, s, &c, &nf));
-        inc_after_full(g, c, !done);
+        inc_after_full(g, s, c, !done);
         r->keys = !done;
         r->iter_ms += g->last_ms;
         if (r->tr) r->tr->record(g, s, c, nf);
@@ -1665,6 +1668,7 @@ pg_status solve_game(pg_game *g, const pg_solve_opts *opts, uint8_t *winner,
   r.max_major = o.max_major;
   r.max_inner = o.max_inner;
   r.reset = o.best_response == PG_BR_SI_RESET;
+  r.given = o.init_sigma || o.init_tau;
   r.tr = &tr;
   pg_status st = PG_OK;
   if (o.best_response != PG_BR_BELLMAN_FORD) {
@@ -1981,7 +1985,7 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
   if (!g->small) fates_reset(g, s);
   Run r;
   r.max_inner = max_inner;
-  r.br_only = true;
+  r.br_only = r.given = true;
   const pg_status st = run_si(g, &r, s);
   if (n_valuations) *n_valuations = (int32_t)r.n_val;
   if (st != PG_OK) return st;

@@ -310,6 +310,8 @@ struct pg_game {
                             // since the last All_Even
     bool even = false;      // Even switched since the last full valuation
     bool grown = false;     // the block form gave the pending step up
+    bool offrow = false;    // a choice may be no edge of its row
+    int32_t check = 0;      // number of the last check for that
     int cur = 0;
     int32_t nsw = 0, a0 = 0;
     int32_t inner = 0, major = 0;   // the run's iteration counts
@@ -608,7 +610,10 @@ void inc_release(pg_game *g);
 bool inc_ready(const pg_game *g);
 void inc_commit(pg_game *g, hipStream_t s);
 void inc_before_full(pg_game *g, hipStream_t s, bool coarse);
-void inc_after_full(pg_game *g, int32_t switches, bool exact);
+void inc_after_full(pg_game *g, hipStream_t s, int32_t switches, bool exact);
+// For strategies given by the caller: full valuations while a choice is no
+// edge of its row (looked at again after each).
+void inc_check_rows(pg_game *g, hipStream_t s);
 // a full valuation may use coarse keys / did not fit them
 bool inc_coarse(const pg_game *g);
 void inc_backoff(pg_game *g);

@@ -64,7 +64,10 @@ enum IncCounter : int {
   I_WORDS = 64,   // the part copied to the host
   // the find's queue, a line each
   I_TICKET = 64, I_QTAIL = 96, I_QDONE = 128,
-  I_ALL = 160
+  I_ALL = 160,    // the part cleared before a step
+  I_OFFROW = 160, // the last check of the rows that failed (its number); the
+                  // host's copy follows the I_WORDS
+  I_SIZE = 161
 };
 static_assert((int)I_ERR == (int)C_ERR, "the ng walk reports through ctr[0]");
 constexpr int kFindLevels = 512;     // levels of a device form's find
@@ -866,6 +869,46 @@ __global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
   }
 }
 
+// Stores `check` when a vertex's choice is no edge of its row (a strategy
+// given at the C ABI may name any vertex): the find follows in-edges only.
+// Bound by one read of the rows, before the run's first full valuation
+// (300,000 vertices: 5 us); rows beyond kWideRow entries are read by the
+// whole block, or a hub's would keep one thread.
+constexpr int kWideRow = 128;
+__global__ __launch_bounds__(kBlock) void k_inc_rows_hold(IncP P,
+                                                          int32_t check,
+                                                          int32_t *word,
+                                                          int32_t *host) {
+  __shared__ int32_t wide[kBlock], s_n;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  bool off = false;
+  const int32_t to = v < P.N ? P.sp[v].x : P.N;
+  if (to != P.N) {
+    const int64_t e0 = P.off[v], e1 = P.off[v + 1];
+    if (e1 - e0 > kWideRow) {
+      wide[atomicAdd(&s_n, 1)] = (int32_t)v;
+    } else {
+      off = true;
+      for (int64_t e = e0; e < e1 && off; ++e) off = P.tgt[e] != to;
+    }
+  }
+  __syncthreads();
+  const int n = s_n;
+  for (int k = 0; k < n; ++k) {
+    const int32_t w = wide[k], cur = P.sp[w].x;
+    bool hit = false;
+    for (int64_t e = P.off[w] + threadIdx.x, e1 = P.off[w + 1]; e < e1;
+         e += kBlock)
+      hit |= P.tgt[e] == cur;
+    off |= !__syncthreads_or(hit);
+  }
+  if (__ballot(off) && (threadIdx.x & (kWave - 1)) == 0 &&
+      ld_relaxed(word) != check && atomicExch(word, check) != check)
+    *host = check;
+}
+
 // Applies decisions before a full valuation or an export.
 __global__ __launch_bounds__(kBlock) void k_inc_commit(
     const int2 *__restrict__ dec, int32_t n, const int32_t *__restrict__ pri,
@@ -1231,7 +1274,7 @@ static void in_lists(pg_game *g, hipStream_t s) {
 bool inc_prepare(pg_game *g, hipStream_t s) {
   pg_game::Inc &x = g->inc;
   x.dirty = x.pending = x.d_valid = x.grown = x.even = x.exact = false;
-  x.queue = false;
+  x.queue = x.offrow = false;
   x.nsw = x.a0 = 0;
   x.skip = x.back = 0;
   x.on = false;
@@ -1242,9 +1285,9 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     if (st == PG_OK) st = dev_alloc(&x.in, M);
     if (st == PG_OK) st = dev_alloc(&x.mark, N);
     if (st == PG_OK) st = dev_alloc(&x.cmark, N);
-    if (st == PG_OK) st = dev_alloc(&x.ic, I_ALL);
+    if (st == PG_OK) st = dev_alloc(&x.ic, I_SIZE);
     if (st == PG_OK)
-      st = host_alloc((void **)&x.h, sizeof(int32_t) * I_WORDS);
+      st = host_alloc((void **)&x.h, sizeof(int32_t) * (I_WORDS + 1));
     if (st != PG_OK) {
       inc_release(g);
       x.state = -1;
@@ -1254,7 +1297,8 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     in_lists(g, s);
     fill_i32(x.mark, 0, N, s);
     fill_i32(x.cmark, 0, N, s);
-    x.epoch = 0;
+    fill_i32(x.ic, 0, I_SIZE, s);
+    x.epoch = x.check = 0;
     x.state = 1;
   } else if (x.epoch >= kEpochMax) {
     fill_i32(x.mark, 0, N, s);
@@ -1295,9 +1339,25 @@ void inc_commit(pg_game *g, hipStream_t s) {
               x.nsw, g->pri, (int32_t)g->n_aug, g->sp);
 }
 
+// Looks whether every choice is an edge of its row; the answer is there after
+// the stream's next synchronisation.
+void inc_check_rows(pg_game *g, hipStream_t s) {
+  pg_game::Inc &x = g->inc;
+  if (!x.on) return;
+  x.offrow = true;
+  ++x.check;
+  x.h[I_WORDS] = 0;
+  const bool direct = host_pinned(x.h);
+  PG_LAUNCH(&g->prof, K_OTHER, 24.0 * g->n_aug + 4.0 * g->m_aug,
+            k_inc_rows_hold, dim3(grid_for(g->n_aug)), dim3(kBlock), 0, s,
+            inc_params(g), x.check, x.ic + I_OFFROW,
+            direct ? x.h + I_WORDS : x.ic + I_OFFROW);
+  if (!direct) publish(x.h + I_WORDS, x.ic + I_OFFROW, 1, s);
+}
+
 bool inc_ready(const pg_game *g) {
   const pg_game::Inc &x = g->inc;
-  return x.on && x.pending && x.skip == 0 && !x.exact &&
+  return x.on && x.pending && x.skip == 0 && !x.exact && !x.offrow &&
          ((int64_t)x.nsw * (g->dense ? kIncSwitchShareCounts
                                      : kIncSwitchShare) <= g->n_aug ||
           g->n_aug <= kBlockA);
@@ -1330,7 +1390,7 @@ void inc_before_full(pg_game *g, hipStream_t s, bool coarse) {
   x.even = false;
 }
 
-void inc_after_full(pg_game *g, int32_t switches, bool exact) {
+void inc_after_full(pg_game *g, hipStream_t s, int32_t switches, bool exact) {
   pg_game::Inc &x = g->inc;
   if (!x.on) return;
   x.dirty = !exact;
@@ -1344,6 +1404,10 @@ void inc_after_full(pg_game *g, int32_t switches, bool exact) {
   x.pairs = nullptr;
   x.cur = 0;
   x.nsw = switches;
+  if (x.offrow) {   // (of the check before this valuation)
+    x.offrow = x.h[I_WORDS] == x.check;
+    if (x.offrow) inc_check_rows(g, s);
+  }
 }
 
 // A step that gave up: full valuations for a while.
