@@ -1314,7 +1314,11 @@ void inc_release(pg_game *g) {
   void *ptrs[] = {x.in_off, x.in, x.mark, x.cmark, x.ic, x.pairs};
   for (void *p : ptrs) dev_free(p);
   host_free(x.h);
+  // a run that goes on without the lists keeps its counts
+  const int32_t inner = x.inner, major = x.major;
   x = pg_game::Inc();
+  x.inner = inner;
+  x.major = major;
 }
 
 // direct: the kernel wrote its results to the host's words itself

@@ -1,0 +1,106 @@
+/*
+ * Drives the C ABI over a HIP runtime that refuses memory on request
+ * (tests/test_gpu_runtime.py): this program's own hipMalloc and
+ * hipHostMalloc stand before the runtime's for the library too.
+ *
+ * runtime_main deep GAME
+ *     solves a small game that its one-block form leaves to the general
+ *     path, with no further memory to be had; prints "deep status n_major
+ *     n_valuations" for a whole run and for one with max_major = 2.
+ *
+ * GAME (little endian): int64 n, int64 m, int64 offsets[n+1], int32
+ * targets[m], uint8 owner[n], int32 pri[n].
+ */
+#define _GNU_SOURCE
+#include <dlfcn.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include "../include/pg.h"
+
+#define HIP_OUT_OF_MEMORY 2
+
+static int refuse;
+
+int hipMalloc(void **p, size_t bytes)
+{
+    static int (*next)(void **, size_t);
+    if (!next)
+        next = (int (*)(void **, size_t))dlsym(RTLD_NEXT, "hipMalloc");
+    return refuse ? HIP_OUT_OF_MEMORY : next(p, bytes);
+}
+
+int hipHostMalloc(void **p, size_t bytes, unsigned flags)
+{
+    static int (*next)(void **, size_t, unsigned);
+    if (!next)
+        next = (int (*)(void **, size_t, unsigned))dlsym(RTLD_NEXT,
+                                                         "hipHostMalloc");
+    return refuse ? HIP_OUT_OF_MEMORY : next(p, bytes, flags);
+}
+
+typedef struct {
+    int64_t n, m, *off;
+    int32_t *tgt, *pri;
+    uint8_t *owner;
+} game;
+
+static void *part(FILE *f, size_t size, int64_t count)
+{
+    void *p = malloc(size * (size_t)count);
+    if (!p || fread(p, size, (size_t)count, f) != (size_t)count) {
+        fprintf(stderr, "short game file\n");
+        exit(3);
+    }
+    return p;
+}
+
+static game read_game(const char *path)
+{
+    game g;
+    FILE *f = fopen(path, "rb");
+    if (!f || fread(&g.n, 8, 1, f) != 1 || fread(&g.m, 8, 1, f) != 1)
+        exit(3);
+    g.off = part(f, 8, g.n + 1);
+    g.tgt = part(f, 4, g.m);
+    g.owner = part(f, 1, g.n);
+    g.pri = part(f, 4, g.n);
+    fclose(f);
+    return g;
+}
+
+static pg_status load(const game *g, pg_game **out)
+{
+    return pg_load_csr(g->n, g->m, g->off, g->tgt, g->owner, g->pri, 0, NULL,
+                       out);
+}
+
+static int deep(const char *path)
+{
+    game g = read_game(path);
+    uint8_t *winner = malloc((size_t)g.n);
+    for (int cap = 0; cap <= 2; cap += 2) {
+        pg_game *d = NULL;
+        pg_solve_opts o;
+        pg_stats st;
+        memset(&o, 0, sizeof o);
+        o.max_major = cap;
+        if (load(&g, &d) != PG_OK) return 2;
+        refuse = 1;
+        pg_status rc = pg_solve(d, &o, winner, NULL, NULL, &st, NULL);
+        refuse = 0;
+        printf("deep %d %lld %lld\n", (int)rc, (long long)st.n_major,
+               (long long)st.n_valuations);
+        pg_free(d);
+        pg_release_cache();
+    }
+    return 0;
+}
+
+int main(int argc, char **argv)
+{
+    if (argc == 3 && !strcmp(argv[1], "deep")) return deep(argv[2]);
+    fprintf(stderr, "usage: runtime_main MODE [GAME]\n");
+    return 64;
+}
