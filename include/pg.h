@@ -147,7 +147,9 @@ enum {
  * PG_HOST_REDUCED_LIST, nor while a strategy given by the caller names a
  * vertex outside its row): same results.  The first such
  * call lays out the game's in-edges for it (4 bytes per edge, 12 per
- * vertex); without room for them every valuation is a full one.
+ * vertex; from 2^17 to 2^26 vertices over a scratch of 8 bytes per edge,
+ * which the call gives back); without room for them every valuation is a
+ * full one.
  *
  * A full best-response iteration (walks, valuation, All_Odd) of pg_solve and
  * pg_best_response is captured once per game as a HIP graph (on a stream of

@@ -1344,7 +1344,7 @@ struct Run {
   bool keys = false;   // g->key holds the last valuation's ranks
 };
 
-pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
+pg_status run_loop(pg_game *g, Run *r, hipStream_t s) {
   const int32_t N = (int32_t)g->n_aug;
   // a trace reports every valuation's ranks
   const bool traced = r->tr && r->tr->o->trace_cap > 0;
@@ -1439,6 +1439,12 @@ pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
     // a new inner loop: Even's switches may make finite vertices top
     if (!inc) fates_reset(g, s);
   }
+}
+
+pg_status run_si(pg_game *g, Run *r, hipStream_t s) {
+  const pg_status st = run_loop(g, r, s);
+  inc_end(g, s);
+  return st;
 }
 
 }  // namespace

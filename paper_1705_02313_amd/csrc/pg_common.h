@@ -605,6 +605,8 @@ bool inc_eligible(const pg_game *g);
 // Start of a run: builds the in-edge lists if they are not there; false
 // when the game takes full valuations only.
 bool inc_prepare(pg_game *g, hipStream_t s);
+// End of a run, refused ones too: what only its first valuation needed.
+void inc_end(pg_game *g, hipStream_t s);
 void inc_release(pg_game *g);
 // true when the pending switches are few enough for inc_step
 bool inc_ready(const pg_game *g);

@@ -1309,6 +1309,14 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
   return true;
 }
 
+void inc_end(pg_game *g, hipStream_t s) {
+  pg_game::Inc &x = g->inc;
+  if (!x.pairs) return;
+  (void)hipStreamSynchronize(s);
+  dev_free(x.pairs);
+  x.pairs = nullptr;
+}
+
 void inc_release(pg_game *g) {
   pg_game::Inc &x = g->inc;
   void *ptrs[] = {x.in_off, x.in, x.mark, x.cmark, x.ic, x.pairs};

@@ -8,6 +8,12 @@
  *     path, with no further memory to be had; prints "deep status n_major
  *     n_valuations" for a whole run and for one with max_major = 2.
  *
+ * runtime_main pairs GAME
+ *     a best response refused in its first valuation (the last but one
+ *     vertex is Even and answers with the last), then one that is not;
+ *     prints "pairs status bytes" twice, the bytes held on the device with
+ *     the cache given back.
+ *
  * GAME (little endian): int64 n, int64 m, int64 offsets[n+1], int32
  * targets[m], uint8 owner[n], int32 pri[n].
  */
@@ -21,14 +27,39 @@
 
 #define HIP_OUT_OF_MEMORY 2
 
+#define MOST_BLOCKS 65536
+
 static int refuse;
+static struct { void *p; size_t bytes; } blocks[MOST_BLOCKS];
+static int n_blocks;
+static size_t held;   /* device bytes */
 
 int hipMalloc(void **p, size_t bytes)
 {
     static int (*next)(void **, size_t);
     if (!next)
         next = (int (*)(void **, size_t))dlsym(RTLD_NEXT, "hipMalloc");
-    return refuse ? HIP_OUT_OF_MEMORY : next(p, bytes);
+    if (refuse || n_blocks == MOST_BLOCKS) return HIP_OUT_OF_MEMORY;
+    int rc = next(p, bytes);
+    if (rc == 0) {
+        blocks[n_blocks].p = *p;
+        blocks[n_blocks++].bytes = bytes;
+        held += bytes;
+    }
+    return rc;
+}
+
+int hipFree(void *p)
+{
+    static int (*next)(void *);
+    if (!next) next = (int (*)(void *))dlsym(RTLD_NEXT, "hipFree");
+    for (int i = 0; i < n_blocks; ++i)
+        if (blocks[i].p == p) {
+            held -= blocks[i].bytes;
+            blocks[i] = blocks[--n_blocks];
+            break;
+        }
+    return next(p);
 }
 
 int hipHostMalloc(void **p, size_t bytes, unsigned flags)
@@ -98,9 +129,29 @@ static int deep(const char *path)
     return 0;
 }
 
+static int pairs(const char *path)
+{
+    game g = read_game(path);
+    pg_game *d = NULL;
+    int64_t na = 0;
+    if (load(&g, &d) != PG_OK || pg_game_info(d, 0, 0, &na, 0) != PG_OK)
+        return 2;
+    int32_t *sigma = malloc(4 * (size_t)na), *tau = malloc(4 * (size_t)na);
+    if (pg_initial_strategies(d, sigma, tau, 0, NULL) != PG_OK) return 2;
+    for (int k = 0; k < 2; ++k) {
+        sigma[g.n - 2] = k ? PG_SINK : (int32_t)(g.n - 1);
+        pg_status rc = pg_best_response(d, sigma, tau, NULL, NULL, 0, 0,
+                                        NULL);
+        pg_release_cache();
+        printf("pairs %d %lld\n", (int)rc, (long long)held);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc == 3 && !strcmp(argv[1], "deep")) return deep(argv[2]);
+    if (argc == 3 && !strcmp(argv[1], "pairs")) return pairs(argv[2]);
     fprintf(stderr, "usage: runtime_main MODE [GAME]\n");
     return 64;
 }

@@ -69,3 +69,19 @@ def test_counts_of_a_run_that_finds_no_memory_on_the_way(run, tmp_path):
     assert [int(x) for x in whole] == [pg.PG_OK, ref["n_major"],
                                        ref["n_valuations"]]
     assert [int(x) for x in capped[:2]] == [pg.PG_EITERLIMIT, 2]
+
+
+def test_a_refused_run_keeps_no_scratch(run, tmp_path):
+    """The in-edges of a large game are built over pairs of 8 bytes an edge,
+    which a run gives back also when its first valuation is refused."""
+    g = synth.random_game(140001, 2, 5, 3)
+    n, m = g["n"], g["m"]
+    g = {"n": n + 2, "m": m + 2,
+         "offsets": np.append(g["offsets"], [m + 1, m + 2]),
+         "targets": np.append(g["targets"], [n + 1, n]),
+         "owner": np.append(g["owner"], [0, 1]),
+         "pri": np.append(g["pri"], [n + n % 2 + 1, n + n % 2])}
+    refused, fine = run("pairs", _write(tmp_path / "g", g))
+    assert int(refused[0]) == pg.PG_EINADMISSIBLE
+    assert int(fine[0]) == pg.PG_OK
+    assert int(refused[1]) == int(fine[1])
