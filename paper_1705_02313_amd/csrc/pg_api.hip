@@ -1354,6 +1354,16 @@ pg_status run_loop(pg_game *g, Run *r, hipStream_t s) {
   if (r->given) inc_check_rows(g, s);
   int32_t &inner = g->inc.inner, &major = g->inc.major;
   major = 0;
+  // what a step had done, of a refused one too
+  auto done_step = [&](pg_status st, const IncOut &o) {
+    r->keys = false;
+    r->iter_ms += g->last_ms;
+    r->n_major = major;
+    r->n_val += o.nval;
+    r->n_odd += o.odd;
+    r->n_even += o.even;
+    return st;
+  };
   for (;;) {
     if (r->max_major > 0 && major >= r->max_major) {
       inc_commit(g, s);
@@ -1377,13 +1387,8 @@ pg_status run_loop(pg_game *g, Run *r, hipStream_t s) {
       if (small) {
         IncOut o;
         bool deep = false;
-        PG_TRY(small_step(g, s, r->br_only, r->reset, r->max_inner,
-                          r->max_major, &deep, &o));
-        r->keys = false;
-        r->iter_ms += g->last_ms;
-        r->n_val += o.nval;
-        r->n_odd += o.odd;
-        r->n_even += o.even;
+        PG_TRY(done_step(small_step(g, s, r->br_only, r->reset, r->max_inner,
+                                    r->max_major, &deep, &o), o));
         end = o.state;
         if (deep) {   // the general path goes on from here
           small = false;
@@ -1393,13 +1398,8 @@ pg_status run_loop(pg_game *g, Run *r, hipStream_t s) {
         }
       } else if (inc && inc_ready(g)) {
         IncOut o;
-        PG_TRY(inc_step(g, s, !r->reset && !r->br_only, r->max_inner,
-                        r->max_major, &o));
-        r->keys = false;
-        r->iter_ms += g->last_ms;
-        r->n_val += o.nval;
-        r->n_odd += o.odd;
-        r->n_even += o.even;
+        PG_TRY(done_step(inc_step(g, s, !r->reset && !r->br_only,
+                                  r->max_inner, r->max_major, &o), o));
         end = o.state;
       } else {
         int32_t c = 0;

@@ -1495,11 +1495,13 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
   }
   const pg_status st = inc_read(g, s, block && host_pinned(x.h));
   // a refused run's epochs are used all the same: its marks stay
-  if (st != PG_OK && st != PG_EINADMISSIBLE) x.epoch = kEpochMax;
-  else if (block) x.epoch = x.h[I_EPOCH];
-  if (st != PG_OK) return st;
+  if (st != PG_OK && st != PG_EINADMISSIBLE) {
+    x.epoch = kEpochMax;
+    return st;
+  }
   g->last_ms = clock_ms(g, x.h[I_CLOCK], x.h[I_CLOCK_END]);
   if (block) {
+    x.epoch = x.h[I_EPOCH];
     x.a0 = x.h[I_A0];
     x.cur = x.h[I_CUR];
     x.nsw = x.h[I_NDEC];
@@ -1508,6 +1510,7 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     out->nval = x.h[I_NVAL];
     out->odd = x.h[I_ODDSW];
     out->even = x.h[I_EVENSW];
+    if (st != PG_OK) return st;   // (what it had done is reported)
     switch (x.h[I_STATE]) {
       case IS_BR: out->state = INC_BR; break;
       case IS_SOLVED: out->state = INC_SOLVED; break;
@@ -1522,6 +1525,8 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
         else inc_backoff(g);
         break;
     }
+  } else if (st != PG_OK) {
+    return st;
   } else if (x.h[I_STOP]) {
     x.queue = false;
     inc_backoff(g);

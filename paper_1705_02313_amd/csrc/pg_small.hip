@@ -862,15 +862,18 @@ pg_status small_step(pg_game *g, hipStream_t s, bool br_only, bool reset,
   R.val_cap = 512;
   PG_LAUNCH(&g->prof, K_SMALL, 0.0, k_small_run, dim3(1), dim3(kSmallThreads),
             run_lds(g->n_aug, g->m_aug), s, small_game(g), R);
-  PG_TRY(small_read(g, s));
-  g->last_ms = clock_ms(g, g->hctr[S_CLOCK], g->hctr[S_CLOCK_END]);
   *out = IncOut();
+  *deep = false;
+  const pg_status st = small_read(g, s);
+  if (st != PG_OK && st != PG_EINADMISSIBLE) return st;
+  // (a refused run reports what it had done, too)
+  g->last_ms = clock_ms(g, g->hctr[S_CLOCK], g->hctr[S_CLOCK_END]);
   out->nval = g->hctr[S_NVAL];
   out->odd = g->hctr[S_ODDSW];
   out->even = g->hctr[S_EVENSW];
   g->inc.inner = g->hctr[S_INNER];
   g->inc.major = g->hctr[S_MAJOR];
-  *deep = false;
+  if (st != PG_OK) return st;
   switch (g->hctr[S_STATE]) {
     case SS_BR: out->state = INC_BR; break;
     case SS_SOLVED: out->state = INC_SOLVED; break;

@@ -3,11 +3,14 @@ a valuation by the changed part (the odd cycle closes when Odd answers), and
 then the runs that follow on the same handle, against the oracle."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 
 from oracle import orc
-from paper_1705_02313_amd.pg import PG_EINADMISSIBLE, Game, PgError
+from paper_1705_02313_amd.pg import (PG_EINADMISSIBLE, Game, PgError,
+                                     SolveOpts, Stats, lib)
 from tests.helpers import to_np
 
 pytestmark = pytest.mark.gpu
@@ -78,3 +81,32 @@ def test_runs_after_a_refused_strategy(few):
             np.testing.assert_array_equal(to_np(out["tau"]), ref["tau_orig"])
             for k in ("n_major", "n_valuations"):
                 assert out["stats"][k] == ref[k], k
+
+
+@pytest.mark.parametrize("few", [False, True], ids=["ranks", "counts"])
+@pytest.mark.parametrize("n", [3001, 9001])   # in one block, and above
+def test_counts_of_a_refused_run(n, few):
+    """What a refused run had done is reported whatever form it took: as by
+    the same run on full valuations (a trace asks for those)."""
+    g, e, o = _game(n, few)
+    winner = np.zeros(n, np.uint8)
+    with Game.from_dict(g) as d:
+        bad, tau = d.initial_strategies()
+        bad[e] = o
+        seen = []
+        for cap in (0, 64):
+            finite = np.zeros(64, np.int64)
+            opts = SolveOpts(0, 0, 0, 0, bad.ctypes.data, tau.ctypes.data,
+                             cap, 0, None, finite.ctypes.data, None, None)
+            st = Stats()
+            rc = lib().pg_solve(d._h, ctypes.byref(opts),
+                                winner.ctypes.data, None, None,
+                                ctypes.byref(st), None)
+            assert rc == PG_EINADMISSIBLE
+            seen.append([st.n_major, st.n_valuations, st.n_odd_switches,
+                         st.n_even_switches])
+        assert seen[0] == seen[1]
+        nv = ctypes.c_int32(-1)
+        rc = lib().pg_best_response(d._h, bad.ctypes.data, tau.ctypes.data,
+                                    None, ctypes.byref(nv), 0, 0, None)
+        assert rc == PG_EINADMISSIBLE and nv.value == seen[1][1]
