@@ -568,8 +568,23 @@ pg_status copy_out(void *dst, const void *src, size_t bytes, bool device,
 
 thread_local DevPool *tl_pool = nullptr;
 
+hipError_t runtime_alloc(void **p, size_t bytes, bool host) {
+  auto ask = [&]() {
+    return host ? hipHostMalloc(p, bytes, hipHostMallocDefault)
+                : hipMalloc(p, bytes);
+  };
+  hipError_t e = ask();
+  if (e != hipSuccess) {
+    (void)hipGetLastError();   // reported by the status
+    trim_caches();
+    e = ask();
+    if (e != hipSuccess) (void)hipGetLastError();
+  }
+  return e;
+}
+
 pg_status DevPool::alloc(void **p, size_t bytes, bool host) {
-  std::lock_guard<std::mutex> lock(mu);
+  std::unique_lock<std::mutex> lock(mu);
   if (bump_dev) {
     size_t &used = host ? bump_hused : bump_used;
     const size_t cap = host ? bump_hcap : bump_cap;
@@ -592,8 +607,15 @@ pg_status DevPool::alloc(void **p, size_t bytes, bool host) {
     const bool slab = b <= kSlabBlockMax;
     const size_t total = slab ? b * kSlabBlocks : b;
     void *base = nullptr;
-    hipError_t e = host ? hipHostMalloc(&base, total, hipHostMallocDefault)
-                        : hipMalloc(&base, total);
+    // (the caches it may give back lock themselves)
+    lock.unlock();
+    hipError_t e = runtime_alloc(&base, total, host);
+    if (e != hipSuccess) {   // this pool's own free blocks, once at rest
+      (void)hipDeviceSynchronize();
+      trim();
+      e = runtime_alloc(&base, total, host);
+    }
+    lock.lock();
     if (e != hipSuccess) {
       *p = nullptr;
       return pg_fail(PG_ENOMEM, std::string("pool allocation failed: ") +
@@ -726,7 +748,7 @@ void give_pool(int device, DevPool *pool) {
   delete pool;
 }
 
-static void trim_caches() {
+void trim_caches() {
   std::lock_guard<std::mutex> lock(g_cache_mu);
   int prev = -1;
   (void)hipGetDevice(&prev);
@@ -803,7 +825,7 @@ float clock_ms(pg_game *g, int32_t begin, int32_t end) {
 
 pg_status host_alloc(void **p, size_t bytes) {
   if (tl_pool) return tl_pool->alloc(p, bytes, true);
-  PG_HIP(hipHostMalloc(p, bytes, hipHostMallocDefault));
+  PG_HIP(runtime_alloc(p, bytes, true));
   return PG_OK;
 }
 

@@ -751,14 +751,18 @@ void drop_step_graphs(pg_batch *b) {
 
 // An arena of up to this many vertices comes from the batch's pool (blocks
 // of power-of-two sizes, kept for the next batch); a larger one from the
-// runtime, exactly sized.
+// runtime, exactly sized, and so one that does not fit otherwise.
 constexpr int64_t kPoolArena = int64_t(4) << 20;
 
-pg_status batch_alloc(pg_batch *b) {
+bool arena_pooled(int64_t cap_v, int64_t cap_e) {
+  return cap_v <= kPoolArena && cap_e <= 8 * kPoolArena;
+}
+
+// pooled: the arena's memory too
+pg_status batch_alloc(pg_batch *b, bool pooled) {
   b->pool = take_pool(b->device);
   if (!b->pool) return pg_fail(PG_ENOMEM, "host allocation failed");
-  PoolScope ps(b->cap_v <= kPoolArena && b->cap_e <= 8 * kPoolArena ? b->pool
-                                                                   : nullptr);
+  PoolScope ps(pooled ? b->pool : nullptr);
   pg_game *a = new (std::nothrow) pg_game();
   if (!a) return pg_fail(PG_ENOMEM, "host allocation failed");
   b->arena = a;
@@ -1437,23 +1441,26 @@ pg_status pg_batch_create(int64_t max_vertices, int64_t max_edges,
   if (max_vertices < 1 || max_edges < 1 || max_vertices > kMaxVertices ||
       max_games < 1)
     return pg_fail(PG_EINVAL, "bad batch capacity");
-  pg_batch *b = new (std::nothrow) pg_batch();
-  if (!b) return pg_fail(PG_ENOMEM, "host allocation failed");
-  if (hipGetDevice(&b->device) != hipSuccess) {
-    delete b;
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess)
     return pg_fail(PG_EDEVICE, "no HIP device");
-  }
-  b->stream = (hipStream_t)hip_stream;
-  b->cap_v = max_vertices;
-  b->cap_e = max_edges;
-  b->max_games = max_games;
-  pg_status st = batch_alloc(b);
-  if (st != PG_OK) {
+  for (bool pooled = arena_pooled(max_vertices, max_edges);; pooled = false) {
+    pg_batch *b = new (std::nothrow) pg_batch();
+    if (!b) return pg_fail(PG_ENOMEM, "host allocation failed");
+    b->device = device;
+    b->stream = (hipStream_t)hip_stream;
+    b->cap_v = max_vertices;
+    b->cap_e = max_edges;
+    b->max_games = max_games;
+    const pg_status st = batch_alloc(b, pooled);
+    if (st == PG_OK) {
+      *out = b;
+      return PG_OK;
+    }
     batch_release(b);
-    return st;
+    if (st != PG_ENOMEM || !pooled) return st;
+    trim_caches();   // (its pool is idle now)
   }
-  *out = b;
-  return PG_OK;
 }
 
 pg_status pg_batch_submit(pg_batch *b, int64_t n, int64_t m,

@@ -749,6 +749,12 @@ constexpr size_t kIdlePoolBytes = size_t(1) << 30;
 constexpr size_t kIdlePoolHost = size_t(1) << 28;
 DevPool *take_pool(int device);             // an idle one, else a new one
 void give_pool(int device, DevPool *pool);  // kept, or cleared and deleted
+// Hands the idle pools and the free blocks of every device's game cache back
+// to the runtime.
+void trim_caches();
+// hipMalloc or hipHostMalloc, a second time without the caches when memory is
+// short: what a freed batch keeps for the next one is nobody's loss.
+hipError_t runtime_alloc(void **p, size_t bytes, bool host);
 // The cache of the calling thread's current device that single games
 // allocate from and return their memory to (see pg_release_cache).
 DevPool *game_cache(int device);
@@ -804,7 +810,7 @@ template <typename T>
 pg_status dev_alloc(T **p, int64_t count) {
   size_t bytes = sizeof(T) * (size_t)(count > 0 ? count : 1);
   if (tl_pool) return tl_pool->alloc((void **)p, bytes, false);
-  hipError_t e = hipMalloc((void **)p, bytes);
+  hipError_t e = runtime_alloc((void **)p, bytes, false);
   if (e != hipSuccess) {
     *p = nullptr;
     return pg_fail(PG_ENOMEM, "hipMalloc of " + std::to_string(bytes) +

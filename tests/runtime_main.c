@@ -14,6 +14,13 @@
  *     prints "pairs status bytes" twice, the bytes held on the device with
  *     the cache given back.
  *
+ * runtime_main idle GAME
+ *     a batch leaves its memory for the next one; prints "idle status" of a
+ *     load that finds no other memory.
+ * runtime_main exact
+ *     an arena just past powers of two that are not to be had; prints
+ *     "exact status".
+ *
  * GAME (little endian): int64 n, int64 m, int64 offsets[n+1], int32
  * targets[m], uint8 owner[n], int32 pri[n].
  */
@@ -32,14 +39,15 @@
 static int refuse;
 static struct { void *p; size_t bytes; } blocks[MOST_BLOCKS];
 static int n_blocks;
-static size_t held;   /* device bytes */
+static size_t held, most = (size_t)-1;   /* device bytes */
 
 int hipMalloc(void **p, size_t bytes)
 {
     static int (*next)(void **, size_t);
     if (!next)
         next = (int (*)(void **, size_t))dlsym(RTLD_NEXT, "hipMalloc");
-    if (refuse || n_blocks == MOST_BLOCKS) return HIP_OUT_OF_MEMORY;
+    if (refuse || n_blocks == MOST_BLOCKS || held + bytes > most)
+        return HIP_OUT_OF_MEMORY;
     int rc = next(p, bytes);
     if (rc == 0) {
         blocks[n_blocks].p = *p;
@@ -148,10 +156,37 @@ static int pairs(const char *path)
     return 0;
 }
 
+static int idle(const char *path)
+{
+    game g = read_game(path);
+    pg_game *d = NULL;
+    pg_batch *b = NULL;
+    if (pg_batch_create(1 << 20, 8 << 20, 16, NULL, &b) != PG_OK) return 2;
+    pg_batch_free(b);
+    most = held;
+    printf("idle %d\n", (int)load(&g, &d));
+    return 0;
+}
+
+static int exact(void)
+{
+    const int64_t v = (1 << 21) + 1, e = (1 << 23) + 1;
+    pg_batch *b = NULL;
+    if (pg_batch_create(v, e, 16, NULL, &b) != PG_OK) return 2;
+    const size_t all = held;
+    pg_batch_free(b);
+    pg_release_cache();
+    most = held + (all - held) / 4 * 3;
+    printf("exact %d\n", (int)pg_batch_create(v, e, 16, NULL, &b));
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc == 3 && !strcmp(argv[1], "deep")) return deep(argv[2]);
     if (argc == 3 && !strcmp(argv[1], "pairs")) return pairs(argv[2]);
+    if (argc == 3 && !strcmp(argv[1], "idle")) return idle(argv[2]);
+    if (argc == 2 && !strcmp(argv[1], "exact")) return exact();
     fprintf(stderr, "usage: runtime_main MODE [GAME]\n");
     return 64;
 }

@@ -85,3 +85,11 @@ def test_a_refused_run_keeps_no_scratch(run, tmp_path):
     assert int(refused[0]) == pg.PG_EINADMISSIBLE
     assert int(fine[0]) == pg.PG_OK
     assert int(refused[1]) == int(fine[1])
+
+
+def test_memory_kept_for_the_next_batch_is_given_up(run, tmp_path):
+    """What a freed batch left for the next one goes back when a load finds
+    no other memory; an arena that fits only in its exact size is made so."""
+    g = synth.random_game(200000, 2, 5, 3)
+    assert int(run("idle", _write(tmp_path / "g", g))[0][0]) == pg.PG_OK
+    assert int(run("exact")[0][0]) == pg.PG_OK
