@@ -1802,9 +1802,10 @@ pg_status pg_batch_poll_many(pg_batch *b, int32_t count,
   if (one) {
     const unsigned gx =
         std::min<unsigned>(64, grid_for((most + 15) / 16, 4 * kBlock));
-    hipLaunchKernelGGL(k_copy_many, dim3(gx, (unsigned)items.size()),
-                       dim3(kBlock), 0, s, list.p);
-    PG_HIP(hipGetLastError());
+    void *args[] = {&list.p};
+    PG_HIP(hipLaunchKernel(reinterpret_cast<const void *>(k_copy_many),
+                           dim3(gx, (unsigned)items.size()), dim3(kBlock),
+                           args, 0, s));
   } else {
     for (const CopyItem &c : items)
       PG_TRY(copy_out(c.dst, c.src, (size_t)c.bytes, dev, s));

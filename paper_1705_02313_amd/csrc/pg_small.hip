@@ -830,9 +830,11 @@ pg_status small_load(pg_game *g, int64_t n, int64_t m, const void *offsets,
   L.sp = g->sp;
   L.ctr = host_pinned(g->hctr) ? g->hctr : g->ctr;
   auto a = [](size_t b) { return (b + 15) & ~size_t(15); };
-  hipLaunchKernelGGL(k_small_load, dim3(1), dim3(kSmallThreads),
-                     2 * a(2 * n) + 2 * a(n) + 8 * (size_t)L.sort_n, s, L);
-  PG_HIP(hipGetLastError());
+  // (the launch's own status: the thread's last error may be another call's)
+  void *args[] = {&L};
+  PG_HIP(hipLaunchKernel(reinterpret_cast<const void *>(k_small_load), dim3(1),
+                         dim3(kSmallThreads), args,
+                         2 * a(2 * n) + 2 * a(n) + 8 * (size_t)L.sort_n, s));
   if (!host_pinned(g->hctr)) publish(g->hctr, g->ctr, L_END, s);
   PG_HIP(hipStreamSynchronize(s));
   if (!g->hctr[L_STATE]) return PG_OK;

@@ -21,6 +21,10 @@
  *     an arena just past powers of two that are not to be had; prints
  *     "exact status".
  *
+ * runtime_main stale GAME
+ *     calls after another HIP call of the thread failed and left its error
+ *     behind; prints "stale status" of a load and of a poll of two games.
+ *
  * GAME (little endian): int64 n, int64 m, int64 offsets[n+1], int32
  * targets[m], uint8 owner[n], int32 pri[n].
  */
@@ -33,6 +37,8 @@
 #include "../include/pg.h"
 
 #define HIP_OUT_OF_MEMORY 2
+
+int hipSetDevice(int device);
 
 #define MOST_BLOCKS 65536
 
@@ -181,12 +187,37 @@ static int exact(void)
     return 0;
 }
 
+static int stale(const char *path)
+{
+    game g = read_game(path);
+    pg_game *d = NULL;
+    pg_batch *b = NULL;
+    int64_t t[2];
+    int32_t done[2] = {0, 0};
+    uint8_t *w[2];
+    if (pg_batch_create(1 << 18, 1 << 20, 16, NULL, &b) != PG_OK) return 2;
+    for (int k = 0; k < 2; ++k)
+        if (pg_batch_submit(b, g.n, g.m, g.off, g.tgt, g.owner, g.pri, 0,
+                            &t[k]) != PG_OK ||
+            hipHostMalloc((void **)&w[k], (size_t)g.n, 0) != 0)
+            return 2;
+    for (int32_t live = 1, queued = 1; live + queued > 0;)
+        if (pg_batch_step(b, &live, &queued, NULL) != PG_OK) return 2;
+    if (hipSetDevice(1000) == 0) return 2;
+    printf("stale %d\n", (int)load(&g, &d));
+    if (hipSetDevice(1000) == 0) return 2;
+    printf("stale %d\n", (int)pg_batch_poll_many(b, 2, t, done, w, NULL, NULL,
+                                                 NULL, 0));
+    return !(done[0] && done[1]);
+}
+
 int main(int argc, char **argv)
 {
     if (argc == 3 && !strcmp(argv[1], "deep")) return deep(argv[2]);
     if (argc == 3 && !strcmp(argv[1], "pairs")) return pairs(argv[2]);
     if (argc == 3 && !strcmp(argv[1], "idle")) return idle(argv[2]);
     if (argc == 2 && !strcmp(argv[1], "exact")) return exact();
+    if (argc == 3 && !strcmp(argv[1], "stale")) return stale(argv[2]);
     fprintf(stderr, "usage: runtime_main MODE [GAME]\n");
     return 64;
 }

@@ -93,3 +93,11 @@ def test_memory_kept_for_the_next_batch_is_given_up(run, tmp_path):
     g = synth.random_game(200000, 2, 5, 3)
     assert int(run("idle", _write(tmp_path / "g", g))[0][0]) == pg.PG_OK
     assert int(run("exact")[0][0]) == pg.PG_OK
+
+
+def test_errors_of_other_calls_are_not_taken_over(run, tmp_path):
+    """The error that a HIP call of the program left behind is not this
+    library's: a small load and a poll of several games go through."""
+    g = synth.random_game(1000, 2, 5, 3)
+    got = run("stale", _write(tmp_path / "g", g))
+    assert [int(x[0]) for x in got] == [pg.PG_OK, pg.PG_OK]
