@@ -813,6 +813,17 @@ bool host_pinned(const void *p) {
            q < tl_pool->bump_host + tl_pool->bump_hcap);
 }
 
+bool on_device(const void *p, size_t bytes, int device) {
+  hipPointerAttribute_t a{}, z{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+      hipPointerGetAttributes(&z, (const char *)p + bytes - 1) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && z.type == hipMemoryTypeDevice &&
+         a.device == device && z.device == device;
+}
+
 float clock_ms(pg_game *g, int32_t begin, int32_t end) {
   if (!g->timed) return 0.0f;
   if (g->clock_khz == 0 &&
@@ -1503,7 +1514,7 @@ constexpr uint32_t kGeneralFlags =
 constexpr uint32_t kGeneralLoad =
     kGeneralFlags | PG_ODD_REGION | PG_COUNT_VALUATION;
 
-// The small-game load: host arrays are copied to the device first.
+// The small-game load: what its kernel cannot read in place is copied first.
 pg_status load_small(int64_t n, int64_t m, const void *offsets,
                      const int32_t *targets, const uint8_t *owner,
                      const int32_t *priority, uint32_t flags, hipStream_t s,
@@ -1521,21 +1532,28 @@ pg_status load_small(int64_t n, int64_t m, const void *offsets,
       for (void *x : p) dev_free(x);
     }
   } tmp{s, {}};
-  if (!(flags & PG_PTR_DEVICE)) {
-    const size_t ob = (flags & PG_OFFSETS_I32) ? 4 : 8;
-    auto stage = [&](const void *src, size_t bytes, const void **out) {
-      uint8_t *d = nullptr;
-      PG_TRY(dev_alloc(&d, (int64_t)bytes));
-      tmp.p.push_back(d);
-      *out = d;
-      return copy_in(d, src, bytes, false, s);
-    };
-    PG_TRY(stage(offsets, ob * (n + 1), &offsets));
-    PG_TRY(stage(targets, 4 * m, (const void **)&targets));
-    PG_TRY(stage(owner, n, (const void **)&owner));
-    PG_TRY(stage(priority, 4 * n, (const void **)&priority));
-  }
-  return small_load(g, n, m, offsets, targets, owner, priority, flags, s,
+  const bool dev = flags & PG_PTR_DEVICE;
+  const size_t ob = (flags & PG_OFFSETS_I32) ? 4 : 8;
+  // the kernel reads memory of its own device, elements on their boundaries;
+  // a copy takes whatever else the caller may hand in
+  auto stage = [&](const void **src, size_t size, int64_t count) {
+    if (dev && (uintptr_t)*src % size == 0 &&
+        on_device(*src, size * (size_t)count, g->device))
+      return PG_OK;
+    uint8_t *d = nullptr;
+    PG_TRY(dev_alloc(&d, (int64_t)size * count));
+    tmp.p.push_back(d);
+    const void *from = *src;
+    *src = d;
+    return copy_in(d, from, size * (size_t)count, dev, s);
+  };
+  const void *in[] = {offsets, targets, owner, priority};
+  PG_TRY(stage(&in[0], ob, n + 1));
+  PG_TRY(stage(&in[1], 4, m));
+  PG_TRY(stage(&in[2], 1, n));
+  PG_TRY(stage(&in[3], 4, n));
+  return small_load(g, n, m, in[0], (const int32_t *)in[1],
+                    (const uint8_t *)in[2], (const int32_t *)in[3], flags, s,
                     done);
 }
 

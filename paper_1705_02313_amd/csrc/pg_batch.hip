@@ -1794,7 +1794,9 @@ pg_status pg_batch_poll_many(pg_batch *b, int32_t count,
                  PG_OK;
   for (size_t k = 0; one && k < items.size(); ++k) {
     list.p[k] = items[k];
-    if (!dev) {
+    if (dev) {
+      one = on_device(items[k].dst, (size_t)items[k].bytes, b->device);
+    } else {
       list.p[k].dst = device_view(items[k].dst, (size_t)items[k].bytes);
       one = list.p[k].dst != nullptr;
     }

@@ -771,6 +771,9 @@ pg_status host_alloc(void **p, size_t bytes);
 // Whether host_alloc's memory p is pinned and so has the same address on the
 // device: all of it but the static host words of pg_solve_noalloc.
 bool host_pinned(const void *p);
+// Whether [p, p + bytes) is memory of that device, which its kernels may use
+// without peer access.
+bool on_device(const void *p, size_t bytes, int device);
 // the time between two clock32 values, for a game that is timed
 float clock_ms(pg_game *g, int32_t begin, int32_t end);
 // n ints of device memory to host_alloc's memory, there after the stream's
