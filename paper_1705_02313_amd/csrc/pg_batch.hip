@@ -228,35 +228,37 @@ __global__ __launch_bounds__(kBlock) void k_batch_switch(
     int32_t *cnt, int32_t *ctr) {
   if (ctr[C_ABORT]) return;
   __shared__ int32_t tied[kBlock], s_n;
+  __shared__ WideLds<kBlock> W;
   if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool sw = false, tie = false;
+  bool sw = false, tie = false, live = false, stop = false;
   int s = 0;
-  int32_t v = 0, to = 0;
+  int32_t v = 0, to = 0, cur = 0;
   if (t < count) {
     v = ids[t];
     s = gid[v];
     const int2 me = sp[v];
+    cur = me.x;
     // a vertex known to stay top keeps its choice
-    if (on[s] && me.y != kTopMark)
-      sw = coarse_row(P, v, me.x, odd, &to, &tie);
+    live = on[s] && me.y != kTopMark;
   }
+  if (wide_rows(P, live, v, odd, sp, W, &sw, &to, &stop)) live = false;
+  if (live) sw = coarse_row(P, v, cur, odd, &to, &tie);
   sw = sw && !tie;
   if (sw) sp[v] = make_int2(to, to == P.N ? 2147483647 : P.pri[to]);
   count_game(cnt, s, sw);
   if (tie) tied[atomicAdd(&s_n, 1)] = v;
+  // (the coarse walks bound every chain: no climb stops)
+  if (stop) atomicOr(&ctr[C_ERR], ERR_LISTWALK);
   __syncthreads();
   if ((int)(threadIdx.x & ~(kWave - 1)) >= s_n) return;   // whole waves
-  sw = false;
+  sw = stop = false;
   s = 0;
   if ((int)threadIdx.x < s_n) {
-    bool stop = false;
     v = tied[threadIdx.x];
     s = gid[v];
     sw = coarse_exact(P, v, sp[v].x, odd, &to, &stop);
     if (sw) sp[v] = make_int2(to, to == P.N ? 2147483647 : P.pri[to]);
-    // (the coarse walks bound every chain: no climb stops)
     if (stop) atomicOr(&ctr[C_ERR], ERR_LISTWALK);
   }
   count_game(cnt, s, sw);

@@ -59,6 +59,7 @@ enum IncCounter : int {
   // block form only
   I_STATE = 5, I_NVAL = 6, I_ODDSW = 7, I_EVENSW = 8, I_MAJOR = 9,
   I_INNER = 10, I_A0 = 11, I_CUR = 12, I_EPOCH = 13,
+  I_NWIDE = 14,   // candidates with wide rows (device form)
   I_OPEN = 16,    // passes after the first: vertices left for them
   I_CLOCK = 32, I_CLOCK_END = 33,   // a step's start and end (clock32)
   I_WORDS = 64,   // the part copied to the host
@@ -67,7 +68,8 @@ enum IncCounter : int {
   I_ALL = 160,    // the part cleared before a step
   I_OFFROW = 160, // the last check of the rows that failed (its number); the
                   // host's copy follows the I_WORDS
-  I_SIZE = 161
+  I_WIDE = 161,   // the game has rows beyond kWideRow entries (its copy next)
+  I_SIZE = 162
 };
 static_assert((int)I_ERR == (int)C_ERR, "the ng walk reports through ctr[0]");
 constexpr int kFindLevels = 512;     // levels of a device form's find
@@ -90,11 +92,29 @@ __global__ __launch_bounds__(kBlock) void k_in_count(
 __global__ __launch_bounds__(kBlock) void k_in_fill(
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
     const uint8_t *__restrict__ owner, uint32_t *cursor, uint32_t *in,
-    int32_t N) {
+    int32_t N, int32_t *any_wide) {
+  __shared__ int32_t wide[kBlock], s_n;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= N) return;
+  const int64_t e0 = v < N ? off[v] : 0, end = v < N ? off[v + 1] : 0;
+  if (end - e0 > kWideRow) wide[atomicAdd(&s_n, 1)] = (int32_t)v;
+  __syncthreads();
+  // wide rows by the whole block (see wide_rows)
+  const int n = s_n;
+  if (n && threadIdx.x == 0) *any_wide = 1;
+  for (int k = 0; k < n; ++k) {
+    const int32_t w = wide[k];
+    const int64_t w0 = off[w], w1 = off[w + 1];
+    if (w1 - w0 <= (int64_t)kWideShare * n) continue;
+    const uint32_t x = (uint32_t)w | ((uint32_t)owner[w] << 31);
+    for (int64_t e = w0 + threadIdx.x; e < w1; e += kBlock)
+      in[atomicAdd(&cursor[tgt[e]], 1u)] = x;
+  }
+  if (v >= N || (end - e0 > kWideRow && end - e0 > (int64_t)kWideShare * n))
+    return;
   const uint32_t x = (uint32_t)v | ((uint32_t)owner[v] << 31);
-  for (int64_t e = off[v], end = off[v + 1]; e < end; e += 4) {
+  for (int64_t e = e0; e < end; e += 4) {
     int32_t t[4];
     uint32_t at[4];
 #pragma unroll
@@ -147,8 +167,10 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_hist(
 __global__ __launch_bounds__(kInPartThreads) void k_in_part(
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
     const uint8_t *__restrict__ owner, int32_t N, int vb, int shift, int nr,
-    const uint32_t *__restrict__ at, uint2 *pairs) {
+    const uint32_t *__restrict__ at, uint2 *pairs, int32_t *any_wide) {
   __shared__ uint32_t c[kInRanges];
+  __shared__ int32_t wide[kInPartThreads], s_n;
+  if (threadIdx.x == 0) s_n = 0;
   for (int k = threadIdx.x; k < nr; k += kInPartThreads)
     c[k] = at[(int64_t)k * gridDim.x + blockIdx.x];
   __syncthreads();
@@ -157,7 +179,16 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_part(
   const uint32_t low = (1u << shift) - 1u;
   for (int64_t v = v0 + threadIdx.x; v < v1; v += kInPartThreads) {
     const uint32_t x = (uint32_t)v | ((uint32_t)owner[v] << 31);
-    for (int64_t e = off[v], end = off[v + 1]; e < end; e += 4) {
+    const int64_t e0 = off[v], end = off[v + 1];
+    if (end - e0 > kWideRow) {
+      *any_wide = 1;
+      const int k = atomicAdd(&s_n, 1);
+      if (k < kInPartThreads) {
+        wide[k] = (int32_t)v;
+        continue;
+      }
+    }
+    for (int64_t e = e0; e < end; e += 4) {
       int32_t t[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) t[j] = e + j < end ? tgt[e + j] : -1;
@@ -166,6 +197,21 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_part(
         if (t[j] >= 0)
           pairs[atomicAdd(&c[t[j] >> shift], 1u)] =
               make_uint2((uint32_t)t[j] & low, x);
+    }
+  }
+  __syncthreads();
+  // wide rows by the whole block, or by a thread each (see wide_rows)
+  const int n = min(s_n, kInPartThreads);
+  for (int k = 0; k < n; ++k) {
+    const int32_t w = wide[k];
+    const int64_t e0 = off[w], end = off[w + 1];
+    const bool all = end - e0 > (int64_t)kWideShare * n;
+    if (!all && threadIdx.x != k) continue;
+    const uint32_t x = (uint32_t)w | ((uint32_t)owner[w] << 31);
+    for (int64_t e = e0 + (all ? threadIdx.x : 0); e < end;
+         e += all ? kInPartThreads : 1) {
+      const int32_t t = tgt[e];
+      pairs[atomicAdd(&c[t >> shift], 1u)] = make_uint2((uint32_t)t & low, x);
     }
   }
 }
@@ -230,6 +276,8 @@ struct IncP {
   int32_t cl_cap;
   int32_t *q;              // the find's queue (kFindChunk-int chunks, -1)
   int32_t q_cap;           // chunks
+  bool wide;               // the game has rows beyond kWideRow entries
+  int32_t *wl;             // the candidates that have them
   // count valuations (kernels with D > 0)
   int32_t *cnt;
   const uint8_t *pidx;
@@ -263,6 +311,17 @@ __device__ __forceinline__ bool rule(const IncP &P, int32_t v, bool odd,
                : cnt_decide_even<D>(P.N, P.off, P.tgt, P.cnt, P.odd_cols, v,
                                     me, to);
   }
+}
+
+// wide_rows for the vertices of the step's candidates (a vertex known to stay
+// top keeps its choice).
+template <int T>
+__device__ __forceinline__ bool inc_wide(const IncP &P, bool live, int32_t v,
+                                         bool odd, WideLds<T> &W, bool *sw,
+                                         int32_t *to, bool *stop,
+                                         unsigned long long most = ~0ull) {
+  return wide_rows<T>(coarse(P), live && P.sp[v].y != kTopMark, v, odd, P.sp,
+                      W, sw, to, stop, most);
 }
 
 // The ng of a vertex of A is open until its walk (count valuations walk
@@ -785,15 +844,47 @@ __global__ __launch_bounds__(kBlock) void k_inc_decide(IncP P, int32_t epoch,
   for (int32_t i0 = blockIdx.x * blockDim.x; i0 < n;
        i0 += gridDim.x * blockDim.x) {
     const int32_t i = i0 + threadIdx.x;
-    bool sw = false;
+    bool sw = false, live = false;
     int32_t v = 0, to = 0;
     if (i < n) {
       v = P.cl[i];
-      if (!odd || atomicExch(&P.cmark[v], epoch) != epoch)
-        sw = rule<D>(P, v, odd != 0, &to, &stop);
+      live = !odd || atomicExch(&P.cmark[v], epoch) != epoch;
     }
+    if constexpr (D == 0) {
+      if (P.wide) {   // wide rows are listed for k_inc_wide
+        const bool wide = live && P.off[v + 1] - P.off[v] > kWideRow;
+        const int32_t at = wave_place(&ic[I_NWIDE], wide);
+        if (wide) P.wl[at] = v;
+        live = live && !wide;
+      }
+    }
+    if (live) sw = rule<D>(P, v, odd != 0, &to, &stop);
     const int32_t p = wave_place(&ic[I_NDEC], sw);
     if (sw) dec[p] = make_int2(v, to);
+  }
+  if (stop) atomicOr(&ic[I_STOP], 1);
+}
+
+// The rule for the candidates with wide rows, a block to each (the blocks of
+// k_inc_decide would hold some of them in a row).
+constexpr int kWideThreads = 1024, kWideBlocks = 512;
+__global__ __launch_bounds__(kWideThreads) void k_inc_wide(IncP P, int odd,
+                                                           int2 *dec,
+                                                           int32_t *ic) {
+  __shared__ WideLds<kWideThreads> W;
+  // (one look for the block: a climb that outlasts its bound raises it)
+  if (__syncthreads_or(threadIdx.x == 0 && ld_relaxed(&ic[I_STOP]))) return;
+  const int32_t n = ic[I_NWIDE];
+  bool stop = false;
+  for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int32_t v = P.wl[i];
+    const int2 me = P.sp[v];
+    int32_t to = 0;
+    if (me.y != kTopMark &&
+        coarse_wide<kWideThreads>(coarse(P), v, me.x, odd != 0, &to, &stop,
+                                  W) &&
+        threadIdx.x == 0)
+      dec[atomicAdd(&ic[I_NDEC], 1)] = make_int2(v, to);
   }
   if (stop) atomicOr(&ic[I_STOP], 1);
 }
@@ -833,12 +924,15 @@ __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
   if (threadIdx.x == 0) n = 0;
   __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool sw = false, stop = false;
+  bool sw = false, stop = false, live = t < count;
   int32_t v = 0, to = 0;
-  if (t < count) {
-    v = ids[t];
-    sw = rule<D>(P, v, false, &to, &stop);
+  if (live) v = ids[t];
+  if constexpr (D == 0) {
+    __shared__ WideLds<even_block(D)> W;
+    if (P.wide && inc_wide(P, live, v, false, W, &sw, &to, &stop))
+      live = false;
   }
+  if (live) sw = rule<D>(P, v, false, &to, &stop);
   const int32_t at = wave_place(&n, sw);
   __syncthreads();
   if (threadIdx.x == 0 && n) base = atomicAdd(&ic[I_NDEC], n);
@@ -852,17 +946,17 @@ __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
 __global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
                                                        int2 *dec) {
   if (ctr[C_ABORT]) return;
+  __shared__ WideLds<kBlock> W;
   const int32_t n = ctr[C_NTIE];
   for (int32_t i0 = blockIdx.x * blockDim.x; i0 < n;
        i0 += gridDim.x * blockDim.x) {
     const int32_t i = i0 + threadIdx.x;
-    bool sw = false, stop = false;
+    bool sw = false, stop = false, live = i < n;
     int32_t v = 0, to = 0;
-    if (i < n) {
-      v = P.cl[i];
-      sw = inc_decide(P, v, true, &to, &stop);
-      if (sw) P.sp[v] = make_int2(to, P.pri[to]);
-    }
+    if (live) v = P.cl[i];
+    if (inc_wide(P, live, v, true, W, &sw, &to, &stop)) live = false;
+    if (live) sw = inc_decide(P, v, true, &to, &stop);
+    if (sw) P.sp[v] = make_int2(to, P.pri[to]);
     // (the walks bound every chain: no climb stops)
     if (stop) atomicOr(&ctr[C_ERR], ERR_LISTWALK);
     list_block(&ctr[C_NDEC], dec, sw, v, to);
@@ -874,7 +968,6 @@ __global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
 // Bound by one read of the rows, before the run's first full valuation
 // (300,000 vertices: 5 us); rows beyond kWideRow entries are read by the
 // whole block, or a hub's would keep one thread.
-constexpr int kWideRow = 128;
 __global__ __launch_bounds__(kBlock) void k_inc_rows_hold(IncP P,
                                                           int32_t check,
                                                           int32_t *word,
@@ -928,6 +1021,9 @@ __global__ __launch_bounds__(kBlock) void k_inc_commit(
 // chains (the depth of A, the ng chains), not by their size.
 constexpr int32_t kBlockA = 4096;  // most vertices of its A (LDS)
 constexpr int kBlockEven = 8192;   // most changed vertices of its All_Even
+constexpr int kBlockWide = 8192;   // most entries of wide rows among 1,024
+                                   // candidates: one CU reads them in some
+                                   // 10 us, the device form the rest
 enum IncState : int {
   IS_GROWN = 0,    // the pending decisions need the device form (or full)
   IS_BR = 1,       // best response reached; All_Even is the host's
@@ -957,6 +1053,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
   __shared__ int32_t la[kBlockA];   // A
   __shared__ uint2 lr[kBlockA];     // its in-edge ranges
   __shared__ int32_t s_na, s_nc, s_nd, s_stop, s_open, s_err;
+  __shared__ WideLds<D == 0 ? T : kWave> W;
   const int tid = threadIdx.x;
   int32_t nval = 0, oddsw = 0, evensw = 0, state = IS_GROWN;
   if (tid == 0) {
@@ -1062,13 +1159,17 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
     if (bad) break;
     for (int32_t i0 = 0; i0 < nc; i0 += T) {
       const int32_t i = i0 + tid;
-      bool sw = false, stop = false;
+      bool sw = false, stop = false, live = false;
       int32_t v = 0, to = 0;
       if (i < nc) {
         v = P.cl[i];
-        if (atomicExch(&P.cmark[v], epoch) != epoch)
-          sw = rule<D>(P, v, true, &to, &stop);
+        live = atomicExch(&P.cmark[v], epoch) != epoch;
       }
+      if constexpr (D == 0)
+        if (P.wide &&
+            inc_wide(P, live, v, true, W, &sw, &to, &stop, kBlockWide))
+          live = false;
+      if (live) sw = rule<D>(P, v, true, &to, &stop);
       if (stop) s_stop = 1;
       const int32_t p = wave_place(&s_nd, sw);
       if (sw) dout[p] = make_int2(v, to);
@@ -1121,12 +1222,14 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
     const int32_t ne = s_nc;
     for (int32_t i0 = 0; i0 < ne; i0 += T) {
       const int32_t i = i0 + tid;
-      bool sw = false, stop = false;
+      bool sw = false, stop = false, live = i < ne;
       int32_t v = 0, to = 0;
-      if (i < ne) {
-        v = P.cl[i];
-        sw = rule<D>(P, v, false, &to, &stop);
-      }
+      if (live) v = P.cl[i];
+      if constexpr (D == 0)
+        if (P.wide &&
+            inc_wide(P, live, v, false, W, &sw, &to, &stop, kBlockWide))
+          live = false;
+      if (live) sw = rule<D>(P, v, false, &to, &stop);
       if (stop) s_stop = 1;
       const int32_t p = wave_place(&s_nd, sw);
       if (sw) eout[p] = make_int2(v, to);
@@ -1211,6 +1314,8 @@ static IncP inc_params(const pg_game *g) {
   P.cl_cap = 2 * N;
   P.q = reinterpret_cast<int32_t *>(g->sk0);
   P.q_cap = N / kFindChunk;
+  P.wide = g->inc.h && g->inc.h[I_WORDS + 1];
+  P.wl = g->rcand;   // (between full valuations)
   return P;
 }
 
@@ -1248,7 +1353,7 @@ static void in_lists(pg_game *g, hipStream_t s) {
       scan_excl_u32(hist, at, (int64_t)nr * nb, g->scan_tmp, s);
       hipLaunchKernelGGL(k_in_part, dim3(nb), dim3(kInPartThreads), 0, s,
                          g->off, g->tgt, g->owner, (int32_t)N, vb, shift, nr,
-                         at, pairs);
+                         at, pairs, x.ic + I_WIDE);
       hipLaunchKernelGGL(k_in_range, dim3(nr), dim3(kInPartThreads),
                          sizeof(uint32_t) << shift, s, pairs, at, nb,
                          (uint32_t)M, (int32_t)N, shift, x.in_off, x.in);
@@ -1266,7 +1371,8 @@ static void in_lists(pg_game *g, hipStream_t s) {
   hipLaunchKernelGGL(k_copy_u32, dim3(grid_for(N)), dim3(kBlock), 0, s,
                      x.in_off, cursor, N);
   hipLaunchKernelGGL(k_in_fill, dim3(grid_for(N)), dim3(kBlock), 0, s,
-                     g->off, g->tgt, g->owner, cursor, x.in, (int32_t)N);
+                     g->off, g->tgt, g->owner, cursor, x.in, (int32_t)N,
+                     x.ic + I_WIDE);
 }
 
 // Builds the in-edge lists at the first solve of a game.  Without memory
@@ -1287,17 +1393,18 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     if (st == PG_OK) st = dev_alloc(&x.cmark, N);
     if (st == PG_OK) st = dev_alloc(&x.ic, I_SIZE);
     if (st == PG_OK)
-      st = host_alloc((void **)&x.h, sizeof(int32_t) * (I_WORDS + 1));
+      st = host_alloc((void **)&x.h, sizeof(int32_t) * (I_WORDS + 2));
     if (st != PG_OK) {
       inc_release(g);
       x.state = -1;
       pg_fail(PG_OK, "");
       return false;
     }
+    fill_i32(x.ic, 0, I_SIZE, s);
     in_lists(g, s);
+    publish(x.h + I_WORDS + 1, x.ic + I_WIDE, 1, s);
     fill_i32(x.mark, 0, N, s);
     fill_i32(x.cmark, 0, N, s);
-    fill_i32(x.ic, 0, I_SIZE, s);
     x.epoch = x.check = 0;
     x.state = 1;
   } else if (x.epoch >= kEpochMax) {
@@ -1490,8 +1597,11 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
       PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_rows<D>, grid, blk, 0, s, P, epoch,
                 x.a0, 1024, 1, 1, x.ic);
     }
-    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide<D>, grid, blk, 0, s, P, epoch, 1,
-              inc_dec(g, x.cur ^ 1), x.ic);
+    PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide<D>, grid, blk, 0, s, P,
+              epoch, 1, inc_dec(g, x.cur ^ 1), x.ic);
+    if (D == 0 && P.wide)
+      PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_wide, dim3(kWideBlocks),
+                dim3(kWideThreads), 0, s, P, 1, inc_dec(g, x.cur ^ 1), x.ic);
   }
   const pg_status st = inc_read(g, s, block && host_pinned(x.h));
   // a refused run's epochs are used all the same: its marks stay
@@ -1559,6 +1669,9 @@ static pg_status inc_even_t(pg_game *g, hipStream_t s, int32_t *count) {
               P, ++x.epoch, x.a0, x.ic);
     PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_decide<D>, grid, dim3(kBlock), 0, s,
               P, x.epoch, 0, inc_dec(g, 0), x.ic);
+    if (D == 0 && P.wide)
+      PG_LAUNCH(pf, K_INC_DECIDE, 0.0, k_inc_wide, dim3(kWideBlocks),
+                dim3(kWideThreads), 0, s, P, 0, inc_dec(g, 0), x.ic);
     PG_TRY(inc_read(g, s));
   }
   for (int pass = 0; x.h[I_STOP]; ++pass) {
