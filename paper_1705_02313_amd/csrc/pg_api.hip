@@ -158,23 +158,37 @@ __global__ void k_x_round(const int64_t *__restrict__ off,
 // synchronisations less the load's part up to the dummies went from 3.3 to
 // 2.0 ms).  A wave owns the word of its 64 vertices.  A bit read too early
 // (another XCD's change of the same sweep) is read again by the next sweep,
-// which runs because that change raised the flag.
+// which runs because that change raised the flag.  X only shrinks, so the
+// entries before a lost witness stay out of it: a row beyond kWitRow entries
+// goes on from there (pos), a shorter one costs less to read again than to
+// keep the place for (8 rows of 8,000 entries that lose a witness each sweep:
+// the load 2.9 s from the front, 53 ms so).
+constexpr int64_t kWitRow = 128;
 __device__ __forceinline__ bool bit_of(const uint64_t *bits, int32_t v) {
   return (bits[v >> 6] >> (v & 63)) & 1ull;
 }
 
+// a place in a row as pos holds it (beyond 32 bits: from the front again)
+__device__ __forceinline__ uint32_t xb_place(int64_t e) {
+  return e <= 0xffffffffLL ? (uint32_t)e : 0u;
+}
+
 __global__ __launch_bounds__(kBlock) void k_xb_first(
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
-    const uint8_t *__restrict__ owner, int64_t n, int32_t *wit,
+    const uint8_t *__restrict__ owner, int64_t n, int32_t *wit, uint32_t *pos,
     uint64_t *bits) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int32_t w = -1;
-  if (v < n && owner[v] == 1)
-    for (int64_t e = off[v], end = off[v + 1]; e < end; ++e)
+  if (v < n && owner[v] == 1) {
+    const int64_t e0 = off[v], end = off[v + 1];
+    int64_t e = e0;
+    for (; e < end; ++e)
       if (owner[tgt[e]] == 1) {
         w = tgt[e];
         break;
       }
+    if (end - e0 > kWitRow) pos[v] = xb_place(e - e0);
+  }
   if (v < n) wit[v] = w;
   const uint64_t b = __ballot(w >= 0);
   if ((threadIdx.x & (kWave - 1)) == 0 && v < n) bits[v >> 6] = b;
@@ -183,20 +197,25 @@ __global__ __launch_bounds__(kBlock) void k_xb_first(
 // before: the flag of the sweep before (null for a group's first)
 __global__ __launch_bounds__(kBlock) void k_xb_sweep(
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
-    int64_t n, int32_t *wit, uint64_t *bits, const int32_t *before,
-    int32_t *changed) {
-  if (before && !*before) return;
+    int64_t n, int32_t *wit, uint32_t *pos, uint64_t *bits,
+    const int32_t *before, int32_t *changed) {
+  // (the flag and the witness in one round trip)
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t w = v < n ? wit[v] : -1;
+  if (before && !*before) return;
   bool drop = false;
   if (v < n) {
-    const int32_t w = wit[v];
     if (w >= 0 && !bit_of(bits, w)) {
       int32_t nw = -1;
-      for (int64_t e = off[v], end = off[v + 1]; e < end; ++e)
+      const int64_t e0 = off[v], end = off[v + 1];
+      const bool keep = end - e0 > kWitRow;
+      int64_t e = keep ? e0 + pos[v] : e0;
+      for (; e < end; ++e)
         if (bit_of(bits, tgt[e])) {
           nw = tgt[e];
           break;
         }
+      if (keep) pos[v] = xb_place(e - e0);
       wit[v] = nw;
       drop = nw < 0;
     }
@@ -1070,9 +1089,11 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
   if (!(flags & PG_NO_PREPROCESS)) {
     const int64_t nw = (n + 63) / 64;
     int32_t *wit = nullptr;
-    uint32_t *cnt = nullptr;
+    uint32_t *cnt = nullptr, *pos = nullptr;
     PG_TRY(dev_alloc(&wit, n));
     tmp.p.push_back(wit);
+    PG_TRY(dev_alloc(&pos, n));
+    tmp.p.push_back(pos);
     PG_TRY(dev_alloc(&xb, nw));
     tmp.p.push_back(xb);
     PG_TRY(dev_alloc(&xp, nw));
@@ -1086,7 +1107,7 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
     PG_TRY(dev_alloc((uint8_t **)&stmp, (int64_t)need + 16));
     tmp.p.push_back(stmp);
     hipLaunchKernelGGL(k_xb_first, dim3(grid_for(n)), dim3(kBlock), 0, s,
-                       off_in, tgt_in, own_in, n, wit, xb);
+                       off_in, tgt_in, own_in, n, wit, pos, xb);
     const bool region = flags & PG_ODD_REGION;
     uint8_t *mark = nullptr;
     PG_TRY(dev_alloc(&mark, n));
@@ -1104,18 +1125,19 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
     };
     // groups of sweeps with one synchronisation each, the first one's with
     // X' as if it had found X (random games below 1M vertices take 6 to 8
-    // sweeps, 10M vertices 15, the 2M chain 40)
-    const int group = n < 1000000 ? kXGroup / 2 : kXGroup;
+    // sweeps, 10M vertices 15, the 2M chain 40); past the first, long ones:
+    // a long Odd line leaves X vertex by vertex
+    int group = n < 1000000 ? kXGroup / 2 : kXGroup;
     int64_t round = 0;
-    for (;; round += group) {
+    for (;; round += group, group = kXGroup) {
       if (round > n + kXGroup)
         return pg_fail(PG_EINTERNAL, "preprocessing did not converge");
       int32_t *ch = g->ctr + C_XN;
       if (round > 0) fill_i32(ch, 0, kXGroup, s);
       for (int k = 0; k < group; ++k)
         hipLaunchKernelGGL(k_xb_sweep, dim3(grid_for(n)), dim3(kBlock), 0, s,
-                           off_in, tgt_in, n, wit, xb, k ? ch + k - 1 : nullptr,
-                           ch + k);
+                           off_in, tgt_in, n, wit, pos, xb,
+                           k ? ch + k - 1 : nullptr, ch + k);
       if (round == 0 && !region) find_xp();
       publish(g->hctr, g->ctr, C_DIST_SW, s);
       PG_HIP(hipStreamSynchronize(s));

@@ -597,14 +597,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_load(SmallLoad L) {
   (void)block_excl(nodd, part, &no);
   if (L.preprocess) {
     // X: members without a successor in X leave until nobody does (in
-    // place: any order ends at the same set)
+    // place: any order ends at the same set).  A row is read on from the
+    // entry last seen in X (X only shrinks); did holds the places meanwhile.
+    for (int32_t v = tid; v < n; v += kSmallThreads) did[v] = 0;
     for (;;) {
       int drop = 0;
       for (int32_t v = tid; v < n; v += kSmallThreads) {
         if (!inx[v]) continue;
         bool any = false;
-        for (int64_t e = row(v), e1 = row(v + 1); e < e1 && !any; ++e)
-          any = *(volatile uint8_t *)&inx[L.tgt[e]] != 0;
+        const int64_t e0 = row(v), e1 = row(v + 1);
+        int64_t e = e0 + did[v];
+        for (; e < e1; ++e)
+          if (*(volatile uint8_t *)&inx[L.tgt[e]]) {
+            any = true;
+            break;
+          }
+        if (any) did[v] = (uint16_t)(e - e0);   // (rows: below 65,536 entries)
         if (!any) {
           inx[v] = 0;
           drop = 1;
