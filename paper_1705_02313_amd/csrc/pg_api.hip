@@ -1465,7 +1465,7 @@ pg_status run_loop(pg_game *g, Run *r, hipStream_t s) {
         if (coarse) {
           PG_TRY(iteration_coarse(g, s, &c, &done));
           if (!done) {   // chains too long: ranks for a while
-            inc_backoff(g);
+            inc_use_ranks(g);
             fates_reset(g, s);
             r->iter_ms += g->last_ms;
           }

@@ -316,6 +316,8 @@ struct pg_game {
     int32_t nsw = 0, a0 = 0;
     int32_t inner = 0, major = 0;   // the run's iteration counts
     int skip = 0, back = 0;         // full valuations to take after a give-up
+    int ranks = 0, ranks_back = 0;  // ranked ones after one on coarse keys
+                                    // that its chains outlasted
   } inc;
 
   unsigned long long *u64tmp = nullptr;  // [2] scratch for 64-bit sums
@@ -618,7 +620,7 @@ void inc_after_full(pg_game *g, hipStream_t s, int32_t switches, bool exact);
 void inc_check_rows(pg_game *g, hipStream_t s);
 // a full valuation may use coarse keys / did not fit them
 bool inc_coarse(const pg_game *g);
-void inc_backoff(pg_game *g);
+void inc_use_ranks(pg_game *g);
 // All_Odd's vertices left open by the coarse keys (after a coarse valuation)
 void enqueue_ties(pg_game *g, hipStream_t s);
 // room for the vertices left open (n_odd entries at most)

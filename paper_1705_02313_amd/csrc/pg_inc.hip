@@ -1382,7 +1382,7 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
   x.dirty = x.pending = x.d_valid = x.grown = x.even = x.exact = false;
   x.queue = x.offrow = false;
   x.nsw = x.a0 = 0;
-  x.skip = x.back = 0;
+  x.skip = x.back = x.ranks = x.ranks_back = 0;
   x.on = false;
   if (x.state < 0 || !inc_eligible(g)) return false;
   const int64_t N = g->n_aug, M = g->m_aug;
@@ -1484,7 +1484,7 @@ bool inc_ready(const pg_game *g) {
 
 // Coarse keys serve the rank games of a run until something outgrows them.
 bool inc_coarse(const pg_game *g) {
-  return g->inc.on && !g->dense && g->inc.skip == 0;
+  return g->inc.on && !g->dense && g->inc.ranks == 0;
 }
 
 int32_t *tie_list(const pg_game *g) {
@@ -1504,8 +1504,9 @@ void inc_before_full(pg_game *g, hipStream_t s, bool coarse) {
   inc_commit(g, s);
   if (!coarse) {
     if (x.dirty || x.even) fates_reset(g, s);
-    if (x.skip > 0) --x.skip;
+    if (x.ranks > 0) --x.ranks;
   }
+  if (x.skip > 0) --x.skip;
   x.even = false;
 }
 
@@ -1515,6 +1516,7 @@ void inc_after_full(pg_game *g, hipStream_t s, int32_t switches, bool exact) {
   x.dirty = !exact;
   x.exact = exact && !g->dense;
   if (exact) x.queue = false;
+  else x.ranks_back = 0;
   x.d_valid = false;
   x.a0 = 0;
   x.grown = false;
@@ -1529,11 +1531,19 @@ void inc_after_full(pg_game *g, hipStream_t s, int32_t switches, bool exact) {
   }
 }
 
-// A step that gave up: full valuations for a while.
-void inc_backoff(pg_game *g) {
+// A step that gave up: full valuations for a while, on coarse keys all the
+// same (a hub's in-edges stop the find, not the walks).
+static void inc_backoff(pg_game *g) {
   pg_game::Inc &x = g->inc;
   x.back = x.back ? std::min(2 * x.back, 16) : 1;
   x.skip = x.back;
+}
+
+// A coarse valuation whose chains are too long: ranks for a while.
+void inc_use_ranks(pg_game *g) {
+  pg_game::Inc &x = g->inc;
+  x.ranks_back = x.ranks_back ? std::min(2 * x.ranks_back, 16) : 1;
+  x.ranks = x.ranks_back;
 }
 
 // One step (device form) or a run of steps (block form) from the pending

@@ -74,3 +74,18 @@ def test_hubs_within_the_degree_bound(n, hubs, degree, few):
         assert "inc_block" in ran
         if hubs * (degree + 1) >= 4096:
             assert "inc_find" in ran
+
+
+def test_a_hub_beyond_the_degree_bound_costs_no_ranks():
+    """A find that gives up at a hub leaves the full valuations that follow on
+    coarse keys: nothing of the run sorts or ranks."""
+    g = _hubs(20000, 3, 3000, False)
+    ref = orc.solve(g)
+    with Game.from_dict(g) as d:
+        d.profile()
+        out = d.solve()
+        ran = d.profile_read()
+    np.testing.assert_array_equal(to_np(out["sigma"]), ref["sigma"])
+    assert out["stats"]["n_valuations"] == ref["n_valuations"]
+    assert "inc_find" in ran or "inc_block" in ran
+    assert not {"sort_split", "sort_pass", "lr_sum1", "lr_emit1"} & set(ran)
