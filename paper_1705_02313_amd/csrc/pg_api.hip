@@ -1986,7 +1986,7 @@ pg_status pg_valuation(pg_game *g, const int32_t *sigma, const int32_t *tau,
   PoolScope cache(game_cache(g->device));
   hipStream_t s = (hipStream_t)hip_stream;
   const bool dev = flags & PG_PTR_DEVICE;
-  if (g->small) {
+  if (small_due(g)) {
     const int64_t N = g->n_aug;
     const int32_t *ds = sigma, *dt = tau;
     int32_t *dk = key;
@@ -2058,7 +2058,7 @@ pg_status pg_best_response(pg_game *g, const int32_t *sigma, int32_t *tau,
   if (n_valuations) *n_valuations = (int32_t)r.n_val;
   if (st != PG_OK) return st;
   bool deep = true;
-  if (key && !r.keys && g->small) {
+  if (key && !r.keys && small_due(g)) {
     int32_t *dk = dev ? key : (int32_t *)g->elem;
     PG_TRY(small_valuation(g, nullptr, nullptr, dk, s, &deep, nullptr));
     if (!deep && !dev)

@@ -286,8 +286,10 @@ struct pg_game {
   int32_t *vsum[pgk::kMaxLevels] = {};   // per level: dw ints per splitter
   int32_t *vbase[pgk::kMaxLevels] = {};
 
-  // small games run whole in one block (pg_small.hip)
+  // small games run whole in one block (pg_small.hip); valuations whose
+  // chains are too deep for it: as many calls go to the general path at once
   bool small = false;
+  int small_skip = 0, small_back = 0;
 
   // valuations by their changed part (pg_inc.hip)
   struct Inc {
@@ -659,7 +661,9 @@ pg_status small_step(pg_game *g, hipStream_t s, bool br_only, bool reset,
                      int32_t max_inner, int32_t max_major, bool *deep,
                      IncOut *out);
 // pg_valuation on device arrays in the caller's ids (null sigma: of the
-// strategies in g->sp); *deep: nothing written
+// strategies in g->sp); *deep: nothing written.  small_due: whether to try
+// (after one that was too deep the next 1, 2, 4 ... 16 are not).
+bool small_due(pg_game *g);
 pg_status small_valuation(pg_game *g, const int32_t *sigma, const int32_t *tau,
                           int32_t *key, hipStream_t s, bool *deep,
                           int64_t *n_finite);

@@ -24,6 +24,8 @@
 //
 // ng chains longer than kSmallDepth (none of the random or chain workloads
 // comes near) are left to the general path, before anything was switched.
+#include <algorithm>
+
 #include "pg_common.h"
 
 namespace pgk {
@@ -896,6 +898,13 @@ pg_status small_step(pg_game *g, hipStream_t s, bool br_only, bool reset,
   return PG_OK;
 }
 
+bool small_due(pg_game *g) {
+  if (!g->small) return false;
+  if (g->small_skip == 0) return true;
+  --g->small_skip;
+  return false;
+}
+
 pg_status small_valuation(pg_game *g, const int32_t *sigma, const int32_t *tau,
                           int32_t *key, hipStream_t s, bool *deep,
                           int64_t *n_finite) {
@@ -912,6 +921,10 @@ pg_status small_valuation(pg_game *g, const int32_t *sigma, const int32_t *tau,
             dim3(kSmallThreads), value_lds(g->n_aug), s, small_game(g), V);
   PG_TRY(small_read(g, s));
   *deep = g->hctr[S_STATE] == SS_DEEP;
+  g->small_back = !*deep ? 0
+                  : g->small_back ? std::min(2 * g->small_back, 16)
+                                  : 1;
+  g->small_skip = g->small_back;
   if (n_finite) *n_finite = g->hctr[S_NFIN];
   return PG_OK;
 }
