@@ -69,11 +69,16 @@ enum IncCounter : int {
   I_OFFROW = 160, // the last check of the rows that failed (its number); the
                   // host's copy follows the I_WORDS
   I_WIDE = 161,   // the game has rows beyond kWideRow entries (its copy next)
-  I_SIZE = 162
+  I_HUB = 162,    // and vertices of more than kHub in-edges
+  I_SIZE = 163
 };
 static_assert((int)I_ERR == (int)C_ERR, "the ng walk reports through ctr[0]");
 constexpr int kFindLevels = 512;     // levels of a device form's find
 constexpr int kIncMaxDegree = 2048;  // in-edges of one vertex, else give up
+// In-edges beyond which all threads of a block share a vertex's: two lanes
+// to eight took a hub's 2,000 at 1.5 us a round trip, more than a full
+// valuation (1M vertices with 500 such hubs: finds of up to 3.9 ms, 0.23 ms so).
+constexpr uint32_t kHub = 128;
 constexpr int kIncFate = 1024;       // ng steps of one fate
 constexpr int kIncBlocks = 1024;
 constexpr int32_t kEpochMax = 1 << 30;   // the marks are cleared at the start
@@ -128,9 +133,13 @@ __global__ __launch_bounds__(kBlock) void k_in_fill(
   }
 }
 
-__global__ void k_copy_u32(const uint32_t *a, uint32_t *b, int64_t n) {
+// the lists' starts (n + 1) as cursors, and whether one of them is a hub's
+__global__ void k_in_cursors(const uint32_t *a, uint32_t *b, int64_t n,
+                             int32_t *any_hub) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = a[i];
+  if (i >= n) return;
+  b[i] = a[i];
+  if (a[i + 1] - a[i] > kHub) *any_hub = 1;
 }
 
 // Large games: the edges partitioned by ranges of their targets first, then
@@ -235,7 +244,8 @@ __device__ __forceinline__ uint32_t lds_place(uint32_t *c, uint32_t x) {
 // a range's in-edge lists: range blockIdx.x, 1 << shift vertices, nb parts
 __global__ __launch_bounds__(kInPartThreads) void k_in_range(
     const uint2 *__restrict__ pairs, const uint32_t *__restrict__ at, int nb,
-    uint32_t M, int32_t N, int shift, uint32_t *in_off, uint32_t *in) {
+    uint32_t M, int32_t N, int shift, uint32_t *in_off, uint32_t *in,
+    int32_t *any_hub) {
   extern __shared__ uint32_t rc[];   // a counter per vertex
   __shared__ uint32_t s_w[kInPartThreads / kWave];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), R = 1 << shift;
@@ -274,6 +284,7 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_range(
     rc[tid * per + j] = base;
     const int64_t v = (k << shift) + tid * per + j;
     if (v < N) in_off[v] = base;
+    if (c > kHub) *any_hub = 1;
     base += c;
   }
   __syncthreads();
@@ -309,6 +320,7 @@ struct IncP {
   int32_t q_cap;           // chunks
   bool wide;               // the game has rows beyond kWideRow entries
   int32_t *wl;             // the candidates that have them
+  bool hub;                // it has vertices of more than kHub in-edges
   // count valuations (kernels with D > 0)
   int32_t *cnt;
   const uint8_t *pidx;
@@ -566,6 +578,25 @@ __device__ __forceinline__ bool inc_edge(const IncP &P, int32_t epoch,
   return a;
 }
 
+// The same for an in-edge of a hub, whose sources the whole block looks at:
+// the mark's exchange tells one source's edges apart.
+__device__ __forceinline__ bool inc_hub_edge(const IncP &P, int32_t epoch,
+                                             int32_t w, uint32_t x, bool live,
+                                             uint2 *range) {
+  const int32_t u = (int32_t)(x & 0x7fffffffu);
+  bool a = false;
+  *range = make_uint2(0u, 0u);
+  if (live) {
+    const int32_t su = P.sp[u].x;
+    const int32_t mk = ld_relaxed(&P.mark[u]);
+    range->x = P.in_off[u];
+    range->y = P.in_off[u + 1];
+    a = su == w && mk != epoch && atomicExch(&P.mark[u], epoch) != epoch;
+  }
+  if (a) inc_open(P, u);
+  return a;
+}
+
 // Lanes per vertex of a find level of n vertices for T threads: a level is
 // bound by its round trips, so few vertices spread their in-edges over up
 // to 8 lanes.
@@ -601,6 +632,7 @@ __device__ __forceinline__ int find_lanes(int n, int T) {
 // ticket names a place at or past q_cap.
 constexpr int kFindChunk = 64, kFindA = 1024, kFindC = 2048;
 constexpr int kFindKeep = 128, kFindBlocks = 512;
+constexpr int kFindHubs = 2048;   // in-edges of hubs a block keeps to itself
 constexpr int kFindItems = kFindChunk - 1;   // of a queue chunk: word 0 is
                                              // its level, -2 no item
 constexpr int kFindWait = 1 << 20;           // polls, then the step gives up
@@ -631,6 +663,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
   __shared__ int32_t la[kFindA], lc[kFindC];
   __shared__ uint2 lr[kFindA];   // in-edge ranges of la
   __shared__ int32_t s_na, s_nc, s_base, s_q, s_stop, s_t, s_level;
+  __shared__ int32_t lh[kFindKeep], s_nh, s_hd;   // the level's hubs
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int32_t S = (nsw + kFindChunk - 1) / kFindChunk;
@@ -648,6 +681,47 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
       else s_stop = 1;
     }
     __syncthreads();
+  };
+  // a source u joins A (a) with its in-edge range, or is a candidate (c); all
+  // lanes of the wave
+  auto place = [&](bool a, bool c, int32_t u, uint2 range, int level) {
+    const int pc = wave_place(&s_nc, c);
+    if (c && pc < kFindC) lc[pc] = u;
+    const int pa = wave_place(&s_na, a);
+    if (a && pa < kFindA) {
+      la[pa] = u;
+      lr[pa] = range;
+    }
+    // past the LDS lists (rare): to the global ones
+    const bool oc = c && pc >= kFindC, oa = a && pa >= kFindA;
+    if (__ballot(oc)) {
+      const int32_t at = wave_place(&ic[I_NC], oc);
+      if (oc && at < P.cl_cap) P.cl[at] = u;
+      else if (oc) s_stop = 1;
+    }
+    const uint64_t bo = __ballot(oa);
+    if (bo) {   // one or two chunks of the wave's own
+      const int32_t at = wave_place(&ic[I_NA], oa);
+      if (oa && a0 + at >= P.list_cap) s_stop = 1;
+      else if (oa) P.list[a0 + at] = u;
+      const int n = __popcll(bo), nq = (n + kFindItems - 1) / kFindItems;
+      int32_t q0 = 0;
+      if (lane == 0) q0 = atomicAdd(&ic[I_QTAIL], nq);
+      q0 = __shfl(q0, 0);
+      if (q0 + nq > P.q_cap) {
+        if (lane == 0) atomicOr(&ic[I_STOP], 1);
+      } else {
+        int32_t *q = P.q + (int64_t)q0 * kFindChunk;
+        for (int k = 0; k < nq; ++k)
+          if (lane == 0 || k * kFindItems + lane - 1 >= n)
+            st_relaxed(q + k * kFindChunk + lane,
+                       lane == 0 ? level + 1 : -2);
+        const int r = __popcll(bo & ((1ull << lane) - 1ull));
+        if (oa)
+          st_relaxed(q + r / kFindItems * kFindChunk + 1 +
+                         r % kFindItems, u);
+      }
+    }
   };
   for (;;) {
     __syncthreads();
@@ -692,63 +766,76 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
         break;
       }
       const int L = find_lanes(end - beg, kBlock);
+      int hubs = 0;
+      if (P.hub) {
+        if (tid == 0) s_nh = s_hd = 0;
+        __syncthreads();
+        if (tid < end - beg) {
+          const uint32_t d = lr[beg + tid].y - lr[beg + tid].x;
+          if (d > (uint32_t)kIncMaxDegree) {
+            s_stop = 1;
+          } else if (d > kHub) {
+            lh[atomicAdd(&s_nh, 1)] = beg + tid;
+            atomicAdd(&s_hd, (int)d);
+          }
+        }
+        __syncthreads();
+        hubs = s_nh;
+      }
       for (int i0 = beg; i0 < end; i0 += kBlock / L) {
         const int i = i0 + tid / L;
         uint32_t e = 0, e1 = 0;
         int32_t w = -1;
-        if (i < end) {
+        if (i < end && lr[i].y - lr[i].x <= kHub) {
           w = la[i];
           e = lr[i].x + tid % L;
           e1 = lr[i].y;
-          if (e1 > e + (uint32_t)kIncMaxDegree) {
-            s_stop = 1;
-            e1 = 0;
-          }
         }
         for (; __ballot(e < e1); e += L) {
           const bool live = e < e1;
           const uint32_t x = live ? P.in[e] : 0u;
           uint2 range;
           const bool a = inc_edge(P, epoch, w, x, live, L, &range);
-          const bool c = live && (x >> 31);
-          const int32_t u = (int32_t)(x & 0x7fffffffu);
-          const int pc = wave_place(&s_nc, c);
-          if (c && pc < kFindC) lc[pc] = u;
-          const int pa = wave_place(&s_na, a);
-          if (a && pa < kFindA) {
-            la[pa] = u;
-            lr[pa] = range;
+          place(a, live && (x >> 31), (int32_t)(x & 0x7fffffffu), range,
+                level);
+        }
+      }
+      if (hubs > 0 && s_hd > 2 * kFindHubs) {
+        // all but the first kFindHubs in-edges to the queue, as many in a
+        // chunk by the average
+        const int per =
+            min(max((int)((int64_t)kFindHubs * hubs / s_hd), 1), kFindItems);
+        const int nq = (hubs - per + per - 1) / per;
+        __syncthreads();
+        if (tid == 0) {
+          s_q = atomicAdd(&ic[I_QTAIL], nq);
+          if (s_q + nq > P.q_cap) atomicOr(&ic[I_STOP], 1);
+        }
+        __syncthreads();
+        if (s_q + nq > P.q_cap) {
+          s_stop = 1;
+        } else {
+          for (int i = tid; i < nq * kFindChunk; i += kBlock) {
+            const int j = i % kFindChunk;
+            const int h = per + i / kFindChunk * per + j - 1;
+            st_relaxed(P.q + (int64_t)s_q * kFindChunk + i,
+                       j == 0                      ? level
+                       : j <= per && h < hubs ? la[lh[h]]
+                                                   : -2);
           }
-          // past the LDS lists (rare): to the global ones
-          const bool oc = c && pc >= kFindC, oa = a && pa >= kFindA;
-          if (__ballot(oc)) {
-            const int32_t at = wave_place(&ic[I_NC], oc);
-            if (oc && at < P.cl_cap) P.cl[at] = u;
-            else if (oc) s_stop = 1;
-          }
-          const uint64_t bo = __ballot(oa);
-          if (bo) {   // one or two chunks of the wave's own
-            const int32_t at = wave_place(&ic[I_NA], oa);
-            if (oa && a0 + at >= P.list_cap) s_stop = 1;
-            else if (oa) P.list[a0 + at] = u;
-            const int n = __popcll(bo), nq = (n + kFindItems - 1) / kFindItems;
-            int32_t q0 = 0;
-            if (lane == 0) q0 = atomicAdd(&ic[I_QTAIL], nq);
-            q0 = __shfl(q0, 0);
-            if (q0 + nq > P.q_cap) {
-              if (lane == 0) atomicOr(&ic[I_STOP], 1);
-            } else {
-              int32_t *q = P.q + (int64_t)q0 * kFindChunk;
-              for (int k = 0; k < nq; ++k)
-                if (lane == 0 || k * kFindItems + lane - 1 >= n)
-                  st_relaxed(q + k * kFindChunk + lane,
-                             lane == 0 ? level + 1 : -2);
-              const int r = __popcll(bo & ((1ull << lane) - 1ull));
-              if (oa)
-                st_relaxed(q + r / kFindItems * kFindChunk + 1 +
-                               r % kFindItems, u);
-            }
-          }
+        }
+        hubs = min(per, hubs);
+      }
+      for (int k = 0; k < hubs; ++k) {
+        const int32_t w = la[lh[k]];
+        const uint32_t e1 = lr[lh[k]].y;
+        for (uint32_t e = lr[lh[k]].x + tid; __ballot(e < e1); e += kBlock) {
+          const bool live = e < e1;
+          const uint32_t x = live ? P.in[e] : 0u;
+          uint2 range;
+          const bool a = inc_hub_edge(P, epoch, w, x, live, &range);
+          place(a, live && (x >> 31), (int32_t)(x & 0x7fffffffu), range,
+                level);
         }
       }
       __syncthreads();
@@ -926,6 +1013,8 @@ __global__ __launch_bounds__(kBlock) void k_inc_even_cand(IncP P,
                                                           int32_t epoch,
                                                           int32_t nd,
                                                           int32_t *ic) {
+  __shared__ uint2 hub[kBlock];
+  __shared__ int32_t s_n;
   for (int32_t i0 = blockIdx.x * blockDim.x; i0 < nd;
        i0 += gridDim.x * blockDim.x) {
     const int32_t i = i0 + threadIdx.x;
@@ -935,13 +1024,29 @@ __global__ __launch_bounds__(kBlock) void k_inc_even_cand(IncP P,
       e = P.in_off[w];
       e1 = P.in_off[w + 1];
     }
-    for (; __ballot(e < e1); ++e) {
+    auto take = [&](uint32_t e, uint32_t e1) {
       const uint32_t x = e < e1 ? P.in[e] : 0x80000000u;
       const bool c =
           e < e1 && !(x >> 31) && atomicExch(&P.cmark[x], epoch) != epoch;
       const int32_t p = wave_place(&ic[I_NC], c);
       if (c) P.cl[p] = (int32_t)x;
+    };
+    if (P.hub) {   // a hub's by the whole block
+      __syncthreads();
+      if (threadIdx.x == 0) s_n = 0;
+      __syncthreads();
+      if (e1 - e > kHub) {
+        hub[atomicAdd(&s_n, 1)] = make_uint2(e, e1);
+        e1 = e;
+      }
+      __syncthreads();
+      const int n = s_n;
+      for (int k = 0; k < n; ++k)
+        for (uint32_t q = hub[k].x + threadIdx.x; __ballot(q < hub[k].y);
+             q += kBlock)
+          take(q, hub[k].y);
     }
+    for (; __ballot(e < e1); ++e) take(e, e1);
   }
 }
 
@@ -1055,6 +1160,9 @@ constexpr int kBlockEven = 8192;   // most changed vertices of its All_Even
 constexpr int kBlockWide = 8192;   // most entries of wide rows among 1,024
                                    // candidates: one CU reads them in some
                                    // 10 us, the device form the rest
+constexpr int kBlockHubs = 256;    // most hubs of one of its levels
+constexpr int kBlockIn = 32768;    // and most in-edges of those: 1,024 a round
+                                   // trip, as long as a small device step
 enum IncState : int {
   IS_GROWN = 0,    // the pending decisions need the device form (or full)
   IS_BR = 1,       // best response reached; All_Even is the host's
@@ -1085,6 +1193,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
   __shared__ uint2 lr[kBlockA];     // its in-edge ranges
   __shared__ int32_t s_na, s_nc, s_nd, s_stop, s_open, s_err;
   __shared__ WideLds<D == 0 ? T : kWave> W;
+  __shared__ int32_t lh[kBlockHubs], s_nh, s_hd;   // a level's hubs
   const int tid = threadIdx.x;
   int32_t nval = 0, oddsw = 0, evensw = 0, state = IS_GROWN;
   if (tid == 0) {
@@ -1114,33 +1223,59 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
     int32_t beg = 0, end = R.nsw;
     while (beg < end) {
       const int L = find_lanes(end - beg, T);
+      auto place = [&](bool a, bool c, int32_t u, uint2 range) {
+        const int32_t pc = wave_place(&s_nc, c);
+        if (c && pc < P.cl_cap) P.cl[pc] = u;
+        const int32_t pa = wave_place(&s_na, a);
+        if (a && pa < R.a_cap) {
+          la[pa] = u;
+          lr[pa] = range;
+        }
+      };
+      int hubs = 0;
+      if (P.hub) {
+        if (tid == 0) s_nh = s_hd = 0;
+        __syncthreads();
+        for (int32_t i = beg + tid; i < end; i += T) {
+          const uint32_t d = lr[i].y - lr[i].x;
+          if (d <= kHub) continue;
+          const int k = atomicAdd(&s_nh, 1);
+          if (k < kBlockHubs) lh[k] = i;
+          // (saturates: 4,096 of 2,048 at most)
+          if (d > (uint32_t)kIncMaxDegree ||
+              atomicAdd(&s_hd, (int)d) + (int)d > kBlockIn ||
+              k >= kBlockHubs)
+            s_stop = 1;
+        }
+        __syncthreads();
+        hubs = s_stop ? 0 : s_nh;
+      }
       for (int32_t i0 = beg; i0 < end; i0 += T / L) {
         const int32_t i = i0 + tid / L;
         uint32_t e = 0, e1 = 0;
         int32_t w = -1;
-        if (i < end) {
+        if (i < end && lr[i].y - lr[i].x <= kHub) {
           w = la[i];
           e = lr[i].x + tid % L;
           e1 = lr[i].y;
-          if (e1 > e + (uint32_t)kIncMaxDegree) {
-            s_stop = 1;
-            e1 = 0;
-          }
         }
         for (; __ballot(e < e1); e += L) {
           const bool live = e < e1;
           const uint32_t x = live ? P.in[e] : 0u;
           uint2 range;
           const bool a = inc_edge(P, epoch, w, x, live, L, &range);
-          const bool c = live && (x >> 31);
-          const int32_t u = (int32_t)(x & 0x7fffffffu);
-          const int32_t pc = wave_place(&s_nc, c);
-          if (c && pc < P.cl_cap) P.cl[pc] = u;
-          const int32_t pa = wave_place(&s_na, a);
-          if (a && pa < R.a_cap) {
-            la[pa] = u;
-            lr[pa] = range;
-          }
+          place(a, live && (x >> 31), (int32_t)(x & 0x7fffffffu), range);
+        }
+      }
+      for (int k = 0; k < hubs; ++k) {
+        const int32_t w = la[lh[k]];
+        const uint32_t e1 = lr[lh[k]].y;
+        for (uint32_t e = lr[lh[k]].x + tid; __ballot(e < e1); e += T) {
+          const bool live = e < e1;
+          const uint32_t x = live ? P.in[e] : 0u;
+          uint2 range;
+          const bool a = inc_hub_edge(P, epoch, w, x, live, &range);
+          place(a, live && (x >> 31), (int32_t)(x & 0x7fffffffu), range);
         }
       }
       __syncthreads();
@@ -1240,6 +1375,10 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
         const int32_t w = P.list[i];
         e = P.in_off[w];
         e1 = P.in_off[w + 1];
+        if (e1 - e > kHub) {   // the device's All_Even shares them out
+          s_stop = 1;
+          e1 = e;
+        }
       }
       for (; __ballot(e < e1); ++e) {
         const uint32_t x = e < e1 ? P.in[e] : 0x80000000u;
@@ -1250,6 +1389,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
       }
     }
     __syncthreads();
+    if (s_stop) break;   // (the host's All_Even starts over)
     const int32_t ne = s_nc;
     for (int32_t i0 = 0; i0 < ne; i0 += T) {
       const int32_t i = i0 + tid;
@@ -1347,6 +1487,7 @@ static IncP inc_params(const pg_game *g) {
   P.q_cap = N / kFindChunk;
   P.wide = g->inc.h && g->inc.h[I_WORDS + 1];
   P.wl = g->rcand;   // (between full valuations)
+  P.hub = g->inc.h && g->inc.h[I_WORDS + 2];
   return P;
 }
 
@@ -1387,7 +1528,8 @@ static void in_lists(pg_game *g, hipStream_t s) {
                          at, pairs, x.ic + I_WIDE);
       hipLaunchKernelGGL(k_in_range, dim3(nr), dim3(kInPartThreads),
                          sizeof(uint32_t) << shift, s, pairs, at, nb,
-                         (uint32_t)M, (int32_t)N, shift, x.in_off, x.in);
+                         (uint32_t)M, (int32_t)N, shift, x.in_off, x.in,
+                         x.ic + I_HUB);
       fill_i32((int32_t *)x.in_off + N, (int32_t)M, 1, s);
       return;
     }
@@ -1399,8 +1541,8 @@ static void in_lists(pg_game *g, hipStream_t s) {
   scan_excl_u32(x.in_off, x.in_off, N, g->scan_tmp, s);
   fill_i32((int32_t *)x.in_off + N, (int32_t)M, 1, s);
   uint32_t *cursor = reinterpret_cast<uint32_t *>(g->elem);
-  hipLaunchKernelGGL(k_copy_u32, dim3(grid_for(N)), dim3(kBlock), 0, s,
-                     x.in_off, cursor, N);
+  hipLaunchKernelGGL(k_in_cursors, dim3(grid_for(N)), dim3(kBlock), 0, s,
+                     x.in_off, cursor, N, x.ic + I_HUB);
   hipLaunchKernelGGL(k_in_fill, dim3(grid_for(N)), dim3(kBlock), 0, s,
                      g->off, g->tgt, g->owner, cursor, x.in, (int32_t)N,
                      x.ic + I_WIDE);
@@ -1424,7 +1566,7 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     if (st == PG_OK) st = dev_alloc(&x.cmark, N);
     if (st == PG_OK) st = dev_alloc(&x.ic, I_SIZE);
     if (st == PG_OK)
-      st = host_alloc((void **)&x.h, sizeof(int32_t) * (I_WORDS + 2));
+      st = host_alloc((void **)&x.h, sizeof(int32_t) * (I_WORDS + 3));
     if (st != PG_OK) {
       inc_release(g);
       x.state = -1;
@@ -1433,7 +1575,7 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     }
     fill_i32(x.ic, 0, I_SIZE, s);
     in_lists(g, s);
-    publish(x.h + I_WORDS + 1, x.ic + I_WIDE, 1, s);
+    publish(x.h + I_WORDS + 1, x.ic + I_WIDE, 2, s);
     fill_i32(x.mark, 0, N, s);
     fill_i32(x.cmark, 0, N, s);
     x.epoch = x.check = 0;

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 from oracle import orc
+from paper_1705_02313_amd import synth
 from paper_1705_02313_amd.pg import Game
 from tests.helpers import to_np
 
@@ -89,3 +90,36 @@ def test_a_hub_beyond_the_degree_bound_costs_no_ranks():
     assert out["stats"]["n_valuations"] == ref["n_valuations"]
     assert "inc_find" in ran or "inc_block" in ran
     assert not {"sort_split", "sort_pass", "lr_sum1", "lr_emit1"} & set(ran)
+
+
+@pytest.mark.parametrize("few", [0, 4], ids=["ranks", "counts"])
+@pytest.mark.parametrize("n,hubs,degree", [
+    (9000, 30, 126), (9000, 60, 140), (9000, 3, 2000), (60000, 40, 1200),
+    (60000, 400, 129), (140003, 60, 2047), (140003, 60, 2100)])
+def test_random_games_with_hubs(n, hubs, degree, few):
+    """Random games whose hubs change their plays all along a run, with some
+    edges into them repeated."""
+    rng = np.random.default_rng([n, hubs, degree])
+    g = synth.few_priorities_game(n, 2, 4, few, 3) if few else \
+        synth.random_game(n, 2, 4, 3)
+    src = np.concatenate([np.repeat(np.arange(n), np.diff(g["offsets"])),
+                          rng.integers(0, n, hubs * degree)])
+    tgt = np.concatenate([g["targets"],
+                          np.repeat(rng.choice(n, hubs, replace=False),
+                                    degree)])
+    again = rng.random(src.size) < 0.1
+    src, tgt = np.append(src, src[again]), np.append(tgt, tgt[again])
+    order = np.lexsort((rng.random(src.size), src))
+    off = np.zeros(n + 1, np.int64)
+    off[1:] = np.cumsum(np.bincount(src, minlength=n))
+    g = dict(g, m=int(off[-1]), offsets=off,
+             targets=tgt[order].astype(np.int32))
+    ref = orc.dense_solve(g) if few else orc.solve(g)
+    with Game.from_dict(g) as d:
+        for _ in range(2):
+            out = d.solve()
+            for k in ("winner", "sigma"):
+                np.testing.assert_array_equal(to_np(out[k]), ref[k])
+            np.testing.assert_array_equal(to_np(out["tau"]), ref["tau_orig"])
+            for k in ("n_major", "n_valuations"):
+                assert out["stats"][k] == ref[k], k
