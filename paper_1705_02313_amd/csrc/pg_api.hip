@@ -860,9 +860,9 @@ pg_status host_alloc(void **p, size_t bytes) {
 }
 
 pg_status sync_ctr(pg_game *g, hipStream_t s) {
-  publish(g->hctr, g->ctr, C_COUNT, s);
+  publish_ctr(g->hctr, g->ctr, s);
   PG_HIP(hipStreamSynchronize(s));
-  fold_switches(g->hctr);
+  counters_here(g->hctr);
   if (g->prof.on) g->prof.flush();
   return PG_OK;
 }

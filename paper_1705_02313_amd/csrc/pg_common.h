@@ -41,11 +41,11 @@ enum Counter : int {
   // Hot counts are spread over kDistSlots slots kDistStride ints apart (one
   // atomic per block into slot blockIdx % kDistSlots) and summed afterwards:
   // a single address hit by every block serialises.  The switch slots are
-  // summed by the host (fold_switches), the others by a small kernel (a
+  // summed on the way to the host (publish_ctr), the others by a kernel (a
   // last-block-done sum inside the producing kernel would need a release
   // fence per block, which writes back the L2 each time: 10x slower).
   C_DIST_SW = 32,
-  C_COUNT = 32 + 1024,   // the part copied back to the host
+  C_COUNT = 32 + 1024,   // the part a copy takes to the host
   C_DIST_NF = C_COUNT,
   C_DIST_MISC = C_COUNT + 1024,
   // lengths of the open-walk lists (one list per slot, see append_block)
@@ -789,6 +789,15 @@ float clock_ms(pg_game *g, int32_t begin, int32_t end);
 // end >= 0: host[end] receives the time of the copy (clock32).
 void publish(int32_t *host, const int32_t *src, int n, hipStream_t s,
              int end = -1);
+// The counters that come before their slots, the switch count summed:
+// 128 bytes over the bus where a copy of the slots' 4 KB and the host's sum
+// made a Bellman-Ford round 5 % slower.  After the synchronisation:
+// counters_here.
+void publish_ctr(int32_t *host, const int32_t *ctr, hipStream_t s,
+                 int end = -1);
+inline void counters_here(int32_t *hctr) {
+  if (!host_pinned(hctr)) fold_switches(hctr);   // (copied with the slots)
+}
 }  // namespace pgk
 
 // ---- loading helpers shared by single games and batches (pg_api.hip) ------

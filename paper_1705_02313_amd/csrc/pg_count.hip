@@ -737,9 +737,9 @@ static pg_status bf_best_response_t(pg_game *g, hipStream_t s,
               k_bf_round<D>, dim3(grid_for(N)), dim3(kBlock), 0, s, N, g->off,
               g->tgt, g->owner, g->pidx, g->sp, g->cnt, g->cnt2, g->odd_cols,
               g->ctr);
-    publish(g->hctr, g->ctr, C_COUNT, s);
+    publish_ctr(g->hctr, g->ctr, s);
     PG_HIP(hipStreamSynchronize(s));
-    fold_switches(g->hctr);
+    counters_here(g->hctr);
     if (g->prof.on) g->prof.flush();
     std::swap(g->cnt, g->cnt2);
     ++r;

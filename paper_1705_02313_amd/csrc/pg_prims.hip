@@ -96,6 +96,27 @@ __global__ void k_publish(int32_t *host, const int32_t *src, int n, int end) {
     host[end] = clock32();
 }
 
+// One wave: the first C_DIST_SW counters, C_SWITCH the sum of its slots.
+__global__ __launch_bounds__(kWave) void k_publish_ctr(int32_t *host,
+                                                       const int32_t *ctr,
+                                                       int end) {
+  const int lane = threadIdx.x;
+  int32_t sum = ctr[C_DIST_SW + lane * kDistStride];
+  for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if (lane < C_DIST_SW)
+    host[lane] = lane == C_SWITCH ? sum : lane == end ? clock32() : ctr[lane];
+}
+static_assert(kDistSlots == kWave, "k_publish_ctr");
+
+void publish_ctr(int32_t *host, const int32_t *ctr, hipStream_t s, int end) {
+  if (host_pinned(host))
+    hipLaunchKernelGGL(k_publish_ctr, dim3(1), dim3(kWave), 0, s, host, ctr,
+                       end);
+  else
+    (void)hipMemcpyAsync(host, ctr, sizeof(int32_t) * C_COUNT,
+                         hipMemcpyDeviceToHost, s);
+}
+
 void publish(int32_t *host, const int32_t *src, int n, hipStream_t s,
              int end) {
   if (host_pinned(host))

@@ -921,9 +921,9 @@ static int walk_block(const pg_game *g) {
 constexpr int kMaxRounds = 64;    // rounds of the careful path before failing
 
 static pg_status read_ctr(pg_game *g, hipStream_t s) {
-  publish(g->hctr, g->ctr, C_COUNT, s, C_CLOCK_END);
+  publish_ctr(g->hctr, g->ctr, s, C_CLOCK_END);
   PG_HIP(hipStreamSynchronize(s));
-  fold_switches(g->hctr);
+  counters_here(g->hctr);
   if (g->prof.on) {
     g->prof.nf = (double)g->hctr[C_NFIN];
     g->prof.ni = (double)g->hctr[C_NINNER];
