@@ -35,6 +35,7 @@ __global__ void k_check_offsets(const int64_t *off, int64_t n, int64_t m,
   if (v == 0 && a != 0) bad = true;
   if (v == n - 1 && b != m) bad = true;
   if (bad) atomicOr(&ctr[C_ERR], ERR_OFFSETS);
+  if (b - a > kWideRow) ctr[C_WIDE] = 1;
 }
 
 __global__ void k_check_targets(const int32_t *tgt, int64_t m, int64_t n,
@@ -1039,6 +1040,7 @@ pg_status load_modified(int64_t n, int64_t m, const void *offsets,
                    "targets must lie in [0, n), owners in {0, 1} and "
                    "priorities be >= 0");
 
+  g->wide = g->hctr[C_WIDE];
   g->dense = mode == kLoadCount;
   if (mode == kLoadAuto) {
     // repeated input priorities select count valuations.  Fewer values

@@ -221,15 +221,15 @@ __device__ __forceinline__ void count_game(int32_t *cnt, int s, bool sw) {
 // needed.  96 random games, 1.1M vertices: both rules 28 + 16 us a step on
 // ranks, 36 + 27 us here, and the step 370 -> 205 us for want of the ranks
 // (a batch's 42 steps 15.5 -> 9.0 ms).
-template <bool odd>
+template <bool odd, bool W>   // W: for layouts with wide rows
 __global__ __launch_bounds__(kBlock) void k_batch_switch(
     CoarseP P, int64_t count, const int32_t *__restrict__ ids, int2 *sp,
     const int32_t *__restrict__ gid, const uint8_t *__restrict__ on,
     int32_t *cnt, int32_t *ctr) {
   if (ctr[C_ABORT]) return;
   __shared__ int32_t tied[kBlock], s_n;
-  __shared__ WideLds<kBlock> W;
   if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool sw = false, tie = false, live = false, stop = false;
   int s = 0;
@@ -242,7 +242,10 @@ __global__ __launch_bounds__(kBlock) void k_batch_switch(
     // a vertex known to stay top keeps its choice
     live = on[s] && me.y != kTopMark;
   }
-  if (wide_rows(P, live, v, odd, sp, W, &sw, &to, &stop)) live = false;
+  if constexpr (W) {
+    __shared__ WideLds<kBlock> wl;
+    if (wide_rows(P, live, v, odd, sp, wl, &sw, &to, &stop)) live = false;
+  }
   if (live) sw = coarse_row(P, v, cur, odd, &to, &tie);
   sw = sw && !tie;
   if (sw) sp[v] = make_int2(to, to == P.N ? 2147483647 : P.pri[to]);
@@ -390,7 +393,7 @@ __device__ __forceinline__ void bm_max(int32_t *mx, int g, int32_t x) {
 template <typename OffT>
 __global__ void k_bm_offsets(const OffT *raw, const int64_t *ostart,
                              const int64_t *vs, const int64_t *es, int count,
-                             int64_t *uoff, int32_t *err) {
+                             int64_t *uoff, int32_t *err, int32_t *wide) {
   const int64_t R = ostart[count];
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= R) return;
@@ -403,6 +406,7 @@ __global__ void k_bm_offsets(const OffT *raw, const int64_t *ostart,
     bad |= x != mg;
   } else {
     bad |= (int64_t)raw[j + 1] <= x;
+    if ((int64_t)raw[j + 1] - x > kWideRow) wide[g] = 1;
     uoff[vs[g] + i] = es[g] + x;
   }
   if (j == R - 1) uoff[vs[count]] = es[count];
@@ -949,6 +953,8 @@ pg_status rebuild(pg_batch *b, bool *built_any) {
   if (G == 0) return PG_OK;
   // the launch and walk parameters of the arena's size class
   a->tune = tuning_for(vb);
+  a->wide = false;
+  for (BGame *g : next) a->wide |= g->g->wide;
   PG_HIP(hipMemcpyAsync(b->d_desc, b->h_desc.data(), sizeof(GameDesc) * G,
                         hipMemcpyHostToDevice, s));
   PG_HIP(hipMemcpyAsync(b->d_pstart, b->h_pstart.data(),
@@ -1002,8 +1008,10 @@ void enqueue_step_rest(pg_batch *b, hipStream_t s) {
   const int32_t N = (int32_t)a->n_aug;
   const CoarseP P{N, a->n_oddpri, a->off, a->tgt, a->pri, a->ng, a->key};
   if (a->n_odd > 0)
-    hipLaunchKernelGGL(k_batch_switch<true>, dim3(grid_for(a->n_odd)),
-                       dim3(kBlock), 0, s, P, a->n_odd, a->odd_ids, a->sp,
+    hipLaunchKernelGGL((a->wide ? k_batch_switch<true, true>
+                                : k_batch_switch<true, false>),
+                       dim3(grid_for(a->n_odd)), dim3(kBlock), 0, s, P,
+                       a->n_odd, a->odd_ids, a->sp,
                        b->d_gid, b->d_run, b->d_cnt_odd, a->ctr);
   hipLaunchKernelGGL(k_batch_ctl1, dim3(grid_for(G)), dim3(kBlock), 0, s, G,
                      b->d_run, b->d_cnt_odd, b->d_pending, b->d_nval,
@@ -1013,8 +1021,9 @@ void enqueue_step_rest(pg_batch *b, hipStream_t s) {
                        b->d_gid, b->d_pending, a->rs, a->sp, a->ctr);
   const int64_t ne = N - a->n_odd;
   if (ne > 0)
-    hipLaunchKernelGGL(k_batch_switch<false>, dim3(grid_for(ne)),
-                       dim3(kBlock), 0, s, P, ne, a->even_ids, a->sp,
+    hipLaunchKernelGGL((a->wide ? k_batch_switch<false, true>
+                                : k_batch_switch<false, false>),
+                       dim3(grid_for(ne)), dim3(kBlock), 0, s, P, ne, a->even_ids, a->sp,
                        b->d_gid, b->d_pending, b->d_cnt_even, a->ctr);
   hipLaunchKernelGGL(k_batch_ctl2, dim3(grid_for(G)), dim3(kBlock), 0, s, G,
                      b->d_run, b->d_pending, b->d_cnt_odd, b->d_cnt_even,
@@ -1162,7 +1171,7 @@ pg_status submit_union(pg_batch *b, const std::vector<int> &idx,
   PG_TRY(alloc(&uown, N));
   PG_TRY(alloc(&upri, N));
   PG_TRY(alloc(&gid, N));
-  PG_TRY(alloc(&err, count));
+  PG_TRY(alloc(&err, 2 * (int64_t)count));   // errors, then wide rows
   const size_t ob = i32 ? 4 : 8;
   for (int k = 0; k < count; ++k) {
     const int q = idx[k];
@@ -1173,21 +1182,21 @@ pg_status submit_union(pg_batch *b, const std::vector<int> &idx,
     PG_TRY(copy_in(upri + hv[k], priority[q], sizeof(int32_t) * n[q], dev,
                    s));
   }
-  fill_i32(err, 0, count, s);
+  fill_i32(err, 0, 2 * (int64_t)count, s);
   if (i32)
     hipLaunchKernelGGL(k_bm_offsets<int32_t>, dim3(grid_for(R)),
                        dim3(kBlock), 0, s, (const int32_t *)raw, d_os, d_vs,
-                       d_es, count, uoff, err);
+                       d_es, count, uoff, err, err + count);
   else
     hipLaunchKernelGGL(k_bm_offsets<int64_t>, dim3(grid_for(R)),
                        dim3(kBlock), 0, s, (const int64_t *)raw, d_os, d_vs,
-                       d_es, count, uoff, err);
+                       d_es, count, uoff, err, err + count);
   hipLaunchKernelGGL(k_bm_targets, dim3(grid_for(M)), dim3(kBlock), 0, s,
                      utgt, d_vs, d_es, count, err);
   hipLaunchKernelGGL(k_bm_vertices, dim3(grid_for(N)), dim3(kBlock), 0, s,
                      uown, upri, d_vs, count, gid, err);
-  std::vector<int32_t> herr(count);
-  PG_HIP(hipMemcpyAsync(herr.data(), err, sizeof(int32_t) * count,
+  std::vector<int32_t> herr(2 * (size_t)count);
+  PG_HIP(hipMemcpyAsync(herr.data(), err, sizeof(int32_t) * 2 * count,
                         hipMemcpyDeviceToHost, s));
   PG_HIP(hipStreamSynchronize(s));
   {
@@ -1346,6 +1355,7 @@ pg_status submit_union(pg_batch *b, const std::vector<int> &idx,
     gg->n_aug = na;
     gg->m_aug = ma;
     gg->relabeled = true;
+    gg->wide = herr[count + k];
     PG_TRY(dev_alloc(&gg->off, na + 1));
     PG_TRY(dev_alloc(&gg->tgt, ma));
     PG_TRY(dev_alloc(&gg->owner, na));

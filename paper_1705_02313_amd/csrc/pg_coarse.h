@@ -152,7 +152,7 @@ __device__ __forceinline__ bool coarse_exact(const CoarseP &P, int32_t v,
 // 100,000 entries 1,212 -> 116 ms (nearly all of it the load), 200 of 5,000
 // 133 -> 20 ms, four Even ones of 100,000 130 -> 43 ms; a batch of 20 games
 // with two rows of 8,000 each 187 -> 16 ms.
-constexpr int kWideRow = 128, kWideShare = 16;
+constexpr int kWideShare = 16;
 
 template <int T>
 struct WideLds {

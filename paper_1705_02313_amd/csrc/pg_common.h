@@ -20,6 +20,8 @@ constexpr int kBlock = 256;            // threads per block for flat kernels
 constexpr int32_t kTopMark = INT32_MIN;
 constexpr int kWave = 64;              // CDNA wavefront width
 constexpr int kMaxVertices = (1 << 30) - 2;
+// a row (or in-edge list) of more entries is shared by a block
+constexpr int kWideRow = 128;
 
 // Counters and flags kept in one small device array so that a single
 // device-to-host copy returns all of them.
@@ -37,6 +39,7 @@ enum Counter : int {
   C_CLOCK_END = 9,    // and its end (in the host's copy)
   C_DUP = 10,         // loading: a priority repeats
   C_MAXPRI = 11,      // the largest priority
+  C_WIDE = 12,        // loading: a row beyond kWideRow entries
   C_XN = 16,          // X's sweeps: a change in each (kXGroup)
   // Hot counts are spread over kDistSlots slots kDistStride ints apart (one
   // atomic per block into slot blockIdx % kDistSlots) and summed afterwards:
@@ -180,6 +183,7 @@ struct pg_game {
   int64_t n_aug = 0, m_aug = 0;  // modified game (sink not counted)
   int32_t n_oddpri = 0;          // vertices with an odd priority
   int64_t n_odd = 0, m_odd = 0;  // Odd vertices and the edges of their rows
+  bool wide = true;              // rows beyond kWideRow entries (pg_coarse.h)
   int sort_bits = 0;             // bits of a parent id key (ids 0..n_aug+1)
   bool careful = false;          // PG_CAREFUL_WALKS: host-driven walk rounds
   // a solve marks, after each best response, the vertices whose valuation

@@ -68,9 +68,9 @@ enum IncCounter : int {
   I_ALL = 160,    // the part cleared before a step
   I_OFFROW = 160, // the last check of the rows that failed (its number); the
                   // host's copy follows the I_WORDS
-  I_WIDE = 161,   // the game has rows beyond kWideRow entries (its copy next)
-  I_HUB = 162,    // and vertices of more than kHub in-edges
-  I_SIZE = 163
+  I_HUB = 161,    // the game has vertices of more than kHub in-edges (its
+                  // copy next)
+  I_SIZE = 162
 };
 static_assert((int)I_ERR == (int)C_ERR, "the ng walk reports through ctr[0]");
 constexpr int kFindLevels = 512;     // levels of a device form's find
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kBlock) void k_in_count(
 __global__ __launch_bounds__(kBlock) void k_in_fill(
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
     const uint8_t *__restrict__ owner, uint32_t *cursor, uint32_t *in,
-    int32_t N, int32_t *any_wide) {
+    int32_t N) {
   __shared__ int32_t wide[kBlock], s_n;
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
@@ -107,7 +107,6 @@ __global__ __launch_bounds__(kBlock) void k_in_fill(
   __syncthreads();
   // wide rows by the whole block (see wide_rows)
   const int n = s_n;
-  if (n && threadIdx.x == 0) *any_wide = 1;
   for (int k = 0; k < n; ++k) {
     const int32_t w = wide[k];
     const int64_t w0 = off[w], w1 = off[w + 1];
@@ -176,7 +175,7 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_hist(
 __global__ __launch_bounds__(kInPartThreads) void k_in_part(
     const int64_t *__restrict__ off, const int32_t *__restrict__ tgt,
     const uint8_t *__restrict__ owner, int32_t N, int vb, int shift, int nr,
-    const uint32_t *__restrict__ at, uint2 *pairs, int32_t *any_wide) {
+    const uint32_t *__restrict__ at, uint2 *pairs) {
   __shared__ uint32_t c[kInRanges];
   __shared__ int32_t wide[kInPartThreads], s_n;
   if (threadIdx.x == 0) s_n = 0;
@@ -190,7 +189,6 @@ __global__ __launch_bounds__(kInPartThreads) void k_in_part(
     const uint32_t x = (uint32_t)v | ((uint32_t)owner[v] << 31);
     const int64_t e0 = off[v], end = off[v + 1];
     if (end - e0 > kWideRow) {
-      *any_wide = 1;
       const int k = atomicAdd(&s_n, 1);
       if (k < kInPartThreads) {
         wide[k] = (int32_t)v;
@@ -657,6 +655,9 @@ __device__ __forceinline__ int32_t find_ticket(int32_t S, int32_t q_cap,
   return -1;
 }
 
+// H: for games with hubs (the code for them slows the others' down, here and
+// in the kernels with S and W below, by 3 to 15 %).
+template <bool H>
 __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
                                                      int32_t a0, int32_t nsw,
                                                      int32_t *ic) {
@@ -767,7 +768,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
       }
       const int L = find_lanes(end - beg, kBlock);
       int hubs = 0;
-      if (P.hub) {
+      if constexpr (H) {
         if (tid == 0) s_nh = s_hd = 0;
         __syncthreads();
         if (tid < end - beg) {
@@ -786,7 +787,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
         const int i = i0 + tid / L;
         uint32_t e = 0, e1 = 0;
         int32_t w = -1;
-        if (i < end && lr[i].y - lr[i].x <= kHub) {
+        if (i < end && (!H || lr[i].y - lr[i].x <= kHub)) {
           w = la[i];
           e = lr[i].x + tid % L;
           e1 = lr[i].y;
@@ -800,7 +801,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
                 level);
         }
       }
-      if (hubs > 0 && s_hd > 2 * kFindHubs) {
+      if (H && hubs > 0 && s_hd > 2 * kFindHubs) {
         // all but the first kFindHubs in-edges to the queue, as many in a
         // chunk by the average
         const int per =
@@ -826,7 +827,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_find(IncP P, int32_t epoch,
         }
         hubs = min(per, hubs);
       }
-      for (int k = 0; k < hubs; ++k) {
+      for (int k = 0; H && k < hubs; ++k) {
         const int32_t w = la[lh[k]];
         const uint32_t e1 = lr[lh[k]].y;
         for (uint32_t e = lr[lh[k]].x + tid; __ballot(e < e1); e += kBlock) {
@@ -1052,7 +1053,7 @@ __global__ __launch_bounds__(kBlock) void k_inc_even_cand(IncP P,
 
 // All_Even over every Even vertex; decisions only.
 constexpr int even_block(int D) { return D >= 16 ? 256 : 1024; }
-template <int D>
+template <int D, bool W>
 __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
     IncP P, int64_t count, const int32_t *__restrict__ ids, int2 *dec,
     int32_t *ic) {
@@ -1063,10 +1064,9 @@ __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
   bool sw = false, stop = false, live = t < count;
   int32_t v = 0, to = 0;
   if (live) v = ids[t];
-  if constexpr (D == 0) {
-    __shared__ WideLds<even_block(D)> W;
-    if (P.wide && inc_wide(P, live, v, false, W, &sw, &to, &stop))
-      live = false;
+  if constexpr (W) {
+    __shared__ WideLds<even_block(D)> wl;
+    if (inc_wide(P, live, v, false, wl, &sw, &to, &stop)) live = false;
   }
   if (live) sw = rule<D>(P, v, false, &to, &stop);
   const int32_t at = wave_place(&n, sw);
@@ -1079,10 +1079,10 @@ __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
 
 // All_Odd for the vertices a coarse valuation left open: switched in place
 // and listed, like the others' switches.
+template <bool W>
 __global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
                                                        int2 *dec) {
   if (ctr[C_ABORT]) return;
-  __shared__ WideLds<kBlock> W;
   const int32_t n = ctr[C_NTIE];
   for (int32_t i0 = blockIdx.x * blockDim.x; i0 < n;
        i0 += gridDim.x * blockDim.x) {
@@ -1090,7 +1090,10 @@ __global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
     bool sw = false, stop = false, live = i < n;
     int32_t v = 0, to = 0;
     if (live) v = P.cl[i];
-    if (inc_wide(P, live, v, true, W, &sw, &to, &stop)) live = false;
+    if constexpr (W) {
+      __shared__ WideLds<kBlock> wl;
+      if (inc_wide(P, live, v, true, wl, &sw, &to, &stop)) live = false;
+    }
     if (live) sw = inc_decide(P, v, true, &to, &stop);
     if (sw) P.sp[v] = make_int2(to, P.pri[to]);
     // (the walks bound every chain: no climb stops)
@@ -1120,7 +1123,13 @@ __global__ __launch_bounds__(kBlock) void k_inc_rows_hold(IncP P,
       wide[atomicAdd(&s_n, 1)] = (int32_t)v;
     } else {
       off = true;
-      for (int64_t e = e0; e < e1 && off; ++e) off = P.tgt[e] != to;
+      for (int64_t e = e0; e < e1 && off; e += 4) {
+        int32_t t[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t[j] = e + j < e1 ? P.tgt[e + j] : -1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) off = off && t[j] != to;
+      }
     }
   }
   __syncthreads();
@@ -1183,7 +1192,7 @@ struct IncRun {
 
 // (wide count rows: fewer threads, so that the rows stay in registers)
 constexpr int inc_threads(int D) { return D >= 16 ? 512 : 1024; }
-template <int D>
+template <int D, bool S>   // S: for games with hubs or wide rows
 __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
                                                               int2 *dec0,
                                                               int2 *dec1,
@@ -1192,7 +1201,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
   __shared__ int32_t la[kBlockA];   // A
   __shared__ uint2 lr[kBlockA];     // its in-edge ranges
   __shared__ int32_t s_na, s_nc, s_nd, s_stop, s_open, s_err;
-  __shared__ WideLds<D == 0 ? T : kWave> W;
+  __shared__ WideLds<D == 0 && S ? T : kWave> wl;
   __shared__ int32_t lh[kBlockHubs], s_nh, s_hd;   // a level's hubs
   const int tid = threadIdx.x;
   int32_t nval = 0, oddsw = 0, evensw = 0, state = IS_GROWN;
@@ -1233,7 +1242,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
         }
       };
       int hubs = 0;
-      if (P.hub) {
+      if (S && P.hub) {
         if (tid == 0) s_nh = s_hd = 0;
         __syncthreads();
         for (int32_t i = beg + tid; i < end; i += T) {
@@ -1254,7 +1263,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
         const int32_t i = i0 + tid / L;
         uint32_t e = 0, e1 = 0;
         int32_t w = -1;
-        if (i < end && lr[i].y - lr[i].x <= kHub) {
+        if (i < end && (!S || lr[i].y - lr[i].x <= kHub)) {
           w = la[i];
           e = lr[i].x + tid % L;
           e1 = lr[i].y;
@@ -1267,7 +1276,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
           place(a, live && (x >> 31), (int32_t)(x & 0x7fffffffu), range);
         }
       }
-      for (int k = 0; k < hubs; ++k) {
+      for (int k = 0; S && k < hubs; ++k) {
         const int32_t w = la[lh[k]];
         const uint32_t e1 = lr[lh[k]].y;
         for (uint32_t e = lr[lh[k]].x + tid; __ballot(e < e1); e += T) {
@@ -1331,9 +1340,9 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
         v = P.cl[i];
         live = atomicExch(&P.cmark[v], epoch) != epoch;
       }
-      if constexpr (D == 0)
+      if constexpr (D == 0 && S)
         if (P.wide &&
-            inc_wide(P, live, v, true, W, &sw, &to, &stop, kBlockWide))
+            inc_wide(P, live, v, true, wl, &sw, &to, &stop, kBlockWide))
           live = false;
       if (live) sw = rule<D>(P, v, true, &to, &stop);
       if (stop) s_stop = 1;
@@ -1375,7 +1384,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
         const int32_t w = P.list[i];
         e = P.in_off[w];
         e1 = P.in_off[w + 1];
-        if (e1 - e > kHub) {   // the device's All_Even shares them out
+        if (S && e1 - e > kHub) {   // the device's All_Even shares them out
           s_stop = 1;
           e1 = e;
         }
@@ -1396,9 +1405,9 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
       bool sw = false, stop = false, live = i < ne;
       int32_t v = 0, to = 0;
       if (live) v = P.cl[i];
-      if constexpr (D == 0)
+      if constexpr (D == 0 && S)
         if (P.wide &&
-            inc_wide(P, live, v, false, W, &sw, &to, &stop, kBlockWide))
+            inc_wide(P, live, v, false, wl, &sw, &to, &stop, kBlockWide))
           live = false;
       if (live) sw = rule<D>(P, v, false, &to, &stop);
       if (stop) s_stop = 1;
@@ -1485,9 +1494,9 @@ static IncP inc_params(const pg_game *g) {
   P.cl_cap = 2 * N;
   P.q = reinterpret_cast<int32_t *>(g->sk0);
   P.q_cap = N / kFindChunk;
-  P.wide = g->inc.h && g->inc.h[I_WORDS + 1];
+  P.wide = g->wide;
   P.wl = g->rcand;   // (between full valuations)
-  P.hub = g->inc.h && g->inc.h[I_WORDS + 2];
+  P.hub = g->inc.h && g->inc.h[I_WORDS + 1];
   return P;
 }
 
@@ -1525,7 +1534,7 @@ static void in_lists(pg_game *g, hipStream_t s) {
       scan_excl_u32(hist, at, (int64_t)nr * nb, g->scan_tmp, s);
       hipLaunchKernelGGL(k_in_part, dim3(nb), dim3(kInPartThreads), 0, s,
                          g->off, g->tgt, g->owner, (int32_t)N, vb, shift, nr,
-                         at, pairs, x.ic + I_WIDE);
+                         at, pairs);
       hipLaunchKernelGGL(k_in_range, dim3(nr), dim3(kInPartThreads),
                          sizeof(uint32_t) << shift, s, pairs, at, nb,
                          (uint32_t)M, (int32_t)N, shift, x.in_off, x.in,
@@ -1544,8 +1553,7 @@ static void in_lists(pg_game *g, hipStream_t s) {
   hipLaunchKernelGGL(k_in_cursors, dim3(grid_for(N)), dim3(kBlock), 0, s,
                      x.in_off, cursor, N, x.ic + I_HUB);
   hipLaunchKernelGGL(k_in_fill, dim3(grid_for(N)), dim3(kBlock), 0, s,
-                     g->off, g->tgt, g->owner, cursor, x.in, (int32_t)N,
-                     x.ic + I_WIDE);
+                     g->off, g->tgt, g->owner, cursor, x.in, (int32_t)N);
 }
 
 // Builds the in-edge lists at the first solve of a game.  Without memory
@@ -1566,7 +1574,7 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     if (st == PG_OK) st = dev_alloc(&x.cmark, N);
     if (st == PG_OK) st = dev_alloc(&x.ic, I_SIZE);
     if (st == PG_OK)
-      st = host_alloc((void **)&x.h, sizeof(int32_t) * (I_WORDS + 3));
+      st = host_alloc((void **)&x.h, sizeof(int32_t) * (I_WORDS + 2));
     if (st != PG_OK) {
       inc_release(g);
       x.state = -1;
@@ -1575,7 +1583,7 @@ bool inc_prepare(pg_game *g, hipStream_t s) {
     }
     fill_i32(x.ic, 0, I_SIZE, s);
     in_lists(g, s);
-    publish(x.h + I_WORDS + 1, x.ic + I_WIDE, 2, s);
+    publish(x.h + I_WORDS + 1, x.ic + I_HUB, 1, s);
     fill_i32(x.mark, 0, N, s);
     fill_i32(x.cmark, 0, N, s);
     x.epoch = x.check = 0;
@@ -1665,7 +1673,8 @@ int32_t *tie_list(const pg_game *g) {
 }
 
 void enqueue_ties(pg_game *g, hipStream_t s) {
-  PG_LAUNCH(&g->prof, K_INC_DECIDE, 0.0, k_tie_decide, dim3(1024),
+  PG_LAUNCH(&g->prof, K_INC_DECIDE, 0.0,
+            g->wide ? k_tie_decide<true> : k_tie_decide<false>, dim3(1024),
             dim3(kBlock), 0, s, inc_params(g), g->ctr, inc_dec(g, 0));
 }
 
@@ -1752,9 +1761,11 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     R.major = x.major;
     R.d_valid = x.d_valid;
     R.with_even = with_even;
-    PG_LAUNCH(pf, K_INC_BLOCK, 0.0, k_inc_block<D>, dim3(1),
-              dim3(inc_threads(D)), 0, s, P, R, inc_dec(g, 0), inc_dec(g, 1),
-              host_pinned(x.h) ? x.h : x.ic);
+    PG_LAUNCH(pf, K_INC_BLOCK, 0.0,
+              (P.hub || (D == 0 && P.wide) ? k_inc_block<D, true>
+                                           : k_inc_block<D, false>),
+              dim3(1), dim3(inc_threads(D)), 0, s, P, R, inc_dec(g, 0),
+              inc_dec(g, 1), host_pinned(x.h) ? x.h : x.ic);
   } else {
     const int32_t epoch = ++x.epoch;
     const unsigned gb =
@@ -1765,8 +1776,8 @@ static pg_status inc_step_t(pg_game *g, hipStream_t s, bool with_even,
     fill_i32(x.ic, 0, I_ALL, s, pf);
     PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_begin, dim3(grid_for(x.nsw)), blk, 0,
               s, P, epoch, x.a0, inc_dec(g, x.cur), x.nsw, x.ic);
-    PG_LAUNCH(pf, K_INC_FIND, 0.0, k_inc_find, dim3(kFindBlocks), blk, 0, s,
-              P, epoch, x.a0, x.nsw, x.ic);
+    PG_LAUNCH(pf, K_INC_FIND, 0.0, P.hub ? k_inc_find<true> : k_inc_find<false>,
+              dim3(kFindBlocks), blk, 0, s, P, epoch, x.a0, x.nsw, x.ic);
     if constexpr (D == 0) {
       PG_LAUNCH(pf, K_INC_WALK, 0.0, k_inc_walk, grid, blk, 0, s, P, x.a0, 64,
                 0, 0, x.ic);
@@ -1866,7 +1877,9 @@ static pg_status inc_even_t(pg_game *g, hipStream_t s, int32_t *count) {
     fill_i32(x.ic, 0, I_WORDS, s, pf);
     if (ne > 0)
       PG_LAUNCH(pf, K_EVEN_SWITCH, 28.0 * ne + 8.0 * (g->m_aug - g->m_odd),
-                k_inc_even_all<D>, dim3(grid_for(ne, even_block(D))),
+                (D == 0 && P.wide ? k_inc_even_all<D, D == 0>
+                                  : k_inc_even_all<D, false>),
+                dim3(grid_for(ne, even_block(D))),
                 dim3(even_block(D)), 0, s, P, ne, g->even_ids, inc_dec(g, 0),
                 x.ic);
     PG_TRY(inc_read(g, s));

@@ -502,7 +502,7 @@ struct SmallLoad {
 };
 // the words it reports in
 enum LoadCounter : int {
-  L_STATE = 8, L_NAUG, L_NODDPRI, L_NODD, L_MODD, L_END
+  L_STATE = 8, L_NAUG, L_NODDPRI, L_NODD, L_MODD, L_WIDE, L_END
 };
 static_assert((int)L_END <= (int)C_DIST_SW, "the load kernel's words");
 
@@ -530,10 +530,11 @@ __device__ __forceinline__ int32_t block_excl(int32_t x, int32_t *part,
 
 __global__ __launch_bounds__(kSmallThreads) void k_small_load(SmallLoad L) {
   extern __shared__ __align__(16) char lds[];
-  __shared__ int32_t part[kSmallThreads / kWave], s_sum[3];
+  __shared__ int32_t part[kSmallThreads / kWave], s_sum[3], s_wide;
   const int tid = threadIdx.x;
   const int32_t n = L.n, m = L.m;
   if (tid < 3) s_sum[tid] = 0;
+  if (tid == 0) s_wide = 0;
   __syncthreads();
   BlockSum sum{s_sum};
   char *p = lds;
@@ -553,6 +554,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_load(SmallLoad L) {
     const int64_t a = row(v), b = row(v + 1);
     bad |= b <= a || b > m || a < 0 || (v == 0 && a != 0) ||
            (v == n - 1 && b != m) || L.owner[v] > 1 || L.pri[v] < 0;
+    if (b - a > kWideRow) s_wide = 1;
     inx[v] = L.owner[v] == 1;
     xp[v] = 0;
   }
@@ -724,6 +726,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_load(SmallLoad L) {
     L.ctr[L_NODDPRI] = no + nxp / 2;
     L.ctr[L_NODD] = n_odd;
     L.ctr[L_MODD] = m_odd;
+    L.ctr[L_WIDE] = s_wide;
   }
 }
 
@@ -854,6 +857,7 @@ pg_status small_load(pg_game *g, int64_t n, int64_t m, const void *offsets,
   g->n_oddpri = g->hctr[L_NODDPRI];
   g->n_odd = g->hctr[L_NODD];
   g->m_odd = g->hctr[L_MODD];
+  g->wide = g->hctr[L_WIDE];
   g->sort_bits = 1;
   while ((int64_t(1) << g->sort_bits) <= g->n_aug + 1) ++g->sort_bits;
   g->relabeled = true;
