@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_switch(
   if ((int)threadIdx.x < s_n) {
     v = tied[threadIdx.x];
     s = gid[v];
-    sw = coarse_exact(P, v, sp[v].x, odd, &to, &stop);
+    sw = coarse_exact<W>(P, v, sp[v].x, odd, &to, &stop);
     if (sw) sp[v] = make_int2(to, to == P.N ? 2147483647 : P.pri[to]);
     if (stop) atomicOr(&ctr[C_ERR], ERR_LISTWALK);
   }

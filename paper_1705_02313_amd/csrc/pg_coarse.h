@@ -111,26 +111,38 @@ __device__ __forceinline__ bool coarse_row(const CoarseP &P, int32_t v,
   return odd ? kb < kc : kb > kc;
 }
 
+// F: four entries a round trip, for kernels that meet long rows here (short
+// ones are done sooner one by one: ties of the 10M-vertex game 25 against 28
+// us a valuation).
+template <bool F = false>
 __device__ __forceinline__ bool coarse_exact(const CoarseP &P, int32_t v,
                                              int32_t cur, bool odd,
                                              int32_t *to, bool *stop) {
   const int64_t e0 = P.off[v], e1 = P.off[v + 1];
   int32_t best = odd ? -1 : P.N, kb = odd ? 0 : P.key[P.N];
-  for (int64_t q = e0; q < e1; q += 4) {
-    int32_t u[4], k[4];
+  auto take = [&](int32_t u, int32_t k) {
+    if (best >= 0) {
+      const int c = coarse_cmp(P, u, k, best, kb, stop);
+      if (!(odd ? c < 0 : c > 0)) return;
+    }
+    best = u;
+    kb = k;
+  };
+  if constexpr (F) {
+    for (int64_t q = e0; q < e1; q += 4) {
+      int32_t u[4], k[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) u[j] = q + j < e1 ? P.tgt[q + j] : -1;
+      for (int j = 0; j < 4; ++j) u[j] = q + j < e1 ? P.tgt[q + j] : -1;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) k[j] = u[j] >= 0 ? P.key[u[j]] : 0;
+      for (int j = 0; j < 4; ++j) k[j] = u[j] >= 0 ? P.key[u[j]] : 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (u[j] < 0) continue;
-      if (best >= 0) {
-        const int c = coarse_cmp(P, u[j], k[j], best, kb, stop);
-        if (!(odd ? c < 0 : c > 0)) continue;
-      }
-      best = u[j];
-      kb = k[j];
+      for (int j = 0; j < 4; ++j)
+        if (u[j] >= 0) take(u[j], k[j]);
+    }
+  } else {
+    for (int64_t q = e0; q < e1; ++q) {
+      const int32_t u = P.tgt[q];
+      take(u, P.key[u]);
     }
   }
   if (best == cur) return false;

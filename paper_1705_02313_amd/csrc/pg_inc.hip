@@ -329,6 +329,7 @@ __device__ __forceinline__ CoarseP coarse(const IncP &P) {
   return CoarseP{P.N, P.n_oddpri, P.off, P.tgt, P.pri, P.ng, P.key};
 }
 
+template <bool F = false>
 __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
                                            int32_t *to, bool *stop) {
   const int2 me = P.sp[v];
@@ -336,15 +337,15 @@ __device__ __forceinline__ bool inc_decide(const IncP &P, int32_t v, bool odd,
   const CoarseP C = coarse(P);
   bool tie;
   const bool sw = coarse_row(C, v, me.x, odd, to, &tie);
-  return tie ? coarse_exact(C, v, me.x, odd, to, stop) : sw;
+  return tie ? coarse_exact<F>(C, v, me.x, odd, to, stop) : sw;
 }
 
 // The rule of a rank game (D = 0) or with count rows of D ints.
-template <int D>
+template <int D, bool F = false>
 __device__ __forceinline__ bool rule(const IncP &P, int32_t v, bool odd,
                                      int32_t *to, bool *stop) {
   if constexpr (D == 0) {
-    return inc_decide(P, v, odd, to, stop);
+    return inc_decide<F>(P, v, odd, to, stop);
   } else {
     const int2 me = P.sp[v];
     if (me.y == kTopMark) return false;   // known to stay top
@@ -627,7 +628,8 @@ __device__ __forceinline__ int find_lanes(int n, int T) {
 // the LDS lists takes a chunk for the few sources it has just found, so a
 // hub's in-edges can ask for more than the q_cap chunks that every vertex of
 // the game once would need.  Whoever asks beyond them sets I_STOP, and no
-// ticket names a place at or past q_cap.
+// ticket names a place at or past q_cap; one that names a place nobody got to
+// write ends its wait by I_STOP.
 constexpr int kFindChunk = 64, kFindA = 1024, kFindC = 2048;
 constexpr int kFindKeep = 128, kFindBlocks = 512;
 constexpr int kFindHubs = 2048;   // in-edges of hubs a block keeps to itself
@@ -642,13 +644,12 @@ __device__ __forceinline__ int32_t find_ticket(int32_t S, int32_t q_cap,
   if (t < S) return t;
   if (t - S >= q_cap) return -1;
   for (int k = 0; k < kFindWait; ++k) {
-    if (ld_relaxed(&ic[I_STOP])) return -1;
     // done first (never negative: the tail's address waits for it): when it
     // has reached S + tail, no chunk was open then
     const int32_t done = ld_relaxed(&ic[I_QDONE]);
     const int32_t tail = ld_relaxed(&ic[I_QTAIL + (done < 0)]);
     if (tail > t - S) return t;
-    if (done == S + tail) return -1;
+    if (done == S + tail || ld_relaxed(&ic[I_STOP])) return -1;
     __builtin_amdgcn_s_sleep(8);
   }
   atomicOr(&ic[I_STOP], 1);
@@ -1068,7 +1069,7 @@ __global__ __launch_bounds__(even_block(D)) void k_inc_even_all(
     __shared__ WideLds<even_block(D)> wl;
     if (inc_wide(P, live, v, false, wl, &sw, &to, &stop)) live = false;
   }
-  if (live) sw = rule<D>(P, v, false, &to, &stop);
+  if (live) sw = rule<D, W>(P, v, false, &to, &stop);
   const int32_t at = wave_place(&n, sw);
   __syncthreads();
   if (threadIdx.x == 0 && n) base = atomicAdd(&ic[I_NDEC], n);
@@ -1094,7 +1095,7 @@ __global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
       __shared__ WideLds<kBlock> wl;
       if (inc_wide(P, live, v, true, wl, &sw, &to, &stop)) live = false;
     }
-    if (live) sw = inc_decide(P, v, true, &to, &stop);
+    if (live) sw = inc_decide<W>(P, v, true, &to, &stop);
     if (sw) P.sp[v] = make_int2(to, P.pri[to]);
     // (the walks bound every chain: no climb stops)
     if (stop) atomicOr(&ctr[C_ERR], ERR_LISTWALK);
@@ -1344,7 +1345,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
         if (P.wide &&
             inc_wide(P, live, v, true, wl, &sw, &to, &stop, kBlockWide))
           live = false;
-      if (live) sw = rule<D>(P, v, true, &to, &stop);
+      if (live) sw = rule<D, S>(P, v, true, &to, &stop);
       if (stop) s_stop = 1;
       const int32_t p = wave_place(&s_nd, sw);
       if (sw) dout[p] = make_int2(v, to);
@@ -1409,7 +1410,7 @@ __global__ __launch_bounds__(inc_threads(D)) void k_inc_block(IncP P, IncRun R,
         if (P.wide &&
             inc_wide(P, live, v, false, wl, &sw, &to, &stop, kBlockWide))
           live = false;
-      if (live) sw = rule<D>(P, v, false, &to, &stop);
+      if (live) sw = rule<D, S>(P, v, false, &to, &stop);
       if (stop) s_stop = 1;
       const int32_t p = wave_place(&s_nd, sw);
       if (sw) eout[p] = make_int2(v, to);
