@@ -25,27 +25,29 @@ Workloads (seeded, synthetic; see paper_1705_02313_amd/synth.py):
       quarter of the mix's modified vertices (latency p50/p99)
 
 Printed: one JSON line with the driver's fields plus
-  "roofline"   the best-response iteration as the unit: the least bytes of
-               a valuation that ranks every vertex (CSR offsets and targets,
-               one key gather per edge, 25 B per vertex, 12 B per element of
-               a 2n'-element Euler list) over the iterations' average device
-               time, by the device's clock over the timed steps (most
-               iterations recompute a changed part only, so this compares
-               with that method and is no bandwidth),
-               against 8 TB/s; "traffic" is the
-               rocprofv3 counter bytes per iteration (FETCH_SIZE +
-               WRITE_SIZE scaled on a plain copy: bytes through the L2's
-               fabric port, Infinity Cache hits included, so an upper bound
-               on HBM bytes) when they were taken on the current sources
+  "roofline"   the best-response iteration as the unit, against 8 TB/s:
+               "achieved" is the rocprofv3 counter bytes per iteration
+               (FETCH_SIZE + WRITE_SIZE scaled on a plain copy: bytes through
+               the L2's fabric port, Infinity Cache hits included, so an upper
+               bound on HBM bytes) over the iterations' average device time,
+               by the device's clock over the timed steps; null unless the
+               counters were taken on the current sources.
+               "ranked_method" is what a valuation that ranks every vertex
+               has to move at least (CSR offsets and targets, one key gather
+               per edge, 25 B per vertex, 12 B per element of a 2n'-element
+               Euler list) over the same time: most iterations recompute a
+               changed part only, so it compares with that method and is no
+               bandwidth
   "dominant_kernel"  the kernel with the largest summed time in up to two
-               profiled steps after the timed steps, its own algorithmic
-               bytes over its event-timed duration
+               profiled steps after the timed steps: its counter bytes over
+               its event-timed duration (null as above), and its algorithmic
+               bytes where they follow from the sizes
   "iteration_bytes"  every kernel's algorithmic bytes per iteration, the
                counter bytes, a measured 1 GiB copy rate
   "mix"        (c2 runs, unless --no-mix) the 1,024-game batched/served
                workload: games/s one at a time, batched and served, p50/p99
-               latency, identical results, a roofline fraction and the CPU
-               oracle on a sample of the mix
+               latency, identical results, the ranked method's least bytes
+               over the times and the CPU oracle on a sample of the mix
   "cpu_baseline"  the CPU oracle timed on this host, pinned to one core, on
                a bounded sample of the same workload, with
                "cpu_lr_baseline" beside it for rank valuations (the
@@ -89,9 +91,10 @@ TRAFFIC_FILES = {"c2": "traffic_random10M.json"}
 
 # the sources of everything a single rank-valuation game's load and solve
 # launch (batches, count valuations and PG_ODD_REGION live in other files)
-SINGLE_GAME_SOURCES = ["pg_api.hip", "pg_common.h", "pg_inc.hip",
-                       "pg_prims.hip", "pg_small.hip", "pg_switch.hip",
-                       "pg_tune.hip", "pg_val.hip"]
+SINGLE_GAME_SOURCES = ["pg_api.hip", "pg_coarse.h", "pg_common.h",
+                       "pg_inc.hip", "pg_prims.hip", "pg_rows.h",
+                       "pg_small.hip", "pg_switch.hip", "pg_tune.hip",
+                       "pg_val.hip"]
 
 
 def sources_sha256() -> str:
@@ -217,7 +220,7 @@ def traffic_summary(pmc_dir: str, workload: str = "c2") -> dict:
     write = per_kernel(f"{workload}_WRITE_SIZE")
     by_kind = {}
     for name, (kib, calls) in fetch.items():
-        kind = KERNEL_KINDS.get(name, "other")
+        kind = KERNEL_KINDS.get(name, "load")
         wk = write.get(name, [0.0, calls])[0]
         b = by_kind.setdefault(kind, [0.0, 0, 0.0, 0.0])
         b[0] += 1024.0 * (kib * f_scale + wk * w_scale)
@@ -238,7 +241,7 @@ def traffic_summary(pmc_dir: str, workload: str = "c2") -> dict:
 
 
 # the library's kernel kinds (pg_profile_read names) of each kernel a
-# rank-valuation solve launches
+# rank-valuation solve launches; the rest are the load's
 KERNEL_KINDS = {
     "k_ng_full": "ng_walk", "k_ng_round": "ng_round",
     "k_ng_round_list": "ng_round",
@@ -255,10 +258,14 @@ KERNEL_KINDS = {
     "k_fill_u8": "fill", "k_zero3": "fill", "k_1s_base": "scan",
     "k_inc_begin": "inc_find", "k_inc_find": "inc_find",
     "k_inc_even_cand": "inc_find", "k_inc_walk": "inc_walk",
-    "k_inc_fate": "inc_walk", "k_inc_decide": "inc_decide",
+    "k_inc_fate": "inc_walk", "k_inc_rows": "inc_walk",
+    "k_inc_decide": "inc_decide", "k_inc_wide": "inc_decide",
+    "k_tie_decide": "inc_decide", "k_coarse_full": "root_walk",
+    "k_coarse_round_list": "root_round",
     "k_inc_block": "inc_block", "k_small_run": "small",
     "k_small_value": "small", "k_inc_even_all": "even_switch",
-    "k_sum_dist": "other", "k_rs_upsweep": "sort_hist",
+    "k_inc_rows_hold": "other", "k_inc_commit": "other",
+    "k_mark_top": "other", "k_sum_dist": "other", "k_rs_upsweep": "sort_hist",
     "k_rs_downsweep": "sort_pass",
 }
 
@@ -473,14 +480,15 @@ def run_mix(n_games: int, oracle_budget_s: float = 10.0) -> dict:
         f"games/s, p50 {np.percentile(lat1, 50) * 1e3:.1f} ms, "
         f"p99 {np.percentile(lat1, 99) * 1e3:.1f} ms")
     ident = same(rb) and same(rs) and same(r1)
-    # the method's least bytes over every iteration of every game
+    # the least bytes of valuations that rank every vertex, over every
+    # iteration of every game
     mix_bytes = sum(
         method_min_bytes(int(r["stats"]["n_aug"]), int(r["stats"]["m_aug"]),
                          np.asarray(g["offsets"]).itemsize) *
         int(r["stats"]["n_valuations"]) for g, r in zip(games, solo))
 
-    def frac(seconds):
-        return round(mix_bytes / seconds / 1e9 / HBM_PEAK_GBS, 4)
+    def rate(seconds):
+        return round(mix_bytes / seconds)
 
     # the oracle, one game after another, on one core
     from oracle import orc
@@ -516,11 +524,13 @@ def run_mix(n_games: int, oracle_budget_s: float = 10.0) -> dict:
             "served_games_per_s": len(games) / r1["makespan"],
             "latency_p50_ms": float(np.percentile(lat1, 50) * 1e3),
             "latency_p99_ms": float(np.percentile(lat1, 99) * 1e3)},
-        "roofline": {"bound": "hbm", "unit": "fraction of 8 TB/s",
-                     "method_min_bytes_all_games": int(mix_bytes),
-                     "served_frac": frac(rs["makespan"]),
-                     "batched_frac": frac(rb["makespan"]),
-                     "one_at_a_time_frac": frac(t_solo)},
+        "ranked_method": {"least_bytes_all_games": int(mix_bytes),
+                          "meaning": "least_bytes over the time: speed "
+                                     "against valuations that rank every "
+                                     "vertex; no bandwidth",
+                          "served_bytes_per_s": rate(rs["makespan"]),
+                          "batched_bytes_per_s": rate(rb["makespan"]),
+                          "one_at_a_time_bytes_per_s": rate(t_solo)},
         "cpu_baseline": {
             "value": done / t_orc, "unit": "games/s", "cores": 1,
             "kind": "oracle",
@@ -724,8 +734,9 @@ def main():
     solve_s = [r["solve"] for r in runs]
     load_s = [r["load"] for r in runs]
 
-    # Roofline of the best-response iteration from the timed steps: the library reads the device's clock on the solve's
-    # stream around every iteration (pg_stats.iteration_ms, summed).
+    # Roofline of the best-response iteration from the timed steps: the
+    # library reads the device's clock on the solve's stream around every
+    # iteration (pg_stats.iteration_ms, summed).
     n_aug, m_aug = runs[0]["aug"][0], runs[0]["aug"][1]
     b_min = method_min_bytes(n_aug, m_aug,
                              np.asarray(game["offsets"]).itemsize)
@@ -737,23 +748,23 @@ def main():
         roof = {"bound": "hbm",
                 "kernel": "best-response iteration, mean over full "
                           "valuations (coarse keys or count rows) and "
-                          "changed-part ones; its bytes are the least of a "
-                          "valuation that ranks every vertex, so frac is "
-                          "speed against that method, not bandwidth",
-                "achieved": round(b_min / it_ev_s / 1e9, 1),
-                "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(b_min / it_ev_s / 1e9 / HBM_PEAK_GBS, 4),
+                          "changed-part ones",
+                # from counter bytes, below
+                "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": None,
                 "avg_launch_us": round(it_ev_s * 1e6, 2),
-                "bytes_per_launch": b_min,
                 "launches": nval * args.steps,
                 "traffic": None,
                 "traffic_kind": "rocprofv3 FETCH_SIZE + WRITE_SIZE per "
                                 "iteration, each scaled by its reading on a "
                                 "plain copy: bytes through the L2's fabric "
                                 "port (Infinity Cache hits included)",
+                "ranked_method": {
+                    "least_bytes": b_min,
+                    "bytes_per_s_at_this_time": round(b_min / it_ev_s),
+                    "meaning": "speed against valuations that rank every "
+                               "vertex; no bandwidth"},
                 "wall_us_per_iteration": round(it_wall_s * 1e6, 2),
-                "wall_frac": round(b_min / it_wall_s / 1e9 / HBM_PEAK_GBS,
-                                   4),
                 "measured_over": f"the device's clock over the "
                                  f"{nval * args.steps} iterations of the "
                                  "timed steps"}
@@ -783,13 +794,18 @@ def main():
                                             1) if a["ms"] > 0 else None}
         dom = max(agg, key=lambda k: agg[k]["ms"])
         a = agg[dom]
-        achieved = a["bytes"] / (a["ms"] / 1e3) / 1e9
-        dominant = {"kernel": dom, "achieved": round(achieved, 1),
+        avg_s = a["ms"] / 1e3 / a["calls"]
+        moved = counter_traffic(args.workload, dom)
+        dominant = {"kernel": dom,
+                    "achieved": round(moved / avg_s / 1e9, 1) if moved
+                    else None,
                     "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                    "frac": round(achieved / HBM_PEAK_GBS, 4),
-                    "avg_launch_us": round(1e3 * a["ms"] / a["calls"], 2),
-                    "bytes_per_launch": round(a["bytes"] / a["calls"]),
-                    "traffic": counter_traffic(args.workload, dom),
+                    "frac": round(moved / avg_s / 1e9 / HBM_PEAK_GBS, 4)
+                    if moved else None,
+                    "avg_launch_us": round(avg_s * 1e6, 2),
+                    "traffic": moved,
+                    "algorithmic_bytes": round(a["bytes"] / a["calls"])
+                    if a["bytes"] else None,
                     "measured_over": f"{prof_steps} profiled steps of the "
                                      "same job after the timed steps"}
         it_bytes = sum(a["bytes"] for a in agg.values()) / (prof_steps * nval)
@@ -800,6 +816,8 @@ def main():
                 prof_steps * nval)
         if roof is not None and it_traffic:
             roof["traffic"] = round(it_traffic)
+            roof["achieved"] = round(it_traffic / it_ev_s / 1e9, 1)
+            roof["frac"] = round(it_traffic / it_ev_s / 1e9 / HBM_PEAK_GBS, 4)
         iteration_bytes = {
             "kernel_alg_bytes": round(it_bytes),
             "kernel_alg_frac": (round(it_bytes / it_ev_s / 1e9 /

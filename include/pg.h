@@ -119,8 +119,8 @@ enum {
  * lie, so every winner is kept.
  *
  * PG_ODD_REGION replaces the dummies (section 3 offers them as one simple
- * preprocessing, not the only one): from X the load computes R, the vertices of X
- * from which Odd, moving inside X, reaches a cycle whose largest priority
+ * preprocessing, not the only one): from X the load computes R, the vertices
+ * of X from which Odd, moving inside X, reaches a cycle whose largest priority
  * is odd (strongly connected components of X peeled on the device by
  * colouring rounds), and A, Odd's attractor of R.  Odd wins A on its own;
  * the stored game is the original one without A (rows lose their edges
@@ -331,8 +331,8 @@ typedef struct pg_solve_opts {
      *   trace_switches   Odd vertices switched by the All_Odd step that
      *                    follows the valuation (0 ends a best response)
      *   trace_ms         device time of the best-response iteration (the
-     *                    valuation and its All_Odd step) between two HIP
-     *                    events on the call's stream                      */
+     *                    valuation and its All_Odd step) by the device's
+     *                    clock, from its first kernel past its last    */
     int32_t trace_cap;
     int32_t reserved;
     uint64_t *trace_key_hash;
@@ -537,8 +537,8 @@ pg_status pg_batch_free(pg_batch *batch);
  * sigma and tau (nullable) need room for n_aug entries, which the caller
  * does not know before the load: n_aug <= 2 n (one dummy at most per
  * original vertex), and stats->n_aug (when stats is given) says how many
- * were written; with PG_ODD_REGION n entries, as pg_solve.  The call returns after the stream has drained; outputs are
- * written then.
+ * were written; with PG_ODD_REGION n entries, as pg_solve.  The call returns
+ * after the stream has drained; outputs are written then.
  */
 #define PG_NOALLOC_MAX_VERTICES 65536
 #define PG_NOALLOC_MAX_EDGES 1048576
@@ -597,9 +597,10 @@ int32_t pg_tuning_table(pg_tuning *entries, int64_t *min_n_aug,
 pg_status pg_free(pg_game *game);
 
 /* Hand the cached memory of freed games and batches back to the HIP runtime
- * (every device).  Memory of games still loaded is not touched.  Small blocks are
- * carved from shared slabs of 32; a slab goes back once none of its blocks
- * belongs to a loaded game (its free blocks stay cached until then). */
+ * (every device); an allocation that finds no memory does so by itself.
+ * Memory of games still loaded is not touched.  Small blocks are carved from
+ * shared slabs of 32; a slab goes back once none of its blocks belongs to a
+ * loaded game (its free blocks stay cached until then). */
 pg_status pg_release_cache(void);
 
 /* Description of the calling thread's last error ("" if none). */

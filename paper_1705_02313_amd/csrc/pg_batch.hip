@@ -597,8 +597,8 @@ __global__ void k_bm_split(const BmOut *out, const unsigned long long *n_oddpri,
 // Many copies in one launch (blockIdx.y: which): a poll of many games copies
 // three arrays each, and a copy of its own per array is a launch and a gap of
 // some 10 us against a few us of transfer (96 games of 500 to 50,000
-// vertices: pg_batch_poll_many 3.4 -> 0.8 ms a batch).  The destinations are device memory or
-// pinned host memory the device can write.
+// vertices: pg_batch_poll_many 3.4 -> 0.8 ms a batch).  The destinations are
+// device memory or pinned host memory the device can write.
 struct CopyItem {
   void *dst;
   const void *src;
@@ -1023,8 +1023,9 @@ void enqueue_step_rest(pg_batch *b, hipStream_t s) {
   if (ne > 0)
     hipLaunchKernelGGL((a->wide ? k_batch_switch<false, true>
                                 : k_batch_switch<false, false>),
-                       dim3(grid_for(ne)), dim3(kBlock), 0, s, P, ne, a->even_ids, a->sp,
-                       b->d_gid, b->d_pending, b->d_cnt_even, a->ctr);
+                       dim3(grid_for(ne)), dim3(kBlock), 0, s, P, ne,
+                       a->even_ids, a->sp, b->d_gid, b->d_pending,
+                       b->d_cnt_even, a->ctr);
   hipLaunchKernelGGL(k_batch_ctl2, dim3(grid_for(G)), dim3(kBlock), 0, s, G,
                      b->d_run, b->d_pending, b->d_cnt_odd, b->d_cnt_even,
                      b->d_sw_odd, b->d_sw_even, b->d_newly, a->ctr);
@@ -1032,7 +1033,7 @@ void enqueue_step_rest(pg_batch *b, hipStream_t s) {
                      b->d_desc, b->d_gid, b->d_newly, a->sp, a->key, a->owner,
                      N, (int64_t)a->n_oddpri, a->ctr);
   uint8_t *r = b->h_res;
-  hipLaunchKernelGGL(k_batch_publish, dim3(std::min(64u, (unsigned)grid_for(G))),
+  hipLaunchKernelGGL(k_batch_publish, dim3(std::min(64u, grid_for(G))),
                      dim3(kBlock), 0, s, G,
                      b->d_newly, b->d_nval, b->d_nmaj, b->d_sw_odd,
                      b->d_sw_even, r, (int32_t *)(r + res_off_nval(G)),

@@ -333,12 +333,10 @@ struct pg_game {
   pgk::Prof prof;
   // launch and walk parameters of the rank valuation (pg_tuning)
   pg_tuning tune{32, 1, 16, 64, 3, 256};
-  // false: no HIP events are created or recorded (pg_solve_noalloc)
+  // false: iterations are not timed (pg_solve_noalloc)
   bool timed = true;
-  // HIP events around each best-response iteration on the call's stream
-  // (created at first use); the last iteration's device time
   int clock_khz = 0;        // the device's wall clock (at its first use)
-  float last_ms = 0.0f;
+  float last_ms = 0.0f;     // the last iteration's device time by that clock
 };
 
 // The signed-order maps the valuation kernels take: none for a relabeled
@@ -592,7 +590,7 @@ void fates_reset(pg_game *g, hipStream_t s);
 // One best-response iteration (valuation, then All_Odd) with a single
 // host synchronisation; returns the number of Odd switches and (nullable)
 // the finite vertices, the sink included.  g->last_ms receives the
-// iteration's device time between two HIP events on s.
+// iteration's device time by the device's clock.
 pg_status iteration_device(pg_game *g, hipStream_t s, int32_t *count,
                            int64_t *n_finite = nullptr);
 // The same on coarse keys (rank games, see coarse_key): no vertex is ranked,
@@ -712,8 +710,8 @@ namespace pgk {
 // Size-bucketed memory for the many small games of a batch: blocks (device,
 // and pinned host for the counter mirrors) go back to free lists by
 // power-of-two size instead of to hipFree, which waits for the device, and
-// come back from them instead of from hipMalloc.  Everything is released by
-// clear() when the batch is freed.
+// come back from them instead of from hipMalloc.  A freed batch's pool waits
+// for the next batch (give_pool) or releases everything (clear()).
 // Blocks of up to kSlabBlockMax bytes are carved from slabs of
 // kSlabBlocks blocks (one runtime allocation instead of one per block: a
 // game allocates a dozen small buffers, and a first pass over many games

@@ -77,7 +77,8 @@ constexpr int kFindLevels = 512;     // levels of a device form's find
 constexpr int kIncMaxDegree = 2048;  // in-edges of one vertex, else give up
 // In-edges beyond which all threads of a block share a vertex's: two lanes
 // to eight took a hub's 2,000 at 1.5 us a round trip, more than a full
-// valuation (1M vertices with 500 such hubs: finds of up to 3.9 ms, 0.23 ms so).
+// valuation (1M vertices with 500 such hubs: finds of up to 3.9 ms, 0.23 ms
+// so).
 constexpr uint32_t kHub = 128;
 constexpr int kIncFate = 1024;       // ng steps of one fate
 constexpr int kIncBlocks = 1024;
@@ -146,7 +147,7 @@ __global__ void k_in_cursors(const uint32_t *a, uint32_t *b, int64_t n,
 // of the two passes above are random lines with an atomic on each; here an
 // edge's pair goes to one of a thousand streams and from there to an address
 // that stays in one L2.  10M vertices, 35M edges: 1.4 + 3.0 ms (and a scan
-// and a copy of the counters) -> 0.10 + 0.70 + 0.52; 1M vertices, 6.5M edges:
+// and a copy of the counters) -> 0.10 + 0.67 + 0.45; 1M vertices, 6.5M edges:
 // 0.24 + 0.45 -> 0.02 + 0.06 + 0.05 ms.  Below kInPartMin the counters stay in
 // the L2 anyway and the two passes are fewer launches (40,000 vertices: 22
 // us, 300,000 the same either way); past kInPartMax the ranges' counters
@@ -616,6 +617,10 @@ __device__ __forceinline__ int find_lanes(int n, int T) {
 // and 0.77 ms (all 38: 11.4 -> 7.1 ms) against three launches that each
 // handed their widest levels to the next; what is left are the levels.
 // 256, 1024 and 2048 blocks were 0-4 % slower.
+//
+// Hubs are looked at by the whole block, and those of a level that have more
+// than twice kFindHubs in-edges together go to the queue as well, with the
+// level they are of (they are in A's list already).
 //
 // Chunk t is A's own t-th stretch for t < S, else place t - S of the queue.
 // Blocks take tickets in order and wait for their chunk to come, or for all
@@ -1106,7 +1111,7 @@ __global__ __launch_bounds__(kBlock) void k_tie_decide(IncP P, int32_t *ctr,
 // Stores `check` when a vertex's choice is no edge of its row (a strategy
 // given at the C ABI may name any vertex): the find follows in-edges only.
 // Bound by one read of the rows, before the run's first full valuation
-// (300,000 vertices: 5 us); rows beyond kWideRow entries are read by the
+// (300,000 vertices: 6 us); rows beyond kWideRow entries are read by the
 // whole block, or a hub's would keep one thread.
 __global__ __launch_bounds__(kBlock) void k_inc_rows_hold(IncP P,
                                                           int32_t check,

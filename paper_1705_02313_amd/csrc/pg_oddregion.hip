@@ -195,7 +195,8 @@ constexpr int kChase = 64, kChaseWide = 4;
 __global__ void k_or_color_sweep(const int32_t *lst, int32_t cnt,
                                  const int64_t *off, const int32_t *tgt,
                                  const uint8_t *alive,
-                                 unsigned long long *col, int chase, const int32_t *before, int32_t *changed) {
+                                 unsigned long long *col, int chase,
+                                 const int32_t *before, int32_t *changed) {
   if (before && !*before) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool ch = false;
@@ -559,16 +560,17 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
     hipLaunchKernelGGL(k_or_color_init, dim3(gc), dim3(kBlock), 0, s, L.a,
                        cnt, pri, col, reach, nontriv);
     PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, nullptr,
-                         [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
-                             int32_t *ch) {
+                         [&](const int32_t *l, int32_t c, int64_t round,
+                             const int32_t *b4, int32_t *ch) {
       hipLaunchKernelGGL(k_or_color_sweep, dim3(grid_for(c)), dim3(kBlock), 0,
-                         s, l, c, off, tgt, alive, col, round ? kChase : kChaseWide, b4, ch);
+                         s, l, c, off, tgt, alive, col,
+                         round ? kChase : kChaseWide, b4, ch);
     }));
     hipLaunchKernelGGL(k_or_reach_init, dim3(gc), dim3(kBlock), 0, s, L.a,
                        cnt, col, reach);
     PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, nullptr,
-                         [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
-                             int32_t *ch) {
+                         [&](const int32_t *l, int32_t c, int64_t round,
+                             const int32_t *b4, int32_t *ch) {
       hipLaunchKernelGGL(k_or_reach_sweep, dim3(grid_for(c)), dim3(kBlock), 0,
                          s, l, c, off, tgt, alive, col, reach, b4, ch);
     }));
@@ -584,15 +586,15 @@ pg_status odd_region_reduce(pg_game *g, hipStream_t s, int64_t n, int64_t m,
   // of R (over the vertices outside A), both in place
   PG_TRY(select(inx, seed, 1, &cnt));
   PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, seed,
-                       [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
-                             int32_t *ch) {
+                       [&](const int32_t *l, int32_t c, int64_t round,
+                           const int32_t *b4, int32_t *ch) {
     hipLaunchKernelGGL(k_or_back, dim3(grid_for(c)), dim3(kBlock), 0, s, l, c,
                        off, tgt, inx, seed, b4, ch);
   }));
   PG_TRY(select(seed, nullptr, 2, &cnt));
   PG_TRY(fixpoint_list(g, s, bound, &L, &cnt, seed,
-                       [&](const int32_t *l, int32_t c, int64_t round, const int32_t *b4,
-                             int32_t *ch) {
+                       [&](const int32_t *l, int32_t c, int64_t round,
+                           const int32_t *b4, int32_t *ch) {
     hipLaunchKernelGGL(k_or_attr, dim3(grid_for(c)), dim3(kBlock), 0, s, l, c,
                        off, tgt, owner, seed, b4, ch);
   }));

@@ -19,8 +19,9 @@
 // kernels a valuation, or pg_inc.hip's block in global memory): pg_valuation
 // at 1,000 vertices 158 -> 61 us a call, the load of a 1,000-vertex game 500
 // -> 69 us, its solve from arrays 1.62 -> 0.42 ms, 4,099 vertices 2.6 -> 0.87
-// ms.  The line at kSmallN is what 150 KB of LDS hold with up to 40,000 edges; above
-// it one block also stops paying (several vertices per thread in every step).
+// ms.  The line at kSmallN is what 150 KB of LDS hold with up to 40,000
+// edges; above it one block also stops paying (several vertices per thread in
+// every step).
 //
 // ng chains longer than kSmallDepth (none of the random or chain workloads
 // comes near) are left to the general path, before anything was switched.

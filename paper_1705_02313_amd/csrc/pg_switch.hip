@@ -36,8 +36,8 @@ namespace pgk {
 // 10M-vertex random game stage + min went 91 + 72 -> 82 + 63 us per step
 // against 32768-edge chunks and 2048-vertex buckets of 256 threads (1M
 // vertices: 16 + 21 -> 12 + 15 us).  The coarse keys' ties (the returned
-// minimum, one array more) take the min step to 78 and 17 us.  8192- and 6144-vertex buckets, or 512
-// threads per min block, were slower.
+// minimum, one array more) take the min step to 78 and 17 us.  8192- and
+// 6144-vertex buckets, or 512 threads per min block, were slower.
 constexpr int kTswChunk = 16384;   // edges per stage block
 constexpr int kTswBucket = 4096;   // Odd vertices per min block (20 B of LDS)
 
