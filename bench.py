@@ -809,11 +809,13 @@ def main():
                     "measured_over": f"{prof_steps} profiled steps of the "
                                      "same job after the timed steps"}
         it_bytes = sum(a["bytes"] for a in agg.values()) / (prof_steps * nval)
-        traffic = {k: counter_traffic(args.workload, k) for k in agg}
+        # (All_Even, the top marks and the commits lie between iterations)
+        traffic = {k: counter_traffic(args.workload, k) for k in agg
+                   if k not in ("even_switch", "other")}
         it_traffic = None
         if all(v is not None for v in traffic.values()):
-            it_traffic = sum(traffic[k] * agg[k]["calls"] for k in agg) / (
-                prof_steps * nval)
+            it_traffic = sum(traffic[k] * agg[k]["calls"] for k in traffic) \
+                / (prof_steps * nval)
         if roof is not None and it_traffic:
             roof["traffic"] = round(it_traffic)
             roof["achieved"] = round(it_traffic / it_ev_s / 1e9, 1)
